@@ -612,7 +612,7 @@ extern "C" int bagel_prepare_posterior(bagel_ctx *c, const float *X, const float
         const size_t Np = (size_t)c->post_Np, B = (size_t)c->dm.B, M = (size_t)c->M;
         hipError_t e = dev_alloc(c, &c->post_alpha, M * Np);
         if (e == hipSuccess) e = dev_alloc(c, &c->post_Kinv, M * Np * Np);
-        if (e == hipSuccess) e = dev_alloc(c, &c->post_Kx, M * Np * B);
+        if (e == hipSuccess) e = dev_alloc(c, &c->post_Kx, M * Np * ((B + 63) / 64 * 64));
         if (e == hipSuccess) e = dev_alloc(c, &c->post_sums, M * (Np / 64) * 2 * (1 + (size_t)c->D) * B);
         if (e != hipSuccess) {
             void *ptrs[] = {c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};

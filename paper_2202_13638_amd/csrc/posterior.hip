@@ -11,8 +11,8 @@
 //      scalar operands, the same expanded-distance form and software exp2 as the pathwise step kernel);
 //   2. posterior_gemm_kernel: Q = K_hat_m^-1 Kx_m, a float64 product [Np x Np] x [Np x B] per output and
 //      the dominant cost (2 N^2 flop per trajectory, step and output).  Q is never written: the
-//      workgroup that finishes a 64 x 64 tile of it multiplies the tile with the kernel rows and adds
-//      up, over the tile's 64 training points, the sums the moments are made of,
+//      workgroup that finishes a tile of it multiplies the tile with the kernel rows and adds
+//      up, over the tile's training points, the sums the moments are made of,
 //        sum_n a_n k_n, sum_n q_n k_n, sum_n a_n k_n Xs_nd, sum_n q_n k_n Xs_nd     (a = alpha_m, q = Q column),
 //      one set per tile row and trajectory;
 //   3. posterior_final_kernel adds the tile rows in order and finishes mu, var and their derivatives,
@@ -22,7 +22,7 @@
 // A variance below 1e-12 is held there and its derivative set to zero.
 // Everything after that (state update, cost, tape, policy, backward sweep) is shared with the pathwise sampler.
 #include "bagel_internal.h"
-#include "dgemm_tile.h"
+#include "f64_tile.h"
 
 namespace {
 
@@ -48,19 +48,19 @@ __device__ __forceinline__ double exp2_f64(double t)
     return ldexp(p * p, (int)n);
 }
 
-// Kx[m][n][b] for m = blockIdx.z, n in [32 blockIdx.y, +32), b = lane; rows n >= N (padding) are zero
+// Kx[m][n][b] for m = blockIdx.z, n in [32 blockIdx.y, +32), b = lane; rows n >= N (padding) are zero.  Rows are
+// Bp = B rounded up to 64 long; the columns past B repeat the last trajectory and nothing uses their results.
 template <int D>
 __global__ __launch_bounds__(256) void posterior_rows_kernel(const double *__restrict__ Xs, const double *__restrict__ A,
                                                              const double *__restrict__ xbuf, double *__restrict__ Kx,
-                                                             int B, int N, int Np, int Np_model)
+                                                             int B, int Bp, int N, int Np, int Np_model)
 {
     const int m = blockIdx.z;
     const double *__restrict__ Xs_m = Xs + (size_t)m * Np_model * (D + 1);
     const double *__restrict__ A_m = A + (size_t)m * D;
-    double *__restrict__ Kx_m = Kx + (size_t)m * Np * B;
+    double *__restrict__ Kx_m = Kx + (size_t)m * Np * Bp;
     const int b_raw = blockIdx.x * 256 + threadIdx.x;
-    const bool live = b_raw < B;
-    const int b = live ? b_raw : B - 1;
+    const int b = b_raw < B ? b_raw : B - 1;
     double x[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) x[d] = xbuf[(size_t)d * B + b];
@@ -77,66 +77,72 @@ __global__ __launch_bounds__(256) void posterior_rows_kernel(const double *__res
             for (int d = 0; d < D; ++d) t = fma(x[d], r[d], t);
             k = exp2_f64(t);
         }
-        if (live) Kx_m[(size_t)n * B + b] = k;
+        if (b_raw < Bp) Kx_m[(size_t)n * Bp + b_raw] = k;
     }
 }
 
-// Tile (blockIdx.y, blockIdx.x) of Q_m = K_hat_m^-1 Kx_m for m = blockIdx.z, folded at once into the
-// sums over the tile's 64 training points: sums[m][blockIdx.y][v][b], v = 0: sum a k, 1: sum q k,
-// 2 + d: sum a k Xs_d, 2 + D + d: sum q k Xs_d.  Every sum is formed in a fixed order (a lane's eight
-// rows, then the four lane groups, then the two waves that share the columns).
-template <int D>
-__global__ __launch_bounds__(256, (D <= 8 ? 4 : 2)) void posterior_gemm_kernel(const double *__restrict__ Kinv, const double *__restrict__ Kx,
-                                                             const double *__restrict__ alpha,
-                                                             const double *__restrict__ Xs, double *__restrict__ sums,
-                                                             int B, int N, int Np, int Np_model)
+// Tile (blockIdx.y, blockIdx.x) of Q_m = K_hat_m^-1 Kx_m for m = blockIdx.z (K_hat^-1 is symmetric: its rows are the
+// columns the product wants), folded at once into the sums over the tile's T training points:
+// sums[m][blockIdx.y][v][b], v = 0: sum a k, 1: sum q k, 2 + d: sum a k Xs_d, 2 + D + d: sum q k Xs_d.  Every sum
+// is formed in a fixed order (a lane's rows, then the four lane groups, then the two waves that share the
+// columns).  Bound: the float64 matrix pipe: N = 2048, B = 1024, M = 4 takes 499 us = 69 TFLOP/s with T = 128 (a
+// large library product reaches 72 on this chip; the 64 x 64 tile staged through registers that this replaced
+// took 637 us).  T = 128 halves the operand traffic and barriers per matrix instruction; see step_d for when the
+// smaller tile is taken.
+template <int D, int T>
+__global__ __launch_bounds__(256, 2) void posterior_gemm_kernel(const double *__restrict__ Kinv, const double *__restrict__ Kx,
+                                                                const double *__restrict__ alpha,
+                                                                const double *__restrict__ Xs, double *__restrict__ sums,
+                                                                int B, int Bp, int N, int Np, int Np_model)
 {
-    constexpr int NV = 2 * (1 + D);
-    __shared__ bagel_gemm::tile_lds sh;
-    __shared__ double red[2][2][NV][16];
+    constexpr int NV = 2 * (1 + D), LW = D + 1, H = f64_tile::shape<T>::H;
+    __shared__ __align__(16) double lds[f64_tile::shape<T>::LDS_DOUBLES];
+    static_assert(T * LW + NV * T <= f64_tile::shape<T>::LDS_DOUBLES, "staged rows and sums must fit the product's LDS");
     const int m = blockIdx.z;
-    const int i0 = blockIdx.y * bagel_gemm::TM, j0 = blockIdx.x * bagel_gemm::TN;
-    const double *__restrict__ Kx_m = Kx + (size_t)m * Np * B;
+    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T;
+    const double *__restrict__ Kx_m = Kx + (size_t)m * Np * Bp;
     const double *__restrict__ alpha_m = alpha + (size_t)m * Np;
     const double *__restrict__ Xs_m = Xs + (size_t)m * Np_model * (D + 1);
-    bagel_gemm::d4v acc[2][2];
-    bagel_gemm::tile_product(acc, sh, i0, j0, Np, B, Np, Kinv + (size_t)m * Np * Np, Np, 1, Kx_m, B, 1);
-    // scaled inputs and alpha of the tile's 64 training points, into the LDS the product is done with
-    // (zero on the padding rows); tile_product ended with a barrier
-    constexpr int LW = D + 1;
-    double *xl = reinterpret_cast<double *>(&sh);
-    static_assert(64 * LW * sizeof(double) <= sizeof(bagel_gemm::tile_lds), "tile LDS too small for the staged rows");
-    for (int idx = threadIdx.x; idx < 64 * LW; idx += 256) {
+    f64_tile::accumulators<T> acc;
+    f64_tile::clear(acc);
+    f64_tile::product<T>(acc, lds, i0, j0, Np, Bp, Np, Kinv + (size_t)m * Np * Np, Np, Kx_m, Bp);
+    // scaled inputs and alpha of the tile's training points, into the LDS the product is done with (zero on the
+    // padding rows and on the rows past Np, whose products count for nothing that way)
+    double *xl = lds, *red = lds + T * LW;
+    for (int idx = threadIdx.x; idx < T * LW; idx += 256) {
         const int row = idx / LW, col = idx - row * LW, gi = i0 + row;
         double val = 0.0;
         if (gi < N) val = col < D ? Xs_m[(size_t)gi * (D + 1) + col] : alpha_m[gi];
         xl[idx] = val;
     }
     __syncthreads();
-    const bagel_gemm::lane_pos pos = bagel_gemm::lane_position();
+    const f64_tile::lane_pos pos = f64_tile::lane_position<T>();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = wave & 1;                        // which 32 columns of the tile
     double *__restrict__ out = sums + ((size_t)m * gridDim.y + blockIdx.y) * NV * B;
-    // one of the lane's two columns at a time, to keep the sums within the register budget
+    // one of the lane's columns at a time, to keep the sums within the register budget
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-        const int gj = j0 + pos.col0 + 16 * y;
-        double kv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {                 // e = 4 x + r; padding rows of Kx are zero
-            const int gi = i0 + pos.row0 + 16 * (e >> 2) + 4 * (e & 3);
-            kv[e] = gj < B ? Kx_m[(size_t)gi * B + gj] : 0.0;
-        }
+    for (int y = 0; y < 2 * H; ++y) {
+        const int col = pos.col0 + 32 * (y >> 1) + (y & 1);
+        const int gj = j0 + col;
+        const double *kcol = Kx_m + min(gj, Bp - 1);
         double s[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) s[v] = 0.0;
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < 2 * H; ++x) {
+            asm volatile("" ::: "memory");                // no reads kept or moved ahead: there are no registers for them
+            double kv[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                 // padding rows of Kx are zero; so are the rows past Np
+                const int gi = i0 + pos.row0 + 32 * (x >> 1) + (x & 1) + 8 * r;
+                const double k = kcol[(size_t)min(gi, Np - 1) * Bp];
+                kv[r] = gi < Np ? k : 0.0;
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const double *__restrict__ row = xl + (pos.row0 + 16 * x + 4 * r) * LW;
-                const double k = kv[4 * x + r];
-                const double ak = row[D] * k, qk = acc[x][y][r] * k;
+                const double *row = xl + (pos.row0 + 32 * (x >> 1) + (x & 1) + 8 * r) * LW;
+                const double k = kv[r];
+                const double ak = row[D] * k, qk = acc.v[x][y][r] * k;
                 s[0] += ak;
                 s[1] += qk;
 #pragma unroll
@@ -145,6 +151,7 @@ __global__ __launch_bounds__(256, (D <= 8 ? 4 : 2)) void posterior_gemm_kernel(c
                     s[2 + D + d] = fma(qk, row[d], s[2 + D + d]);
                 }
             }
+        }
         // the four lane groups of a wave hold different rows of the same columns
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
@@ -154,12 +161,12 @@ __global__ __launch_bounds__(256, (D <= 8 ? 4 : 2)) void posterior_gemm_kernel(c
         // the waves of the lower half of the tile hand their sums to the waves of the upper half
         if ((wave >> 1) == 1 && lane < 16) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) red[half][y][v][lane] = s[v];
+            for (int v = 0; v < NV; ++v) red[v * T + col] = s[v];
         }
         __syncthreads();
         if ((wave >> 1) == 0 && lane < 16 && gj < B) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) out[(size_t)v * B + gj] = s[v] + red[half][y][v][lane];
+            for (int v = 0; v < NV; ++v) out[(size_t)v * B + gj] = s[v] + red[v * T + col];
         }
     }
 }
@@ -203,17 +210,32 @@ __global__ __launch_bounds__(256) void posterior_final_kernel(const double *__re
     }
 }
 
+template <int D, int T>
+void launch_gemm(bagel_ctx *c, int ntile)
+{
+    const int B = c->dm.B, Bp = (B + 63) / 64 * 64;
+    hipLaunchKernelGGL((posterior_gemm_kernel<D, T>), dim3((Bp + T - 1) / T, ntile, c->M), dim3(256), 0, c->stream,
+                       c->post_Kinv, c->post_Kx, c->post_alpha, c->Xs, c->post_sums, B, Bp, c->dm.N, c->post_Np, c->Np);
+}
+
 template <int D>
 hipError_t step_d(bagel_ctx *c, bool jac, const float *xi_t)
 {
-    const int B = c->dm.B, N = c->dm.N, Np = c->post_Np, M = c->M;
-    const int ntile = Np / bagel_gemm::TM;
+    const int B = c->dm.B, Bp = (B + 63) / 64 * 64, N = c->dm.N, Np = c->post_Np, M = c->M;
     bagel_post_sf2 sf2;
     for (int m = 0; m < 8; ++m) sf2.v[m] = c->post_sf2[m];
+    // A 128 x 128 tile keeps a compute unit's matrix pipes busy on its own, so its product takes whole passes of 256
+    // tiles: it wins where the last pass is (nearly) full and loses what is missing there otherwise.  Measured per
+    // step, 64 against 128 (N, B, M): 512 tiles (2048, 1024, 4) 556 / 529 us; 256 tiles (2048, 512, 4) 321 / 311,
+    // (4096, 512, 2) 577 / 563; 384 tiles (2048, 768, 4) 440 / 520; 64 tiles (1024, 256, 4) 89 / 178.
+    const long tiles128 = (long)((Bp + 127) / 128) * ((Np + 127) / 128) * M;
+    const long passes = (tiles128 + 255) / 256;
+    const bool large = 100 * tiles128 >= 95 * 256 * passes;
+    const int ntile = large ? (Np + 127) / 128 : Np / 64;
     hipLaunchKernelGGL((posterior_rows_kernel<D>), dim3((B + 255) / 256, (Np + 31) / 32, M), dim3(256), 0, c->stream,
-                       c->Xs, c->A, c->xbuf, c->post_Kx, B, N, Np, c->Np);
-    hipLaunchKernelGGL((posterior_gemm_kernel<D>), dim3((B + 63) / 64, ntile, M), dim3(256), 0, c->stream, c->post_Kinv,
-                       c->post_Kx, c->post_alpha, c->Xs, c->post_sums, B, N, Np, c->Np);
+                       c->Xs, c->A, c->xbuf, c->post_Kx, B, Bp, N, Np, c->Np);
+    if (large) launch_gemm<D, 128>(c, ntile);
+    else launch_gemm<D, 64>(c, ntile);
     hipLaunchKernelGGL((posterior_final_kernel<D>), dim3((B + 255) / 256, jac ? 1 + D : 1, M), dim3(256), 0, c->stream,
                        c->post_sums, c->A, c->xbuf, xi_t, sf2, c->part, B, M, ntile);
     return hipGetLastError();

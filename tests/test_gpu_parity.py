@@ -764,6 +764,16 @@ def test_posterior_sampler_shapes(d_s, d_a, d_g, N, B, H, hidden, bound):
 
 
 @pytest.mark.timeout(600)
+@pytest.mark.parametrize("N,B", [(943, 950),    # 8 x 8 tiles of 128 per output, the last row and column of tiles half empty
+                                 (1024, 1024),  # 8 x 8 whole tiles
+                                 (961, 961)])   # the last tiles reach the end, one row and column of data in their last 64
+def test_posterior_sampler_large_tiles(N, B):
+    """Batches whose products fill the chip with 128 x 128 tiles (256 of them here), to the same tolerance as above."""
+    cfg = synth.Config("pl", 51, 4, 1, 1, N, 16, B, 2, (8,), 1.0, "sinusoid", "steps", 0, 0.6, 1e-3)
+    _posterior_case(cfg, f"posterior-large-tiles-{N}-{B}")
+
+
+@pytest.mark.timeout(600)
 def test_posterior_sampler_small_config_size():
     """The Small configuration's model (N=512, 4 outputs, policy 5-64-64-1) with a shorter batch and horizon."""
     _posterior_case(_cfg("small", B=64, H=20), "posterior-small")
