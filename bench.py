@@ -266,7 +266,7 @@ def main():
                    "arithmetic": "kernel row and feature phase in f64, policy and sin/cos in f32, f32 interface",
                    "prepare_s": round(t_prep, 3), "input_generation_s": round(t_gen, 1),
                    "workspace_GB": round(ctx.workspace_bytes() / 1e9, 2)},
-        "roofline": {"bound": "alu", "kernel": "posterior step: rows + dgemm_kernel + reduce, all outputs" if posterior
+        "roofline": {"bound": "alu", "kernel": "posterior step: rows, posterior_gemm_kernel and final, all outputs" if posterior
                      else "gp_step_kernel<D,jac>", "achieved": achieved,
                      "peak": PEAK_FP64_VECTOR_TFLOPS, "unit": "TFLOP/s", "frac": achieved / PEAK_FP64_VECTOR_TFLOPS,
                      "traffic": None if posterior else measured_traffic(cfg, S, args.horizon),

@@ -110,8 +110,8 @@ int bagel_num_params(const bagel_dims *dims);
  * Create a context for fixed dims on the current HIP device.  Allocates every buffer the rollout
  * calls, bagel_set_samples, bagel_sample_eval, bagel_adam_step and bagel_optimize need (model copy,
  * tape, partial sums); those calls allocate nothing.  The set-up calls allocate on their own:
- * bagel_prepare_samples, bagel_prepare_posterior and bagel_hyper_* share one float64 work space and up to
- * three internal streams, which the first of them makes, a later one enlarges if it needs more, and the
+ * bagel_prepare_samples, bagel_prepare_posterior and bagel_hyper_* share one float64 work space, which the
+ * first of them makes, a later one enlarges if it needs more, and the
  * context keeps until bagel_destroy (so a loop over set-up calls allocates in its first pass only); the
  * first bagel_prepare_posterior also allocates the posterior cache, which the context keeps as well
  * (sizes at their declarations; bagel_workspace_bytes counts all of it).  `hip_stream` is a hipStream_t (NULL = default stream); all later work of this
@@ -136,10 +136,9 @@ int64_t bagel_workspace_bytes(const bagel_ctx *ctx);
  *   w[S][M][L]  eps[S][M][N]      (M = d_s)
  *   v_out[S][M][N] or NULL: receives the float32 representer weights.
  * Synchronises the stream (it must learn whether the factorisation succeeded).  Set-up work: it
- * needs 8 (Np^2 + Np L + Np S + S L) bytes of the set-up work space (see bagel_create) for each of up
- * to three outputs that it works on side by side on internal streams (ordered after what is already
- * enqueued on the context's stream; all finished on return; fewer side by side if the memory for three
- * cannot be had).
+ * needs 8 (Np^2 + Np max(Np, Lp) + Np Sp + Sp max(Np, Lp) + 513 Np) bytes of the set-up work space (see
+ * bagel_create; Np, Lp, Sp: N, L, S rounded up to 64) for each of the outputs, which it works on all together
+ * (in several passes if the memory for all cannot be had).
  * Errors: EINVAL, ENOMEM, ENOTPD (context is left unprepared), EHIP.
  */
 int bagel_prepare_samples(bagel_ctx *ctx, const float *X, const float *y, const float *lengthscale,
@@ -240,8 +239,8 @@ int bagel_optimize(bagel_ctx *ctx, float *theta, float *adam_m, float *adam_v, c
  * with respect to the logarithms of the hyper-parameters of eq. (4):
  *   log_hyp[M][D+2] = (log l_1 .. log l_D, log alpha^2, log sigma_n^2) per output.
  * X[N][D], y[M][N] as in bagel_prepare_samples; lml[M]; grad[M][D+2] or NULL.  Float64 inside.
- * Set-up work: needs three Np x Np float64 matrices per output worked on (set-up work space, see
- * bagel_create) and synchronises the stream.
+ * Set-up work: needs four Np x Np float64 matrices per output (set-up work space, see bagel_create; the outputs
+ * in several passes if the memory for all cannot be had) and synchronises the stream.
  * Errors: EINVAL, ENOMEM, ENOTPD, EHIP.
  *
  * bagel_hyper_fit: n_iters Adam updates of log_hyp (in place) that raise lml / N of every output;

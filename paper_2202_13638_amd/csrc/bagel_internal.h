@@ -86,7 +86,7 @@ struct bagel_ctx {
     double *post_sums;           // [M][post_Np/64][2(1+D)][B]: per-tile sums of the moments
     const float *cur_xi;         // draws of the rollout in progress (null: pathwise sampler)
 
-    // ---- set-up calls (prepare.hip): side streams and float64 work space, made by the first of them --
+    // ---- set-up calls (prepare.hip): float64 work space, made by the first of them ----------------
     void *setup;
 
     // ---- measurement hooks -------------------------------------------------------------------
@@ -169,11 +169,8 @@ int bagel_prepare_impl(bagel_ctx *ctx, const float *X, const float *y, const flo
 // K_hat^-1 and K_hat^-1 y of every output into ctx->post_Kinv / post_alpha (float64)
 int bagel_prepare_posterior_impl(bagel_ctx *ctx, const float *X, const float *y, const float *ell, const float *sf2,
                                  const float *sn2);
-// release the side streams and work space of the set-up calls (bagel_destroy)
+// release the work space of the set-up calls (bagel_destroy)
 void bagel_release_setup(bagel_ctx *ctx);
-// C (+)= alpha * A * B in float64 with element strides (see dgemm_kernel); overwrite: C = alpha * A * B
-void bagel_dgemm(hipStream_t st, int Mr, int Nc, int Kd, double alpha, const double *A, long sai, long sak,
-                 const double *Bm, long sbk, long sbj, double *Cm, long ldc, bool overwrite);
 // lml[iters][M] and grad[M][D+2] of the log hyper-parameters log_hyp[M][D+2]; n_iters > 0: Adam fit in place
 int bagel_hyper_impl(bagel_ctx *ctx, const float *X, const float *y, float *log_hyp, float *lml, float *grad,
                      float *adam_m, float *adam_v, int n_iters, int first_step, double lr, double beta1, double beta2,

@@ -1,593 +1,682 @@
-// Sample-set precompute: v_sm = (K_m + noise_m I)^-1 (y_m - Phi_m w_sm - eps_sm) for every
-// function sample s and output m (Matheron update of a pathwise sample; K_hat as defined below
-// eq. (3), kernel of eq. (4)).  Everything is float64 on the device: the condition number of
-// K_hat is ~ signal/noise variance times N, far beyond float32.  Per output:
-//   1. K_hat (padded to a multiple of 64 with an identity block) and Phi are built from the
-//      float32 inputs;
-//   2. recursively blocked Cholesky: 64x64 diagonal factorisation and panel solve inside ranges of
-//      256 columns, the larger ranges updated by tiled float64 GEMMs as deep as half the range;
-//   3. R = y 1^T - Phi W^T - Eps^T as one GEMM over the L features (R is [N][S]);
-//   4. blocked forward and backward substitution on all S right-hand sides at once, again
-//      GEMM-dominated;
-//   5. v is rounded to float32 once, written to v_out[S][M][N] and packed for the step kernel.
-// This is set-up work outside the timed rollouts; buffers are allocated here and freed on return.
+// Set-up of the two samplers and hyper-parameter learning: everything that needs K_hat = K + noise I
+// (eq. (4), text below eq. (3)) factored.
+//   bagel_prepare_impl            v_sm = K_hat_m^-1 (y_m - Phi_m w_sm - eps_sm) for every function sample and output
+//                                 (Matheron update of a pathwise sample)
+//   bagel_prepare_posterior_impl  K_hat_m^-1 and K_hat_m^-1 y_m (eq. (2), (3))
+//   bagel_hyper_impl              log marginal likelihood and its gradient (eq. (5), (6)), Adam ascent on it
+// Everything is float64 on the device: the condition number of K_hat is ~ signal/noise variance times N, far
+// beyond float32.
+//
+// Layout.  Np = N rounded up to 64; the padding rows of K_hat are an identity block.  All GP outputs are worked on
+// by the same launches (one more grid dimension): the chain of small dependent kernels of a factorisation
+// is walked once instead of once per output.  Matrices of one output, row-major with row length Np:
+//   K  the upper triangle of K_hat (whole 64 x 64 blocks), updated in place while it is factored;
+//   U  the factor, K_hat = U^T U (L = U^T), block rows written as they are finished; with `mirror` also L below;
+//   W  L^-1 (lower), V = W^T = U^-1 (upper): the 64 x 64 diagonal blocks come out of the factorisation of the
+//      diagonal block, larger blocks from them level by level (triangular_inverse).
+// With U, V and W at hand every product has its contraction index as the row of both operands (f64_tile.h).
+//
+// Factorisation (struct solver): recursive halving with products as deep as half the range down to ranges of
+// four blocks; inside a range one launch per block column (chol_step_kernel), which also factors and inverts the
+// next diagonal block.  A triangular solve with 64 unknowns is a product with the inverted diagonal block.
 #include <math.h>
 #include <stdio.h>
 
+#include <new>
+
 #include "bagel_internal.h"
-#include "dgemm_tile.h"
+#include "f64_tile.h"
 
 namespace {
 
-constexpr int NB = 64;    // Cholesky / substitution block
-using bagel_gemm::TM;
-using bagel_gemm::TN;
+constexpr int NB = 64;           // block of the factorisation
+constexpr int RB = 4;            // blocks per range that is worked on block column by block column
+using f64_tile::d4v;
 
-// K_hat[i][j] for i, j < Np (row-major, leading dimension Np); identity on the padding
-__global__ void build_khat_kernel(const float *__restrict__ X, const float *__restrict__ ell, float sf2, float sn2,
-                                  double *__restrict__ K, int N, int Np, int D)
+// ---- K_hat --------------------------------------------------------------------------------------------------
+// Hyper-parameters of output m, either as they are (log = 0: ell[M][D], sf2[M], sn2[M]) or as logarithms
+// (log = 1: ell[M][D + 2] = log l_1 .. log l_D, log alpha^2, log sigma_n^2).
+struct hyper_ptr {
+    const float *ell, *sf2, *sn2;
+    int log;
+};
+__device__ __forceinline__ double inv_length(const hyper_ptr &h, int m, int D, int d)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= Np) return;
-    double val;
-    if (i < N && j < N) {
-        double r = 0.0;
-        for (int d = 0; d < D; ++d) {
-            const double t = ((double)X[(size_t)i * D + d] - (double)X[(size_t)j * D + d]) / (double)ell[d];
-            r += t * t;
+    return h.log ? exp(-(double)h.ell[m * (D + 2) + d]) : 1.0 / (double)h.ell[m * D + d];
+}
+__device__ __forceinline__ double signal_variance(const hyper_ptr &h, int m, int D)
+{
+    return h.log ? exp((double)h.ell[m * (D + 2) + D]) : (double)h.sf2[m];
+}
+__device__ __forceinline__ double noise_variance(const hyper_ptr &h, int m, int D)
+{
+    return h.log ? exp((double)h.ell[m * (D + 2) + D + 1]) : (double)h.sn2[m];
+}
+
+// Block (blockIdx.y, blockIdx.x) of the upper triangle of K_hat for output m0 + blockIdx.z; identity on the padding.
+// Thread = column and 16 of the rows; inputs of the block's rows and columns in LDS.
+__global__ __launch_bounds__(256) void build_khat_kernel(const float *__restrict__ X, hyper_ptr h, double *__restrict__ K,
+                                                         size_t sK, int N, int Np, int D, int m0)
+{
+    if (blockIdx.x < blockIdx.y) return;
+    __shared__ double xr[NB][BAGEL_MAX_D], xc[BAGEL_MAX_D][NB + 1], il[BAGEL_MAX_D];
+    const int m = m0 + blockIdx.z, i0 = blockIdx.y * NB, j0 = blockIdx.x * NB;
+    for (int e = threadIdx.x; e < NB * D; e += 256) {
+        const int r = e / D, d = e - r * D;
+        xr[r][d] = i0 + r < N ? (double)X[(size_t)(i0 + r) * D + d] : 0.0;
+        xc[d][r] = j0 + r < N ? (double)X[(size_t)(j0 + r) * D + d] : 0.0;
+    }
+    if ((int)threadIdx.x < D) il[threadIdx.x] = inv_length(h, m, D, threadIdx.x);
+    __syncthreads();
+    const int c = threadIdx.x & 63, r0 = 16 * (threadIdx.x >> 6);
+    double s[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[e] = 0.0;
+    for (int d = 0; d < D; ++d) {
+        const double x = xc[d][c], l = il[d];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const double t = (xr[r0 + e][d] - x) * l;
+            s[e] = fma(t, t, s[e]);
         }
-        val = (double)sf2 * exp(-0.5 * r);
-        if (i == j) val += (double)sn2;
-    } else {
-        val = (i == j) ? 1.0 : 0.0;
     }
-    K[(size_t)i * Np + j] = val;
-}
-
-// Phi[n][l] = sqrt(2 sf2 / L) cos(omega_l . X_n + phase_l); zero rows on the padding
-__global__ void build_phi_kernel(const float *__restrict__ X, const float *__restrict__ omega,
-                                 const float *__restrict__ phase, float sf2, double *__restrict__ Phi, int N,
-                                 int Np, int L, int D)
-{
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = blockIdx.y;
-    if (l >= L) return;
-    double val = 0.0;
-    if (n < N) {
-        double z = (double)phase[l];
-        for (int d = 0; d < D; ++d) z += (double)omega[(size_t)l * D + d] * (double)X[(size_t)n * D + d];
-        val = sqrt(2.0 * (double)sf2 / (double)L) * cos(z);
+    const double sf2 = signal_variance(h, m, D), sn2 = noise_variance(h, m, D);
+    double *dst = K + blockIdx.z * sK + (size_t)(i0 + r0) * Np + j0 + c;
+    const int j = j0 + c;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int i = i0 + r0 + e;
+        double v = i == j ? 1.0 : 0.0;
+        if (i < N && j < N) {
+            v = sf2 * exp(-0.5 * s[e]);
+            if (i == j) v += sn2;
+        }
+        dst[(size_t)e * Np] = v;
     }
-    Phi[(size_t)n * L + l] = val;
 }
 
-// R[n][s] = y[n] - eps[s][n] (zero on the padding); eps is [S][M][N] at output m
-__global__ void init_rhs_kernel(const float *__restrict__ y_m, const float *__restrict__ eps, double *__restrict__ R,
-                                int N, int Np, int S, int M, int m)
+// ---- diagonal block: factor and inverse -------------------------------------------------------------------------
+// Where the 64 x 64 ... 256 x 256 diagonal blocks of V and W are: the whole matrix, or (compact) only the diagonal
+// blocks of 256, one after the other.
+struct tri_matrix {
+    double *p;
+    size_t ld;                   // 0: compact, rows of 256
+    size_t stride;               // per output
+    __device__ __forceinline__ size_t row_length() const { return ld ? ld : (size_t)(NB * RB); }
+    __device__ __forceinline__ double *at(int o, int r, int c) const
+    {
+        return p + o * stride + (ld ? (size_t)r * ld + c : (size_t)r * (NB * RB) + (c & (NB * RB - 1)));
+    }
+};
+
+struct factor_args {
+    double *K, *U;
+    size_t sK, sU;               // per output
+    tri_matrix V, W;
+    double *diag;                // [outputs][Np]: diagonal of U
+    int *flag;                   // [outputs]: 0, or 1 + first pivot that is not positive
+    int Np;
+};
+
+constexpr int LT = 66;           // LDS row stride of a block: even, so that pairs stay aligned
+
+__device__ __forceinline__ double read_lane(double v, int lane)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = blockIdx.y;
-    if (s >= S) return;
-    double val = 0.0;
-    if (n < N) val = (double)y_m[n] - (double)eps[((size_t)s * M + m) * N + n];
-    R[(size_t)n * S + s] = val;
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-// Wd[s][l] = w[s][m][l]
-__global__ void convert_w_kernel(const float *__restrict__ w, double *__restrict__ Wd, int S, int M, int L, int m)
+// 1/sqrt(d): hardware estimate, one third-order and one second-order correction (a chain of eight instructions,
+// a quarter of what the library's division after its square root takes)
+__device__ __forceinline__ double inv_sqrt(double d)
 {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    const int s = blockIdx.y;
-    if (l < L) Wd[(size_t)s * L + l] = (double)w[((size_t)s * M + m) * L + l];
+    double y = __builtin_amdgcn_rsq(d);
+    double e = fma(-(d * y), y, 1.0);
+    y = fma(y * e, fma(0.375, e, 0.5), y);
+    e = fma(-(d * y), y, 1.0);
+    return fma(0.5 * e, y, y);
 }
 
-// C[i][j] (ldc) += alpha * sum_k A(i,k) * B(k,j), A(i,k) = A[i*sai + k*sak], B(k,j) = B[k*sbk + j*sbj]
-// (C = alpha * ... with overwrite).  lower_only: skip tiles entirely above the diagonal j = i + diag
-// (used for the symmetric products).  The tile product itself is in dgemm_tile.h.
-__global__ __launch_bounds__(256, 4) void dgemm_kernel(int Mr, int Nc, int Kd, double alpha,
-                                                    const double *__restrict__ A, long sai, long sak,
-                                                    const double *__restrict__ Bm, long sbk, long sbj,
-                                                    double *__restrict__ Cm, long ldc, int lower_only, int diag, int overwrite)
+// A 16-column panel of the factorisation, right-looking, one wave: lane = row of the panel, its 16 entries in x.
+// Lane J holds the pivot row of column J (J = 0 .. 15).  Every lane does the same to its row, so lanes that start
+// with a column of the identity end with that column of the inverse of the panel's diagonal block.
+template <int J>
+__device__ __forceinline__ void panel_column(double (&x)[16], int &bad)
 {
-    const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
-    if (lower_only && j0 > i0 + diag + TM - 1) return;
-    __shared__ bagel_gemm::tile_lds sh;
-    bagel_gemm::d4v acc[2][2];
-    bagel_gemm::tile_product(acc, sh, i0, j0, Mr, Nc, Kd, A, sai, sak, Bm, sbk, sbj);
-    const bagel_gemm::lane_pos pos = bagel_gemm::lane_position();
+    const double d = read_lane(x[J], J);
+    bad = (bad == 0 && !(d > 0.0)) ? J + 1 : bad;
+    x[J] *= inv_sqrt(d);
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int c = J + 1; c < 16; ++c) x[c] = fma(-read_lane(x[J], c), x[J], x[c]);
+    __builtin_amdgcn_sched_barrier(0);           // one column's broadcasts at a time: they live in scalar registers
+    if constexpr (J + 1 < 16) panel_column<J + 1>(x, bad);
+}
+
+// D[16 x 16] tile of a product of 16 x 16 blocks in LDS: acc += a(i, k) b(k, j), a = A[i][k], b given by rows or by
+// columns (transposed)
+template <bool NEG, bool BT>
+__device__ __forceinline__ d4v block16(d4v acc, const double *A, const double *B)
+{
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
+    for (int s = 0; s < 4; ++s) {
+        const double a = A[i * LT + g + 4 * s];
+        const double b = BT ? B[i * LT + g + 4 * s] : B[(g + 4 * s) * LT + i];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(NEG ? -a : a, b, acc, 0, 0, 0);
+    }
+    return acc;
+}
+// the same with the second operand in accumulator layout (rows g + 4 s of the lane's column): no exchange needed
+template <bool NEG>
+__device__ __forceinline__ d4v block16_reg(d4v acc, const double *A, const d4v &b)
+{
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const double a = A[i * LT + g + 4 * s];
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(NEG ? -a : a, b[s], acc, 0, 0, 0);
+    }
+    return acc;
+}
+__device__ __forceinline__ d4v load16(const double *C)
+{
+    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
+    d4v v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = C[(g + 4 * r) * LT + j];
+    return v;
+}
+__device__ __forceinline__ void store16(double *C, const d4v &v)
+{
+    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) C[(g + 4 * r) * LT + j] = v[r];
+}
+
+// Diagonal block k of output o, in T (LDS, [64][LT], lower triangle used): its factor to U (upper form) and
+// `diag`, the inverse of the factor to W and V.  Wl: LDS of the same size.  256 threads; T is overwritten.
+// Four panels of 16 columns: wave 0 factors the panel for all rows below (lane = row), wave 1 the panel's diagonal
+// block beside the identity, which gives that block's inverse; then the waves update the blocks to the right
+// on the matrix cores.  The 64 x 64 inverse is put together from the four of 16 x 16 in two levels.
+// Bound: the chain of 64 pivots (about 0.1 us each); 23 us per block with one wave holding a row of 64 per lane,
+// and another 13 us for each solve with it, before.
+__device__ __forceinline__ void factor_diagonal(const factor_args &f, int o, int k, double *T, double *Wl)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int e = tid; e < NB * LT; e += 256) Wl[e] = 0.0;
+    __syncthreads();
+#pragma unroll 1
+    for (int p = 0; p < 4; ++p) {
+        double x[16];
+        const int r = min(16 * p + lane, NB - 1);            // row of the block (wave 0), or of the panel's own 16 (wave 1)
+        const bool row = wave == 0 ? 16 * p + lane < NB : lane < 16;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const double t = T[r * LT + 16 * p + c];
+            x[c] = row ? t : ((wave == 1 && lane == 16 + c) ? 1.0 : 0.0);
+        }
+        __syncthreads();                                     // both waves have read the panel
+        if (wave < 2) {
+            int bad = 0;
+            panel_column<0>(x, bad);
+            if (bad && tid == 0) atomicCAS(f.flag + o, 0, NB * k + 16 * p + bad);
+            if (wave == 0 && row) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) T[r * LT + 16 * p + c] = c <= lane ? x[c] : 0.0;
+            }
+            if (wave == 1 && lane >= 16 && lane < 32) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) Wl[(16 * p + c) * LT + 16 * p + lane - 16] = x[c];
+            }
+        }
+        __syncthreads();
+        // blocks (bi, bj), p < bj <= bi, numbered column by column
+        const int n = 3 - p, count = n * (n + 1) / 2;
+        for (int t = wave; t < count; t += 4) {
+            int bj = 0, left = t;
+            while (left >= n - bj) left -= n - bj++;
+            const int bi = p + 1 + bj + left;
+            bj += p + 1;
+            double *C = T + 16 * bi * LT + 16 * bj;
+            store16(C, block16<true, true>(load16(C), T + 16 * bi * LT + 16 * p, T + 16 * bj * LT + 16 * p));
+        }
+        __syncthreads();
+    }
+    const d4v zero = {0.0, 0.0, 0.0, 0.0};
+    if (wave < 2) {                                          // W10 = -W11 L10 W00 in the two 32 x 32 blocks
+        const int a = 32 * wave, b = a + 16;
+        const d4v t = block16<false, false>(zero, T + b * LT + a, Wl + a * LT + a);
+        store16(Wl + b * LT + a, block16_reg<true>(zero, Wl + b * LT + b, t));
+    }
+    __syncthreads();
+    {                                                        // and of the 64 x 64 block: block (2 + wave / 2, wave % 2)
+        const int bj = 16 * (wave & 1), bi = 32 + 16 * (wave >> 1);
+        d4v out = zero;
+        for (int c = 32; c <= bi; c += 16) {
+            d4v t = zero;
+            for (int q = bj; q < 32; q += 16) t = block16<false, false>(t, T + c * LT + q, Wl + q * LT + bj);
+            out = block16_reg<true>(out, Wl + bi * LT + c, t);
+        }
+        store16(Wl + bi * LT + bj, out);
+    }
+    __syncthreads();
+    double *Ug = f.U + o * f.sU + (size_t)(NB * k) * f.Np + NB * k;
+    const size_t ldv = f.V.row_length();
+    double *Vg = f.V.at(o, NB * k, NB * k), *Wg = f.W.at(o, NB * k, NB * k);
+    const int c = lane;
+#pragma unroll 4
+    for (int r = wave; r < NB; r += 4) {
+        Ug[(size_t)r * f.Np + c] = c >= r ? T[c * LT + r] : 0.0;
+        Vg[(size_t)r * ldv + c] = Wl[c * LT + r];
+        Wg[(size_t)r * ldv + c] = Wl[r * LT + c];
+    }
+    if (tid < NB) f.diag[(size_t)o * f.Np + NB * k + tid] = T[tid * LT + tid];
+}
+
+// First diagonal block of a range, for every output (blockIdx.x)
+__global__ __launch_bounds__(256) void factor_diagonal_kernel(factor_args f, int k)
+{
+    __shared__ __align__(16) double T[NB * LT], Wl[NB * LT];
+    const int o = blockIdx.x;
+    const double *src = f.K + o * f.sK + (size_t)(NB * k) * f.Np + NB * k;
+    // row r of the upper triangle is column r of the lower one
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {
+        const int r = e >> 6, c = e & 63;
+        const double v = src[(size_t)r * f.Np + c];
+        if (c >= r) T[c * LT + r] = v;
+        if (c > r) T[r * LT + c] = 0.0;
+    }
+    __syncthreads();
+    factor_diagonal(f, o, k, T, Wl);
+}
+
+// ---- one block column of the factorisation ------------------------------------------------------------------------
+// 64 x 64 block of a row-major matrix to LDS, rows of 64, by direct loads (two rows per wave and instruction)
+__device__ __forceinline__ void block_to_lds(const double *src, size_t ld, unsigned lds)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned off = 16u * (unsigned)(lane & 31) + (unsigned)(lane >> 5) * (unsigned)(ld * 8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        f64_tile::load_row_to_lds(src + (size_t)(2 * wave + 8 * e) * ld, off, lds + 1024u * (unsigned)wave + 4096u * e);
+}
+
+// acc = sum_c A[c][i] B[c][j] over 64 rows in LDS (rows of 64), in the accumulator layout of f64_tile
+__device__ __forceinline__ void lds_product(f64_tile::accumulators<64> &acc, const double *A, const double *B)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const double *pa = A + (lane >> 4) * NB + (wave >> 1) * 32 + 2 * (lane & 15);
+    const double *pb = B + (lane >> 4) * NB + (wave & 1) * 32 + 2 * (lane & 15);
+    f64_tile::clear(acc);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) {
+        const double2 a = *reinterpret_cast<const double2 *>(pa + 4 * s * NB), b = *reinterpret_cast<const double2 *>(pb + 4 * s * NB);
+        acc.v[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, acc.v[0][0], 0, 0, 0);
+        acc.v[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, acc.v[0][1], 0, 0, 0);
+        acc.v[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, acc.v[1][0], 0, 0, 0);
+        acc.v[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, acc.v[1][1], 0, 0, 0);
+    }
+}
+
+// Block column j = k + 1 + blockIdx.x of output blockIdx.y, with block row k factored on the diagonal:
+//   U_kj = L_kk^-1 K_kj, and for the rows i of the range (k < i < k_end, i <= j): K_ij -= U_ki^T U_kj.
+// U_ki is computed again by every column that needs it (at most three extra products of 64 x 64 x 64 per workgroup)
+// instead of waiting for another launch.  The workgroup of the next diagonal block goes on to factor it.
+// Bound: the chain of launches: 2 products and the diagonal block, about 14 us per block column for all outputs
+// together, where three launches per column and output took 50.
+constexpr size_t STEP_LDS = (size_t)4 * NB * NB * sizeof(double);
+static_assert(2 * NB * LT <= 4 * NB * NB, "the diagonal block and its inverse take the place of the blocks");
+__global__ __launch_bounds__(256) void chol_step_kernel(factor_args f, int k, int k_end)
+{
+    extern __shared__ __align__(16) double lds[];
+    double *Vb = lds, *Jb = lds + NB * NB, *Ib = lds + 2 * NB * NB;       // Ib: two blocks
+    const unsigned base = (unsigned)(size_t)(__attribute__((address_space(3))) double *)lds;
+    constexpr unsigned BLK = NB * NB * 8;
+    const int o = blockIdx.y, j = k + 1 + blockIdx.x;
+    const size_t Np = f.Np;
+    double *Krow = f.K + o * f.sK + (size_t)(NB * k) * Np;               // block row k of K
+    block_to_lds(f.V.at(o, NB * k, NB * k), f.V.row_length(), base);
+    block_to_lds(Krow + NB * j, Np, base + BLK);
+    const int i_last = j < k_end ? j : k_end - 1;                        // rows k + 1 .. i_last of this column
+    if (k + 1 < j && k + 1 <= i_last) block_to_lds(Krow + NB * (k + 1), Np, base + 2 * BLK);
+    f64_tile::wait_loads_at_most<0>();
+    __syncthreads();
+    const f64_tile::lane_pos pos = f64_tile::lane_position<64>();
+    f64_tile::accumulators<64> acc;
+    lds_product(acc, Vb, Jb);
+    __syncthreads();
+    double *Urow = f.U + o * f.sU + (size_t)(NB * k) * Np + NB * j;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = pos.row0 + e + 8 * r;
+            const double2 v = make_double2(acc.v[e][0][r], acc.v[e][1][r]);
+            *reinterpret_cast<double2 *>(Jb + row * NB + pos.col0) = v;
+            *reinterpret_cast<double2 *>(Urow + (size_t)row * Np + pos.col0) = v;
+        }
+    __syncthreads();
+    for (int i = k + 1; i <= i_last; ++i) {
+        const int s = (i - k - 1) & 1;
+        const double *Ui = Jb;
+        if (i < j) {
+            double *Is = Ib + s * NB * NB;
+            // the next row's block goes to the other buffer, which was last read before the barriers above
+            if (i + 1 < j && i + 1 <= i_last) block_to_lds(Krow + NB * (i + 1), Np, base + (2 + (s ^ 1)) * BLK);
+            lds_product(acc, Vb, Is);
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    *reinterpret_cast<double2 *>(Is + (pos.row0 + e + 8 * r) * NB + pos.col0) =
+                        make_double2(acc.v[e][0][r], acc.v[e][1][r]);
+            __syncthreads();
+            Ui = Is;
+        }
+        double *C = f.K + o * f.sK + (size_t)(NB * i) * Np + NB * j;
+        double2 cv[2][4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                cv[e][r] = *reinterpret_cast<const double2 *>(C + (size_t)(pos.row0 + e + 8 * r) * Np + pos.col0);
+        lds_product(acc, Ui, Jb);
+        const bool next = i == j && j == k + 1;                          // the next diagonal block: stays here
+        if (next) __syncthreads();                                       // (every wave is done with the blocks it overwrites)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int gi = i0 + pos.row0 + 16 * x + 4 * r;
-                const int gj = j0 + pos.col0 + 16 * y;
-                if (gi < Mr && gj < Nc) {
-                    double *dst = Cm + (long)gi * ldc + gj;
-                    *dst = (overwrite ? 0.0 : *dst) + alpha * acc[x][y][r];
+                const int row = pos.row0 + e + 8 * r;
+                const double2 v = make_double2(cv[e][r].x - acc.v[e][0][r], cv[e][r].y - acc.v[e][1][r]);
+                if (next) {                                              // upper entry (row, col) is lower entry (col, row)
+                    double *T = lds;
+                    if (pos.col0 >= row) T[pos.col0 * LT + row] = v.x;
+                    if (pos.col0 + 1 >= row) T[(pos.col0 + 1) * LT + row] = v.y;
+                    if (pos.col0 > row) T[row * LT + pos.col0] = 0.0;
+                    if (pos.col0 + 1 > row) T[row * LT + pos.col0 + 1] = 0.0;
+                } else {
+                    *reinterpret_cast<double2 *>(C + (size_t)row * Np + pos.col0) = v;
+                }
+            }
+        f64_tile::wait_loads_at_most<0>();                               // the next row's block, if requested, has landed
+        __syncthreads();
+        if (next) factor_diagonal(f, o, j, lds, lds + NB * LT);
+    }
+}
+
+// ---- products -----------------------------------------------------------------------------------------------------
+// C (ni x nj) -= or = sum_k A[k][i] B[k][j] for every output (blockIdx.z); upper: tiles that lie below the diagonal
+// of C are left out.
+struct gemm_args {
+    const double *A, *B;
+    double *C;
+    size_t lda, ldb, ldc, sA, sB, sC;
+    int ni, nj, K;
+    int subtract, upper;
+};
+
+template <int T>
+__global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_kernel(gemm_args g)
+{
+    __shared__ __align__(16) double lds[f64_tile::shape<T>::LDS_DOUBLES];
+    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T, o = blockIdx.z;
+    if (g.upper && j0 + T <= i0) return;
+    f64_tile::accumulators<T> acc;
+    f64_tile::clear(acc);
+    f64_tile::product<T>(acc, lds, i0, j0, g.ni, g.nj, g.K, g.A + o * g.sA, g.lda, g.B + o * g.sB, g.ldb);
+    const f64_tile::lane_pos pos = f64_tile::lane_position<T>();
+    constexpr int H = f64_tile::shape<T>::H;
+    double *C = g.C + o * g.sC;
+#pragma unroll
+    for (int x = 0; x < 2 * H; ++x)
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gi = i0 + pos.row0 + 32 * (x >> 1) + (x & 1) + 8 * r, gj = j0 + pos.col0 + 32 * h;
+                if (gi < g.ni && gj < g.nj) {
+                    double2 *dst = reinterpret_cast<double2 *>(C + (size_t)gi * g.ldc + gj);
+                    double2 v = make_double2(acc.v[x][2 * h][r], acc.v[x][2 * h + 1][r]);
+                    if (g.subtract) {
+                        const double2 c = *dst;
+                        v = make_double2(c.x - v.x, c.y - v.y);
+                    }
+                    *dst = v;
                 }
             }
 }
 
-// The kernels below work on 64 x 64 blocks with one wave, lane = row or column of the block, the
-// lane's vector in registers and the shared triangular block in LDS, read as broadcasts.  What bounds
-// them is the latency between an LDS read and the FMA that uses it, so every step requests the
-// triangular row it needs as one burst of reads one step ahead (scheduling barriers keep the burst
-// together) and then runs independent FMAs on values that have already arrived.
-constexpr int LDB = NB + 2;      // LDS row stride: rows stay 16-byte aligned for two-element reads
-
-// A 64 x 64 block of a row-major matrix <-> LDS, by one wave: lane = column, so every global access is
-// one contiguous row; all 64 loads are requested before the first one is used.
-template <bool TRANSPOSE>
-__device__ __forceinline__ void block_to_lds(const double *__restrict__ src, size_t ld, double (*dst)[LDB])
+// Does a launch of `tiles` tiles of 128 fill whole passes over the chip?  A tile of 128 keeps a compute unit's
+// matrix pipes busy on its own, one of 64 takes a quarter of its time: the large tile wins by 5 % where its
+// last pass is nearly full (measured on the product of the posterior step, posterior.hip) and loses what is
+// missing there otherwise.
+bool whole_passes(long tiles)
 {
-    const int r = threadIdx.x;
-    double t[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) t[i] = src[(size_t)i * ld + r];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        if (TRANSPOSE) dst[r][i] = t[i];
-        else dst[i][r] = t[i];
-    }
+    const long passes = (tiles + 255) / 256;
+    return 100 * tiles >= 95 * 256 * passes;
 }
 
-__device__ __forceinline__ void lds_to_block(double (*src)[LDB], double *__restrict__ dst, size_t ld)
+void gemm(hipStream_t st, int outputs, const gemm_args &g)
 {
-    const int r = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) dst[(size_t)i * ld + r] = src[i][r];
+    if (g.ni <= 0 || g.nj <= 0 || g.K <= 0) return;
+    const long ti = (g.ni + 127) / 128, tj = (g.nj + 127) / 128;
+    const long tiles = outputs * (g.upper ? ti * tj - ti * (ti - 1) / 2 : ti * tj);
+    if (whole_passes(tiles))
+        hipLaunchKernelGGL(gemm_kernel<128>, dim3(tj, ti, outputs), dim3(256), 0, st, g);
+    else
+        hipLaunchKernelGGL(gemm_kernel<64>, dim3((g.nj + 63) / 64, (g.ni + 63) / 64, outputs), dim3(256), 0, st, g);
 }
 
-constexpr int CH = 16;           // entries of a triangular row requested per burst
+// ---- inverse of the factor -----------------------------------------------------------------------------------------
+// One level: in pairs of neighbouring diagonal blocks of h (64-blocks each; the second of the last pair may be
+// shorter), with U = [U11 U12; 0 U22], V = U^-1, W = V^T and the diagonal blocks of V and W known,
+//   first launch   T[j][i] = sum_c U12[c][j] W11[c][i]            (T = (W11 ... )^T, c >= i)
+//   second launch  W21[j][i] = - sum_c V22[c][j] T[c][i] = V12[i][j]  (c <= j)
+// blockIdx.z = output * pairs + pair; T goes to the lower triangle of K.  Every level is two launches for all pairs and
+// outputs: log2(N / 64) of them instead of a chain of N / 64 block solves.
+struct level_args {
+    const double *U;
+    double *T;
+    size_t sU, sT;
+    tri_matrix V, W;
+    int Np, h, pairs;
+};
 
-// entries [16 q, 16 q + 16) of a row of the shared block, as one burst of broadcast reads
-__device__ __forceinline__ void read_chunk(const double *row, int q, double (&dst)[CH])
+template <bool SECOND>
+__global__ __launch_bounds__(256, 3) void inverse_level_kernel(level_args a)
 {
+    __shared__ __align__(16) double lds[f64_tile::shape<64>::LDS_DOUBLES];
+    const int o = blockIdx.z / a.pairs, p = blockIdx.z - o * a.pairs;
+    const int r1 = 2 * p * a.h * NB, r2 = r1 + a.h * NB;                     // first rows of the two blocks
+    const int n2 = min(a.h * NB, a.Np - r2);
+    const int j0 = blockIdx.y * NB, i0 = blockIdx.x * NB;                    // row of block 2, column of block 1
+    if (j0 >= n2) return;
+    const size_t Np = a.Np;
+    f64_tile::accumulators<64> acc;
+    f64_tile::clear(acc);
+    const double *U12 = a.U + o * a.sU + (size_t)r1 * Np + r2;
+    double *T = a.T + o * a.sT + (size_t)r2 * Np + r1;
+    const size_t ldv = a.V.row_length();
+    if (!SECOND)
+        f64_tile::product<64>(acc, lds, j0, i0, n2, a.h * NB, a.h * NB - i0, U12 + (size_t)i0 * Np, Np,
+                              a.W.at(o, r1, r1) + (size_t)i0 * ldv, ldv);
+    else
+        f64_tile::product<64>(acc, lds, j0, i0, n2, a.h * NB, j0 + NB, a.V.at(o, r2, r2), ldv, T, Np);
+    const f64_tile::lane_pos pos = f64_tile::lane_position<64>();
+    double *W21 = a.W.at(o, r2, r1) + (size_t)j0 * ldv + i0, *V12 = a.V.at(o, r1, r2) + (size_t)i0 * ldv + j0;
 #pragma unroll
-    for (int e = 0; e < CH; ++e) dst[e] = row[q * CH + e];
-}
-
-// x <- L^-1 x for the lane's vector x, L lower triangular, given as its transpose Lt[i][c] = L[c][i]
-// and the reciprocals of its diagonal: column by column, x[c] -= x[i] L[c][i] for c > i.
-// The lane's vector takes half of the directly addressable registers, so the rows of Lt come in
-// chunks of 16 entries, the next chunk in flight while the FMAs of the current one issue.
-// One template instance per (row I, chunk Q): every register index is a compile-time constant.
-template <int I, int Q, int IDX>
-__device__ __forceinline__ void lower_item(double (&x)[NB], double (*Lt)[LDB], const double *rinv,
-                                           double (&buf)[2][CH], double rc)
-{
-    constexpr int NQ = NB / CH;
-    if constexpr (Q == (I + 1) / CH) x[I] *= rc;                  // first chunk of the row: x[I] is final
-    constexpr bool same_row = Q + 1 < NQ;
-    constexpr bool next_row = !same_row && (I + 2) / CH < NQ;     // row I + 1 has entries right of its diagonal
-    double rn = rc;
-    if constexpr (same_row) {
-        read_chunk(Lt[I], Q + 1, buf[(IDX + 1) & 1]);
-    } else {
-        rn = rinv[I + 1];
-        if constexpr (next_row) read_chunk(Lt[I + 1], (I + 2) / CH, buf[(IDX + 1) & 1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int r = 0; r < 4; ++r) {
+        const int row = pos.row0 + 8 * r;                                    // rows row, row + 1; columns col0, col0 + 1
+        if (!SECOND) {
 #pragma unroll
-    for (int e = 0; e < CH; ++e) {
-        const int c = Q * CH + e;
-        if (c > I) x[c] = fma(-x[I], buf[IDX & 1][e], x[c]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (same_row) lower_item<I, Q + 1, IDX + 1>(x, Lt, rinv, buf, rc);
-    else if constexpr (next_row) lower_item<I + 1, (I + 2) / CH, IDX + 1>(x, Lt, rinv, buf, rn);
-    else x[I + 1] *= rn;                                         // the last row has nothing right of its diagonal
-}
-
-__device__ __forceinline__ void solve_lower(double (&x)[NB], double (*Lt)[LDB], const double *rinv)
-{
-    double buf[2][CH];
-    read_chunk(Lt[0], 0, buf[0]);
-    lower_item<0, 0, 0>(x, Lt, rinv, buf, rinv[0]);
-}
-
-// x <- L^-T x, L given by rows: from the last entry up, x[c] -= x[i] L[i][c] for c < i.
-template <int I, int Q, int IDX>
-__device__ __forceinline__ void upper_item(double (&x)[NB], double (*Ls)[LDB], const double *rinv,
-                                           double (&buf)[2][CH], double rc)
-{
-    if constexpr (Q == 0) x[I] *= rc;
-    constexpr bool same_row = Q + 1 <= (I - 1) / CH;
-    constexpr bool next_row = !same_row && I - 1 >= 1;
-    double rn = rc;
-    if constexpr (same_row) {
-        read_chunk(Ls[I], Q + 1, buf[(IDX + 1) & 1]);
-    } else {
-        rn = rinv[I - 1];
-        if constexpr (next_row) read_chunk(Ls[I - 1], 0, buf[(IDX + 1) & 1]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 2; ++e)
+                *reinterpret_cast<double2 *>(T + (size_t)(j0 + row + e) * Np + i0 + pos.col0) =
+                    make_double2(acc.v[e][0][r], acc.v[e][1][r]);
+        } else {
 #pragma unroll
-    for (int e = 0; e < CH; ++e) {
-        const int c = Q * CH + e;
-        if (c < I) x[c] = fma(-x[I], buf[IDX & 1][e], x[c]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (same_row) upper_item<I, Q + 1, IDX + 1>(x, Ls, rinv, buf, rc);
-    else if constexpr (next_row) upper_item<I - 1, 0, IDX + 1>(x, Ls, rinv, buf, rn);
-    else x[0] *= rn;
-}
-
-__device__ __forceinline__ void solve_lower_transposed(double (&x)[NB], double (*Ls)[LDB], const double *rinv)
-{
-    double buf[2][CH];
-    read_chunk(Ls[NB - 1], 0, buf[0]);
-    upper_item<NB - 1, 0, 0>(x, Ls, rinv, buf, rinv[NB - 1]);
-}
-
-// Step J of the factorisation of a diagonal block (see potrf_diag_kernel)
-template <int J>
-__device__ __forceinline__ void potrf_step(double (&a)[NB], double (*col)[NB], int r, int *__restrict__ flag,
-                                           int flag_value)
-{
-    constexpr int NQ = NB / CH;
-    const double d = __shfl(a[J], J);
-    if (!(d > 0.0) && r == 0) atomicCAS(flag, 0, flag_value + J);
-    // keep going with a harmless pivot so that the result stays finite
-    const double piv = (d > 0.0) ? sqrt(d) : 1.0;
-    const double l = (r == J) ? piv : a[J] / piv;
-    a[J] = l;
-    if constexpr (J + 1 < NB) {
-        col[J & 1][r] = l;
-        __syncthreads();
-        // the column comes back in chunks of 16, the next chunk in flight under the FMAs of this one
-        double buf[2][CH];
-        constexpr int Q0 = (J + 1) / CH;
-        read_chunk(col[J & 1], Q0, buf[Q0 & 1]);
-#pragma unroll
-        for (int q = Q0; q < NQ; ++q) {
-            if (q + 1 < NQ) read_chunk(col[J & 1], q + 1, buf[(q + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int e = 0; e < CH; ++e) {
-                const int c = q * CH + e;
-                if (c > J) a[c] = fma(-l, buf[q & 1][e], a[c]);
+            for (int e = 0; e < 2; ++e) {
+                *reinterpret_cast<double2 *>(W21 + (size_t)(row + e) * ldv + pos.col0) =
+                    make_double2(-acc.v[e][0][r], -acc.v[e][1][r]);
+                *reinterpret_cast<double2 *>(V12 + (size_t)(pos.col0 + e) * ldv + row) =
+                    make_double2(-acc.v[0][e][r], -acc.v[1][e][r]);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
-        potrf_step<J + 1>(a, col, r, flag, flag_value);
     }
 }
 
-// Factor the NB x NB diagonal block at (k,k) in place (lower).  Lane = row, the row lives in
-// registers; right-looking: at step j the pivot comes from lane j, every lane scales its entry of
-// column j, the column is broadcast through LDS and each lane updates the rest of its row with
-// independent FMAs.  Entries above the diagonal are kept at zero, so no lane needs a predicate.
-// Sets *flag = 1 + global row index on a pivot that is not positive.
-__global__ __launch_bounds__(NB) void potrf_diag_kernel(double *__restrict__ K, int Np, int k, int flag_base,
-                                                        int *__restrict__ flag)
+// U's blocks above the diagonal, transposed, to their places below it
+__global__ __launch_bounds__(256) void mirror_factor_kernel(double *__restrict__ U, size_t sU, int Np)
 {
-    __shared__ __align__(16) double Ls[NB][LDB];
-    __shared__ __align__(16) double col[2][NB];
-    const int r = threadIdx.x;
-    block_to_lds<false>(K + (size_t)k * Np + k, Np, Ls);
+    if (blockIdx.x <= blockIdx.y) return;
+    __shared__ double t[NB][NB + 1];
+    double *src = U + blockIdx.z * sU + (size_t)(blockIdx.y * NB) * Np + blockIdx.x * NB;
+    double *dst = U + blockIdx.z * sU + (size_t)(blockIdx.x * NB) * Np + blockIdx.y * NB;
+    const int c = threadIdx.x & 63;
+    for (int r = threadIdx.x >> 6; r < NB; r += 4) t[r][c] = src[(size_t)r * Np + c];
     __syncthreads();
-    double a[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) a[c] = (c <= r) ? Ls[r][c] : 0.0;
-    potrf_step<0>(a, col, r, flag, 1 + flag_base + k);
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NB; ++c) Ls[r][c] = a[c];
-    __syncthreads();
-    lds_to_block(Ls, K + (size_t)k * Np + k, Np);
+    for (int r = threadIdx.x >> 6; r < NB; r += 4) dst[(size_t)r * Np + c] = t[c][r];
 }
-
-// Diagonal block L_kk into LDS (by rows, or transposed), with the reciprocals of its diagonal beside it
-template <bool TRANSPOSE>
-__device__ __forceinline__ void load_diag_block(const double *__restrict__ K, int Np, int k, double (*Ls)[LDB],
-                                                double *rinv)
-{
-    block_to_lds<TRANSPOSE>(K + (size_t)k * Np + k, Np, Ls);
-    __syncthreads();
-    rinv[threadIdx.x] = 1.0 / Ls[threadIdx.x][threadIdx.x];
-    __syncthreads();
-}
-
-// Panel solve: rows i >= k+NB of columns k..k+NB-1:  P <- P * L_kk^-T, which is a forward substitution
-// with L_kk on every row of P.  One wave per 64 rows, lane = row; the rows go through LDS so that
-// global accesses are coalesced.
-__global__ __launch_bounds__(NB) void trsm_panel_kernel(double *__restrict__ K, int Np, int k)
-{
-    __shared__ __align__(16) double Lt[NB][LDB];
-    __shared__ __align__(16) double Ps[NB][LDB];
-    __shared__ double rinv[NB];
-    load_diag_block<true>(K, Np, k, Lt, rinv);
-    const int r = threadIdx.x;
-    const int i0 = k + NB + blockIdx.x * NB;            // Np is a multiple of NB: the block of rows is whole
-    block_to_lds<false>(K + (size_t)i0 * Np + k, Np, Ps);
-    __syncthreads();
-    double x[NB];
-#pragma unroll
-    for (int j = 0; j < NB; ++j) x[j] = Ps[r][j];
-    solve_lower(x, Lt, rinv);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) Ps[r][j] = x[j];
-    __syncthreads();
-    lds_to_block(Ps, K + (size_t)i0 * Np + k, Np);
-}
-
-// Forward substitution on block k for all right-hand sides: Z_k = L_kk^-1 R_k.  Lane = column s.
-__global__ __launch_bounds__(NB) void trsv_fwd_kernel(const double *__restrict__ K, int Np, int k,
-                                                      double *__restrict__ R, int S)
-{
-    __shared__ __align__(16) double Lt[NB][LDB];
-    __shared__ double rinv[NB];
-    load_diag_block<true>(K, Np, k, Lt, rinv);
-    const int s = blockIdx.x * NB + threadIdx.x;
-    if (s >= S) return;
-    double z[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) z[i] = R[(size_t)(k + i) * S + s];
-    solve_lower(z, Lt, rinv);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) R[(size_t)(k + i) * S + s] = z[i];
-}
-
-// Backward substitution on block k: V_k = L_kk^-T Z_k.
-__global__ __launch_bounds__(NB) void trsv_bwd_kernel(const double *__restrict__ K, int Np, int k,
-                                                      double *__restrict__ R, int S)
-{
-    __shared__ __align__(16) double Ls[NB][LDB];
-    __shared__ double rinv[NB];
-    load_diag_block<false>(K, Np, k, Ls, rinv);
-    const int s = blockIdx.x * NB + threadIdx.x;
-    if (s >= S) return;
-    double z[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) z[i] = R[(size_t)(k + i) * S + s];
-    solve_lower_transposed(z, Ls, rinv);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) R[(size_t)(k + i) * S + s] = z[i];
-}
-
-// V[n][s] (float64) -> v_out[s][m][n] (float32) and the packed stream v4[m][n4][s]
-__global__ void emit_v_kernel(const double *__restrict__ V, float *__restrict__ v_out, float4 *__restrict__ v4,
-                              int N, int Npk, int S, int M, int m)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n4 = blockIdx.y;
-    if (s >= S) return;
-    float t[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int n = n4 * 4 + j;
-        t[j] = n < N ? (float)V[(size_t)n * S + s] : 0.0f;
-        if (v_out && n < N) v_out[((size_t)s * M + m) * N + n] = t[j];
-    }
-    v4[((size_t)m * (Npk / 4) + n4) * S + s] = make_float4(t[0], t[1], t[2], t[3]);
-}
-
-void gemm(hipStream_t st, int Mr, int Nc, int Kd, double alpha, const double *A, long sai, long sak,
-          const double *Bm, long sbk, long sbj, double *Cm, long ldc, bool lower_only, bool overwrite = false,
-          int diag = 0)
-{
-    if (Mr <= 0 || Nc <= 0 || Kd <= 0) return;
-    dim3 grid((Nc + TN - 1) / TN, (Mr + TM - 1) / TM);
-    hipLaunchKernelGGL(dgemm_kernel, grid, dim3(256), 0, st, Mr, Nc, Kd, alpha, A, sai, sak, Bm, sbk, sbj, Cm, ldc,
-                       lower_only ? 1 : 0, diag, overwrite ? 1 : 0);
-}
-
-// In-place blocked Cholesky of K [Np][Np] (lower; Np a multiple of NB), then K_hat^-1 applied to the S
-// right-hand sides R [Np][S] in place.  A pivot that is not positive is reported through *flag.
-// Recursive blocking: a range of columns (or of unknowns) is split in halves, the first half is done,
-// one product as deep as that half updates the second half, then the second half is done; ranges of
-// at most OB columns advance in steps of NB with the one-wave block kernels.  A product only NB deep
-// reads and writes every element it updates for NB multiply-adds on it, which is bound by memory
-// traffic; the deep products of the upper levels, which carry most of the work, are bound by the
-// matrix pipe.  (Flat blocking with 256-deep updates: 283 ms per hyper-parameter iteration at
-// N = 8192; 512 deep: 270 ms; 1024 deep: 278 ms.)
-constexpr int OB = 256;
 
 struct solver {
     hipStream_t st;
-    double *K;
-    int Np;
-    double *R;
-    int S;
-    int flag_base;
-    int *flag;
+    factor_args f;
+    int nb, outputs;             // 64-blocks per row, outputs worked on
 
-    static int half(int n) { return (n / NB + 1) / 2 * NB; }       // first part of a split, a multiple of NB
+    static int half(int w) { return (w / RB + 1) / 2 * RB; }     // first part of a split, a whole number of ranges
 
-    // columns [k, k + w) of the factor, for all rows down to Np
-    void panel(int k, int w)
+    // block columns [k, k + w) of the factor (block rows of U), for all columns to the right
+    void factor(int k, int w)
     {
-        if (w > OB) {
-            const int h = half(w);
-            panel(k, h);
-            // K[i][j] -= sum_c P[i][c] P[j][c] for i >= j in the rest of the range, P = columns [k, k + h)
-            const double *Pn = K + (size_t)(k + h) * Np + k;
-            gemm(st, Np - k - h, w - h, h, -1.0, Pn, Np, 1, Pn, 1, Np, K + (size_t)(k + h) * Np + (k + h), Np, true);
-            panel(k + h, w - h);
+        if (w > RB) {
+            const int h = half(w), r = NB * (k + h);
+            factor(k, h);
+            const double *P = f.U + (size_t)(NB * k) * f.Np + r;
+            gemm_args g = {P, P, f.K + (size_t)r * f.Np + r, (size_t)f.Np, (size_t)f.Np, (size_t)f.Np, f.sU, f.sU, f.sK,
+                           NB * (w - h), f.Np - r, NB * h, 1, 1};
+            gemm(st, outputs, g);
+            factor(k + h, w - h);
             return;
         }
-        for (int kk = k; kk < k + w; kk += NB) {
-            hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(NB), 0, st, K, Np, kk, flag_base, flag);
-            const int below = Np - kk - NB;
-            if (below <= 0) continue;
-            hipLaunchKernelGGL(trsm_panel_kernel, dim3(below / NB), dim3(NB), 0, st, K, Np, kk);
-            const int cols = k + w - kk - NB;           // columns of the range still to be factored
-            const double *Pn = K + (size_t)(kk + NB) * Np + kk;
-            if (cols > 0)
-                gemm(st, below, cols, NB, -1.0, Pn, Np, 1, Pn, 1, Np, K + (size_t)(kk + NB) * Np + (kk + NB), Np, true);
+        hipLaunchKernelGGL(factor_diagonal_kernel, dim3(outputs), dim3(256), 0, st, f, k);
+        for (int kk = k; kk < k + w && kk + 1 < nb; ++kk)
+            hipLaunchKernelGGL(chol_step_kernel, dim3(nb - kk - 1, outputs), dim3(256), STEP_LDS, st, f, kk, k + w);
+    }
+
+    // V and W inside diagonal blocks of `size` 64-blocks (K's lower triangle is the work space)
+    void triangular_inverse(int size)
+    {
+        for (int h = 1; h < size && h < nb; h *= 2) {
+            const int pairs = (nb + h - 1) / (2 * h);
+            level_args a = {f.U, f.K, f.sU, f.sK, f.V, f.W, f.Np, h, pairs};
+            const dim3 grid(h, h, outputs * pairs);
+            hipLaunchKernelGGL(inverse_level_kernel<false>, grid, dim3(256), 0, st, a);
+            hipLaunchKernelGGL(inverse_level_kernel<true>, grid, dim3(256), 0, st, a);
         }
     }
 
-    // forward substitution L Z = R on the unknowns [k, k + n); the rows below are updated by the caller
-    void forward(int k, int n)
+    // right-hand sides of all outputs: [Np][ld] each, `stride` apart
+    struct rhs {
+        double *p;
+        size_t stride, ld;
+        double *row(int r) const { return p + (size_t)r * ld; }
+    };
+
+    // One range of unknowns [64 k, 64 (k + w)), w <= RB: out = W in (forward: the rows of V are the columns of W) or V in
+    void solve_range(bool fwd, int k, int w, const rhs &in, const rhs &out)
     {
-        if (n > OB) {
-            const int h = half(n);
-            forward(k, h);
-            gemm(st, n - h, S, h, -1.0, K + (size_t)(k + h) * Np + k, Np, 1, R + (size_t)k * S, S, 1,
-                 R + (size_t)(k + h) * S, S, false);
-            forward(k + h, n - h);
-            return;
-        }
-        for (int kk = k; kk < k + n; kk += NB) {
-            hipLaunchKernelGGL(trsv_fwd_kernel, dim3((S + NB - 1) / NB), dim3(NB), 0, st, K, Np, kk, R, S);
-            const int rows = k + n - kk - NB;
-            if (rows > 0)
-                gemm(st, rows, S, NB, -1.0, K + (size_t)(kk + NB) * Np + kk, Np, 1, R + (size_t)kk * S, S, 1,
-                     R + (size_t)(kk + NB) * S, S, false);
-        }
+        const tri_matrix &M = fwd ? f.V : f.W;
+        gemm_args g = {M.p + (size_t)(NB * k) * (NB * RB), in.row(NB * k), out.row(NB * k), (size_t)(NB * RB), in.ld, out.ld,
+                       M.stride, in.stride, out.stride, NB * w, (int)in.ld, NB * w, 0, 0};
+        gemm(st, outputs, g);
     }
 
-    // The same with R = identity (S = Np columns): Z = L^-1 is lower triangular, so while the unknowns
-    // [k, k + n) are worked on only the columns below k + n hold anything; the products and block
-    // solves stop there, which leaves N^3/4 of the N^3/2 multiply-adds of the general case.
-    void forward_identity(int k, int n)
+    // Z = L^-1 R on the unknowns of blocks [k, k + w); R's rows below are updated by the caller.  R is used up.
+    void forward(int k, int w, const rhs &R, const rhs &Z)
     {
-        if (n > OB) {
-            const int h = half(n);
-            forward_identity(k, h);
-            gemm(st, n - h, k + h, h, -1.0, K + (size_t)(k + h) * Np + k, Np, 1, R + (size_t)k * S, S, 1,
-                 R + (size_t)(k + h) * S, S, false);
-            forward_identity(k + h, n - h);
-            return;
-        }
-        for (int kk = k; kk < k + n; kk += NB) {
-            hipLaunchKernelGGL(trsv_fwd_kernel, dim3((kk + NB) / NB), dim3(NB), 0, st, K, Np, kk, R, S);
-            const int rows = k + n - kk - NB;
-            if (rows > 0)
-                gemm(st, rows, kk + NB, NB, -1.0, K + (size_t)(kk + NB) * Np + kk, Np, 1, R + (size_t)kk * S, S, 1,
-                     R + (size_t)(kk + NB) * S, S, false);
-        }
+        if (w <= RB) return solve_range(true, k, w, R, Z);
+        const int h = half(w), r = NB * (k + h);
+        forward(k, h, R, Z);
+        gemm_args g = {f.U + (size_t)(NB * k) * f.Np + r, Z.row(NB * k), R.row(r), (size_t)f.Np, Z.ld, R.ld,
+                       f.sU, Z.stride, R.stride, NB * (w - h), (int)R.ld, NB * h, 1, 0};
+        gemm(st, outputs, g);
+        forward(k + h, w - h, R, Z);
     }
 
-    // backward substitution L^T V = Z on the unknowns [k, k + n)
-    void backward(int k, int n)
+    // X = L^-T Z likewise, from the last block up (needs the mirrored factor)
+    void backward(int k, int w, const rhs &Z, const rhs &X)
     {
-        if (n > OB) {
-            const int h = half(n);
-            backward(k + h, n - h);
-            // R[k : k+h] -= L[k+h : k+n, k : k+h]^T V[k+h : k+n] : A(i, c) = K[(k+h+c)*Np + k + i]
-            gemm(st, h, S, n - h, -1.0, K + (size_t)(k + h) * Np + k, 1, Np, R + (size_t)(k + h) * S, S, 1,
-                 R + (size_t)k * S, S, false);
-            backward(k, h);
-            return;
-        }
-        for (int kk = k + n - NB; kk >= k; kk -= NB) {
-            hipLaunchKernelGGL(trsv_bwd_kernel, dim3((S + NB - 1) / NB), dim3(NB), 0, st, K, Np, kk, R, S);
-            if (kk > k)   // R[k:kk] -= L[kk:kk+NB, k:kk]^T V_kk : A(i, c) = K[(kk+c)*Np + k + i]
-                gemm(st, kk - k, S, NB, -1.0, K + (size_t)kk * Np + k, 1, Np, R + (size_t)kk * S, S, 1,
-                     R + (size_t)k * S, S, false);
-        }
+        if (w <= RB) return solve_range(false, k, w, Z, X);
+        const int h = half(w), r = NB * (k + h);
+        backward(k + h, w - h, Z, X);
+        gemm_args g = {f.U + (size_t)r * f.Np + NB * k, X.row(r), Z.row(NB * k), (size_t)f.Np, X.ld, Z.ld,
+                       f.sU, X.stride, Z.stride, NB * h, (int)Z.ld, NB * (w - h), 1, 0};
+        gemm(st, outputs, g);
+        backward(k, h, Z, X);
     }
 };
 
-void factor_and_solve(hipStream_t st, double *K, int Np, double *R, int S, int flag_base, int *flag)
+// ---- K_hat^-1 ------------------------------------------------------------------------------------------------------
+// out[i] = sum_j A[i][j] v[j] for a triangular matrix of whole 64-blocks (upper: j >= 64 (i / 64), lower: j up to the
+// block's end), one wave per row, the lanes' sums added by a fixed butterfly.  v: float y[N] (zero past N) or
+// double.  Grid (Np / 4, outputs).
+__global__ __launch_bounds__(256) void triangle_times_vector_kernel(tri_matrix A, int upper, const float *__restrict__ yf,
+                                                                    const double *__restrict__ v, double *__restrict__ out, int N,
+                                                                    int Np, int m0)
 {
-    solver s{st, K, Np, R, S, flag_base, flag};
-    s.panel(0, Np);
-    s.forward(0, Np);
-    s.backward(0, Np);
-}
-
-// Z = identity [Np][Np]; yd[n] = y[n] in float64 (zero on the padding)
-__global__ void inverse_init_kernel(const float *__restrict__ y_m, double *__restrict__ Z, double *__restrict__ yd, int N,
-                                    int Np)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n = blockIdx.y;
-    if (j >= Np) return;
-    Z[(size_t)n * Np + j] = (j == n) ? 1.0 : 0.0;
-    if (n == 0) yd[j] = (j < N) ? (double)y_m[j] : 0.0;
-}
-
-// A[j][i] = A[i][j] for j > i, 32 x 32 blocks through LDS so that reads and writes are both row segments
-__global__ __launch_bounds__(256) void mirror_lower_kernel(double *__restrict__ A, int Np)
-{
-    __shared__ double t[32][33];
-    const int bi = blockIdx.y, bj = blockIdx.x;      // source block (rows bi, columns bj), bj <= bi
-    if (bj > bi) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) t[r][tx] = A[(size_t)(32 * bi + r) * Np + 32 * bj + tx];
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int row = 32 * bj + r, col = 32 * bi + tx;          // destination (row, col) = source (col, row)
-        if (col > row) A[(size_t)row * Np + col] = t[tx][r];
-    }
-}
-
-// out[i] = sum_k A[i][k] y[k] for a square row-major matrix: one wave per row, the lanes walk the row
-// together (contiguous reads), their sums are added by a fixed butterfly.
-__global__ __launch_bounds__(256) void matrix_times_vector_kernel(const double *__restrict__ A, const double *__restrict__ y,
-                                                                  double *__restrict__ out, int Np)
-{
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, o = blockIdx.y;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= Np) return;
-    const double *row = A + (size_t)i * Np;
+    const int j0 = upper ? i / NB * NB : 0, j1 = upper ? Np : i / NB * NB + NB;
+    const double *row = A.at(o, i, 0);
     double s = 0.0;
-    for (int k = lane; k < Np; k += 64) s += row[k] * y[k];
+    for (int j = j0 + lane; j < j1; j += 64)
+        s += row[j] * (yf ? (j < N ? (double)yf[(size_t)(m0 + o) * N + j] : 0.0) : v[(size_t)o * Np + j]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) out[i] = s;
+    if (lane == 0) out[(size_t)o * Np + i] = s;
 }
 
-// K_hat^-1 and alpha = K_hat^-1 y from the factor L in K (eq. (2), (3), (5), (6) all need both):
-// Z = L^-1 by structured forward substitution on the identity, K_hat^-1 = Z^T Z on and below the
-// diagonal in row panels (entry (i, j) only sums over k >= max(i, j), so a panel that starts at row
-// i0 contracts over Np - i0 rows of Z), mirrored into the upper triangle; alpha = K_hat^-1 y as a
-// matrix-vector product.  N^3/4 + N^3/6 multiply-adds after the N^3/6 of the factorisation, against N^3
-// for substitution both ways on N right-hand sides.  Z [Np][Np] and yd [Np] are work space; Kinv and
-// alpha the results.
-constexpr int INV_PANEL = 512;
-
-void inverse_from_factor(hipStream_t st, double *K, int Np, double *Z, const float *y_m, int N, double *yd, double *Kinv,
-                         double *alpha, int flag_base, int *flag)
+// Lower tile t = (bi, bj), bj <= bi, of the 64-blocks, numbered row by row: the tiles with the longest sums come first
+__device__ __forceinline__ void lower_tile(int t, int &bi, int &bj)
 {
-    hipLaunchKernelGGL(inverse_init_kernel, dim3((Np + 255) / 256, Np), dim3(256), 0, st, y_m, Z, yd, N, Np);
-    solver s{st, K, Np, Z, Np, flag_base, flag};
-    s.panel(0, Np);
-    s.forward_identity(0, Np);
-    for (int i0 = 0; i0 < Np; i0 += INV_PANEL) {
-        const int hb = Np - i0 < INV_PANEL ? Np - i0 : INV_PANEL;
-        // Kinv[i0 + i][j] = sum_k Z[i0 + k][i0 + i] Z[i0 + k][j], j <= i0 + i
-        gemm(st, hb, i0 + hb, Np - i0, 1.0, Z + (size_t)i0 * Np + i0, 1, Np, Z + (size_t)i0 * Np, Np, 1,
-             Kinv + (size_t)i0 * Np, Np, true, true, i0);
-    }
-    hipLaunchKernelGGL(mirror_lower_kernel, dim3(Np / 32, Np / 32), dim3(256), 0, st, Kinv, Np);
-    hipLaunchKernelGGL(matrix_times_vector_kernel, dim3((Np + 3) / 4), dim3(256), 0, st, Kinv, yd, alpha, Np);
+    bi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+    while (bi * (bi + 1) / 2 > t) --bi;
+    bj = t - bi * (bi + 1) / 2;
 }
 
-// ---- hyper-parameter learning: log marginal likelihood and its gradient (eq. (5), (6)) ----------
-// K_hat for hyper-parameters given as logarithms on the device: lh = (log l_1 .. log l_D, log alpha^2,
-// log sigma_n^2); identity on the padding
-__global__ void build_khat_log_kernel(const float *__restrict__ X, const float *__restrict__ lh, double *__restrict__ K,
-                                      int N, int Np, int D)
+// Block (bi, bj) of K_hat^-1 = W^T W: entry (i, j) sums over k >= 64 bi
+__device__ __forceinline__ void inverse_tile(f64_tile::accumulators<64> &acc, double *lds, const tri_matrix &W, int o, int Np,
+                                             int bi, int bj)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= Np) return;
-    double inv_l[BAGEL_MAX_D];                       // 1 / l_d, once per thread
-    for (int d = 0; d < D; ++d) inv_l[d] = exp(-(double)lh[d]);
-    const double sf2 = exp((double)lh[D]), sn2 = exp((double)lh[D + 1]);
-    double val;
-    if (i < N && j < N) {
-        double r = 0.0;
-        for (int d = 0; d < D; ++d) {
-            const double t = ((double)X[(size_t)i * D + d] - (double)X[(size_t)j * D + d]) * inv_l[d];
-            r += t * t;
+    const double *Wk = W.at(o, NB * bi, 0);
+    f64_tile::clear(acc);
+    f64_tile::product<64>(acc, lds, NB * bi, NB * bj, Np, Np, Np - NB * bi, Wk, W.ld, Wk, W.ld);
+}
+
+// K_hat^-1, both triangles (the posterior cache)
+__global__ __launch_bounds__(256, 3) void inverse_store_kernel(tri_matrix W, double *__restrict__ Kinv, int Np)
+{
+    __shared__ __align__(16) double lds[f64_tile::shape<64>::LDS_DOUBLES];
+    const int o = blockIdx.y;
+    int bi, bj;
+    lower_tile(blockIdx.x, bi, bj);
+    f64_tile::accumulators<64> acc;
+    inverse_tile(acc, lds, W, o, Np, bi, bj);
+    const f64_tile::lane_pos pos = f64_tile::lane_position<64>();
+    double *Ko = Kinv + (size_t)o * Np * Np;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int row = NB * bi + pos.row0 + 8 * r, col = NB * bj + pos.col0;
+            *reinterpret_cast<double2 *>(Ko + (size_t)(row + e) * Np + col) = make_double2(acc.v[e][0][r], acc.v[e][1][r]);
+            if (bi != bj)
+                *reinterpret_cast<double2 *>(Ko + (size_t)(col + e) * Np + row) = make_double2(acc.v[0][e][r], acc.v[1][e][r]);
         }
-        val = sf2 * exp(-0.5 * r);
-        if (i == j) val += sn2;
-    } else {
-        val = (i == j) ? 1.0 : 0.0;
-    }
-    K[(size_t)i * Np + j] = val;
 }
 
+// ---- hyper-parameter learning ----------------------------------------------------------------------------------------
 // fixed-order sum of one value per thread over a workgroup of 256 (result valid in thread 0)
 __device__ __forceinline__ double block_sum_256(double v, double *sh)
 {
@@ -600,172 +689,199 @@ __device__ __forceinline__ double block_sum_256(double v, double *sh)
     return sh[0];
 }
 
-// lml = -1/2 y^T a - sum_i log L_ii - N/2 log(2 pi); L = factor in K (diagonal), a = alpha
-__global__ __launch_bounds__(256) void hyper_lml_kernel(const double *__restrict__ Lf, const double *__restrict__ alpha,
-                                                        const float *__restrict__ y_m, int N, int Np,
-                                                        float *__restrict__ lml_out)
+// lml = -1/2 y^T K_hat^-1 y - sum_i log U_ii - N/2 log(2 pi), with y^T K_hat^-1 y = |z|^2, z = L^-1 y; one workgroup per output
+__global__ __launch_bounds__(256) void hyper_lml_kernel(const double *__restrict__ diag, const double *__restrict__ z,
+                                                        int N, int Np, float *__restrict__ lml_out)
 {
     __shared__ double sh[256];
+    const int o = blockIdx.x;
     double ld = 0.0, quad = 0.0;
-    for (int i = threadIdx.x; i < Np; i += 256) ld += log(Lf[(size_t)i * Np + i]);
-    for (int n = threadIdx.x; n < N; n += 256) quad += (double)y_m[n] * alpha[n];
+    for (int i = threadIdx.x; i < Np; i += 256) {
+        const double zi = z[(size_t)o * Np + i];
+        ld += log(diag[(size_t)o * Np + i]);
+        quad += zi * zi;
+    }
     const double ld_tot = block_sum_256(ld, sh);
     __syncthreads();
     const double q_tot = block_sum_256(quad, sh);
-    if (threadIdx.x == 0) lml_out[0] = (float)(-0.5 * q_tot - ld_tot - 0.5 * (double)N * 1.8378770664093453);
+    if (threadIdx.x == 0) lml_out[o] = (float)(-0.5 * q_tot - ld_tot - 0.5 * (double)N * 1.8378770664093453);
 }
 
-// row i of sum_ij (a_i a_j - Kinv_ij) dK_hat_ij / dphi_c for c = 0 .. D+1 -> partial[i][D+2]
-// (eq. (6) with dK/dlog l_d = K (x_d - x'_d)^2 / l_d^2, dK/dlog alpha^2 = K, dK_hat/dlog sigma_n^2 = sigma_n^2 I).
-// One workgroup per row; thread t takes columns t, t + 256, ...; the D + 2 sums are added over the
-// lanes of a wave by a fixed butterfly, then over the four waves in order.  All loops over d have the
-// compile-time bound BAGEL_MAX_D so that the per-thread arrays stay in registers.
-__global__ __launch_bounds__(256) void hyper_grad_rows_kernel(const float *__restrict__ X, const float *__restrict__ lh,
-                                                              const double *__restrict__ Kinv,
-                                                              const double *__restrict__ alpha,
-                                                              double *__restrict__ partial, int N, int Np, int D)
+// Tile of sum_ij (a_i a_j - Kinv_ij) dK_hat_ij / dphi_c for c = 0 .. D+1 -> partial[o][tile][D+2] (eq. (6) with
+// dK/dlog l_d = K (x_d - x'_d)^2 / l_d^2, dK/dlog alpha^2 = K, dK_hat/dlog sigma_n^2 = sigma_n^2 I).  The tile of
+// K_hat^-1 is formed here and never written: only these sums of it are needed.  Tiles off the diagonal count
+// twice.  The sums are added over a lane's entries, the lanes (fixed butterfly) and the four waves in order.
+template <int D>
+__global__ __launch_bounds__(256, 3) void hyper_grad_tiles_kernel(const float *__restrict__ X, const float *__restrict__ log_hyp,
+                                                                  tri_matrix W, const double *__restrict__ alpha,
+                                                                  double *__restrict__ partial, int N, int Np, int m0)
 {
-    __shared__ double sh[4][BAGEL_MAX_D + 2];
-    const int i = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double acc[BAGEL_MAX_D + 2], inv_l[BAGEL_MAX_D], xi[BAGEL_MAX_D];
+    constexpr int LQ = NB + 1, NEED = NB * LQ + 2 * NB * (D + 1) + 4 * (D + 2);
+    constexpr int HAVE = f64_tile::shape<64>::LDS_DOUBLES;
+    __shared__ __align__(16) double lds[NEED > HAVE ? NEED : HAVE];
+    const int o = blockIdx.y;
+    int bi, bj;
+    lower_tile(blockIdx.x, bi, bj);
+    f64_tile::accumulators<64> acc;
+    inverse_tile(acc, lds, W, o, Np, bi, bj);
+    // the tile, and inputs and alpha of its rows and columns, into the LDS the product is done with: thread = column
+    // and 16 rows from here on, in a loop that needs few registers
+    double *Q = lds, *xr = lds + NB * LQ, *xc = xr + NB * (D + 1), *sums = xc + NB * (D + 1);
+    const f64_tile::lane_pos pos = f64_tile::lane_position<64>();
 #pragma unroll
-    for (int c = 0; c < BAGEL_MAX_D + 2; ++c) acc[c] = 0.0;
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int d = 0; d < BAGEL_MAX_D; ++d) {          // 1 / l_d and the row's own input, once per thread
-        inv_l[d] = d < D ? exp(-(double)lh[d]) : 0.0;
-        xi[d] = d < D ? (double)X[(size_t)i * D + d] : 0.0;
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Q[(pos.row0 + x + 8 * r) * LQ + pos.col0 + y] = acc.v[x][y][r];
+    const float *lh = log_hyp + (size_t)(m0 + o) * (D + 2);
+    for (int e = threadIdx.x; e < 2 * NB * (D + 1); e += 256) {
+        const int q = e / (D + 1), d = e - q * (D + 1);
+        const int n = q < NB ? NB * bi + q : NB * bj + q - NB;
+        xr[e] = n < N ? (d < D ? (double)X[(size_t)n * D + d] : alpha[(size_t)o * Np + n]) : 0.0;
     }
+    double il[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) il[d] = exp(-(double)lh[d]);
     const double sf2 = exp((double)lh[D]), sn2 = exp((double)lh[D + 1]);
-    const double ai = alpha[i];
-    for (int j = threadIdx.x; j < N; j += 256) {
-        const double w = ai * alpha[j] - Kinv[(size_t)i * Np + j];
-        double r = 0.0, t2[BAGEL_MAX_D];
+    __syncthreads();
+    const int cl = threadIdx.x & 63, r0 = 16 * (threadIdx.x >> 6);
+    const int j = NB * bj + cl;
+    double xj[D + 1], s[D + 2];
 #pragma unroll
-        for (int d = 0; d < BAGEL_MAX_D; ++d) {
-            if (d < D) {
-                const double t = (xi[d] - (double)X[(size_t)j * D + d]) * inv_l[d];
-                t2[d] = t * t;
-                r += t2[d];
-            }
+    for (int d = 0; d <= D; ++d) xj[d] = xc[cl * (D + 1) + d];
+#pragma unroll
+    for (int c = 0; c < D + 2; ++c) s[c] = 0.0;
+#pragma unroll 2
+    for (int r = r0; r < r0 + 16; ++r) {
+        const double *ri = xr + r * (D + 1);
+        const int i = NB * bi + r;
+        double q = 0.0, t2[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const double t = (ri[d] - xj[d]) * il[d];
+            t2[d] = t * t;
+            q += t2[d];
         }
-        const double wk = w * sf2 * exp(-0.5 * r);
+        double w = ri[D] * xj[D] - Q[r * LQ + cl];
+        w = (i < N && j < N) ? w : 0.0;
+        const double wk = w * sf2 * exp(-0.5 * q);
 #pragma unroll
-        for (int d = 0; d < BAGEL_MAX_D; ++d)
-            if (d < D) acc[d] += wk * t2[d];
-        acc[BAGEL_MAX_D] += wk;
-        if (j == i) acc[BAGEL_MAX_D + 1] += w * sn2;
+        for (int d = 0; d < D; ++d) s[d] += wk * t2[d];
+        s[D] += wk;
+        s[D + 1] += i == j ? w : 0.0;
     }
+    s[D + 1] *= sn2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int c = 0; c < BAGEL_MAX_D + 2; ++c) {
-        if (c < D || c >= BAGEL_MAX_D) {
-            double v = acc[c];
+    for (int c = 0; c < D + 2; ++c) {
+        double v = s[c];
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-            if (lane == 0) sh[wave][c] = v;
-        }
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if (lane == 0) sums[wave * (D + 2) + c] = v;
     }
     __syncthreads();
-    // thread c < D writes the length-scale sums, threads BAGEL_MAX_D and BAGEL_MAX_D + 1 the other two
     const int c = threadIdx.x;
-    if (c < D || c == BAGEL_MAX_D || c == BAGEL_MAX_D + 1) {
-        const double tot = ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
-        partial[(size_t)i * (D + 2) + (c < D ? c : D + (c - BAGEL_MAX_D))] = tot;
+    if (c < D + 2) {
+        const double tot = ((sums[c] + sums[(D + 2) + c]) + sums[2 * (D + 2) + c]) + sums[3 * (D + 2) + c];
+        partial[((size_t)o * gridDim.x + blockIdx.x) * (D + 2) + c] = bi == bj ? tot : 2.0 * tot;
     }
 }
 
-// grad[c] = 1/2 sum_i partial[i][c]; neg_scaled[c] = -grad[c] / N for the Adam update.  One workgroup
-// per hyper-parameter c: thread t adds rows t, t + 256, ... in order, then a fixed tree over the threads.
-__global__ __launch_bounds__(256) void hyper_grad_final_kernel(const double *__restrict__ partial, int N, int D,
-                                                               float *__restrict__ grad,
-                                                               float *__restrict__ neg_scaled)
+// grad[c] = 1/2 sum over the tiles; neg_scaled[c] = -grad[c] / N for the Adam update.  One workgroup per hyper-parameter
+// and output: thread t adds tiles t, t + 256, ... in order, then a fixed tree over the threads.
+__global__ __launch_bounds__(256) void hyper_grad_final_kernel(const double *__restrict__ partial, int tiles, int N, int H2,
+                                                               float *__restrict__ grad, float *__restrict__ neg_scaled)
 {
     __shared__ double sh[256];
-    const int c = blockIdx.x;
+    const int c = blockIdx.x, o = blockIdx.y;
     double s = 0.0;
-    for (int i = threadIdx.x; i < N; i += 256) s += partial[(size_t)i * (D + 2) + c];
+    for (int i = threadIdx.x; i < tiles; i += 256) s += partial[((size_t)o * tiles + i) * H2 + c];
     s = 0.5 * block_sum_256(s, sh);
     if (threadIdx.x == 0) {
-        if (grad) grad[c] = (float)s;
-        if (neg_scaled) neg_scaled[c] = (float)(-s / (double)N);
+        if (grad) grad[o * H2 + c] = (float)s;
+        if (neg_scaled) neg_scaled[o * H2 + c] = (float)(-s / (double)N);
     }
 }
 
-// The GP outputs are independent, and the work on one of them is a chain of small dependent kernels
-// (diagonal blocks, panel solves) between its deep products: on its own it leaves the chip idle a third
-// of the time.  So up to three outputs are worked on side by side, each on a stream of its own with
-// buffers of its own; what one leaves idle the deep products of another fill.  The side streams start
-// after everything already enqueued on the context's stream and the context's stream continues after
-// them; all have the default priority.  (Four or six side by side were measured as well: 142 and 127 ms
-// per hyper-parameter iteration at N = 8192 against 127 ms with three.)
-struct side_lanes {
-    static constexpr int MAXL = 3;
-    int n = 0;
-    hipStream_t st[MAXL] = {};
-    hipEvent_t done[MAXL] = {};
-    hipEvent_t start = nullptr;
+// ---- right-hand sides of the sample set-up ---------------------------------------------------------------------------
+// PhiT[l][n] = sqrt(2 sf2 / L) cos(omega_l . X_n + phase_l); zero for l >= L (padding of the contraction) and n >= N.
+// Grid (Np / 64, Lp / 4, outputs): lane = training point, wave = feature.
+__global__ __launch_bounds__(256) void build_phi_kernel(const float *__restrict__ X, const float *__restrict__ omega,
+                                                        const float *__restrict__ phase, hyper_ptr h, double *__restrict__ PhiT,
+                                                        size_t s_phi, int N, int Np, int L, int D, int m0)
+{
+    const int m = m0 + blockIdx.z;
+    const int n = blockIdx.x * 64 + (threadIdx.x & 63), l = blockIdx.y * 4 + (threadIdx.x >> 6);
+    double val = 0.0;
+    if (n < N && l < L) {
+        const float *om = omega + ((size_t)m * L + l) * D;
+        double z = (double)phase[(size_t)m * L + l];
+        for (int d = 0; d < D; ++d) z += (double)om[d] * (double)X[(size_t)n * D + d];
+        val = sqrt(2.0 * signal_variance(h, m, D) / (double)L) * cos(z);
+    }
+    PhiT[blockIdx.z * s_phi + (size_t)l * Np + n] = val;
+}
 
-    hipError_t open(int want)
-    {
-        if (want > MAXL) want = MAXL;
-        if (want < 1) want = 1;
-        hipError_t e = hipEventCreateWithFlags(&start, hipEventDisableTiming);
-        for (int l = 0; l < want && e == hipSuccess; ++l) {
-            e = hipStreamCreateWithFlags(&st[l], hipStreamNonBlocking);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&done[l], hipEventDisableTiming);
-            if (e == hipSuccess) n = l + 1;
-        }
-        return e;
+// dst[o][q][s] = (y_m ? y_m[q] : 0) +- src[s][m][q] in float64 (plus without y, minus with), zero outside q < n, s < S:
+// 64 x 64 blocks through LDS so that both sides are contiguous.  Grid (Sp / 64, rows / 64, outputs).
+__global__ __launch_bounds__(256) void transpose_in_kernel(const float *__restrict__ src, const float *__restrict__ y,
+                                                           double *__restrict__ dst, size_t s_dst, int n, int S, int Sp, int M,
+                                                           int m0)
+{
+    __shared__ float t[64][65];
+    const int m = m0 + blockIdx.z, s0 = blockIdx.x * 64, q0 = blockIdx.y * 64;
+    const int lane = threadIdx.x & 63;
+    for (int r = threadIdx.x >> 6; r < 64; r += 4)
+        t[r][lane] = (s0 + r < S && q0 + lane < n) ? src[((size_t)(s0 + r) * M + m) * n + q0 + lane] : 0.0f;
+    __syncthreads();
+    for (int r = threadIdx.x >> 6; r < 64; r += 4) {
+        const int q = q0 + r, s = s0 + lane;
+        double v = (double)t[lane][r];
+        if (y) v = (q < n && s < S) ? (double)y[(size_t)m * n + q] - v : 0.0;
+        dst[blockIdx.z * s_dst + (size_t)q * Sp + s] = v;
     }
-    hipError_t fork(hipStream_t main)
-    {
-        hipError_t e = hipEventRecord(start, main);
-        for (int l = 0; l < n && e == hipSuccess; ++l) e = hipStreamWaitEvent(st[l], start, 0);
-        return e;
-    }
-    hipError_t join(hipStream_t main)
-    {
-        hipError_t e = hipSuccess;
-        for (int l = 0; l < n && e == hipSuccess; ++l) {
-            e = hipEventRecord(done[l], st[l]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(main, done[l], 0);
-        }
-        return e;
-    }
-    void sync()
-    {
-        for (int l = 0; l < n; ++l) (void)hipStreamSynchronize(st[l]);
-    }
-    void close()
-    {
-        for (int l = 0; l < MAXL; ++l) {
-            if (st[l]) { (void)hipStreamSynchronize(st[l]); (void)hipStreamDestroy(st[l]); }
-            if (done[l]) (void)hipEventDestroy(done[l]);
-        }
-        if (start) (void)hipEventDestroy(start);
-    }
-};
+}
 
-// What the set-up calls need beyond the context's own buffers: the side streams and one device
-// allocation that their float64 work space is carved from.  Both are made by the first set-up call,
-// grown when a later call needs more, kept for the next call (a caller's own loop over
-// bagel_hyper_lml_grad, or a redraw of the samples with bagel_prepare_samples every few policy
-// updates, allocates nothing after its first pass) and released by bagel_destroy.
+// V[n][s] (float64) -> the packed stream v4[m][n4][s] (zero past N) and v_out[s][m][n], both float32, through LDS.
+// Grid (ceil(S / 64), ceil(Npk / 64), outputs); Npk: rows of the packed stream, which may be more than Np.
+__global__ __launch_bounds__(256) void emit_v_kernel(const double *__restrict__ V, size_t s_v, int Sp, float *__restrict__ v_out,
+                                                     float4 *__restrict__ v4, int N, int Npk, int S, int M, int m0)
+{
+    __shared__ float t[64][65];
+    const int m = m0 + blockIdx.z, s0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int r = wave; r < 64; r += 4)
+        t[r][lane] = n0 + r < N ? (float)V[blockIdx.z * s_v + (size_t)(n0 + r) * Sp + s0 + lane] : 0.0f;
+    __syncthreads();
+    for (int q = wave; q < 16; q += 4)
+        if (n0 + 4 * q < Npk && s0 + lane < S)
+            v4[((size_t)m * (Npk / 4) + (n0 >> 2) + q) * S + s0 + lane] =
+                make_float4(t[4 * q][lane], t[4 * q + 1][lane], t[4 * q + 2][lane], t[4 * q + 3][lane]);
+    if (v_out && n0 + lane < N)
+        for (int r = wave; r < 64 && s0 + r < S; r += 4) v_out[((size_t)(s0 + r) * M + m) * N + n0 + lane] = t[lane][r];
+}
+
+// ---- work space --------------------------------------------------------------------------------------------------------
+// What the set-up calls need beyond the context's own buffers: one device allocation that their float64 work
+// space is carved from.  It is made by the first set-up call, grown when a later call needs more, kept for the
+// next call (a caller's own loop over bagel_hyper_lml_grad, or a redraw of the samples with
+// bagel_prepare_samples every few policy updates, allocates nothing after its first pass) and released by
+// bagel_destroy.
 struct setup_scratch {
-    side_lanes lanes;
-    bool lanes_open = false;
     char *arena = nullptr;
     size_t arena_bytes = 0;
+    bool limited = false;        // memory for all outputs at once could not be had: an arena that fits one is kept
+    bool lds_raised = false;     // the dynamic-LDS limit of chol_step_kernel has been raised on this context's device
 };
 
 constexpr size_t ARENA_ALIGN = 256;
 size_t arena_round(size_t bytes) { return (bytes + ARENA_ALIGN - 1) / ARENA_ALIGN * ARENA_ALIGN; }
 
-// The context's set-up scratch with its side streams open (at most `want` of them) and at least
-// shared_bytes + n * lane_bytes of device memory, n = number of outputs worked on side by side: as many
-// as there are streams, fewer if the memory for that many cannot be had (one must fit).  The stream is
-// idle when the arena is replaced: every set-up call ends with a synchronisation.
-hipError_t setup_reserve(bagel_ctx *c, int want, size_t lane_bytes, size_t shared_bytes, setup_scratch **out, int *n_side)
+// At least shared_bytes + n * output_bytes of device memory, n = number of outputs worked on by one launch: all
+// of them, fewer if the memory for that many cannot be had (one must fit).  The stream is idle when the arena is
+// replaced: every set-up call ends with a synchronisation.
+hipError_t setup_reserve(bagel_ctx *c, size_t output_bytes, size_t shared_bytes, setup_scratch **out, int *n_outputs)
 {
     setup_scratch *sc = static_cast<setup_scratch *>(c->setup);
     if (!sc) {
@@ -773,46 +889,42 @@ hipError_t setup_reserve(bagel_ctx *c, int want, size_t lane_bytes, size_t share
         if (!sc) return hipErrorOutOfMemory;
         c->setup = sc;
     }
-    if (!sc->lanes_open) {
-        const hipError_t e = sc->lanes.open(want);
-        if (e != hipSuccess) {
-            sc->lanes.close();
-            sc->lanes = side_lanes();
-            return e;
-        }
-        sc->lanes_open = true;
-    }
     *out = sc;
-    lane_bytes = arena_round(lane_bytes);
+    if (!sc->lds_raised) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_step_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)STEP_LDS);
+        if (e != hipSuccess) return e;
+        sc->lds_raised = true;
+    }
+    output_bytes = arena_round(output_bytes);
     shared_bytes = arena_round(shared_bytes);
-    for (int n = sc->lanes.n; n >= 1; --n) {
-        const size_t need = shared_bytes + (size_t)n * lane_bytes;
-        if (sc->arena_bytes >= need) {
-            *n_side = n;
-            return hipSuccess;
+    const size_t M = (size_t)c->M;
+    auto fit = [&]() { return sc->arena_bytes < shared_bytes ? (size_t)0 : (sc->arena_bytes - shared_bytes) / output_bytes; };
+    if (fit() < M && !(sc->limited && fit() >= 1)) {
+        (void)hipStreamSynchronize(c->stream);
+        if (sc->arena) {
+            (void)hipFree(sc->arena);
+            c->bytes -= (int64_t)sc->arena_bytes;
+            sc->arena = nullptr;
+            sc->arena_bytes = 0;
         }
-    }
-    (void)hipStreamSynchronize(c->stream);
-    if (sc->arena) {
-        (void)hipFree(sc->arena);
-        c->bytes -= (int64_t)sc->arena_bytes;
-        sc->arena = nullptr;
-        sc->arena_bytes = 0;
-    }
-    hipError_t e = hipErrorOutOfMemory;
-    for (int n = sc->lanes.n; n >= 1; --n) {
-        const size_t need = shared_bytes + (size_t)n * lane_bytes;
-        e = hipMalloc((void **)&sc->arena, need);
-        if (e == hipSuccess) {
-            sc->arena_bytes = need;
-            c->bytes += (int64_t)need;
-            *n_side = n;
-            return hipSuccess;
+        hipError_t e = hipErrorOutOfMemory;
+        for (size_t n = M; n >= 1; --n) {
+            const size_t need = shared_bytes + n * output_bytes;
+            e = hipMalloc((void **)&sc->arena, need);
+            if (e == hipSuccess) {
+                sc->arena_bytes = need;
+                sc->limited = n < M;
+                c->bytes += (int64_t)need;
+                break;
+            }
+            sc->arena = nullptr;
+            (void)hipGetLastError();
         }
-        sc->arena = nullptr;
-        (void)hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    return e;
+    *n_outputs = (int)(fit() < M ? fit() : M);
+    return hipSuccess;
 }
 
 // consecutive pieces of the arena
@@ -827,19 +939,50 @@ struct arena_cursor {
     }
 };
 
-}  // namespace
-
-void bagel_dgemm(hipStream_t st, int Mr, int Nc, int Kd, double alpha, const double *A, long sai, long sak,
-                 const double *Bm, long sbk, long sbj, double *Cm, long ldc, bool overwrite)
+// K_hat of outputs m0 .. m0 + s.outputs - 1 built and factored
+void build_and_factor(solver &s, const float *X, const hyper_ptr &h, int N, int D, int m0)
 {
-    gemm(st, Mr, Nc, Kd, alpha, A, sai, sak, Bm, sbk, sbj, Cm, ldc, false, overwrite);
+    hipLaunchKernelGGL(build_khat_kernel, dim3(s.nb, s.nb, s.outputs), dim3(256), 0, s.st, X, h, s.f.K, s.f.sK, N, s.f.Np, D, m0);
+    s.factor(0, s.nb);
 }
+
+__global__ void clear_flags_kernel(int *flag, int n)
+{
+    if ((int)threadIdx.x < n) flag[threadIdx.x] = 0;
+}
+
+// The first failure among the outputs of the flags, as (output, pivot); output -1: none.  Synchronises.
+hipError_t read_flags(hipStream_t st, const int *flag, int M, int *output, int *pivot)
+{
+    int h[BAGEL_MAX_STATE];
+    *output = -1;
+    hipError_t e = hipMemcpyAsync(h, flag, (size_t)M * sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    for (int m = 0; m < M && *output < 0; ++m)
+        if (h[m]) {
+            *output = m;
+            *pivot = h[m] - 1;
+        }
+    return hipSuccess;
+}
+
+#define P_HIP(call)                                                                                          \
+    do {                                                                                                     \
+        hipError_t e__ = (call);                                                                             \
+        if (e__ != hipSuccess) {                                                                             \
+            snprintf(c->err, sizeof(c->err), "%s: %s failed: %s", who, #call, hipGetErrorString(e__));       \
+            rc = (e__ == hipErrorOutOfMemory) ? BAGEL_ENOMEM : BAGEL_EHIP;                                   \
+            goto done;                                                                                       \
+        }                                                                                                    \
+    } while (0)
+
+}  // namespace
 
 void bagel_release_setup(bagel_ctx *c)
 {
     setup_scratch *sc = static_cast<setup_scratch *>(c->setup);
     if (!sc) return;
-    sc->lanes.close();
     if (sc->arena) {
         (void)hipFree(sc->arena);
         c->bytes -= (int64_t)sc->arena_bytes;
@@ -852,80 +995,97 @@ int bagel_prepare_impl(bagel_ctx *c, const float *X, const float *y, const float
                        const float *sn2, const float *omega, const float *phase, const float *w,
                        const float *eps, float *v_out)
 {
+    static const char who[] = "bagel_prepare_samples";
     const int N = c->dm.N, L = c->dm.L, S = c->dm.S, M = c->M, D = c->D;
-    const int Np = (N + NB - 1) / NB * NB;
+    const int Np = (N + NB - 1) / NB * NB, Sp = (S + 63) / 64 * 64, Lq = (L + 63) / 64 * 64;
     hipStream_t st = c->stream;
     setup_scratch *sc = nullptr;
-    int n_side = 1;
-    double *K[side_lanes::MAXL] = {}, *Phi[side_lanes::MAXL] = {}, *R[side_lanes::MAXL] = {}, *Wd[side_lanes::MAXL] = {};
-    int *flag = nullptr;
-    float h_sf2[8], h_sn2[8];
+    int n_out = 1, bad = -1, pivot = 0;
     int rc = BAGEL_OK;
-    int h_flag = 0;
-
-#define P_HIP(call)                                                                              \
-    do {                                                                                         \
-        hipError_t e__ = (call);                                                                 \
-        if (e__ != hipSuccess) {                                                                 \
-            snprintf(c->err, sizeof(c->err), "bagel_prepare_samples: %s failed: %s", #call,      \
-                     hipGetErrorString(e__));                                                    \
-            rc = (e__ == hipErrorOutOfMemory) ? BAGEL_ENOMEM : BAGEL_EHIP;                       \
-            goto done;                                                                           \
-        }                                                                                        \
-    } while (0)
-
+    // PhiT shares its place with U (the product with W comes before the factorisation), W's transpose with Z
+    const size_t big = (size_t)(Np > Lq ? Np : Lq);
+    const size_t nK = (size_t)Np * Np, nU = (size_t)Np * big, nR = (size_t)Np * Sp, nZ = (size_t)Sp * big, nT = (size_t)Np * NB * RB;
+    solver s;
+    hyper_ptr h = {ell, sf2, sn2, 0};
+    int *flag = nullptr;
+    double *R = nullptr, *Z = nullptr;
+    P_HIP(setup_reserve(c, arena_round(nK * 8) + arena_round(nU * 8) + arena_round(nR * 8) + arena_round(nZ * 8) +
+                               2 * arena_round(nT * 8) + arena_round((size_t)Np * 8),
+                        arena_round(BAGEL_MAX_STATE * sizeof(int)), &sc, &n_out));
     {
-        const size_t nK = (size_t)Np * Np, nPhi = (size_t)Np * L, nR = (size_t)Np * S, nW = (size_t)S * L;
-        P_HIP(setup_reserve(c, M, arena_round(nK * 8) + arena_round(nPhi * 8) + arena_round(nR * 8) + arena_round(nW * 8),
-                            sizeof(int), &sc, &n_side));
         arena_cursor cur{sc->arena};
-        flag = cur.take<int>(1);
-        for (int l = 0; l < n_side; ++l) {
-            K[l] = cur.take<double>(nK);
-            Phi[l] = cur.take<double>(nPhi);
-            R[l] = cur.take<double>(nR);
-            Wd[l] = cur.take<double>(nW);
-        }
+        flag = cur.take<int>(BAGEL_MAX_STATE);
+        const size_t n = (size_t)n_out;
+        s.st = st;
+        s.nb = Np / NB;
+        s.f.Np = Np;
+        s.f.K = cur.take<double>(n * nK); s.f.sK = nK;
+        s.f.U = cur.take<double>(n * nU); s.f.sU = nU;
+        R = cur.take<double>(n * nR);
+        Z = cur.take<double>(n * nZ);
+        s.f.V = tri_matrix{cur.take<double>(n * nT), 0, nT};
+        s.f.W = tri_matrix{cur.take<double>(n * nT), 0, nT};
+        s.f.diag = cur.take<double>(n * Np);
     }
-    P_HIP(hipMemsetAsync(flag, 0, sizeof(int), st));
-    P_HIP(hipMemcpyAsync(h_sf2, sf2, M * sizeof(float), hipMemcpyDeviceToHost, st));
-    P_HIP(hipMemcpyAsync(h_sn2, sn2, M * sizeof(float), hipMemcpyDeviceToHost, st));
-    P_HIP(hipStreamSynchronize(st));
-
-    P_HIP(sc->lanes.fork(st));
-    for (int m = 0; m < M; ++m) {
-        const int l = m % n_side;
-        hipStream_t ls = sc->lanes.st[l];
-        hipLaunchKernelGGL(build_khat_kernel, dim3((Np + 255) / 256, Np), dim3(256), 0, ls, X, ell + (size_t)m * D,
-                           h_sf2[m], h_sn2[m], K[l], N, Np, D);
-        hipLaunchKernelGGL(build_phi_kernel, dim3((L + 255) / 256, Np), dim3(256), 0, ls, X,
-                           omega + (size_t)m * L * D, phase + (size_t)m * L, h_sf2[m], Phi[l], N, Np, L, D);
-        hipLaunchKernelGGL(init_rhs_kernel, dim3((S + 255) / 256, Np), dim3(256), 0, ls, y + (size_t)m * N, eps, R[l],
-                           N, Np, S, M, m);
-        // W of output m as float64 [S][L], so the GEMM reads one layout
-        hipLaunchKernelGGL(convert_w_kernel, dim3((L + 255) / 256, S), dim3(256), 0, ls, w, Wd[l], S, M, L, m);
-        // R -= Phi W^T : A = Phi [Np][L] (k fast), B(k=l, j=s) = Wd[s][l]
-        gemm(ls, Np, S, L, -1.0, Phi[l], L, 1, Wd[l], 1, L, R[l], S, false);
-
-        factor_and_solve(ls, K[l], Np, R[l], S, m * Np, flag);
-        hipLaunchKernelGGL(emit_v_kernel, dim3((S + 255) / 256, c->Np / 4), dim3(256), 0, ls, R[l], v_out, c->v4, N,
-                           c->Np, S, M, m);
+    hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, st, flag, BAGEL_MAX_STATE);
+    for (int m0 = 0; m0 < M; m0 += n_out) {
+        s.outputs = M - m0 < n_out ? M - m0 : n_out;
+        s.f.flag = flag + m0;
+        // R = y - eps - Phi W^T
+        hipLaunchKernelGGL(build_phi_kernel, dim3(Np / 64, Lq / 4, s.outputs), dim3(256), 0, st, X, omega, phase, h, s.f.U, nU, N,
+                           Np, L, D, m0);
+        hipLaunchKernelGGL(transpose_in_kernel, dim3(Sp / 64, Lq / 64, s.outputs), dim3(256), 0, st, w, (const float *)nullptr, Z,
+                           nZ, L, S, Sp, M, m0);
+        hipLaunchKernelGGL(transpose_in_kernel, dim3(Sp / 64, Np / 64, s.outputs), dim3(256), 0, st, eps, y, R, nR, N, S, Sp, M, m0);
+        gemm_args g = {s.f.U, Z, R, (size_t)Np, (size_t)Sp, (size_t)Sp, nU, nZ, nR, Np, Sp, Lq, 1, 0};
+        gemm(st, s.outputs, g);
+        // the range inverses are used as whole squares: what is not written of them must be zero
+        P_HIP(hipMemsetAsync(s.f.V.p, 0, s.outputs * nT * 8, st));
+        P_HIP(hipMemsetAsync(s.f.W.p, 0, s.outputs * nT * 8, st));
+        build_and_factor(s, X, h, N, D, m0);
+        s.triangular_inverse(RB);
+        hipLaunchKernelGGL(mirror_factor_kernel, dim3(s.nb, s.nb, s.outputs), dim3(256), 0, st, s.f.U, s.f.sU, Np);
+        const solver::rhs rR = {R, nR, (size_t)Sp}, rZ = {Z, nZ, (size_t)Sp};
+        s.forward(0, s.nb, rR, rZ);
+        s.backward(0, s.nb, rZ, rR);
+        hipLaunchKernelGGL(emit_v_kernel, dim3(Sp / 64, (c->Np + 63) / 64, s.outputs), dim3(256), 0, st, R, nR, Sp, v_out, c->v4, N,
+                           c->Np, S, M, m0);
         P_HIP(hipGetLastError());
     }
-    P_HIP(sc->lanes.join(st));
-    P_HIP(hipMemcpyAsync(&h_flag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    P_HIP(hipStreamSynchronize(st));
-    if (h_flag != 0) {
-        snprintf(c->err, sizeof(c->err),
-                 "bagel_prepare_samples: K + noise_var I is not positive definite (output %d, pivot %d)",
-                 (h_flag - 1) / Np, (h_flag - 1) % Np);
+    P_HIP(read_flags(st, flag, M, &bad, &pivot));
+    if (bad >= 0) {
+        snprintf(c->err, sizeof(c->err), "%s: K + noise_var I is not positive definite (output %d, pivot %d)", who, bad, pivot);
         rc = BAGEL_ENOTPD;
     }
 done:
-    if (sc) sc->lanes.sync();
     (void)hipStreamSynchronize(st);
     return rc;
-#undef P_HIP
+}
+
+// K, U, V, W [Np][Np], diagonal and two vectors per output: the work space of an inverse
+static size_t inverse_bytes(int Np) { return 4 * arena_round((size_t)Np * Np * 8) + 3 * arena_round((size_t)Np * 8); }
+
+static void inverse_carve(solver &s, arena_cursor &cur, int n_out, int Np, double **vec)
+{
+    const size_t n = (size_t)n_out, nK = (size_t)Np * Np;
+    s.nb = Np / NB;
+    s.f.Np = Np;
+    s.f.K = cur.take<double>(n * nK); s.f.sK = nK;
+    s.f.U = cur.take<double>(n * nK); s.f.sU = nK;
+    s.f.V = tri_matrix{cur.take<double>(n * nK), (size_t)Np, nK};
+    s.f.W = tri_matrix{cur.take<double>(n * nK), (size_t)Np, nK};
+    s.f.diag = cur.take<double>(n * Np);
+    *vec = cur.take<double>(2 * n * Np);
+}
+
+// z = L^-1 y and alpha = K_hat^-1 y = L^-T z
+static void inverse_vectors(solver &s, const float *y, int N, int m0, double *z, double *alpha)
+{
+    const dim3 grid(s.f.Np / 4, s.outputs);
+    hipLaunchKernelGGL(triangle_times_vector_kernel, grid, dim3(256), 0, s.st, s.f.W, 0, y, (const double *)nullptr, z, N, s.f.Np,
+                       m0);
+    hipLaunchKernelGGL(triangle_times_vector_kernel, grid, dim3(256), 0, s.st, s.f.V, 1, (const float *)nullptr, z, alpha, N,
+                       s.f.Np, m0);
 }
 
 // Exact posterior cache of the per-step sampler (eq. (2), (3)): for every output alpha = K_hat^-1 y and
@@ -934,143 +1094,122 @@ done:
 int bagel_prepare_posterior_impl(bagel_ctx *c, const float *X, const float *y, const float *ell, const float *sf2,
                                  const float *sn2)
 {
-    const int N = c->dm.N, M = c->M, D = c->D;
-    const int Np = c->post_Np;
+    static const char who[] = "bagel_prepare_posterior";
+    const int N = c->dm.N, M = c->M, D = c->D, Np = c->post_Np;
     hipStream_t st = c->stream;
     setup_scratch *sc = nullptr;
-    int n_side = 1;
-    double *K[side_lanes::MAXL] = {}, *Z[side_lanes::MAXL] = {}, *vec[side_lanes::MAXL] = {};
-    int *flag = nullptr;
-    float h_sf2[8], h_sn2[8];
+    int n_out = 1, bad = -1, pivot = 0;
     int rc = BAGEL_OK;
-    int h_flag = 0;
-#define P_HIP(call)                                                                              \
-    do {                                                                                         \
-        hipError_t e__ = (call);                                                                 \
-        if (e__ != hipSuccess) {                                                                 \
-            snprintf(c->err, sizeof(c->err), "bagel_prepare_posterior: %s failed: %s", #call,    \
-                     hipGetErrorString(e__));                                                    \
-            rc = (e__ == hipErrorOutOfMemory) ? BAGEL_ENOMEM : BAGEL_EHIP;                       \
-            goto done;                                                                           \
-        }                                                                                        \
-    } while (0)
+    solver s;
+    hyper_ptr h = {ell, sf2, sn2, 0};
+    int *flag = nullptr;
+    double *vec = nullptr;
+    float h_sf2[BAGEL_MAX_STATE];
+    P_HIP(setup_reserve(c, inverse_bytes(Np), arena_round(BAGEL_MAX_STATE * sizeof(int)), &sc, &n_out));
     {
-        const size_t nK = (size_t)Np * Np;
-        P_HIP(setup_reserve(c, M, 2 * arena_round(nK * 8) + arena_round((size_t)Np * 8), sizeof(int), &sc, &n_side));
         arena_cursor cur{sc->arena};
-        flag = cur.take<int>(1);
-        for (int l = 0; l < n_side; ++l) {
-            K[l] = cur.take<double>(nK);
-            Z[l] = cur.take<double>(nK);
-            vec[l] = cur.take<double>(Np);
-        }
+        flag = cur.take<int>(BAGEL_MAX_STATE);
+        s.st = st;
+        inverse_carve(s, cur, n_out, Np, &vec);
     }
-    P_HIP(hipMemsetAsync(flag, 0, sizeof(int), st));
     P_HIP(hipMemcpyAsync(h_sf2, sf2, M * sizeof(float), hipMemcpyDeviceToHost, st));
-    P_HIP(hipMemcpyAsync(h_sn2, sn2, M * sizeof(float), hipMemcpyDeviceToHost, st));
-    P_HIP(hipStreamSynchronize(st));
-    P_HIP(sc->lanes.fork(st));
-    for (int m = 0; m < M; ++m) {
-        const int l = m % n_side;
-        hipStream_t ls = sc->lanes.st[l];
-        c->post_sf2[m] = (double)h_sf2[m];
-        hipLaunchKernelGGL(build_khat_kernel, dim3((Np + 255) / 256, Np), dim3(256), 0, ls, X, ell + (size_t)m * D,
-                           h_sf2[m], h_sn2[m], K[l], N, Np, D);
-        inverse_from_factor(ls, K[l], Np, Z[l], y + (size_t)m * N, N, vec[l], c->post_Kinv + (size_t)m * Np * Np,
-                            c->post_alpha + (size_t)m * Np, m * Np, flag);
+    hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, st, flag, BAGEL_MAX_STATE);
+    for (int m0 = 0; m0 < M; m0 += n_out) {
+        s.outputs = M - m0 < n_out ? M - m0 : n_out;
+        s.f.flag = flag + m0;
+        build_and_factor(s, X, h, N, D, m0);
+        s.triangular_inverse(s.nb);
+        inverse_vectors(s, y, N, m0, vec, c->post_alpha + (size_t)m0 * Np);
+        hipLaunchKernelGGL(inverse_store_kernel, dim3(s.nb * (s.nb + 1) / 2, s.outputs), dim3(256), 0, st, s.f.W,
+                           c->post_Kinv + (size_t)m0 * Np * Np, Np);
         P_HIP(hipGetLastError());
     }
-    P_HIP(sc->lanes.join(st));
-    P_HIP(hipMemcpyAsync(&h_flag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    P_HIP(hipStreamSynchronize(st));
-    if (h_flag != 0) {
-        snprintf(c->err, sizeof(c->err),
-                 "bagel_prepare_posterior: K + noise_var I is not positive definite (output %d, pivot %d)",
-                 (h_flag - 1) / Np, (h_flag - 1) % Np);
+    P_HIP(read_flags(st, flag, M, &bad, &pivot));
+    for (int m = 0; m < M; ++m) c->post_sf2[m] = (double)h_sf2[m];
+    if (bad >= 0) {
+        snprintf(c->err, sizeof(c->err), "%s: K + noise_var I is not positive definite (output %d, pivot %d)", who, bad, pivot);
         rc = BAGEL_ENOTPD;
     }
 done:
-    if (sc) sc->lanes.sync();
     (void)hipStreamSynchronize(st);
     return rc;
-#undef P_HIP
+}
+
+static void launch_hyper_grad(const solver &s, int D, const float *X, const float *log_hyp, const double *alpha, double *partial,
+                              int N, int m0)
+{
+    const dim3 grid(s.nb * (s.nb + 1) / 2, s.outputs);
+    switch (D) {
+#define CASE(n)                                                                                                                \
+    case n:                                                                                                                    \
+        hipLaunchKernelGGL(hyper_grad_tiles_kernel<n>, grid, dim3(256), 0, s.st, X, log_hyp, s.f.W, alpha, partial, N, \
+                           s.f.Np, m0);                                                                                        \
+        break;
+        CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12)
+        CASE(13) CASE(14) CASE(15) CASE(16)
+#undef CASE
+    }
 }
 
 // Log marginal likelihood of every output's GP and its gradient in the log hyper-parameters
 // (eq. (5), (6)), n_iters > 0: Adam ascent on lml / N for n_iters iterations (Algorithm 1, "learn GP
-// transition dynamics").  Buffers are allocated here and freed on return (set-up work).
+// transition dynamics").
 int bagel_hyper_impl(bagel_ctx *c, const float *X, const float *y, float *log_hyp, float *lml, float *grad,
                      float *adam_m, float *adam_v, int n_iters, int first_step, double lr, double beta1, double beta2,
                      double eps)
 {
+    static const char who[] = "bagel_hyper";
     const int N = c->dm.N, M = c->M, D = c->D, H2 = c->D + 2;
-    const int Np = (N + NB - 1) / NB * NB;
+    const int Np = (N + NB - 1) / NB * NB, nb = Np / NB, tiles = nb * (nb + 1) / 2;
     hipStream_t st = c->stream;
     setup_scratch *sc = nullptr;
-    int n_side = 1;
-    double *K[side_lanes::MAXL] = {}, *Z[side_lanes::MAXL] = {}, *Kinv[side_lanes::MAXL] = {},
-           *vec[side_lanes::MAXL] = {}, *partial[side_lanes::MAXL] = {};
-    float *gneg = nullptr;
+    int n_out = 1, bad = -1, pivot = 0;
+    int rc = BAGEL_OK;
+    solver s;
+    hyper_ptr h = {log_hyp, nullptr, nullptr, 1};
     int *flag = nullptr;
-    int rc = BAGEL_OK, h_flag = 0;
-#define P_HIP(call)                                                                              \
-    do {                                                                                         \
-        hipError_t e__ = (call);                                                                 \
-        if (e__ != hipSuccess) {                                                                 \
-            snprintf(c->err, sizeof(c->err), "bagel_hyper: %s failed: %s", #call, hipGetErrorString(e__)); \
-            rc = (e__ == hipErrorOutOfMemory) ? BAGEL_ENOMEM : BAGEL_EHIP;                       \
-            goto done;                                                                           \
-        }                                                                                        \
-    } while (0)
+    float *gneg = nullptr;
+    double *vec = nullptr, *partial = nullptr;
+    P_HIP(setup_reserve(c, inverse_bytes(Np) + arena_round((size_t)tiles * H2 * 8),
+                        arena_round(BAGEL_MAX_STATE * sizeof(int)) + arena_round((size_t)M * H2 * sizeof(float)), &sc, &n_out));
     {
-        const size_t nK = (size_t)Np * Np;
-        P_HIP(setup_reserve(c, M, 3 * arena_round(nK * 8) + arena_round((size_t)2 * Np * 8) + arena_round((size_t)N * H2 * 8),
-                            arena_round(sizeof(int)) + arena_round((size_t)M * H2 * sizeof(float)), &sc, &n_side));
         arena_cursor cur{sc->arena};
-        flag = cur.take<int>(1);
+        flag = cur.take<int>(BAGEL_MAX_STATE);
         gneg = cur.take<float>((size_t)M * H2);
-        for (int l = 0; l < n_side; ++l) {
-            K[l] = cur.take<double>(nK);
-            Z[l] = cur.take<double>(nK);
-            Kinv[l] = cur.take<double>(nK);
-            vec[l] = cur.take<double>((size_t)2 * Np);          // y, alpha
-            partial[l] = cur.take<double>((size_t)N * H2);
-        }
+        s.st = st;
+        inverse_carve(s, cur, n_out, Np, &vec);
+        partial = cur.take<double>((size_t)n_out * tiles * H2);
     }
-    P_HIP(hipMemsetAsync(flag, 0, sizeof(int), st));
+    hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, st, flag, BAGEL_MAX_STATE);
     for (int it = 0; it < (n_iters > 0 ? n_iters : 1); ++it) {
-        P_HIP(sc->lanes.fork(st));                      // after the parameter update of the previous iteration
-        for (int m = 0; m < M; ++m) {
-            const int l = m % n_side;
-            hipStream_t ls = sc->lanes.st[l];
-            const float *lh = log_hyp + (size_t)m * H2;
-            hipLaunchKernelGGL(build_khat_log_kernel, dim3((Np + 255) / 256, Np), dim3(256), 0, ls, X, lh, K[l], N, Np, D);
-            double *al = vec[l] + Np;
-            inverse_from_factor(ls, K[l], Np, Z[l], y + (size_t)m * N, N, vec[l], Kinv[l], al, m * Np, flag);
-            hipLaunchKernelGGL(hyper_lml_kernel, dim3(1), dim3(256), 0, ls, K[l], al, y + (size_t)m * N, N, Np,
-                               lml + (size_t)it * M + m);
-            hipLaunchKernelGGL(hyper_grad_rows_kernel, dim3(N), dim3(256), 0, ls, X, lh, Kinv[l], al, partial[l], N, Np, D);
-            hipLaunchKernelGGL(hyper_grad_final_kernel, dim3(H2), dim3(256), 0, ls, partial[l], N, D,
-                               grad ? grad + (size_t)m * H2 : nullptr, gneg + (size_t)m * H2);
+        for (int m0 = 0; m0 < M; m0 += n_out) {
+            s.outputs = M - m0 < n_out ? M - m0 : n_out;
+            s.f.flag = flag + m0;
+            double *z = vec, *alpha = vec + (size_t)n_out * Np;
+            build_and_factor(s, X, h, N, D, m0);
+            s.triangular_inverse(nb);
+            inverse_vectors(s, y, N, m0, z, alpha);
+            hipLaunchKernelGGL(hyper_lml_kernel, dim3(s.outputs), dim3(256), 0, st, s.f.diag, z, N, Np,
+                               lml + (size_t)it * M + m0);
+            if (grad || n_iters > 0) {
+                launch_hyper_grad(s, D, X, log_hyp, alpha, partial, N, m0);
+                hipLaunchKernelGGL(hyper_grad_final_kernel, dim3(H2, s.outputs), dim3(256), 0, st, partial, tiles, N, H2,
+                                   grad ? grad + (size_t)m0 * H2 : nullptr, gneg + (size_t)m0 * H2);
+            }
             P_HIP(hipGetLastError());
         }
-        P_HIP(sc->lanes.join(st));
         if (n_iters > 0) {
             const int step = first_step + it;
             P_HIP(bagel_launch_adam(c, log_hyp, gneg, adam_m, adam_v, M * H2, lr, beta1, beta2, eps,
                                     1.0 - pow(beta1, (double)step), 1.0 - pow(beta2, (double)step)));
         }
     }
-    P_HIP(hipMemcpyAsync(&h_flag, flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    P_HIP(hipStreamSynchronize(st));
-    if (h_flag != 0) {
-        snprintf(c->err, sizeof(c->err), "bagel_hyper: K + noise_var I is not positive definite (output %d, pivot %d)",
-                 (h_flag - 1) / Np, (h_flag - 1) % Np);
+    P_HIP(read_flags(st, flag, M, &bad, &pivot));
+    if (bad >= 0) {
+        snprintf(c->err, sizeof(c->err), "%s: K + noise_var I is not positive definite (output %d, pivot %d)", who, bad, pivot);
         rc = BAGEL_ENOTPD;
     }
 done:
-    if (sc) sc->lanes.sync();
     (void)hipStreamSynchronize(st);
     return rc;
-#undef P_HIP
 }

@@ -485,6 +485,20 @@ def test_prepare_matches_oracle_solution(name, kw):
         assert d[k] <= 3.0 * cond[k] + tol, (k, d[k], cond[k])
 
 
+@pytest.mark.parametrize("N,L,S", [(257, 65, 130),     # five 64-blocks: the last range of the factorisation is one block
+                                   (321, 64, 64),      # six: two; whole tiles of right-hand sides and features
+                                   (449, 200, 1),      # eight, the last one of a single row; one right-hand side
+                                   (1100, 3, 70)])     # 18: ranges of 4 blocks in two levels of halving and a rest of 2
+def test_prepare_blocking(N, L, S):
+    """v against the oracle's float64 solve where blocks, ranges and tiles do not come out even.  The bound is that of
+    test_prepare_matches_oracle_solution: one float32 rounding (6e-8) and the forward error of a float64 solve."""
+    cfg = synth.Config("pb", 16, 3, 1, 1, N, L, S, 2, (4,), 0.0, "sinusoid", "const", 0, 0.8, 1e-3)
+    inp = synth.make_inputs(cfg)
+    v64 = oracle.prepare_samples(oracle.dims_from_config(cfg), inp)
+    got = harness.gpu_rollout(cfg, inp, None, grad=False, with_prepare=True, want_v=True)
+    assert np.abs(got["v"] - v64).max() <= 5e-7 * np.abs(v64).max()
+
+
 def test_setup_work_space_is_made_once_and_kept():
     """The set-up calls share one work space: a second pass over them allocates nothing and gives the same bits."""
     import torch
@@ -799,6 +813,28 @@ def test_marginal_likelihood_few_training_points(N):
         ref, ref_g = oracle.hyper_lml_grad(inp["X"], inp["y"][m], lh0[m])
         assert abs(float(lml[m]) - ref) <= 2e-7 * abs(ref) + 1e-7
         np.testing.assert_allclose(grad[m].cpu().numpy(), ref_g, rtol=2e-6, atol=2e-6 * np.abs(ref_g).max() + 1e-7)
+    ctx.close()
+
+
+@pytest.mark.parametrize("d_s,d_a,N", [(1, 1, 130), (3, 2, 129), (6, 2, 200), (4, 8, 100), (8, 8, 70)])
+def test_marginal_likelihood_input_dimensions(d_s, d_a, N):
+    """The gradient kernel's instances between the smallest and the largest input dimension (tolerances as below)."""
+    import torch
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("hd", 33, d_s, d_a, 1, N, 16, 4, 2, (4,), 0.0, "sinusoid", "const", 0, 0.5, 1e-3)
+    inp = synth.make_inputs(cfg)
+    lh0 = np.concatenate([np.log(inp["lengthscale"]), np.log(inp["signal_var"])[:, None],
+                          np.log(inp["noise_var"])[:, None]], axis=1).astype(np.float32)
+    ctx = binding.Bagel(binding.dims_from_config(cfg))
+    g = harness.to_gpu(inp)
+    lml = torch.zeros(cfg.M, device="cuda")
+    grad = torch.zeros((cfg.M, cfg.D + 2), device="cuda")
+    ctx.bagel_hyper_lml_grad(g["X"], g["y"], torch.from_numpy(lh0).cuda(), lml, grad)
+    torch.cuda.synchronize()
+    for m in range(cfg.M):
+        ref, ref_g = oracle.hyper_lml_grad(inp["X"], inp["y"][m], lh0[m])
+        assert abs(float(lml[m]) - ref) <= 2e-7 * abs(ref) + 1e-7
+        np.testing.assert_allclose(grad[m].cpu().numpy(), ref_g, rtol=2e-6, atol=2e-6 * np.abs(ref_g).max())
     ctx.close()
 
 
