@@ -120,35 +120,120 @@ struct factor_args {
 
 constexpr int LT = 66;           // LDS row stride of a block: even, so that pairs stay aligned
 
-__device__ __forceinline__ double read_lane(double v, int lane)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
-// 1/sqrt(d): hardware estimate, one third-order and one second-order correction (a chain of eight instructions,
-// a quarter of what the library's division after its square root takes)
+// 1/sqrt(d): hardware estimate (residual 1 - d y^2 below 1.1e-7, measured) and one third-order correction, which
+// leaves less than the rounding
 __device__ __forceinline__ double inv_sqrt(double d)
 {
-    double y = __builtin_amdgcn_rsq(d);
-    double e = fma(-(d * y), y, 1.0);
-    y = fma(y * e, fma(0.375, e, 0.5), y);
-    e = fma(-(d * y), y, 1.0);
-    return fma(0.5 * e, y, y);
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-(d * y), y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// A 16-column panel of the factorisation, right-looking, one wave: lane = row of the panel, its 16 entries in x.
-// Lane J holds the pivot row of column J (J = 0 .. 15).  Every lane does the same to its row, so lanes that start
-// with a column of the identity end with that column of the inverse of the panel's diagonal block.
-template <int J>
-__device__ __forceinline__ void panel_column(double (&x)[16], int &bad)
+// Broadcasts within a row of 16 lanes, as an operand modifier: no trip through LDS or scalar registers.  The hardware
+// wants two wait states between the write of a register and its use as such an operand, which the compiler does
+// not insert for assembly: every block below starts with them (8 cycles, so the blocks are long).
+template <int A, int B>
+__device__ __forceinline__ void row_broadcasts(double u, double v, double &a, double &b, double &c)
 {
-    const double d = read_lane(x[J], J);
-    bad = (bad == 0 && !(d > 0.0)) ? J + 1 : bad;
-    x[J] *= inv_sqrt(d);
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_mov_b64_dpp %1, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_mov_b64_dpp %2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+        : "=&v"(a), "=&v"(b), "=&v"(c)
+        : "v"(u), "v"(v), "n"(A), "n"(B));
+}
+// x0 -= (v of lane C) * f + (w of lane C) * g, x1 the same with lane C + 1
+template <int C>
+__device__ __forceinline__ void pivot_update2(double &x0, double &x1, double v, double f, double w, double g)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%2, %3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, -%4, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%4, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf"
+        : "+v"(x0), "+v"(x1)
+        : "v"(v), "v"(f), "v"(w), "v"(g), "n"(C), "n"(C + 1));
+}
+// the same for four columns
+template <int C>
+__device__ __forceinline__ void pivot_update4(double &x0, double &x1, double &x2, double &x3, double v, double f, double w, double g)
+{
+    asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%4, %5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, -%4, %5 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, -%4, %5 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, -%6, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, -%6, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, -%6, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, -%6, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "v"(v), "v"(f), "v"(w), "v"(g), "n"(C), "n"(C + 1), "n"(C + 2), "n"(C + 3));
+}
+// u and v with the even rows' values in the odd rows too
+__device__ __forceinline__ void even_rows(double &u, double &v)
+{
+    int a = __double2loint(u), b = __double2hiint(u), c = __double2loint(v), d = __double2hiint(v);
+    int a1 = a, b1 = b, c1 = c, d1 = d;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %4\n\tv_permlane16_swap_b32 %1, %5\n\t"
+        "v_permlane16_swap_b32 %2, %6\n\tv_permlane16_swap_b32 %3, %7"
+        : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(a1), "+v"(b1), "+v"(c1), "+v"(d1));
+    u = __hiloint2double(b, a);
+    v = __hiloint2double(d, c);
+}
+
+// Columns J and J + 1 of the factorisation of a 16 x 16 block, right-looking, and of the inverse of the factor.  Lane
+// i of an even row of 16 lanes holds row i of the block in y, lane i of an odd one column i of the identity: what
+// a step does to the rows below the pivots, y[c] -= L[c][J] y[J], is also the step of the forward substitution.
+// Entries of the block above the diagonal hold nothing and feed nothing.
+// Two columns at a time, because the time is the chain of dependent operations from pivot to pivot: with the 2 x 2
+// pivot block [a b; b c] and det = a c - b^2, the second pivot's 1/sqrt(c - b^2/a) is a / sqrt(a det), which
+// does not wait for 1/sqrt(a).  A pivot that is not positive leaves NaN on the diagonal.
+template <int J, int C>
+__device__ __forceinline__ void pivot_update(double (&y)[16], double l1, double l2)
+{
+    if constexpr (C + 4 <= 16) {
+        pivot_update4<C>(y[C], y[C + 1], y[C + 2], y[C + 3], l1, y[J], l2, y[J + 1]);
+        pivot_update<J, C + 4>(y, l1, l2);
+    } else if constexpr (C < 16) {
+        pivot_update2<C>(y[C], y[C + 1], l1, y[J], l2, y[J + 1]);
+    }
+}
+template <int J>
+__device__ __forceinline__ void pivot_columns(double (&y)[16])
+{
+    double u = y[J], v = y[J + 1], a, b, c;
+    even_rows(u, v);                                                     // the block's two columns, in every row
+    row_broadcasts<J, J + 1>(u, v, a, b, c);
+    const double det = fma(a, c, -(b * b));
+    const double r1 = inv_sqrt(a), r2 = a * inv_sqrt(a * det);
+    const double b1 = b * r1;                                            // L[J + 1][J]
+    const double l1 = u * r1, l2 = fma(-b1, l1, v) * r2;
+    y[J] *= r1;
+    y[J + 1] = fma(-b1, y[J], y[J + 1]) * r2;
+    pivot_update<J, J + 2>(y, l1, l2);
+    if constexpr (J + 2 < 16) pivot_columns<J + 2>(y);
+}
+
+// The 16 x 16 diagonal block at T, factored in place, its inverse to Wl; one wave (its two halves do the same)
+__device__ __forceinline__ void factor16(double *T, double *Wl, int *flag, int pivot0)
+{
+    const int lane = threadIdx.x & 63, i = lane & 15;
+    const bool block = (lane & 16) == 0;
+    double y[16];
 #pragma unroll
-    for (int c = J + 1; c < 16; ++c) x[c] = fma(-read_lane(x[J], c), x[J], x[c]);
-    __builtin_amdgcn_sched_barrier(0);           // one column's broadcasts at a time: they live in scalar registers
-    if constexpr (J + 1 < 16) panel_column<J + 1>(x, bad);
+    for (int c = 0; c < 16; ++c) {
+        const double t = T[i * LT + c];
+        y[c] = block ? t : (c == i ? 1.0 : 0.0);
+    }
+    pivot_columns<0>(y);
+    if (lane < 16) {
+#pragma unroll
+        for (int c = 0; c < 16; c += 2)
+            *reinterpret_cast<double2 *>(T + i * LT + c) = make_double2(c <= i ? y[c] : 0.0, c + 1 <= i ? y[c + 1] : 0.0);
+    } else if (lane < 32) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) Wl[c * LT + i] = y[c];
+    }
+    const unsigned long long bad = __ballot(lane < 16 && !(T[i * (LT + 1)] > 0.0));
+    if (bad && lane == 0) atomicCAS(flag, 0, pivot0 + __ffsll(bad));
 }
 
 // D[16 x 16] tile of a product of 16 x 16 blocks in LDS: acc += a(i, k) b(k, j), a = A[i][k], b given by rows or by
@@ -192,84 +277,70 @@ __device__ __forceinline__ void store16(double *C, const d4v &v)
     for (int r = 0; r < 4; ++r) C[(g + 4 * r) * LT + j] = v[r];
 }
 
-// Diagonal block k of output o, in T (LDS, [64][LT], lower triangle used): its factor to U (upper form) and
-// `diag`, the inverse of the factor to W and V.  Wl: LDS of the same size.  256 threads; T is overwritten.
-// Four panels of 16 columns: wave 0 factors the panel for all rows below (lane = row), wave 1 the panel's diagonal
-// block beside the identity, which gives that block's inverse; then the waves update the blocks to the right
-// on the matrix cores.  The 64 x 64 inverse is put together from the four of 16 x 16 in two levels.
-// Bound: the chain of 64 pivots (about 0.1 us each); 23 us per block with one wave holding a row of 64 per lane,
-// and another 13 us for each solve with it, before.
-__device__ __forceinline__ void factor_diagonal(const factor_args &f, int o, int k, double *T, double *Wl)
+// What panel p adds to U, V and W: rows 16 p .. of U and W, columns 16 p .. of V; by waves first .. first + count - 1
+__device__ __forceinline__ void emit_panel(const factor_args &f, int o, int k, int p, const double *T, const double *Wl, int first,
+                                           int count)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < NB * LT; e += 256) Wl[e] = 0.0;
-    __syncthreads();
-#pragma unroll 1
-    for (int p = 0; p < 4; ++p) {
-        double x[16];
-        const int r = min(16 * p + lane, NB - 1);            // row of the block (wave 0), or of the panel's own 16 (wave 1)
-        const bool row = wave == 0 ? 16 * p + lane < NB : lane < 16;
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const double t = T[r * LT + 16 * p + c];
-            x[c] = row ? t : ((wave == 1 && lane == 16 + c) ? 1.0 : 0.0);
-        }
-        __syncthreads();                                     // both waves have read the panel
-        if (wave < 2) {
-            int bad = 0;
-            panel_column<0>(x, bad);
-            if (bad && tid == 0) atomicCAS(f.flag + o, 0, NB * k + 16 * p + bad);
-            if (wave == 0 && row) {
-#pragma unroll
-                for (int c = 0; c < 16; ++c) T[r * LT + 16 * p + c] = c <= lane ? x[c] : 0.0;
-            }
-            if (wave == 1 && lane >= 16 && lane < 32) {
-#pragma unroll
-                for (int c = 0; c < 16; ++c) Wl[(16 * p + c) * LT + 16 * p + lane - 16] = x[c];
-            }
-        }
-        __syncthreads();
-        // blocks (bi, bj), p < bj <= bi, numbered column by column
-        const int n = 3 - p, count = n * (n + 1) / 2;
-        for (int t = wave; t < count; t += 4) {
-            int bj = 0, left = t;
-            while (left >= n - bj) left -= n - bj++;
-            const int bi = p + 1 + bj + left;
-            bj += p + 1;
-            double *C = T + 16 * bi * LT + 16 * bj;
-            store16(C, block16<true, true>(load16(C), T + 16 * bi * LT + 16 * p, T + 16 * bj * LT + 16 * p));
-        }
-        __syncthreads();
-    }
-    const d4v zero = {0.0, 0.0, 0.0, 0.0};
-    if (wave < 2) {                                          // W10 = -W11 L10 W00 in the two 32 x 32 blocks
-        const int a = 32 * wave, b = a + 16;
-        const d4v t = block16<false, false>(zero, T + b * LT + a, Wl + a * LT + a);
-        store16(Wl + b * LT + a, block16_reg<true>(zero, Wl + b * LT + b, t));
-    }
-    __syncthreads();
-    {                                                        // and of the 64 x 64 block: block (2 + wave / 2, wave % 2)
-        const int bj = 16 * (wave & 1), bi = 32 + 16 * (wave >> 1);
-        d4v out = zero;
-        for (int c = 32; c <= bi; c += 16) {
-            d4v t = zero;
-            for (int q = bj; q < 32; q += 16) t = block16<false, false>(t, T + c * LT + q, Wl + q * LT + bj);
-            out = block16_reg<true>(out, Wl + bi * LT + c, t);
-        }
-        store16(Wl + bi * LT + bj, out);
-    }
-    __syncthreads();
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - first;
     double *Ug = f.U + o * f.sU + (size_t)(NB * k) * f.Np + NB * k;
     const size_t ldv = f.V.row_length();
     double *Vg = f.V.at(o, NB * k, NB * k), *Wg = f.W.at(o, NB * k, NB * k);
-    const int c = lane;
-#pragma unroll 4
-    for (int r = wave; r < NB; r += 4) {
-        Ug[(size_t)r * f.Np + c] = c >= r ? T[c * LT + r] : 0.0;
-        Vg[(size_t)r * ldv + c] = Wl[c * LT + r];
-        Wg[(size_t)r * ldv + c] = Wl[r * LT + c];
+    for (int e = wave; e < 16; e += count) {
+        const int r = 16 * p + e;
+        Ug[(size_t)r * f.Np + lane] = lane >= r ? T[lane * LT + r] : 0.0;
+        Wg[(size_t)r * ldv + lane] = lane <= r ? Wl[r * LT + lane] : 0.0;
+        const int vr = 4 * e + (lane >> 4), vc = 16 * p + (lane & 15);
+        Vg[(size_t)vr * ldv + vc] = vr <= vc ? Wl[vc * LT + vr] : 0.0;
+        if (lane == r) f.diag[(size_t)o * f.Np + NB * k + r] = T[r * LT + r];
     }
-    if (tid < NB) f.diag[(size_t)o * f.Np + NB * k + tid] = T[tid * LT + tid];
+}
+
+// Diagonal block k of output o, in T (LDS, [64][LT], lower triangle used): its factor to U (upper form) and
+// `diag`, the inverse of the factor to W and V.  Wl: LDS of the same size.  256 threads; T is overwritten.
+// Four panels of 16 columns.  Wave 0 factors and inverts the panel's 16 x 16 diagonal block; the blocks below it
+// are products with that inverse, one wave each; then wave 0 updates the next diagonal block and goes on with it
+// while the other waves update the blocks to the right, carry the inverse of the whole block along (wave 1 + j its
+// block column j: W(p, j) = -W(p, p) S, S = sum_q L(p, q) W(q, j)) and write out what is finished.
+// Bound: the chain of 32 pairs of pivots (4100 cycles per 16 columns, over half of the time): a launch for one block
+// takes 14 us (21 us with the broadcasts through scalar registers, the inverse after the factor).
+__device__ __forceinline__ void factor_diagonal(const factor_args &f, int o, int k, double *T, double *Wl)
+{
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const d4v zero = {0.0, 0.0, 0.0, 0.0};
+    const int j = wave - 1;                                  // block column of the inverse
+    auto L = [&](int bi, int bj) { return T + 16 * bi * LT + 16 * bj; };
+    auto W = [&](int bi, int bj) { return Wl + 16 * bi * LT + 16 * bj; };
+    d4v S = zero;
+    if (wave == 0) factor16(L(0, 0), W(0, 0), f.flag + o, NB * k);
+#pragma unroll 1
+    for (int p = 0; p < 4; ++p) {
+        __syncthreads();                                     // block p of the diagonal and its inverse are there
+        if (wave < 3 - p) {
+            double *C = L(p + 1 + wave, p);
+            store16(C, block16<false, true>(zero, C, W(p, p)));
+        }
+        if (j >= 0 && j < p) store16(W(p, j), block16_reg<true>(zero, W(p, p), S));
+        __syncthreads();
+        if (p == 3) break;
+        if (wave == 0) {
+            store16(L(p + 1, p + 1), block16<true, true>(load16(L(p + 1, p + 1)), L(p + 1, p), L(p + 1, p)));
+            factor16(L(p + 1, p + 1), W(p + 1, p + 1), f.flag + o, NB * k + 16 * (p + 1));
+        } else {
+            // the other blocks (bi, bj), p < bj <= bi, numbered column by column from the second of the first column
+            const int n = 3 - p, count = n * (n + 1) / 2;
+            for (int t = wave; t < count; t += 3) {
+                int bj = 0, left = t;
+                while (left >= n - bj) left -= n - bj++;
+                const int bi = p + 1 + bj + left;
+                bj += p + 1;
+                store16(L(bi, bj), block16<true, true>(load16(L(bi, bj)), L(bi, p), L(bj, p)));
+            }
+            S = zero;
+            for (int q = j; q <= p; ++q) S = block16<false, false>(S, L(p + 1, q), W(q, j));
+            emit_panel(f, o, k, p, T, Wl, 1, 3);
+        }
+    }
+    emit_panel(f, o, k, 3, T, Wl, 0, 4);
 }
 
 // First diagonal block of a range, for every output (blockIdx.x)
@@ -278,11 +349,15 @@ __global__ __launch_bounds__(256) void factor_diagonal_kernel(factor_args f, int
     __shared__ __align__(16) double T[NB * LT], Wl[NB * LT];
     const int o = blockIdx.x;
     const double *src = f.K + o * f.sK + (size_t)(NB * k) * f.Np + NB * k;
-    // row r of the upper triangle is column r of the lower one
-    for (int e = threadIdx.x; e < NB * NB; e += 256) {
-        const int r = e >> 6, c = e & 63;
-        const double v = src[(size_t)r * f.Np + c];
-        if (c >= r) T[c * LT + r] = v;
+    // row r of the upper triangle is column r of the lower one; all loads before the first use
+    const int c = threadIdx.x & 63, r0 = threadIdx.x >> 6;
+    double v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = src[(size_t)(r0 + 4 * e) * f.Np + c];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int r = r0 + 4 * e;
+        if (c >= r) T[c * LT + r] = v[e];
         if (c > r) T[r * LT + c] = 0.0;
     }
     __syncthreads();
@@ -321,8 +396,8 @@ __device__ __forceinline__ void lds_product(f64_tile::accumulators<64> &acc, con
 //   U_kj = L_kk^-1 K_kj, and for the rows i of the range (k < i < k_end, i <= j): K_ij -= U_ki^T U_kj.
 // U_ki is computed again by every column that needs it (at most three extra products of 64 x 64 x 64 per workgroup)
 // instead of waiting for another launch.  The workgroup of the next diagonal block goes on to factor it.
-// Bound: the chain of launches: 2 products and the diagonal block, about 14 us per block column for all outputs
-// together, where three launches per column and output took 50.
+// Bound: the chain of launches: 2 products and the diagonal block, 16 us per block column for all outputs together,
+// where three launches per column and output took 50.
 constexpr size_t STEP_LDS = (size_t)4 * NB * NB * sizeof(double);
 static_assert(2 * NB * LT <= 4 * NB * NB, "the diagonal block and its inverse take the place of the blocks");
 __global__ __launch_bounds__(256) void chol_step_kernel(factor_args f, int k, int k_end)
