@@ -80,7 +80,7 @@ static void free_all(bagel_ctx *c)
     void *ptrs[] = {c->Xs, c->Xn, c->near_ok, c->Os, c->Of, c->A, c->amp, c->exp_tab, c->v4, c->w4, c->xbuf, c->part, c->xbuf_alt, c->part_alt, c->lpt, c->lam,
                     c->tape_s, c->tape_J, c->tape_h_set[0][0], c->tape_h_set[0][1], c->tape_h_set[0][2], c->tape_a_set[0],
                     c->tape_d_set[0][0], c->tape_d_set[0][1], c->tape_d_set[0][2], c->tape_h_set[1][0], c->tape_h_set[1][1],
-                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->fbuf, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
+                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->fbuf, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -122,6 +122,7 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         delete c;
         CREATE_FAIL(BAGEL_EINVAL, "bagel_create: %s", msg);
     }
+    bagel_plan_policy(c);
     const int B = dims->B, M = c->M, D = c->D;
 
     const int K = dims->ckpt_interval;
@@ -170,8 +171,12 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         ALLOC(c->tape_a_set[set], T * dims->d_a * Bz);
     }
     use_tape_set(c, 0);
-    ALLOC(c->wpad_f, (size_t)wf_total);
-    ALLOC(c->wpad_b, (size_t)wb_total);
+    if (c->p16) {
+        ALLOC(c->wpack16, (size_t)c->pack16_floats);
+    } else {
+        ALLOC(c->wpad_f, (size_t)wf_total);
+        ALLOC(c->wpad_b, (size_t)wb_total);
+    }
     ALLOC(c->gsplit, (size_t)c->ksplit * c->P);
     ALLOC(c->gacc, (size_t)c->P);
     ALLOC(c->gtheta, (size_t)c->P);
@@ -447,6 +452,22 @@ extern "C" int bagel_profile_read(bagel_ctx *c, double *kernel_ms, int *launches
     return BAGEL_OK;
 }
 
+// Packed weights, initial state and policy input; with the kernels of policy16.hip also the policy of step 0
+static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape)
+{
+    if (c->p16) {
+        const hipError_t e = bagel_launch_pack_theta16(c, theta);
+        return e == hipSuccess ? bagel_launch_start16(c, s0, goals, states, tape) : e;
+    }
+    const hipError_t e = bagel_launch_pack_theta(c, theta);
+    return e == hipSuccess ? bagel_launch_init_state(c, s0, goals, states, tape) : e;
+}
+
+static hipError_t backward_sweep(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
+{
+    return c->p16 ? bagel_launch_backward_sweep16(c, t_lo, t_hi, goals, grad_s0) : bagel_launch_backward_sweep(c, t_lo, t_hi, goals, grad_s0);
+}
+
 // Forward steps 0 .. H-1 from the state in xbuf and the policy input in tape slot 0.  jac: the sample
 // evaluation also returns its Jacobian, kept in slot t of the Jacobian tape; acts: the policy's
 // activations are kept in slot t of their tape (otherwise every step reuses slot 0).
@@ -463,11 +484,14 @@ static int run_forward(bagel_ctx *c, bool jac, bool acts, bool write_tape_s, con
     for (int t = 0; t < H; ++t) {
         const int next_slot = t + 1 < H ? (acts ? t + 1 : 0) : -1;
         // the policy of the first step runs on its own; every later one is part of the previous step's tail
-        if (t == 0) BAGEL_HIP(c, bagel_launch_policy_forward(c, 0, theta));
+        if (t == 0 && !c->p16) BAGEL_HIP(c, bagel_launch_policy_forward(c, 0, theta));
         float *prev_jac = (jac && !posterior && t > 0) ? c->tape_J + (size_t)(t - 1) * jslot : nullptr;
         BAGEL_HIP(c, gp_step_timed(c, jac, posterior ? c->cur_xi + (size_t)t * c->dm.B * c->M : nullptr, prev_jac));
-        BAGEL_HIP(c, bagel_launch_step_tail(c, t, t, next_slot, jac, true, write_tape_s, theta, goals, states_out,
-                                            posterior));
+        if (c->p16)
+            BAGEL_HIP(c, bagel_launch_step_tail16(c, t, t, next_slot, jac, write_tape_s, goals, states_out, posterior));
+        else
+            BAGEL_HIP(c, bagel_launch_step_tail(c, t, t, next_slot, jac, true, write_tape_s, theta, goals, states_out,
+                                                posterior));
         double *tx = c->xbuf; c->xbuf = c->xbuf_alt; c->xbuf_alt = tx;
         double *tp = c->part; c->part = c->part_alt; c->part_alt = tp;
     }
@@ -490,8 +514,7 @@ static int rollout_loss_impl(bagel_ctx *c, const char *who, const float *theta, 
     if (posterior ? !c->post_prepared : !c->prepared)
         BAGEL_FAIL(c, BAGEL_ENOTPREPARED, "%s: %s", who, posterior ? "no posterior cache installed" : "no samples installed");
     c->cur_xi = posterior ? xi : nullptr;
-    BAGEL_HIP(c, bagel_launch_pack_theta(c, theta));
-    BAGEL_HIP(c, bagel_launch_init_state(c, s0, goals, states, false));
+    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, false));
     const int rc = run_forward(c, false, false, false, theta, goals, states);
     if (rc != BAGEL_OK) return rc;
     BAGEL_HIP(c, bagel_launch_finish_loss(c, loss, loss_per_traj));
@@ -524,14 +547,13 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
     const int H = c->dm.H, K = c->T_tape;
     const bool ckpt = K < H;
     int rc;
-    BAGEL_HIP(c, bagel_launch_pack_theta(c, theta));
-    BAGEL_HIP(c, bagel_launch_init_state(c, s0, goals, states, true));
+    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, true));
     // One forward pass with Jacobians.  Without checkpointing it also keeps the policy's activations.
     rc = run_forward(c, true, !ckpt, true, theta, goals, states);
     if (rc != BAGEL_OK) return rc;
     BAGEL_HIP(c, bagel_launch_finish_loss(c, loss, loss_per_traj));
     if (!ckpt) {
-        BAGEL_HIP(c, bagel_launch_backward_sweep(c, 0, H, goals, grad_s0));
+        BAGEL_HIP(c, backward_sweep(c, 0, H, goals, grad_s0));
         BAGEL_HIP(c, bagel_launch_weight_grad(c, H, false, grad_theta));
         return BAGEL_OK;
     }
@@ -554,7 +576,7 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
         const int t0 = seg * K, t1 = (t0 + K < H) ? t0 + K : H;
         use_tape_set(c, seg & 1);
         c->stream = c->side;
-        hipError_t r = replay ? bagel_launch_policy_replay(c, t0, t1, theta, goals)
+        hipError_t r = replay ? (c->p16 ? bagel_launch_policy_replay16(c, t0, t1, goals) : bagel_launch_policy_replay(c, t0, t1, theta, goals))
                               : bagel_launch_weight_grad(c, t1 - t0, seg != n_seg - 1, seg == 0 ? grad_theta : nullptr);
         c->stream = main_stream;
         if (r == hipSuccess && replay) r = hipEventRecord(c->ev_replay[seg & 1], c->side);
@@ -567,7 +589,7 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
         const int t0 = seg * K, t1 = (t0 + K < H) ? t0 + K : H, set = seg & 1;
         e = hipStreamWaitEvent(main_stream, c->ev_replay[set], 0);
         use_tape_set(c, set);
-        if (e == hipSuccess) e = bagel_launch_backward_sweep(c, t0, t1, goals, grad_s0);
+        if (e == hipSuccess) e = backward_sweep(c, t0, t1, goals, grad_s0);
         if (e == hipSuccess) e = hipEventRecord(c->ev_sweep[set], main_stream);
         if (e == hipSuccess && seg > 0) e = on_side(seg - 1, true);
         if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev_sweep[set], 0);

@@ -70,6 +70,9 @@ struct bagel_ctx {
     float *wpad_f, *wpad_b;      // zero-padded weights: forward [out pad 32][in pad 32], backward [in pad 32][out pad 32]
     int wpf_off[3], wpf_rp[3], wpf_kp[3];
     int wpb_off[3], wpb_rp[3], wpb_kp[3];
+    int p16;                     // policy kernels: 0 policy.hip, 1 .. 3 an instance of policy16.hip
+    int pack16_floats;
+    float *wpack16;              // packed weights of policy16.hip
     float *gsplit;               // [ksplit][P] split-contraction partial weight gradients
     double *gacc;                // [P] gradient accumulated over segments
     float *gtheta;               // [P] gradient of the current iteration of bagel_optimize
@@ -153,6 +156,18 @@ hipError_t bagel_launch_backward_sweep(bagel_ctx *ctx, int t_lo, int t_hi, const
 hipError_t bagel_launch_weight_grad(bagel_ctx *ctx, int n_slots, bool accumulate, float *grad_theta);
 hipError_t bagel_launch_adam(bagel_ctx *ctx, float *theta, const float *grad, float *m, float *v, int count, double lr,
                              double beta1, double beta2, double eps, double corr1, double corr2);
+
+// ---- policy16.hip (contexts with p16 != 0) -----------------------------------------------
+// sets p16 and pack16_floats from the widths and the batch
+void bagel_plan_policy(bagel_ctx *ctx);
+hipError_t bagel_launch_pack_theta16(bagel_ctx *ctx, const float *theta);
+// start of a rollout: state from s0, tapes, zero cost, policy of step 0 into tape slot 0
+hipError_t bagel_launch_start16(bagel_ctx *ctx, const float *s0, const float *goals, float *states_out, bool tape);
+// the same roles as bagel_launch_step_tail, _policy_replay and _backward_sweep
+hipError_t bagel_launch_step_tail16(bagel_ctx *ctx, int t, int slot, int next_slot, bool jac, bool write_tape_s, const float *goals,
+                                    float *states_out, bool direct);
+hipError_t bagel_launch_policy_replay16(bagel_ctx *ctx, int t0, int t1, const float *goals);
+hipError_t bagel_launch_backward_sweep16(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
 
 // ---- posterior.hip ------------------------------------------------------------------------
 // mu + sqrt(var) xi and its Jacobian for every trajectory and output at xbuf, into ctx->part as

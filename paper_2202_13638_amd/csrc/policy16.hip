@@ -1,0 +1,842 @@
+// The policy network, the end of a rollout step around it and the backward sweep, 16 trajectories per workgroup.
+//
+// Same mathematics as policy.hip, for the sizes at which a step is a chain of latencies: narrow policies at any
+// batch, wide ones while the batch leaves compute units idle with 32 trajectories per workgroup (the rule is in
+// bagel_plan_policy).  What bounds these kernels is not the matrix work (a 64 x 64 layer for 16 trajectories is 512
+// cycles of a wave) but what lies between: launches, trips to memory, barriers, exchanges through LDS.  So:
+//   - v_mfma_f32_16x16x4_f32 (D[16x16] += A[16x4] B[4x16]; lane l = 16 g + j feeds A[l % 16][g] and B[g][j], register
+//     r holds D[4 g + r][j]): rows = units, columns = trajectories.  Wave w owns the NT row tiles w NT .. of every
+//     hidden layer, all weights it needs are in its registers for the whole launch.
+//   - Every sum is formed in the order of policy.hip, so results agree with it bit for bit (a matrix instruction is a
+//     chain of fused multiply-adds over its contraction index, and 16x16x4 continues a chain where 32x32x2 takes
+//     two instructions).  There, a chain runs through eight inputs as 0 4 1 5 2 6 3 7 and a long contraction is cut
+//     into slices that are added up afterwards (slice_blocks).  Hence the order of units inside a block of 16: row
+//     i = 4 g + r of a tile is unit unit16(g, r), and instruction s of a block contracts, in lane group g, unit16(g, s).
+//     A lane's four results of a tile are then its operands of the next contraction over those 16 units, in the order
+//     they are needed: one 16-byte LDS write and reads of [trajectory][tile][4 g + r].
+//   - The output layer (forward) and the input layer (backward) have one row tile: wave w takes slice w of them.
+// Instances: 4 waves of one tile (hidden widths <= 64), 8 of one (<= 128), 8 of two (<= 256).
+#include "bagel_internal.h"
+
+namespace {
+
+constexpr int PL = 16;                       // trajectories per workgroup
+constexpr int HS = 20;                       // LDS row length of the policy input and the action adjoint
+
+// unit within a block of 16 that row 4 g + r of a tile (lane group g's register r) stands for
+__host__ __device__ constexpr int unit16(int g, int r) { return ((g & 1) << 2 | g >> 1) + ((r & 1) << 1 | (r & 2) << 2); }
+// instructions a contraction over the first n <= 16 units of a block needs
+__host__ __device__ constexpr int steps16(int n) { return n <= 2 ? 1 : (n <= 8 ? 2 : (n <= 10 ? 3 : 4)); }
+// blocks of 16 per slice of a contraction over k inputs for `rows` outputs (the split of policy.hip over its eight waves)
+__host__ __device__ inline int slice_blocks(int rows, int k)
+{
+    const int nrt = (rows + 31) / 32, k32 = (k + 31) / 32;
+    int ks = 8 / nrt;
+    if (ks > k32) ks = k32;
+    return 2 * ((k32 + ks - 1) / ks);
+}
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+template <int NW, int NT>
+struct shape16 {
+    static constexpr int TT = NW * NT;       // row tiles of a hidden layer
+    static constexpr int ROWS = 4 * NW;      // thread rows of 16 trajectories
+    static constexpr int AS = 16 * TT + 4;   // LDS row length of the activations: rows start 4 banks apart
+};
+
+struct policy16_args {
+    int B, nl, ds, da;
+    int width[4];
+    float act_bound;
+    const float *pack;                       // packed weights of this pass
+    float *h[3];                             // slot 0 of the tapes of the layer inputs
+    float *a_slot;                           // slot 0: [d_a][B]
+};
+
+// Offsets inside the packed weights, in floats (see pack_theta16_kernel)
+struct pack16 {
+    int nl, TT, nsi, nsa;                    // nsi, nsa: instructions for a contraction over the inputs / actions
+    int fs, bs;                              // blocks per slice of the middle layer, forward and backward
+    __host__ __device__ int mid_size() const { return nl == 3 ? TT * TT * 256 : 0; }
+    __host__ __device__ int f_first() const { return 0; }
+    __host__ __device__ int f_mid() const { return f_first() + TT * nsi * 64; }
+    __host__ __device__ int f_last() const { return f_mid() + mid_size(); }
+    __host__ __device__ int bias(int l) const { return f_last() + TT * 256 + l * TT * 16; }
+    __host__ __device__ int b_top() const { return bias(2) + 16; }
+    __host__ __device__ int b_mid() const { return b_top() + TT * nsa * 64; }
+    __host__ __device__ int b_first() const { return b_mid() + mid_size(); }
+    __host__ __device__ int total() const { return b_first() + TT * 256; }
+};
+
+pack16 make_pack(const bagel_ctx *c)
+{
+    const int TT = c->p16 == 1 ? 4 : (c->p16 == 2 ? 8 : 16);
+    return pack16{c->n_layers, TT, steps16(c->d_in), steps16(c->dm.d_a), slice_blocks(c->width[2], c->width[1]),
+                  slice_blocks(c->width[1], c->width[2])};
+}
+
+// theta -> the register contents of the lanes.  "tile t" = units 16 t .. of the layer that is produced, lane = 16 g + i
+// with i = 4 gi + ri, u = unit16(gi, ri):
+//   wide contraction   [t][kb][lane][s] = W(16 t + u, 16 kb + unit16(g, s))
+//   narrow contraction [t][s][lane]     = W(16 t + u, unit16(g, s))
+// with W(row, k) the layer's matrix (forward) or its transpose (backward), zero outside it.  Also the biases, padded.
+__global__ __launch_bounds__(256) void pack_theta16_kernel(const float *__restrict__ theta, float *__restrict__ dst, pack16 p, int w0,
+                                                           int w1, int w2, int w3, int wo0, int wo1, int wo2, int bo0, int bo1,
+                                                           int bo2)
+{
+    const int idx = blockIdx.x * 256 + threadIdx.x;
+    if (idx >= p.total()) return;
+    const int width[4] = {w0, w1, w2, w3};
+    const int last = p.nl - 1;
+    const int w_last = last == 2 ? wo2 : wo1, b_last = last == 2 ? bo2 : bo1;
+    const int n_last = width[last + 1], h_last = width[last];              // actions, units of the last hidden layer
+    float v = 0.0f;
+    auto wide = [&](int e, int &row, int &k, int kbs) {
+        const int s = e & 3, lane = (e >> 2) & 63, blk = e >> 8;
+        row = 16 * (blk / kbs) + unit16(lane >> 2 & 3, lane & 3);
+        k = 16 * (blk % kbs) + unit16(lane >> 4, s);
+    };
+    auto narrow = [&](int e, int &row, int &k, int ns) {
+        const int lane = e & 63, blk = e >> 6;
+        row = 16 * (blk / ns) + unit16(lane >> 2 & 3, lane & 3);
+        k = unit16(lane >> 4, blk % ns);
+    };
+    int r, k;
+    if (idx < p.f_mid()) {
+        narrow(idx - p.f_first(), r, k, p.nsi);
+        if (r < width[1] && k < width[0]) v = theta[wo0 + r * width[0] + k];
+    } else if (idx < p.f_last()) {
+        wide(idx - p.f_mid(), r, k, p.TT);
+        if (r < width[2] && k < width[1]) v = theta[wo1 + r * width[1] + k];
+    } else if (idx < p.bias(0)) {
+        wide(idx - p.f_last(), r, k, p.TT);
+        if (r < n_last && k < h_last) v = theta[w_last + r * h_last + k];
+    } else if (idx < p.b_top()) {
+        const int e = idx - p.bias(0), l = e / (16 * p.TT), q = e - l * 16 * p.TT;
+        const int u = (q & ~15) + unit16(q >> 2 & 3, q & 3);               // in the order of a lane's registers
+        if (l == 2) v = q < n_last ? theta[b_last + q] : 0.0f;             // the action's bias in the third place, plain
+        else if (l < last && u < width[l + 1]) v = theta[(l == 0 ? bo0 : bo1) + u];
+    } else if (idx < p.b_mid()) {
+        narrow(idx - p.b_top(), r, k, p.nsa);
+        if (r < h_last && k < n_last) v = theta[w_last + k * h_last + r];
+    } else if (idx < p.b_first()) {
+        wide(idx - p.b_mid(), r, k, p.TT);
+        if (r < width[1] && k < width[2]) v = theta[wo1 + k * width[1] + r];
+    } else {
+        wide(idx - p.b_first(), r, k, p.TT);
+        if (r < width[0] && k < width[1]) v = theta[wo0 + k * width[0] + r];
+    }
+    dst[idx] = v;
+}
+
+// tanh in float32, 1 - 2 / (e^{2z} + 1): see policy.hip
+__device__ __forceinline__ float tanh_fast(float z)
+{
+    const float t = __builtin_amdgcn_exp2f(z * 2.8853900817779268f);
+    return fmaf(-2.0f, __builtin_amdgcn_rcpf(t + 1.0f), 1.0f);
+}
+
+__device__ __forceinline__ f4v mfma16(float a, float b, f4v acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); }
+
+// 4-byte read that the optimiser keeps where it is written (see policy.hip)
+__device__ __forceinline__ float load_pinned(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); }
+__device__ __forceinline__ double load_pinned(const double *p)
+{
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    return __longlong_as_double((long long)v);
+}
+
+// The weights of the forward pass a wave multiplies with
+template <int NW, int NT>
+struct forward_weights {
+    float first[NT][4];                      // narrow contraction over the policy input, at most 16 wide
+    f4v mid[NT][NW * NT], last[2], bias0[NT], bias1[NT];      // last: the two blocks of slice `wave`
+};
+
+template <int NW, int NT>
+__device__ __forceinline__ void load_weights(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane)
+{
+    constexpr int TT = NW * NT;
+    const f4v *mid = reinterpret_cast<const f4v *>(pack + p.f_mid()) + lane;
+    const f4v *last = reinterpret_cast<const f4v *>(pack + p.f_last()) + lane;
+    const int g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int tile = wave * NT + t;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f.first[t][s] = pack[p.f_first() + (tile * p.nsi + min(s, p.nsi - 1)) * 64 + lane];
+        f.bias0[t] = *reinterpret_cast<const f4v *>(pack + p.bias(0) + 16 * tile + 4 * g);
+        f.bias1[t] = *reinterpret_cast<const f4v *>(pack + p.bias(1) + 16 * tile + 4 * g);
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) f.last[e] = last[min(2 * wave + e, TT - 1) * 64];
+    if (p.nl == 3) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int kb = 0; kb < TT; ++kb) f.mid[t][kb] = mid[((wave * NT + t) * TT + kb) * 64];
+    }
+}
+
+// One contraction over the blocks of a wide layer for the wave's NT tiles: w[t][kb] the weights, act the operands, n inputs,
+// sl blocks per slice; slices are added up in order
+template <int NT, int TT, int AS>
+__device__ __forceinline__ void contract_wide(f4v (&z)[NT], const f4v (&w)[NT][TT], const float *act, int lane, int n, int sl)
+{
+    const float *x0 = act + (lane & 15) * AS + 4 * (lane >> 4);
+    f4v acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) z[t] = acc[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    bool first = true;
+    int left = sl;
+#pragma unroll
+    for (int kb = 0; kb < TT; ++kb)
+        if (16 * kb < n) {
+            const f4v x = *reinterpret_cast<const f4v *>(x0 + 16 * kb);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = mfma16(w[t][kb][s], x[s], acc[t]);
+            if (--left == 0 || 16 * (kb + 1) >= n) {                       // end of a slice (wave-uniform)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    z[t] = first ? acc[t] : z[t] + acc[t];
+                    acc[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+                first = false;
+                left = sl;
+            }
+        }
+}
+
+// Slice `wave` (two blocks) of a contraction with one row tile: operands from act
+template <int TT, int AS>
+__device__ __forceinline__ f4v contract_slice(const f4v (&w)[2], const float *act, int wave, int lane)
+{
+    const float *x0 = act + (lane & 15) * AS + 4 * (lane >> 4) + 32 * wave;
+    f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const f4v x = *reinterpret_cast<const f4v *>(x0 + 16 * e);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma16(w[e][s], x[s], acc);
+    }
+    return acc;
+}
+
+// pi_theta for the 16 trajectories of a workgroup, input in h0 ([trajectory][HS], published by a barrier): hidden activations
+// to slot `slot` of their tapes, the slices of the action's contraction to red ([slice][action][PL]; the caller's barrier
+// publishes them).  act: two buffers.
+template <int NW, int NT>
+__device__ __forceinline__ void policy16_layers(const policy16_args &a, const pack16 &p, const forward_weights<NW, NT> &f, size_t slot,
+                                                int wave, int lane, int b, bool live, const float *h0, float (*act)[PL * shape16<NW, NT>::AS],
+                                                float *red)
+{
+    constexpr int TT = NW * NT, AS = shape16<NW, NT>::AS;
+    const int j = lane & 15, g = lane >> 4;
+    f4v h[NT];
+    float in[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) in[s] = h0[j * HS + unit16(0, s) + ((g & 1) << 2 | g >> 1)];   // zero past the input
+    auto epilogue = [&](int l, const f4v (&bias)[NT], float *out) {
+        const int n = a.width[l + 1];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int u0 = 16 * (wave * NT + t) + ((g & 1) << 2 | g >> 1);
+            float *dst = a.h[l + 1] + (slot * n + u0) * a.B + b;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int u = u0 + unit16(0, r);
+                h[t][r] = u < n ? tanh_fast(h[t][r] + bias[t][r]) : 0.0f;
+                if (live && u < n) dst[(size_t)unit16(0, r) * a.B] = h[t][r];
+            }
+            *reinterpret_cast<f4v *>(out + j * AS + 16 * (wave * NT + t) + 4 * g) = h[t];
+        }
+        __syncthreads();
+    };
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        h[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (s < p.nsi) h[t] = mfma16(f.first[t][s], in[s], h[t]);
+    }
+    epilogue(0, f.bias0, act[0]);
+    if (p.nl == 3) {
+        contract_wide<NT, TT, AS>(h, f.mid, act[0], lane, a.width[1], p.fs);
+        epilogue(1, f.bias1, act[1]);
+    }
+    const int n_last = a.width[p.nl - 1];
+    if (32 * wave < n_last) {
+        const f4v o = contract_slice<TT, AS>(f.last, act[p.nl - 2], wave, lane);
+        const int o0 = (g & 1) << 2 | g >> 1;                               // actions o0 and o0 + 2, at most 8
+#pragma unroll
+        for (int r = 0; r < 2; ++r) red[(wave * 8 + o0 + 2 * r) * PL + j] = o[r];
+    }
+}
+
+// The action of thread (output o, trajectory): slices in order, bias, bound; to the tape and, if x, to the GP input
+__device__ __forceinline__ void finish_action(const policy16_args &a, const pack16 &p, size_t slot, int o, int bl, int b, bool live,
+                                              const float *red, float bias, double *x)
+{
+    const int slices = (a.width[p.nl - 1] + 31) / 32;
+    float z = red[o * PL + bl];
+    for (int w = 1; w < slices; ++w) z += red[(w * 8 + o) * PL + bl];
+    z += bias;
+    float v = z, out = z;
+    if (a.act_bound > 0.0f) {
+        v = tanh_fast(z);
+        out = a.act_bound * v;
+    }
+    if (live) {
+        a.a_slot[(slot * a.da + o) * a.B + b] = v;
+        if (x) x[(size_t)(a.ds + o) * a.B + b] = (double)out;
+    }
+}
+
+// ---- end of step t and policy of step t + 1 ------------------------------------------------------------------------
+// As step_tail_kernel of policy.hip.  s0 != null: the start of a rollout instead (state from s0, no sums, no cost).
+struct tail16_args {
+    int D, M, dg, ngk, ngl, ncomp;
+    int cost_kind, do_policy, direct;
+    float sigma_r;
+    int tracked[8];
+    float q[8];
+    const double *amp, *part, *x_cur;
+    double *x_next, *lpt;
+    float *tape_s_next, *states_out_next;
+    const float *goals_t, *goals_next, *s0;
+    float *jdst;
+    size_t slot;                             // tape slot of the policy's activations
+};
+
+constexpr int TAIL_GROUPS = 128;             // value sums of a trajectory that are staged in LDS
+
+// (p[0] + .. + p[7]) + (p[8] + p[9] + ...): the order in which step_tail_kernel adds n group sums
+template <class P>
+__device__ __forceinline__ double sum_groups16(P p, int n, size_t stride)
+{
+    double s = 0.0, rest = 0.0;
+    for (int c0 = 0; c0 < n; c0 += 8) {
+        double v[8], t = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = c0 + u < n ? p[(size_t)(c0 + u) * stride] : 0.0;
+        if (c0 > 0) t = rest;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t += v[u];
+        if (c0 > 0) rest = t;
+        else s = t;
+    }
+    return n > 8 ? s + rest : s;
+}
+
+template <int NW, int NT>
+__global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, policy16_args a, pack16 p)
+{
+    using S = shape16<NW, NT>;
+    __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
+    __shared__ double fS[TAIL_GROUPS][PL], sS[8][PL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bl = tid & (PL - 1), row = tid >> 4;
+    const int b0 = blockIdx.x * PL;
+    const bool live = b0 + bl < a.B;         // (trajectory bl is also lane % 16: the same for the matrix phases)
+    const int b = live ? b0 + bl : a.B - 1;
+    const int B = a.B, ds = a.ds, d_in = a.width[0];
+
+    // Everything that comes from memory is requested before anything waits, the values needed first first.
+    double x_in = 0.0, lp_in = 0.0;
+    float g_in = 0.0f, gt_in[8], bias_in = 0.0f;
+    const bool cost_row = !r.s0 && row == S::ROWS - 1;
+    if (row < ds) x_in = r.s0 ? (double)r.s0[(size_t)b * ds + row] : r.x_cur[(size_t)row * B + b];
+    else if (row < d_in && r.goals_next) g_in = r.goals_next[(size_t)b * r.dg + (row - ds)];
+    if (cost_row) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) gt_in[j] = j < r.dg ? r.goals_t[(size_t)b * r.dg + j] : 0.0f;
+        lp_in = r.lpt[b];
+    }
+    // The groups' value sums are fetched by all threads, a few each, and added up from LDS in the order of policy.hip (the
+    // first eight, then the rest); more than fit there are added up by one thread row per sum.
+    const size_t stride = (size_t)(1 + r.D) * B;
+    const int groups = r.M * (r.ngk + r.ngl);
+    const bool staged = groups <= TAIL_GROUPS;
+    constexpr int PER = TAIL_GROUPS / S::ROWS;
+    double v[PER];
+    if (r.s0) {
+    } else if (r.direct) {
+        for (int qi = row; qi < r.M * r.ncomp; qi += S::ROWS) {
+            const int m = qi / r.ncomp, comp = qi - m * r.ncomp;
+            const double val = r.part[(size_t)m * stride + (size_t)comp * B + b];
+            if (comp == 0) fS[m][bl] = val;
+            else if (live) r.jdst[(size_t)(m * r.D + comp - 1) * B + b] = (float)val;
+        }
+    } else if (staged) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (u * S::ROWS < groups) v[u] = load_pinned(r.part + (size_t)min(row + u * S::ROWS, groups - 1) * stride + b);
+    }
+    forward_weights<NW, NT> f;
+    if (r.do_policy) {
+        load_weights(f, a.pack, p, wave, lane);
+        bias_in = a.pack[p.bias(2) + min(row, 7)];
+    }
+    if (!r.s0 && !r.direct) {
+        if (staged) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u)
+                if (u * S::ROWS < groups) fS[min(row + u * S::ROWS, TAIL_GROUPS - 1)][bl] = v[u];
+        } else if (row < 2 * r.M) {
+            const bool kernel = row < r.M;
+            fS[row][bl] = sum_groups16(r.part + (size_t)(kernel ? row * r.ngk : r.M * r.ngk + (row - r.M) * r.ngl) * stride + b,
+                                       kernel ? r.ngk : r.ngl, stride);
+        }
+    }
+    __syncthreads();
+    if (row < 16) {
+        float hin = 0.0f;
+        if (row < ds) {
+            double s = x_in;
+            if (r.direct) {
+                s += fS[row][bl];
+            } else if (!r.s0) {
+                double k, e;
+                if (staged) {
+                    k = sum_groups16(&fS[row * r.ngk][bl], r.ngk, PL);
+                    e = sum_groups16(&fS[r.M * r.ngk + row * r.ngl][bl], r.ngl, PL);
+                } else {
+                    k = fS[row][bl];
+                    e = fS[r.M + row][bl];
+                }
+                s += r.amp[row] * e + k;
+            }
+            sS[row][bl] = s;
+            hin = (float)s;
+            if (live) {
+                r.x_next[(size_t)row * B + b] = s;
+                if (r.tape_s_next) r.tape_s_next[(size_t)row * B + b] = hin;
+                if (r.states_out_next) r.states_out_next[(size_t)b * ds + row] = hin;
+            }
+        } else if (row < d_in) {
+            hin = g_in;
+        }
+        h0[bl * HS + row] = hin;
+        if (r.do_policy && live && row < d_in) a.h[0][(r.slot * d_in + row) * B + b] = hin;
+    }
+    if (r.s0 && row == 0 && live) r.lpt[b] = 0.0;
+    __syncthreads();
+    if (r.do_policy) policy16_layers<NW, NT>(a, p, f, r.slot, wave, lane, b, live, h0, act, red);
+    if (cost_row && live) {
+        double e = 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (j < r.dg) {
+                const double dlt = sS[r.tracked[j]][bl] - (double)gt_in[j];
+                e += (double)r.q[j] * dlt * dlt;
+            }
+        if (r.cost_kind == 1) {
+            const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
+            e = -exp(-e / (2.0 * sr2));
+        }
+        r.lpt[b] = lp_in + e;
+    }
+    if (!r.do_policy) return;
+    __syncthreads();
+    if (row < a.da) finish_action(a, p, r.slot, row, bl, b, live, red, bias_in, r.x_next);
+}
+
+// ---- activation tape of the steps t0 .. t0 + n_slots - 1 rebuilt from the kept states (see policy_replay_kernel) --------
+struct replay16_args {
+    const float *tape_s, *goals;
+    int t0, dg, n_slots, per;                // per: steps per workgroup
+};
+
+template <int NW, int NT>
+__global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args r, policy16_args a, pack16 p)
+{
+    using S = shape16<NW, NT>;
+    __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bl = tid & (PL - 1), row = tid >> 4;
+    const bool live = blockIdx.x * PL + bl < a.B;
+    const int b = live ? blockIdx.x * PL + bl : a.B - 1;
+    const int B = a.B, ds = a.ds, d_in = a.width[0];
+    forward_weights<NW, NT> f;
+    load_weights(f, a.pack, p, wave, lane);
+    const float bias = a.pack[p.bias(2) + min(row, 7)];
+    const int s_end = min(r.n_slots, (int)(blockIdx.y + 1) * r.per);
+    auto input = [&](int sl) {
+        const size_t t = (size_t)(r.t0 + sl);
+        if (row < ds) return load_pinned(r.tape_s + (t * ds + row) * B + b);
+        if (row < d_in) return load_pinned(r.goals + (t * B + b) * r.dg + (row - ds));
+        return 0.0f;
+    };
+    float in = input(blockIdx.y * r.per);
+    for (int sl = blockIdx.y * r.per; sl < s_end; ++sl) {
+        if (row < 16) h0[bl * HS + row] = in;
+        if (live && row < d_in) a.h[0][((size_t)sl * d_in + row) * B + b] = in;
+        __syncthreads();
+        if (sl + 1 < s_end) in = input(sl + 1);
+        policy16_layers<NW, NT>(a, p, f, sl, wave, lane, b, live, h0, act, red);
+        __syncthreads();
+        if (row < a.da) finish_action(a, p, sl, row, bl, b, live, red, bias, nullptr);
+    }
+}
+
+// ---- backward sweep -----------------------------------------------------------------------------------------------------
+// As backward_sweep_kernel of policy.hip: the steps t_hi-1 .. t_lo of 16 trajectories per workgroup.  What a step reads from
+// the tapes is requested two steps ahead, into the registers that held the values of the step just done with them
+// (two sets, the loop body handles two steps), so that no value is copied and nothing waits for a load it does not need.
+struct sweep16_args {
+    int B, nl, ds, da, dg, D, M, H, t_hi, t_lo;
+    int width[4];
+    float act_bound, sigma_r;
+    int cost_kind;
+    int tracked[8];
+    float q[8];
+    const float *pack;
+    const float *tape_h[3];
+    float *tape_d[3];
+    const float *tape_a, *tape_J, *tape_s, *goals;
+    double *lam;
+    float *grad_s0;
+};
+
+// MM, DG: at least M and d_g (rounded up to 4 or 8, 2 or 8)
+template <int NT, int MM, int DG>
+struct sweep16_tape {
+    float J[MM], th;                         // rows d < D: J[m][d]; actions: tanh output of the bounded action
+    float sv[DG], gv[DG];                    // tracked states of s_{t-1} and the goals they are compared with
+    f4v top[NT], mid[NT];                    // tanh outputs of the wave's units
+};
+
+// lam + (1/B) d cost / d s_i
+template <int DG>
+__device__ __forceinline__ double add_cost_gradient16(const sweep16_args &a, double lam, int i, const float (&sv)[DG], const float (&gv)[DG])
+{
+    double r[DG], e = 0.0;
+#pragma unroll
+    for (int j = 0; j < DG; ++j) {
+        r[j] = j < a.dg ? (double)sv[j] - (double)gv[j] : 0.0;
+        e += (double)a.q[j] * r[j] * r[j];                                 // (absent components add +0.0)
+    }
+    double factor = 2.0;
+    if (a.cost_kind == 1) {
+        const double sr2 = (double)a.sigma_r * (double)a.sigma_r;
+        factor = exp(-e / (2.0 * sr2)) / sr2;
+    }
+    factor /= (double)a.B;
+#pragma unroll
+    for (int j = 0; j < DG; ++j)
+        if (j < a.dg && a.tracked[j] == i) lam += factor * (double)a.q[j] * r[j];
+    return lam;
+}
+
+template <int NW, int NT, int MM, int DG>
+__global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args a, pack16 p)
+{
+    using S = shape16<NW, NT>;
+    constexpr int TT = S::TT, AS = S::AS;
+    __shared__ __align__(16) float act[2][PL * AS], dS[PL * HS], red[NW * PL * HS];
+    __shared__ double lamS[8][PL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, g = lane >> 4, ug = (g & 1) << 2 | g >> 1;       // unit16(g, r) = ug + unit16(0, r)
+    const int bl = tid & (PL - 1), row = tid >> 4;
+    const bool live = blockIdx.x * PL + bl < a.B;
+    const int b = live ? blockIdx.x * PL + bl : a.B - 1;
+    const int last = a.nl - 1;
+    const size_t B = a.B;
+    const int n_top = a.width[last];
+
+    // weights: top layer (contraction over the actions), middle, input layer (the wave's slice)
+    float w_top[NT][2];
+    f4v w_mid[NT][TT], w_first[2];           // w_first: the two blocks of slice `wave`
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int tile = wave * NT + t;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) w_top[t][s] = a.pack[p.b_top() + (tile * p.nsa + min(s, p.nsa - 1)) * 64 + lane];
+        if (a.nl == 3) {
+#pragma unroll
+            for (int kb = 0; kb < TT; ++kb) w_mid[t][kb] = reinterpret_cast<const f4v *>(a.pack + p.b_mid())[(tile * TT + kb) * 64 + lane];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) w_first[e] = reinterpret_cast<const f4v *>(a.pack + p.b_first())[min(2 * wave + e, TT - 1) * 64 + lane];
+    // rows and units past the end are clamped duplicates nobody uses
+    const int rowc = min(row, a.D - 1), ra = min(max(rowc - a.ds, 0), a.da - 1);
+    auto request_front = [&](int t, sweep16_tape<NT, MM, DG> &s) {          // what the first phase of step t - 1 reads
+        const size_t slot = (size_t)(t - 1 - a.t_lo);
+        const float *Jt = a.tape_J + slot * a.M * a.D * B + (size_t)rowc * B + b;
+#pragma unroll
+        for (int m = 0; m < MM; ++m) s.J[m] = load_pinned(Jt + (size_t)min(m, a.M - 1) * a.D * B);
+        s.th = load_pinned(a.tape_a + (slot * a.da + ra) * B + b);
+    };
+    auto request_units = [&](int t, f4v (&h)[NT], int l) {
+        const size_t slot = (size_t)(t - 1 - a.t_lo);
+        const int n = a.width[l];
+        const float *hl = a.tape_h[l] + slot * n * B + b;
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h[k][r] = load_pinned(hl + (size_t)min(16 * (wave * NT + k) + ug + unit16(0, r), n - 1) * B);
+    };
+    auto request_cost = [&](int t, sweep16_tape<NT, MM, DG> &s) {           // data of the state s_{t-1}, for t - 1 >= 1
+        const int tc = t - 1 >= 1 ? t : 2;
+        const float *st = a.tape_s + (size_t)min(tc - 1, a.H) * a.ds * B + b;
+        const float *gt = a.goals + ((size_t)min(tc - 2, a.H - 1) * B + b) * a.dg;
+#pragma unroll
+        for (int k = 0; k < DG; ++k) {
+            const int kc = min(k, a.dg - 1);
+            s.sv[k] = load_pinned(st + (size_t)a.tracked[kc] * B);
+            s.gv[k] = load_pinned(gt + kc);
+        }
+    };
+    sweep16_tape<NT, MM, DG> set[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int t = max(a.t_hi - e, a.t_lo + 1);
+        request_front(t, set[e]);
+        request_units(t, set[e].top, last);
+        if (a.nl == 3) request_units(t, set[e].mid, 1);
+        request_cost(t, set[e]);
+    }
+
+    // adjoint of the state of thread (row < d_s, trajectory): in its register, and in LDS for the contraction with J
+    double lam = 0.0, us = 0.0;
+    if (row < a.ds) {
+        if (a.t_hi == a.H) {
+            float sv[DG], gv[DG];
+#pragma unroll
+            for (int k = 0; k < DG; ++k) {
+                const int kc = min(k, a.dg - 1);
+                sv[k] = a.tape_s[((size_t)a.H * a.ds + a.tracked[kc]) * B + b];
+                gv[k] = a.goals[((size_t)(a.H - 1) * B + b) * a.dg + kc];
+            }
+            lam = add_cost_gradient16<DG>(a, 0.0, row, sv, gv);
+        } else {
+            lam = a.lam[(size_t)row * B + b];
+        }
+        lamS[row][bl] = lam;
+    } else if (row < 8) {
+        lamS[row][bl] = 0.0;                 // outputs past M add nothing to u
+    }
+    for (int e = tid; e < PL * HS; e += 64 * NW) dS[e] = 0.0f;
+    __syncthreads();
+
+    auto step = [&](int t, sweep16_tape<NT, MM, DG> &s) {
+        const size_t slot = (size_t)(t - 1 - a.t_lo);
+        const int tn = max(t - 2, a.t_lo + 1);                             // the step this register set is requested for next
+        // u = J^T lam: rows d < d_s stay with their thread, the action rows go through the bound to the policy backward
+        if (row < a.D) {
+            double u = 0.0;
+#pragma unroll
+            for (int m = 0; m < MM; ++m) u += (double)s.J[m] * lamS[m][bl];
+            if (row < a.ds) {
+                us = u;
+            } else {
+                if (a.act_bound > 0.0f) u *= (double)a.act_bound * (1.0 - (double)s.th * (double)s.th);
+                const float d = (float)u;
+                dS[bl * HS + row - a.ds] = d;
+                if (live) a.tape_d[last][(slot * a.da + row - a.ds) * B + b] = d;
+            }
+        }
+        request_front(tn, s);
+        __syncthreads();
+        f4v dl[NT];
+        auto derivative = [&](const f4v (&h)[NT], int l, float *out) {     // delta_l = (W^T delta) (1 - h^2), to its tape and LDS
+            const int n = a.width[l];
+#pragma unroll
+            for (int k = 0; k < NT; ++k) {
+                const int u0 = 16 * (wave * NT + k) + ug;
+                float *dst = a.tape_d[l - 1] + (slot * n + u0) * B + b;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int u = u0 + unit16(0, r);
+                    dl[k][r] *= 1.0f - h[k][r] * h[k][r];
+                    if (u >= n) dl[k][r] = 0.0f;
+                    else if (live) dst[(size_t)unit16(0, r) * B] = dl[k][r];
+                }
+                *reinterpret_cast<f4v *>(out + j * AS + 16 * (wave * NT + k) + 4 * g) = dl[k];
+            }
+            __syncthreads();
+        };
+        float din[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) din[e] = dS[j * HS + ug + unit16(0, e)];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            dl[k] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (e < p.nsa) dl[k] = mfma16(w_top[k][e], din[e], dl[k]);
+        }
+        derivative(s.top, last, act[0]);
+        request_units(tn, s.top, last);
+        if (a.nl == 3) {
+            contract_wide<NT, TT, AS>(dl, w_mid, act[0], lane, n_top, p.bs);
+            derivative(s.mid, 1, act[1]);
+            request_units(tn, s.mid, 1);
+        }
+        // adjoint of the policy input: one row tile, wave w takes slice w
+        if (32 * wave < a.width[1]) {
+            const f4v o = contract_slice<TT, AS>(w_first, act[a.nl - 2], wave, lane);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[(wave * PL + j) * HS + ug + unit16(0, r)] = o[r];
+        }
+        __syncthreads();
+        if (row < a.ds) {
+            float dh = red[bl * HS + row];
+            for (int w = 1; 32 * w < a.width[1]; ++w) dh += red[(w * PL + bl) * HS + row];
+            lam = lam + us + (double)dh;
+            if (t - 1 >= 1) lam = add_cost_gradient16<DG>(a, lam, row, s.sv, s.gv);
+            lamS[row][bl] = lam;
+        }
+        request_cost(tn, s);
+        __syncthreads();
+    };
+    int t = a.t_hi;
+    for (; t - 1 > a.t_lo; t -= 2) {
+        step(t, set[0]);
+        step(t - 1, set[1]);
+    }
+    if (t > a.t_lo) step(t, set[0]);
+    if (row < a.ds && live) {
+        a.lam[(size_t)row * B + b] = lam;
+        if (a.t_lo == 0 && a.grad_s0) a.grad_s0[(size_t)b * a.ds + row] = (float)lam;
+    }
+}
+
+policy16_args make_policy(const bagel_ctx *c)
+{
+    policy16_args a;
+    a.B = c->dm.B; a.nl = c->n_layers; a.ds = c->dm.d_s; a.da = c->dm.d_a;
+    for (int i = 0; i < 4; ++i) a.width[i] = c->width[i];
+    a.act_bound = c->dm.act_bound;
+    a.pack = c->wpack16;
+    for (int l = 0; l < 3; ++l) a.h[l] = l < c->n_layers ? c->tape_h[l] : nullptr;
+    a.a_slot = c->tape_a;
+    return a;
+}
+
+template <int NW, int NT>
+void launch_tail(bagel_ctx *c, const tail16_args &r)
+{
+    hipLaunchKernelGGL((step_tail16_kernel<NW, NT>), dim3((c->dm.B + PL - 1) / PL), dim3(64 * NW), 0, c->stream, r, make_policy(c),
+                       make_pack(c));
+}
+
+hipError_t launch_tail(bagel_ctx *c, const tail16_args &r)
+{
+    if (c->p16 == 1) launch_tail<4, 1>(c, r);
+    else if (c->p16 == 2) launch_tail<8, 1>(c, r);
+    else launch_tail<8, 2>(c, r);
+    return hipGetLastError();
+}
+
+template <int NW, int NT>
+void launch_sweep(bagel_ctx *c, const sweep16_args &a)
+{
+    const dim3 grid((c->dm.B + PL - 1) / PL), block(64 * NW);
+    const pack16 p = make_pack(c);
+    if (a.M <= 4 && a.dg <= 2) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 4, 2>), grid, block, 0, c->stream, a, p);
+    else if (a.dg <= 2) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 8, 2>), grid, block, 0, c->stream, a, p);
+    else hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 8, 8>), grid, block, 0, c->stream, a, p);
+}
+
+}  // namespace
+
+// Which policy kernels the context uses: 0 those of policy.hip, 1 .. 3 the instances here.  Measured per step of a gradient
+// call, policy.hip / here (N = 2048, L = 1024 unless said): hidden 64-64 at B = 256 (N = 512) 22.4 / 13.5 us, B = 2048 46.5 / 37.6,
+// B = 8192 111 / 105; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102; 256-256 at B = 1024 55.5 / 43.3, B = 2048 66.9 / 57.4.
+// Wider policies on larger batches fill the chip with 32 trajectories per workgroup, and fetching the weights twice as
+// often costs what the shorter chain gives: forward passes at 128-128, B = 8192 (N = 4096) 104 / 119, at 256-256, B = 4096 with
+// 16 trajectories per sample 64.7 / 68.5.
+void bagel_plan_policy(bagel_ctx *c)
+{
+    int w = 0;
+    for (int l = 1; l < c->n_layers; ++l) w = c->width[l] > w ? c->width[l] : w;
+    c->p16 = w <= 64 ? 1 : (w <= 128 ? 2 : 3);
+    if ((c->p16 == 3 && c->dm.B > 2048) || (c->p16 == 2 && c->dm.B > 4096)) c->p16 = 0;
+    c->pack16_floats = c->p16 ? make_pack(c).total() : 0;
+}
+
+hipError_t bagel_launch_pack_theta16(bagel_ctx *c, const float *theta)
+{
+    const pack16 p = make_pack(c);
+    hipLaunchKernelGGL(pack_theta16_kernel, dim3((p.total() + 255) / 256), dim3(256), 0, c->stream, theta, c->wpack16, p, c->width[0],
+                       c->width[1], c->width[2], c->width[3], c->w_off[0], c->w_off[1], c->w_off[2], c->b_off[0], c->b_off[1],
+                       c->b_off[2]);
+    return hipGetLastError();
+}
+
+hipError_t bagel_launch_start16(bagel_ctx *c, const float *s0, const float *goals, float *states_out, bool tape)
+{
+    tail16_args r = {};
+    r.D = c->D; r.M = c->M; r.dg = c->dm.d_g;
+    r.do_policy = 1;
+    r.x_next = c->xbuf; r.lpt = c->lpt;
+    r.tape_s_next = tape ? c->tape_s : nullptr;
+    r.states_out_next = states_out;
+    r.goals_next = goals; r.s0 = s0;
+    return launch_tail(c, r);
+}
+
+hipError_t bagel_launch_step_tail16(bagel_ctx *c, int t, int slot, int next_slot, bool jac, bool write_tape_s, const float *goals,
+                                    float *states_out, bool direct)
+{
+    const size_t B = c->dm.B;
+    const bool has_next = t + 1 < c->dm.H && next_slot >= 0;
+    tail16_args r = {};
+    r.D = c->D; r.M = c->M; r.dg = c->dm.d_g;
+    r.ngk = (c->nck + 3) / 4; r.ngl = (c->ncl + 3) / 4;
+    r.ncomp = jac ? 1 + c->D : 1;
+    r.cost_kind = c->dm.cost_kind; r.do_policy = has_next ? 1 : 0; r.direct = direct ? 1 : 0;
+    r.sigma_r = c->dm.sigma_r;
+    for (int j = 0; j < 8; ++j) { r.tracked[j] = c->dm.tracked[j]; r.q[j] = c->dm.q[j]; }
+    r.amp = c->amp; r.part = c->part; r.lpt = c->lpt;
+    r.x_cur = c->xbuf; r.x_next = c->xbuf_alt;
+    r.tape_s_next = write_tape_s ? c->tape_s + (size_t)(t + 1) * c->dm.d_s * B : nullptr;
+    r.states_out_next = states_out ? states_out + (size_t)(t + 1) * B * c->dm.d_s : nullptr;
+    r.goals_t = goals + (size_t)t * B * c->dm.d_g;
+    r.goals_next = has_next ? goals + (size_t)(t + 1) * B * c->dm.d_g : nullptr;
+    r.jdst = (jac && direct) ? c->tape_J + (size_t)slot * c->M * c->D * B : nullptr;
+    r.slot = has_next ? (size_t)next_slot : 0;
+    return launch_tail(c, r);
+}
+
+hipError_t bagel_launch_policy_replay16(bagel_ctx *c, int t0, int t1, const float *goals)
+{
+    replay16_args r;
+    r.tape_s = c->tape_s; r.goals = goals; r.t0 = t0; r.dg = c->dm.d_g; r.n_slots = t1 - t0; r.per = 5;
+    const dim3 grid((c->dm.B + PL - 1) / PL, (t1 - t0 + r.per - 1) / r.per);
+    const policy16_args a = make_policy(c);
+    const pack16 p = make_pack(c);
+    if (c->p16 == 1) hipLaunchKernelGGL((policy_replay16_kernel<4, 1>), grid, dim3(256), 0, c->stream, r, a, p);
+    else if (c->p16 == 2) hipLaunchKernelGGL((policy_replay16_kernel<8, 1>), grid, dim3(512), 0, c->stream, r, a, p);
+    else hipLaunchKernelGGL((policy_replay16_kernel<8, 2>), grid, dim3(512), 0, c->stream, r, a, p);
+    return hipGetLastError();
+}
+
+hipError_t bagel_launch_backward_sweep16(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
+{
+    sweep16_args a;
+    a.B = c->dm.B; a.nl = c->n_layers; a.ds = c->dm.d_s; a.da = c->dm.d_a; a.dg = c->dm.d_g; a.D = c->D; a.M = c->M;
+    a.H = c->dm.H; a.t_hi = t_hi; a.t_lo = t_lo;
+    for (int i = 0; i < 4; ++i) a.width[i] = c->width[i];
+    for (int l = 0; l < 3; ++l) {
+        a.tape_h[l] = l < c->n_layers ? c->tape_h[l] : nullptr;
+        a.tape_d[l] = l < c->n_layers ? c->tape_d[l] : nullptr;
+    }
+    a.act_bound = c->dm.act_bound; a.cost_kind = c->dm.cost_kind; a.sigma_r = c->dm.sigma_r;
+    for (int j = 0; j < 8; ++j) { a.tracked[j] = c->dm.tracked[j]; a.q[j] = c->dm.q[j]; }
+    a.pack = c->wpack16;
+    // the Jacobian tape spans the whole horizon when the activation tape is kept per segment
+    const bool per_segment = c->T_tape < c->dm.H;
+    a.tape_a = c->tape_a; a.tape_s = c->tape_s;
+    a.tape_J = c->tape_J + (per_segment ? (size_t)t_lo * c->M * c->D * c->dm.B : 0);
+    a.goals = goals; a.lam = c->lam; a.grad_s0 = grad_s0;
+    if (c->p16 == 1) launch_sweep<4, 1>(c, a);
+    else if (c->p16 == 2) launch_sweep<8, 1>(c, a);
+    else launch_sweep<8, 2>(c, a);
+    return hipGetLastError();
+}

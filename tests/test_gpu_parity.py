@@ -345,6 +345,29 @@ def test_policy_and_state_shape_sweep(hi, monkeypatch):
             assert d[k] <= tol + 20 * cond[k], (label, k, d[k], cond[k])
 
 
+@pytest.mark.parametrize("hidden,B", [((256, 256), 2048), ((200, 130), 2048), ((256,), 2048), ((129, 7), 2048), ((8, 256), 2048),
+                                      ((128, 128), 4096), ((100, 37), 4096), ((65,), 4096), ((70, 128), 4096), ((17, 97), 4096)])
+@pytest.mark.parametrize("ckpt", [0, 2])
+def test_policy_kernels_agree_bit_for_bit(hidden, B, ckpt, monkeypatch):
+    """A batch of 2 B trajectories takes the policy kernels with 32 trajectories per workgroup, its first half alone those
+    with 16.  With the decomposition of the sample evaluation held the same, every trajectory's states and cost and its
+    share of grad_s0 (which carries 1 / batch size, a power of two apart) must be the same bits; grad_theta of one batch is
+    held to the oracle elsewhere."""
+    for k, v in dict(BAGEL_CK="32", BAGEL_CL="32", BAGEL_EXP_TABLE="1").items():
+        monkeypatch.setenv(k, v)
+    cfg = synth.Config("pb16", 17, 3, 2, 2, 40, 24, 2 * B, 5, hidden, 0.7, "sinusoid", "steps", ckpt, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    rng = np.random.default_rng(5)
+    v = rng.standard_normal((2 * B, cfg.M, cfg.N)).astype(np.float32)
+    both = harness.gpu_rollout(cfg, inp, v)
+    half, sub = synth.subset_trajectories(cfg, inp, np.arange(B))
+    one = harness.gpu_rollout(half, sub, v[:B])
+    assert np.isfinite(both["states"]).all()
+    np.testing.assert_array_equal(one["states"], both["states"][:, :B])
+    np.testing.assert_array_equal(one["loss_per_traj"], both["loss_per_traj"][:B])
+    np.testing.assert_array_equal(one["grad_s0"], 2.0 * both["grad_s0"][:B])
+
+
 def test_rollout_with_table_exp2(monkeypatch):
     """The exp2 form of large launches, forced at a size the oracle finishes in seconds."""
     monkeypatch.setenv("BAGEL_EXP_TABLE", EXP2_FORMS["table"])
