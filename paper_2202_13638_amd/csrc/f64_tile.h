@@ -36,6 +36,19 @@ struct shape {
     static constexpr int LOADS = TK * T * 8 / 1024 / 4;      // loads per wave, stage and operand
 };
 
+// Do `tiles` tiles of 128 x 128 fill whole passes over the chip?  Two of them share a compute unit, and one alone keeps
+// its matrix pipes busy nearly as well, so a product takes 1, 2, 4, 6, ... times the time of one tile as its tiles
+// reach 256, 512, 1024, 1536, ... (what is left over after a pass of 512 is not spread one per unit); one of 64 x 64
+// takes a quarter of that time and balances by itself, at 5 % less speed.  Measured on the posterior step, 64 against
+// 128 (N, B, outputs): 512 tiles (2048, 1024, 4) 556 / 529 us; 256 tiles (2048, 512, 4) 321 / 311, (4096, 512, 2) 577 / 563;
+// 384 tiles (2048, 768, 4) 440 / 520; 768 tiles (4000, 500, 6) 1580 / 1944; 64 tiles (1024, 256, 4) 89 / 178.
+inline bool whole_passes(long tiles)
+{
+    if (tiles <= 256) return 100 * tiles >= 95 * 256;
+    const long passes = (tiles + 511) / 512;
+    return 100 * tiles >= 95 * 512 * passes;
+}
+
 template <int T>
 struct accumulators {
     d4v v[2 * shape<T>::H][2 * shape<T>::H];                 // [x = 2 h + e][y = 2 h' + e']

@@ -224,13 +224,7 @@ hipError_t step_d(bagel_ctx *c, bool jac, const float *xi_t)
     const int B = c->dm.B, Bp = (B + 63) / 64 * 64, N = c->dm.N, Np = c->post_Np, M = c->M;
     bagel_post_sf2 sf2;
     for (int m = 0; m < 8; ++m) sf2.v[m] = c->post_sf2[m];
-    // A 128 x 128 tile keeps a compute unit's matrix pipes busy on its own, so its product takes whole passes of 256
-    // tiles: it wins where the last pass is (nearly) full and loses what is missing there otherwise.  Measured per
-    // step, 64 against 128 (N, B, M): 512 tiles (2048, 1024, 4) 556 / 529 us; 256 tiles (2048, 512, 4) 321 / 311,
-    // (4096, 512, 2) 577 / 563; 384 tiles (2048, 768, 4) 440 / 520; 64 tiles (1024, 256, 4) 89 / 178.
-    const long tiles128 = (long)((Bp + 127) / 128) * ((Np + 127) / 128) * M;
-    const long passes = (tiles128 + 255) / 256;
-    const bool large = 100 * tiles128 >= 95 * 256 * passes;
+    const bool large = f64_tile::whole_passes((long)((Bp + 127) / 128) * ((Np + 127) / 128) * M);
     const int ntile = large ? (Np + 127) / 128 : Np / 64;
     hipLaunchKernelGGL((posterior_rows_kernel<D>), dim3((B + 255) / 256, (Np + 31) / 32, M), dim3(256), 0, c->stream,
                        c->Xs, c->A, c->xbuf, c->post_Kx, B, Bp, N, Np, c->Np);

@@ -522,22 +522,12 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_kernel(gemm_args g
             }
 }
 
-// Does a launch of `tiles` tiles of 128 fill whole passes over the chip?  A tile of 128 keeps a compute unit's
-// matrix pipes busy on its own, one of 64 takes a quarter of its time: the large tile wins by 5 % where its
-// last pass is nearly full (measured on the product of the posterior step, posterior.hip) and loses what is
-// missing there otherwise.
-bool whole_passes(long tiles)
-{
-    const long passes = (tiles + 255) / 256;
-    return 100 * tiles >= 95 * 256 * passes;
-}
-
 void gemm(hipStream_t st, int outputs, const gemm_args &g)
 {
     if (g.ni <= 0 || g.nj <= 0 || g.K <= 0) return;
     const long ti = (g.ni + 127) / 128, tj = (g.nj + 127) / 128;
     const long tiles = outputs * (g.upper ? ti * tj - ti * (ti - 1) / 2 : ti * tj);
-    if (whole_passes(tiles))
+    if (f64_tile::whole_passes(tiles))
         hipLaunchKernelGGL(gemm_kernel<128>, dim3(tj, ti, outputs), dim3(256), 0, st, g);
     else
         hipLaunchKernelGGL(gemm_kernel<64>, dim3((g.nj + 63) / 64, (g.ni + 63) / 64, outputs), dim3(256), 0, st, g);
