@@ -51,7 +51,7 @@
  * Tuning knobs (environment variables read once by bagel_create; the defaults are the measured best and
  * none of them changes results beyond the order of floating-point sums):
  *   BAGEL_CK, BAGEL_CL     training points / features per work unit of the sample evaluation (rounded
- *                          up to multiples of 8)
+ *                          up to multiples of 16)
  *   BAGEL_TARGET_WGS       number of workgroups the default unit sizes aim for (default 4096)
  *   BAGEL_EXP_TABLE        1: always the general form of the kernel-row loop, 2: always the table form,
  *                          unset: by launch size

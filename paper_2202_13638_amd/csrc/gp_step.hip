@@ -40,6 +40,8 @@ namespace {
 #ifndef BAGEL_MIN_WAVES
 #define BAGEL_MIN_WAVES(D) ((D) <= 8 ? 8 : ((D) <= 11 ? 5 : 4))
 #endif
+// launches without the table form have at most four waves per SIMD
+#define BAGEL_MIN_WAVES_SMALL(D) ((D) <= 6 ? 4 : 3)
 #ifndef BAGEL_SAME_ROWS
 #define BAGEL_SAME_ROWS 0      // timing experiment only: every work unit reads the first unit's rows
 #endif
@@ -131,19 +133,32 @@ struct jac_sums {
     float *jdst;             // [M][D][B]
 };
 
-__device__ __forceinline__ double sum_in_order(const double *__restrict__ p, int n, size_t stride)
+// K sums of n[k] terms p[k][0] + p[k][stride] + ... each added in order, W loads of every sum in flight at a time: the
+// tile is a chain of trips to memory, one per W terms.
+template <int K, int W>
+__device__ __forceinline__ void sums_in_order(const double *const (&p)[K], const int (&n)[K], size_t stride, double (&s)[K])
 {
-    double s = 0.0;
-    for (int c0 = 0; c0 < n; c0 += 4) {      // four loads in flight at a time, added in order
-        double v[4];
+    int most = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (c0 + i < n) ? p[(size_t)(c0 + i) * stride] : 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s += v[i];
+    for (int k = 0; k < K; ++k) {
+        s[k] = 0.0;
+        most = n[k] > most ? n[k] : most;
     }
-    return s;
+    for (int c0 = 0; c0 < most; c0 += W) {
+        double v[K][W];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < W; ++i) v[k][i] = (c0 + i < n[k]) ? p[k][(size_t)(c0 + i) * stride] : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < W; ++i) s[k] += v[k][i];
+    }
 }
 
+// W: loads in flight per sum (4 inside the large launches, which hide the trips and have few registers; 8 elsewhere)
+template <int W>
 __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
 {
     constexpr double LN2 = 0.69314718055994530942, TWO_PI = 6.28318530717958647693;
@@ -153,18 +168,170 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
     const size_t stride = (size_t)(1 + D) * B;
     const double *pk = j.part + (size_t)(m * ngk) * stride + b;
     const double *pr = j.part + (size_t)(M * ngk + m * ngl) * stride + b;
-    const double u = sum_in_order(pk, ngk, stride);
+    double u[1];
+    if (W < 8) sums_in_order<1, W>({pk}, {ngk}, stride, u);      // (fewer registers: the value sum on its own first)
     for (int d = wave; d < D; d += BAGEL_BLOCK / 64) {
-        const double gk = sum_in_order(pk + (size_t)(1 + d) * B, ngk, stride);
-        const double gr = sum_in_order(pr + (size_t)(1 + d) * B, ngl, stride);
+        const double *const p[3] = {pk + (size_t)(1 + d) * B, pr + (size_t)(1 + d) * B, pk};
+        const int n[3] = {ngk, ngl, ngk};
         const double xd = j.x[(size_t)d * B + b];
-        j.jdst[(size_t)(m * D + d) * B + b] = (float)(-j.amp[m] * TWO_PI * gr + LN2 * (gk - j.A[m * D + d] * xd * u));
+        double s[3];
+        if (W < 8) {
+            double one[1];
+            sums_in_order<1, W>({p[0]}, {ngk}, stride, one);
+            s[0] = one[0];
+            sums_in_order<1, W>({p[1]}, {ngl}, stride, one);
+            s[1] = one[0];
+            s[2] = u[0];
+        } else {
+            sums_in_order<3, W>(p, n, stride, s);
+        }
+        j.jdst[(size_t)(m * D + d) * B + b] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
     }
 }
 
 __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums j, int B, int D, int M, int ngk, int ngl)
 {
-    jacobian_tile(j, blockIdx.x, blockIdx.y, B, D, M, ngk, ngl);
+    jacobian_tile<8>(j, blockIdx.x, blockIdx.y, B, D, M, ngk, ngl);
+}
+
+// ---- the loops of small launches ------------------------------------------------------------------
+// A launch without the table form has at most four waves per SIMD, often one, and nothing else hides what a point
+// waits for: its chain of dependent float64 operations (8 cycles each, where independent ones issue every 5),
+// the trip of its operand row through the scalar cache, the stream.  So points (features) are worked on in pairs,
+// rows are requested a pair ahead, the stream four float4 ahead (into the registers just used: CK and CL are
+// multiples of 16), the matrix-core operands of the features four features ahead.  Every sum keeps the order of the
+// point-by-point loops.  A launch at N = 2200, L = 1024, 100 trajectories, D = 3 takes 9.1 -> 7.8 us, at N = 512, L = 1024, 256
+// trajectories, D = 5 6.4 -> 5.9 us.  For D > 8 two pairs of rows do not fit the scalar registers: those stay with
+// the point-by-point loops.
+template <int D>
+__device__ __forceinline__ void load_row(double (&r)[D + 1], const double *__restrict__ src)
+{
+#pragma unroll
+    for (int d = 0; d <= D; ++d) r[d] = src[d];
+}
+
+// 2^t of exp2_poly for two arguments side by side
+__device__ __forceinline__ void exp2_poly2(double t0, double t1, double c7, double c6, double &k0, double &k1)
+{
+    const double n0 = rint(t0), n1 = rint(t1);
+    const double f0 = t0 - n0, f1 = t1 - n1;
+    double p0 = fma(c7, f0, c6), p1 = fma(c7, f1, c6);
+    p0 = fma(p0, f0, 4.1667353769980764e-05); p1 = fma(p1, f1, 4.1667353769980764e-05);
+    p0 = fma(p0, f0, 0.0006011326659205452); p1 = fma(p1, f1, 0.0006011326659205452);
+    p0 = fma(p0, f0, 0.006938013583872582); p1 = fma(p1, f1, 0.006938013583872582);
+    p0 = fma(p0, f0, 0.060056626759929704); p1 = fma(p1, f1, 0.060056626759929704);
+    p0 = fma(p0, f0, 0.3465735902799663); p1 = fma(p1, f1, 0.3465735902799663);
+    p0 = fma(p0, f0, 0.9999999999998426); p1 = fma(p1, f1, 0.9999999999998426);
+    k0 = ldexp(p0 * p0, (int)n0);
+    k1 = ldexp(p1 * p1, (int)n1);
+}
+
+// n_iter float4 of training points (a multiple of 4) with rows from Xr and the stream vdesc: see the general loop
+template <int D, bool JAC>
+__device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, __amdgpu_buffer_rsrc_t vdesc, unsigned voff,
+                                                 unsigned vstep, int n_iter, const double (&xs)[D], double qs, double &u, double (&G)[D])
+{
+    double ca = 1.192611307487823e-07, cb = 2.409383341728244e-06;
+    asm volatile("" : "+s"(ca), "+v"(cb));
+    const int last = n_iter - 1;
+    auto pair = [&](const double (&r0)[D + 1], const double (&r1)[D + 1], double (&n0)[D + 1], double (&n1)[D + 1],
+                    const double *__restrict__ next, float v0, float v1) {
+        load_row<D>(n0, next);
+        load_row<D>(n1, next + (D + 1));
+        __builtin_amdgcn_sched_barrier(0);
+        double t0 = qs + r0[D], t1 = qs + r1[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            t0 = fma(xs[d], r0[d], t0);
+            t1 = fma(xs[d], r1[d], t1);
+        }
+        double k0, k1;
+        exp2_poly2(t0, t1, ca, cb, k0, k1);
+        const double vk0 = (double)v0 * k0, vk1 = (double)v1 * k1;
+        u += vk0;
+        u += vk1;
+        if (JAC) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) G[d] = fma(vk0, r0[d], G[d]);
+#pragma unroll
+            for (int d = 0; d < D; ++d) G[d] = fma(vk1, r1[d], G[d]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    v4f vb[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vb[i] = stream_load(vdesc, voff, (unsigned)i * vstep);
+    double a0[D + 1], a1[D + 1], b0[D + 1], b1[D + 1];
+    load_row<D>(a0, Xr);
+    load_row<D>(a1, Xr + (D + 1));
+    for (int n4 = 0; n4 < n_iter; n4 += 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double *__restrict__ r = Xr + (size_t)((n4 + i) * 4) * (D + 1);
+            pair(a0, a1, b0, b1, r + 2 * (D + 1), vb[i].x, vb[i].y);
+            pair(b0, b1, a0, a1, n4 + i < last ? r + 4 * (D + 1) : Xr, vb[i].z, vb[i].w);
+            vb[i] = stream_load(vdesc, voff, (unsigned)(n4 + 4 + i < last ? n4 + 4 + i : last) * vstep);
+        }
+    }
+}
+
+// n_iter float4 of random features (a multiple of 4): see the feature loops of the kernel
+template <int D, bool JAC>
+__device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __amdgpu_buffer_rsrc_t wdesc, unsigned woff, unsigned wstep,
+                                              __amdgpu_buffer_rsrc_t odesc, unsigned ooff, unsigned ostep, int n_iter,
+                                              const double (&x)[D], float &p, f4v (&acc)[(D + 3) / 4])
+{
+    constexpr int NQ = (D + 3) / 4;
+    const int last = n_iter - 1;
+    auto pair = [&](const double (&r0)[D + 1], const double (&r1)[D + 1], double (&n0)[D + 1], double (&n1)[D + 1],
+                    const double *__restrict__ next, float w0, float w1, const v4f (&bq)[NQ], int j) {
+        load_row<D>(n0, next);
+        load_row<D>(n1, next + (D + 1));
+        __builtin_amdgcn_sched_barrier(0);
+        double z0 = x[0] * r0[0], z1 = x[0] * r1[0];
+#pragma unroll
+        for (int d = 1; d < D; ++d) {
+            z0 = fma(x[d], r0[d], z0);
+            z1 = fma(x[d], r1[d], z1);
+        }
+        z0 += r0[D];
+        z1 += r1[D];
+        const float y0 = (float)__builtin_amdgcn_fract(z0), y1 = (float)__builtin_amdgcn_fract(z1);
+        p = fmaf(w0, __builtin_amdgcn_cosf(y0), p);
+        p = fmaf(w1, __builtin_amdgcn_cosf(y1), p);
+        if (JAC) {
+            const float s0 = w0 * __builtin_amdgcn_sinf(y0), s1 = w1 * __builtin_amdgcn_sinf(y1);
+#pragma unroll
+            for (int qd = 0; qd < NQ; ++qd) acc[qd] = __builtin_amdgcn_mfma_f32_4x4x1f32(s0, bq[qd][j], acc[qd], 0, 0, 0);
+#pragma unroll
+            for (int qd = 0; qd < NQ; ++qd) acc[qd] = __builtin_amdgcn_mfma_f32_4x4x1f32(s1, bq[qd][j + 1], acc[qd], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    v4f wb[4], bq[2][NQ];
+    auto operands = [&](v4f (&b)[NQ], int l4) {
+        if (JAC) {
+#pragma unroll
+            for (int qd = 0; qd < NQ; ++qd)
+                b[qd] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(odesc, ooff + 16u * qd, (unsigned)l4 * ostep, 0));
+        }
+    };
+    operands(bq[0], 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) wb[i] = stream_load(wdesc, woff, (unsigned)i * wstep);
+    double a0[D + 1], a1[D + 1], b0[D + 1], b1[D + 1];
+    load_row<D>(a0, Or);
+    load_row<D>(a1, Or + (D + 1));
+    for (int l4 = 0; l4 < n_iter; l4 += 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const double *__restrict__ r = Or + (size_t)((l4 + i) * 4) * (D + 1);
+            operands(bq[(i + 1) & 1], l4 + i < last ? l4 + i + 1 : last);
+            pair(a0, a1, b0, b1, r + 2 * (D + 1), wb[i].x, wb[i].y, bq[i & 1], 0);
+            pair(b0, b1, a0, a1, l4 + i < last ? r + 4 * (D + 1) : Or, wb[i].z, wb[i].w, bq[i & 1], 2);
+            wb[i] = stream_load(wdesc, woff, (unsigned)(l4 + 4 + i < last ? l4 + 4 + i : last) * wstep);
+        }
+    }
 }
 
 // NEAR adds the fast form of the kernel-row loop for the normal case that data and trajectory are
@@ -189,7 +356,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums j, int
 // with the scalar loads of the shared operands, so every look-up also waits for the operand rows
 // requested ahead; small launches take the general loop only.
 template <int D, bool JAC, bool NEAR>
-__global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAGEL_MIN_WAVES(D), 8))) void gp_step_kernel(
+__global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEAR ? BAGEL_MIN_WAVES(D) : BAGEL_MIN_WAVES_SMALL(D), 8))) void gp_step_kernel(
     const double *__restrict__ Xs, const double *__restrict__ Xn, const double *__restrict__ Os,
     const float4 *__restrict__ Of, const double *__restrict__ A, const float4 *__restrict__ v4,
     const float4 *__restrict__ w4,
@@ -200,7 +367,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAG
     // M rows of workgroups past the work units: the previous step's Jacobian sums (see jacobian_tile).
     // (Placed first in the grid instead, they made the launch slower: 571 vs 556 us.)
     if ((int)blockIdx.y >= M * (((nck + 3) >> 2) + ((ncl + 3) >> 2))) {
-        jacobian_tile(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
+        jacobian_tile<NEAR ? 4 : 8>(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
                       (nck + 3) >> 2, (ncl + 3) >> 2);
         return;
     }
@@ -305,7 +472,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAG
                 // The stream is requested one float4 ahead, alternating between two register sets (a request
                 // past the end repeats the last row): HBM latency under load is several times a wave's own
                 // work on four points, and the loop was idle waiting for it.
-                // (CK is a multiple of 8: the loop body handles two float4 without a branch, which keeps
+                // (CK is a multiple of 16: the loop body handles two float4 without a branch, which keeps
                 // the compiler from moving a request down to its use.)
                 v4f va = stream_load(vdesc, voff, 0u);
                 for (int n4 = 0; n4 < n_iter; n4 += 2) {
@@ -344,44 +511,48 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAG
             for (int d = 0; d < D; ++d) xs[d] = far ? 0.0 : x[d];
             const double qs = far ? -3000.0 : q;
             const double *__restrict__ Xr = Xs + row0;
-            double ca = 1.192611307487823e-07, cb = 2.409383341728244e-06;
-            asm volatile("" : "+s"(ca), "+v"(cb));
-            // same pipeline as the table form: the next point's row is requested while this one is worked
-            // on, the stream one float4 ahead
-            const int last = n_iter - 1;
-            auto one_point = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
-                                 float vf) {
-#pragma unroll
-                for (int d = 0; d <= D; ++d) rn[d] = next[d];
-                __builtin_amdgcn_sched_barrier(0);
-                double t = qs + rc[D];
-#pragma unroll
-                for (int d = 0; d < D; ++d) t = fma(xs[d], rc[d], t);
-                const double k = exp2_poly(t, ca, cb);
-                const double vk = (double)vf * k;
-                u += vk;
-                if (JAC) {
-#pragma unroll
-                    for (int d = 0; d < D; ++d) G[d] = fma(vk, rc[d], G[d]);
+            if constexpr (!NEAR && D <= 8) {
+                if (n_iter > 0) kernel_row_pairs<D, JAC>(Xr, vdesc, voff, vstep, n_iter, xs, qs, u, G);
+            } else {
+                double ca = 1.192611307487823e-07, cb = 2.409383341728244e-06;
+                asm volatile("" : "+s"(ca), "+v"(cb));
+                // same pipeline as the table form: the next point's row is requested while this one is worked
+                // on, the stream one float4 ahead
+                const int last = n_iter - 1;
+                auto one_point = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
+                                     float vf) {
+    #pragma unroll
+                    for (int d = 0; d <= D; ++d) rn[d] = next[d];
+                    __builtin_amdgcn_sched_barrier(0);
+                    double t = qs + rc[D];
+    #pragma unroll
+                    for (int d = 0; d < D; ++d) t = fma(xs[d], rc[d], t);
+                    const double k = exp2_poly(t, ca, cb);
+                    const double vk = (double)vf * k;
+                    u += vk;
+                    if (JAC) {
+    #pragma unroll
+                        for (int d = 0; d < D; ++d) G[d] = fma(vk, rc[d], G[d]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                double ra[D + 1], rb[D + 1];
+    #pragma unroll
+                for (int d = 0; d <= D; ++d) ra[d] = Xr[d];
+                auto four_points = [&](const v4f vv, int n4) {
+                    const double *__restrict__ r = Xr + (size_t)(n4 * 4) * (D + 1);
+                    one_point(ra, rb, r + 1 * (D + 1), vv.x);
+                    one_point(rb, ra, r + 2 * (D + 1), vv.y);
+                    one_point(ra, rb, r + 3 * (D + 1), vv.z);
+                    one_point(rb, ra, n4 < last ? r + 4 * (D + 1) : Xr, vv.w);
+                };
+                v4f va = stream_load(vdesc, voff, 0u);
+                for (int n4 = 0; n4 < n_iter; n4 += 2) {
+                    const v4f vb = stream_load(vdesc, voff, (unsigned)(n4 + 1) * vstep);
+                    four_points(va, n4);
+                    va = stream_load(vdesc, voff, (unsigned)(n4 + 2 < last ? n4 + 2 : last) * vstep);
+                    four_points(vb, n4 + 1);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            double ra[D + 1], rb[D + 1];
-#pragma unroll
-            for (int d = 0; d <= D; ++d) ra[d] = Xr[d];
-            auto four_points = [&](const v4f vv, int n4) {
-                const double *__restrict__ r = Xr + (size_t)(n4 * 4) * (D + 1);
-                one_point(ra, rb, r + 1 * (D + 1), vv.x);
-                one_point(rb, ra, r + 2 * (D + 1), vv.y);
-                one_point(ra, rb, r + 3 * (D + 1), vv.z);
-                one_point(rb, ra, n4 < last ? r + 4 * (D + 1) : Xr, vv.w);
-            };
-            v4f va = stream_load(vdesc, voff, 0u);
-            for (int n4 = 0; n4 < n_iter; n4 += 2) {
-                const v4f vb = stream_load(vdesc, voff, (unsigned)(n4 + 1) * vstep);
-                four_points(va, n4);
-                va = stream_load(vdesc, voff, (unsigned)(n4 + 2 < last ? n4 + 2 : last) * vstep);
-                four_points(vb, n4 + 1);
             }
         }
         combine_waves<D, JAC, RC>(red, wave, lane, live, out, B, false, u, G);
@@ -415,56 +586,60 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAG
             f4v acc[NQ];
 #pragma unroll
             for (int qd = 0; qd < NQ; ++qd) acc[qd] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-            const int last = n_iter - 1;         // CL is a multiple of 8: two float4 per trip, no branch
-            auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
-                                   float wf, const v4f (&bq)[NQ], int j) {
+            if constexpr (!NEAR && D <= 8) {
+                if (n_iter > 0) feature_pairs<D, true>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc);
+            } else {
+                const int last = n_iter - 1;         // CL is a multiple of 16: two float4 per trip, no branch
+                auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
+                                       float wf, const v4f (&bq)[NQ], int j) {
 #pragma unroll
-                for (int d = 0; d <= D; ++d) rn[d] = next[d];
-                __builtin_amdgcn_sched_barrier(0);
-                // product first, phase offset last: both are scalar operands, and an FMA takes only one
-                double z = x[0] * rc[0];
+                    for (int d = 0; d <= D; ++d) rn[d] = next[d];
+                    __builtin_amdgcn_sched_barrier(0);
+                    // product first, phase offset last: both are scalar operands, and an FMA takes only one
+                    double z = x[0] * rc[0];
 #pragma unroll
-                for (int d = 1; d < D; ++d) z = fma(x[d], rc[d], z);
-                z += rc[D];
-                // z is the phase in revolutions; its fractional part is exact in float64 and the
-                // hardware sin / cos take revolutions (absolute error about one float32 ulp)
-                const float y = (float)__builtin_amdgcn_fract(z);
-                const float sn = __builtin_amdgcn_sinf(y);
-                const float cs = __builtin_amdgcn_cosf(y);
-                p = fmaf(wf, cs, p);
-                const float ws = wf * sn;
+                    for (int d = 1; d < D; ++d) z = fma(x[d], rc[d], z);
+                    z += rc[D];
+                    // z is the phase in revolutions; its fractional part is exact in float64 and the
+                    // hardware sin / cos take revolutions (absolute error about one float32 ulp)
+                    const float y = (float)__builtin_amdgcn_fract(z);
+                    const float sn = __builtin_amdgcn_sinf(y);
+                    const float cs = __builtin_amdgcn_cosf(y);
+                    p = fmaf(wf, cs, p);
+                    const float ws = wf * sn;
 #pragma unroll
-                for (int qd = 0; qd < NQ; ++qd)
-                    acc[qd] = __builtin_amdgcn_mfma_f32_4x4x1f32(ws, bq[qd][j], acc[qd], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            double fa[D + 1], fb[D + 1];
+                    for (int qd = 0; qd < NQ; ++qd)
+                        acc[qd] = __builtin_amdgcn_mfma_f32_4x4x1f32(ws, bq[qd][j], acc[qd], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                double fa[D + 1], fb[D + 1];
 #pragma unroll
-            for (int d = 0; d <= D; ++d) fa[d] = Or[d];
-            // four features whose weights are in ww; `next` receives the stream's float4 of step l4_next,
-            // requested after this step's B operands (loads return in order: the wait for the operands,
-            // which hit in cache, must not include the stream's trip to HBM)
-            auto four_features = [&](const v4f ww, int l4, v4f &next, int l4_next) {
-                v4f bq[NQ];
+                for (int d = 0; d <= D; ++d) fa[d] = Or[d];
+                // four features whose weights are in ww; `next` receives the stream's float4 of step l4_next,
+                // requested after this step's B operands (loads return in order: the wait for the operands,
+                // which hit in cache, must not include the stream's trip to HBM)
+                auto four_features = [&](const v4f ww, int l4, v4f &next, int l4_next) {
+                    v4f bq[NQ];
 #pragma unroll
-                for (int qd = 0; qd < NQ; ++qd)
-                    bq[qd] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(odesc, ooff + 16u * qd, (unsigned)l4 * ostep, 0));
-                __builtin_amdgcn_sched_barrier(0);
-                next = stream_load(wdesc, woff, (unsigned)l4_next * wstep);
-                __builtin_amdgcn_sched_barrier(0);
-                // each feature's row was requested while the previous feature was being worked on (see the
-                // kernel-row loop); the request after the unit's last row stays inside the table
-                const double *__restrict__ r = Or + (size_t)(l4 * 4) * (D + 1);
-                one_feature(fa, fb, r + 1 * (D + 1), ww.x, bq, 0);
-                one_feature(fb, fa, r + 2 * (D + 1), ww.y, bq, 1);
-                one_feature(fa, fb, r + 3 * (D + 1), ww.z, bq, 2);
-                one_feature(fb, fa, l4 < last ? r + 4 * (D + 1) : Or, ww.w, bq, 3);
-            };
-            // the stream of w one float4 ahead in alternating register sets, as in the kernel-row loop
-            v4f wa = stream_load(wdesc, woff, 0u), wb = wa;
-            for (int l4 = 0; l4 < n_iter; l4 += 2) {
-                four_features(wa, l4, wb, l4 + 1);
-                four_features(wb, l4 + 1, wa, l4 + 2 < last ? l4 + 2 : last);
+                    for (int qd = 0; qd < NQ; ++qd)
+                        bq[qd] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(odesc, ooff + 16u * qd, (unsigned)l4 * ostep, 0));
+                    __builtin_amdgcn_sched_barrier(0);
+                    next = stream_load(wdesc, woff, (unsigned)l4_next * wstep);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // each feature's row was requested while the previous feature was being worked on (see the
+                    // kernel-row loop); the request after the unit's last row stays inside the table
+                    const double *__restrict__ r = Or + (size_t)(l4 * 4) * (D + 1);
+                    one_feature(fa, fb, r + 1 * (D + 1), ww.x, bq, 0);
+                    one_feature(fb, fa, r + 2 * (D + 1), ww.y, bq, 1);
+                    one_feature(fa, fb, r + 3 * (D + 1), ww.z, bq, 2);
+                    one_feature(fb, fa, l4 < last ? r + 4 * (D + 1) : Or, ww.w, bq, 3);
+                };
+                // the stream of w one float4 ahead in alternating register sets, as in the kernel-row loop
+                v4f wa = stream_load(wdesc, woff, 0u), wb = wa;
+                for (int l4 = 0; l4 < n_iter; l4 += 2) {
+                    four_features(wa, l4, wb, l4 + 1);
+                    four_features(wb, l4 + 1, wa, l4 + 2 < last ? l4 + 2 : last);
+                }
             }
             // every wave, wave 0 included, hands its sums over through LDS: that is also the transposition
             // from the accumulator layout (lane = column, register = trajectory) to lane = trajectory
@@ -481,37 +656,42 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(BAG
             double u = 0.0, G[D];
             combine_waves<D, JAC, RC>(red, wave, lane, live, out, B, true, u, G);
         } else {
-            // value only: the same pipeline without the Jacobian sums
-            const int last = n_iter - 1;
-            auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
-                                   float wf) {
+            if constexpr (!NEAR && D <= 8) {
+                f4v none[NQ];
+                if (n_iter > 0) feature_pairs<D, false>(Or, wdesc, woff, wstep, wdesc, 0u, 0u, n_iter, x, p, none);
+            } else {
+                // value only: the same pipeline without the Jacobian sums
+                const int last = n_iter - 1;
+                auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
+                                       float wf) {
 #pragma unroll
-                for (int d = 0; d <= D; ++d) rn[d] = next[d];
-                __builtin_amdgcn_sched_barrier(0);
-                double z = x[0] * rc[0];
+                    for (int d = 0; d <= D; ++d) rn[d] = next[d];
+                    __builtin_amdgcn_sched_barrier(0);
+                    double z = x[0] * rc[0];
 #pragma unroll
-                for (int d = 1; d < D; ++d) z = fma(x[d], rc[d], z);
-                z += rc[D];
-                const float y = (float)__builtin_amdgcn_fract(z);
-                p = fmaf(wf, __builtin_amdgcn_cosf(y), p);
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            double fa[D + 1], fb[D + 1];
+                    for (int d = 1; d < D; ++d) z = fma(x[d], rc[d], z);
+                    z += rc[D];
+                    const float y = (float)__builtin_amdgcn_fract(z);
+                    p = fmaf(wf, __builtin_amdgcn_cosf(y), p);
+                    __builtin_amdgcn_sched_barrier(0);
+                };
+                double fa[D + 1], fb[D + 1];
 #pragma unroll
-            for (int d = 0; d <= D; ++d) fa[d] = Or[d];
-            auto four_features = [&](const v4f ww, int l4) {
-                const double *__restrict__ r = Or + (size_t)(l4 * 4) * (D + 1);
-                one_feature(fa, fb, r + 1 * (D + 1), ww.x);
-                one_feature(fb, fa, r + 2 * (D + 1), ww.y);
-                one_feature(fa, fb, r + 3 * (D + 1), ww.z);
-                one_feature(fb, fa, l4 < last ? r + 4 * (D + 1) : Or, ww.w);
-            };
-            v4f wa = stream_load(wdesc, woff, 0u);
-            for (int l4 = 0; l4 < n_iter; l4 += 2) {
-                const v4f wb = stream_load(wdesc, woff, (unsigned)(l4 + 1) * wstep);
-                four_features(wa, l4);
-                wa = stream_load(wdesc, woff, (unsigned)(l4 + 2 < last ? l4 + 2 : last) * wstep);
-                four_features(wb, l4 + 1);
+                for (int d = 0; d <= D; ++d) fa[d] = Or[d];
+                auto four_features = [&](const v4f ww, int l4) {
+                    const double *__restrict__ r = Or + (size_t)(l4 * 4) * (D + 1);
+                    one_feature(fa, fb, r + 1 * (D + 1), ww.x);
+                    one_feature(fb, fa, r + 2 * (D + 1), ww.y);
+                    one_feature(fa, fb, r + 3 * (D + 1), ww.z);
+                    one_feature(fb, fa, l4 < last ? r + 4 * (D + 1) : Or, ww.w);
+                };
+                v4f wa = stream_load(wdesc, woff, 0u);
+                for (int l4 = 0; l4 < n_iter; l4 += 2) {
+                    const v4f wb = stream_load(wdesc, woff, (unsigned)(l4 + 1) * wstep);
+                    four_features(wa, l4);
+                    wa = stream_load(wdesc, woff, (unsigned)(l4 + 2 < last ? l4 + 2 : last) * wstep);
+                    four_features(wb, l4 + 1);
+                }
             }
             double u = (double)p, G[D];
             combine_waves<D, JAC, RC>(red, wave, lane, live, out, B, false, u, G);
@@ -582,8 +762,8 @@ const char *bagel_plan_sample_eval(bagel_ctx *c)
                                         : ((chunk >= 512 && L / chunk >= 8) ? chunk / 2 : chunk);
     c->CK = bagel_env_int("BAGEL_CK", ck_default);
     c->CL = bagel_env_int("BAGEL_CL", cl_default);
-    c->CK = (c->CK + 7) & ~7;         // the sample-evaluation loops take two float4 (eight points) per trip
-    c->CL = (c->CL + 7) & ~7;
+    c->CK = (c->CK + 15) & ~15;       // the sample-evaluation loops take two or four float4 (eight or sixteen points) per trip
+    c->CL = (c->CL + 15) & ~15;
     c->nck = (N + c->CK - 1) / c->CK;
     c->ncl = (L + c->CL - 1) / c->CL;
     c->Np = c->nck * c->CK;

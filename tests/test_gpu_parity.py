@@ -220,6 +220,18 @@ def test_sample_eval_every_input_dimension(D, monkeypatch):
         _check_sample_eval(shape, x)
 
 
+@pytest.mark.parametrize("ck,cl", [(16, 16), (48, 16), (16, 80), (32, 48), (100, 33)])
+@pytest.mark.parametrize("d_s,d_a", [(1, 1), (4, 1), (6, 2), (6, 3)])
+def test_sample_eval_unit_sizes(ck, cl, d_s, d_a, monkeypatch):
+    """Work units of 16, 32, 48, ... points and features (sizes are rounded up to 16), the last workgroup's waves partly past
+    the end, in the loops of small launches (input dimensions 2, 5, 8: in pairs, 9: one by one)."""
+    for k, v in dict(BAGEL_CK=str(ck), BAGEL_CL=str(cl), BAGEL_EXP_TABLE="1").items():
+        monkeypatch.setenv(k, v)
+    shape = dict(d_s=d_s, d_a=d_a, N=5 * ck + 3, L=6 * cl - 5, B=70, S=70)
+    x = np.random.default_rng(ck + d_s).uniform(-1.2, 1.2, (shape["B"], d_s + d_a)).astype(np.float32)
+    _check_sample_eval(shape, x)
+
+
 @pytest.mark.parametrize("form", list(EXP2_FORMS))
 def test_sample_eval_inputs_far_from_the_data(form, monkeypatch):
     """GP inputs hundreds of length scales away from every training point: the kernel row is zero
