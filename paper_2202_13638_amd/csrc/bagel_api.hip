@@ -80,7 +80,7 @@ static void free_all(bagel_ctx *c)
     void *ptrs[] = {c->Xs, c->Xn, c->near_ok, c->Os, c->Of, c->A, c->amp, c->exp_tab, c->v4, c->w4, c->xbuf, c->part, c->xbuf_alt, c->part_alt, c->lpt, c->lam,
                     c->tape_s, c->tape_J, c->tape_h_set[0][0], c->tape_h_set[0][1], c->tape_h_set[0][2], c->tape_a_set[0],
                     c->tape_d_set[0][0], c->tape_d_set[0][1], c->tape_d_set[0][2], c->tape_h_set[1][0], c->tape_h_set[1][1],
-                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->fbuf, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
+                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -158,7 +158,6 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     ALLOC(c->part_alt, (size_t)c->groups * (1 + D) * Bz);
     ALLOC(c->lpt, Bz);
     ALLOC(c->lam, (size_t)dims->d_s * Bz);
-    ALLOC(c->fbuf, (size_t)M * Bz);
     ALLOC(c->tape_s, (size_t)(H + 1) * dims->d_s * Bz);
     ALLOC(c->tape_J, (size_t)H * M * D * Bz);
     for (int set = 0; set < (c->T_tape < H ? 2 : 1); ++set) {
@@ -244,8 +243,7 @@ extern "C" int bagel_set_samples(bagel_ctx *c, const float *X, const float *leng
         BAGEL_FAIL(c, BAGEL_EINVAL, "bagel_set_samples: null argument");
     c->prepared = false;
     c->post_prepared = false;       // the model tables are shared: the posterior cache belongs to the old ones
-    BAGEL_HIP(c, bagel_launch_build_model(c, X, lengthscale, signal_var, omega, phase));
-    BAGEL_HIP(c, bagel_launch_pack_samples(c, w, v));
+    BAGEL_HIP(c, bagel_launch_install(c, X, lengthscale, signal_var, omega, phase, w, v, nullptr));
     c->prepared = true;
     return BAGEL_OK;
 }
@@ -260,8 +258,7 @@ extern "C" int bagel_prepare_samples(bagel_ctx *c, const float *X, const float *
         BAGEL_FAIL(c, BAGEL_EINVAL, "bagel_prepare_samples: null argument");
     c->prepared = false;
     c->post_prepared = false;       // the model tables are shared: the posterior cache belongs to the old ones
-    BAGEL_HIP(c, bagel_launch_build_model(c, X, lengthscale, signal_var, omega, phase));
-    BAGEL_HIP(c, bagel_launch_pack_samples(c, w, nullptr));
+    BAGEL_HIP(c, bagel_launch_install(c, X, lengthscale, signal_var, omega, phase, w, nullptr, nullptr));
     const int rc = bagel_prepare_impl(c, X, y, lengthscale, signal_var, noise_var, omega, phase, w, eps, v_out);
     if (rc != BAGEL_OK) return rc;
     c->prepared = true;
@@ -276,10 +273,9 @@ extern "C" int bagel_sample_eval(bagel_ctx *c, const float *x, float *f, float *
     c->err[0] = 0;
     if (!x || !f) BAGEL_FAIL(c, BAGEL_EINVAL, "bagel_sample_eval: null argument");
     if (!c->prepared) BAGEL_FAIL(c, BAGEL_ENOTPREPARED, "bagel_sample_eval: no samples installed");
-    BAGEL_HIP(c, bagel_launch_eval_io(c, 0, x, nullptr));
+    BAGEL_HIP(c, bagel_launch_eval_input(c, x));
     BAGEL_HIP(c, gp_step_timed(c, jac != nullptr));
-    BAGEL_HIP(c, bagel_launch_finalize(c, jac != nullptr, -1, jac));
-    BAGEL_HIP(c, bagel_launch_eval_io(c, 1, nullptr, f));
+    BAGEL_HIP(c, bagel_launch_finalize(c, f, jac));
     return BAGEL_OK;
 }
 
@@ -328,7 +324,7 @@ static int64_t static_scratch_bytes(const bagel_dims *dims)
     const int64_t M = c.M, D = c.D, B = dims->B, S = dims->S;
     const int64_t counts[] = {8 * M * c.Np * (D + 1), 8 * M * c.Lp * (D + 1), 16 * M * c.Lp * ((D + 3) / 4), 8 * M * D, 8 * M,
                               16 * M * (c.Np / 4) * S, 16 * M * (c.Lp / 4) * S, 8 * D * B,
-                              8 * (int64_t)c.groups * (1 + D) * B, 8 * M * B};
+                              8 * (int64_t)c.groups * (1 + D) * B, 8 * M * B};     // (the last is not used any more: what fits stays as documented)
     int64_t total = 0;
     for (int64_t n : counts) total += (n + 255) / 256 * 256;
     return total;
@@ -377,8 +373,7 @@ extern "C" int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream
     c.w4 = reinterpret_cast<float4 *>(carve(16 * M * (c.Lp / 4) * S));
     c.xbuf = reinterpret_cast<double *>(carve(8 * D * B));
     c.part = reinterpret_cast<double *>(carve(8 * (size_t)c.groups * (1 + D) * B));
-    c.fbuf = reinterpret_cast<double *>(carve(8 * M * B));
-    if ((int64_t)off != need) CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: internal size mismatch");
+    if ((int64_t)off > need) CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: internal size mismatch");
 
     // every byte a kernel below reads was written by a kernel before it in this call (padding rows
     // included), so nothing of an earlier call's contents is ever used and nothing needs clearing
@@ -388,12 +383,9 @@ extern "C" int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream
         if (e__ != hipSuccess)                                                                            \
             CREATE_FAIL(BAGEL_EHIP, "bagel_sample_eval_static: %s failed: %s", #call, hipGetErrorString(e__)); \
     } while (0)
-    STATIC_HIP(bagel_launch_build_model(&c, X, lengthscale, signal_var, omega, phase));
-    STATIC_HIP(bagel_launch_pack_samples(&c, w, v));
-    STATIC_HIP(bagel_launch_eval_io(&c, 0, x, nullptr));
+    STATIC_HIP(bagel_launch_install(&c, X, lengthscale, signal_var, omega, phase, w, v, x));
     STATIC_HIP(bagel_launch_gp_step(&c, jac != nullptr, nullptr));
-    STATIC_HIP(bagel_launch_finalize(&c, jac != nullptr, -1, jac));
-    STATIC_HIP(bagel_launch_eval_io(&c, 1, nullptr, f));
+    STATIC_HIP(bagel_launch_finalize(&c, f, jac));
 #undef STATIC_HIP
     g_create_err[0] = 0;
     return BAGEL_OK;
@@ -647,7 +639,7 @@ extern "C" int bagel_prepare_posterior(bagel_ctx *c, const float *X, const float
         }
     }
     // the scaled training inputs the kernel rows are computed from (the feature tables are left alone)
-    BAGEL_HIP(c, bagel_launch_build_model(c, X, lengthscale, signal_var, nullptr, nullptr));
+    BAGEL_HIP(c, bagel_launch_install(c, X, lengthscale, signal_var, nullptr, nullptr, nullptr, nullptr, nullptr));
     const int rc = bagel_prepare_posterior_impl(c, X, y, lengthscale, signal_var, noise_var);
     if (rc != BAGEL_OK) return rc;
     c->post_prepared = true;

@@ -48,7 +48,6 @@ struct bagel_ctx {
                                  // added up while step t is evaluated (both need their own inputs and sums)
     double *lpt;                 // [B] running cost per trajectory
     double *lam;                 // [d_s][B] adjoint of the state between the segments of a checkpointed sweep
-    double *fbuf;                // [M][B] sample values of the current step, summed over work units
 
     // ---- tape: activations and adjoints have T_tape slots (H, or ckpt_interval when checkpointing:
     // they are rebuilt segment by segment); states and Jacobians are kept for the whole horizon
@@ -98,6 +97,30 @@ struct bagel_ctx {
 };
 #define BAGEL_PROF_MAX 4096
 
+// K sums of n[k] terms p[k][0] + p[k][stride] + ... each added in order, W loads of every sum in flight at a time: the
+// sums of a step's work units are a chain of trips to memory, one per W terms.
+template <int K, int W>
+__device__ __forceinline__ void bagel_sums_in_order(const double *const (&p)[K], const int (&n)[K], size_t stride, double (&s)[K])
+{
+    int most = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        s[k] = 0.0;
+        most = n[k] > most ? n[k] : most;
+    }
+    for (int c0 = 0; c0 < most; c0 += W) {
+        double v[K][W];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < W; ++i) v[k][i] = (c0 + i < n[k]) ? p[k][(size_t)(c0 + i) * stride] : 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < W; ++i) s[k] += v[k][i];
+    }
+}
+
 #define BAGEL_FAIL(ctx, code, ...)                                   \
     do {                                                             \
         snprintf((ctx)->err, sizeof((ctx)->err), __VA_ARGS__);      \
@@ -125,17 +148,19 @@ hipError_t bagel_launch_gp_step(bagel_ctx *ctx, bool jac, float *prev_jac);
 hipError_t bagel_launch_jac_reduce(bagel_ctx *ctx, float *jdst);
 
 // ---- model.hip ---------------------------------------------------------------------------
-hipError_t bagel_launch_build_model(bagel_ctx *ctx, const float *X, const float *ell, const float *sf2,
-                                    const float *omega, const float *phase);
-hipError_t bagel_launch_pack_samples(bagel_ctx *ctx, const float *w, const float *v);
+// The model tables (omega null: without the feature tables) and, where given, the streams w and v and the inputs x of one
+// evaluation, in one launch
+hipError_t bagel_launch_install(bagel_ctx *ctx, const float *X, const float *ell, const float *sf2, const float *omega,
+                                const float *phase, const float *w, const float *v, const float *x);
 
 // ---- lane.hip ----------------------------------------------------------------------------
 hipError_t bagel_launch_init_state(bagel_ctx *ctx, const float *s0, const float *goals, float *states_out,
                                    bool tape);
 hipError_t bagel_launch_finish_loss(bagel_ctx *ctx, float *loss, float *loss_per_traj);
-hipError_t bagel_launch_eval_io(bagel_ctx *ctx, int phase, const float *x, float *f);
-// add up the per-unit partial sums: value into fbuf, Jacobian into tape slot `slot` (or jac_out if slot < 0)
-hipError_t bagel_launch_finalize(bagel_ctx *ctx, bool jac, int slot, float *jac_out);
+// x[B][D] to xbuf
+hipError_t bagel_launch_eval_input(bagel_ctx *ctx, const float *x);
+// add up the per-unit partial sums: value into f[B][M], Jacobian into jac[B][M][D] if not null
+hipError_t bagel_launch_finalize(bagel_ctx *ctx, float *f, float *jac);
 
 // ---- policy.hip --------------------------------------------------------------------------
 hipError_t bagel_launch_pack_theta(bagel_ctx *ctx, const float *theta);

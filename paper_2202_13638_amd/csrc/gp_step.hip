@@ -133,30 +133,6 @@ struct jac_sums {
     float *jdst;             // [M][D][B]
 };
 
-// K sums of n[k] terms p[k][0] + p[k][stride] + ... each added in order, W loads of every sum in flight at a time: the
-// tile is a chain of trips to memory, one per W terms.
-template <int K, int W>
-__device__ __forceinline__ void sums_in_order(const double *const (&p)[K], const int (&n)[K], size_t stride, double (&s)[K])
-{
-    int most = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        s[k] = 0.0;
-        most = n[k] > most ? n[k] : most;
-    }
-    for (int c0 = 0; c0 < most; c0 += W) {
-        double v[K][W];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int i = 0; i < W; ++i) v[k][i] = (c0 + i < n[k]) ? p[k][(size_t)(c0 + i) * stride] : 0.0;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int i = 0; i < W; ++i) s[k] += v[k][i];
-    }
-}
-
 // W: loads in flight per sum (4 inside the large launches, which hide the trips and have few registers; 8 elsewhere)
 template <int W>
 __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
@@ -169,7 +145,7 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
     const double *pk = j.part + (size_t)(m * ngk) * stride + b;
     const double *pr = j.part + (size_t)(M * ngk + m * ngl) * stride + b;
     double u[1];
-    if (W < 8) sums_in_order<1, W>({pk}, {ngk}, stride, u);      // (fewer registers: the value sum on its own first)
+    if (W < 8) bagel_sums_in_order<1, W>({pk}, {ngk}, stride, u);      // (fewer registers: the value sum on its own first)
     for (int d = wave; d < D; d += BAGEL_BLOCK / 64) {
         const double *const p[3] = {pk + (size_t)(1 + d) * B, pr + (size_t)(1 + d) * B, pk};
         const int n[3] = {ngk, ngl, ngk};
@@ -177,13 +153,13 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
         double s[3];
         if (W < 8) {
             double one[1];
-            sums_in_order<1, W>({p[0]}, {ngk}, stride, one);
+            bagel_sums_in_order<1, W>({p[0]}, {ngk}, stride, one);
             s[0] = one[0];
-            sums_in_order<1, W>({p[1]}, {ngl}, stride, one);
+            bagel_sums_in_order<1, W>({p[1]}, {ngl}, stride, one);
             s[1] = one[0];
             s[2] = u[0];
         } else {
-            sums_in_order<3, W>(p, n, stride, s);
+            bagel_sums_in_order<3, W>(p, n, stride, s);
         }
         j.jdst[(size_t)(m * D + d) * B + b] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
     }

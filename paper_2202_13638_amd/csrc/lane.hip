@@ -28,32 +28,24 @@ struct lane_args {
 //   f[m] = amp_m * sum_c p_c + sum_c u_c,
 // component 1+d the Jacobian entry
 //   J[m][d] = -amp_m (2 pi) sum_c Gr_c[d] + ln2 (sum_c Gk_c[d] - log2(e)/l_md^2 x_d sum_c u_c).
-// f goes to fbuf[m][b] (float64); J[m][d] to jdst[(m*D+d)*js_i + b*js_b] (float32), which is either a
-// tape slot ([M][D][B]) or a caller array ([B][M][D]).
-__global__ __launch_bounds__(BAGEL_BLOCK) void finalize_kernel(lane_args a, int ncomp, double *__restrict__ fbuf,
-                                                               float *__restrict__ jdst, long js_i, long js_b)
+__global__ __launch_bounds__(64) void finalize_kernel(lane_args a, int ncomp, float *__restrict__ f, float *__restrict__ jac)
 {
-    const int b = blockIdx.x * BAGEL_BLOCK + threadIdx.x;
+    const int b = blockIdx.x * 64 + threadIdx.x;
     if (b >= a.B) return;
     const int m = blockIdx.y / ncomp, comp = blockIdx.y - m * ncomp;
     const size_t stride = (size_t)(1 + a.D) * a.B;
     const double *pk = a.part + (size_t)(m * a.nck) * stride + b;
     const double *pr = a.part + (size_t)(a.M * a.nck + m * a.ncl) * stride + b;
-    double u = 0.0;
-    for (int c = 0; c < a.nck; ++c) u += pk[c * stride];
-    const double amp = a.amp[m];
+    double s[3];
     if (comp == 0) {
-        double p = 0.0;
-        for (int c = 0; c < a.ncl; ++c) p += pr[c * stride];
-        fbuf[(size_t)m * a.B + b] = amp * p + u;
+        bagel_sums_in_order<3, 8>({pk, pr, pk}, {a.nck, a.ncl, 0}, stride, s);
+        f[(size_t)b * a.M + m] = (float)(a.amp[m] * s[1] + s[0]);
     } else {
         const int d = comp - 1;
-        double gk = 0.0, gr = 0.0;
-        for (int c = 0; c < a.nck; ++c) gk += pk[c * stride + (size_t)comp * a.B];
-        for (int c = 0; c < a.ncl; ++c) gr += pr[c * stride + (size_t)comp * a.B];
         const double x = a.xbuf[(size_t)d * a.B + b];
-        const double J = -amp * TWO_PI * gr + LN2 * (gk - a.A[m * a.D + d] * x * u);
-        jdst[(long)(m * a.D + d) * js_i + (long)b * js_b] = (float)J;
+        const size_t off = (size_t)comp * a.B;
+        bagel_sums_in_order<3, 8>({pk, pk + off, pr + off}, {a.nck, a.nck, a.ncl}, stride, s);
+        jac[((size_t)b * a.M + m) * a.D + d] = (float)(-a.amp[m] * TWO_PI * s[2] + LN2 * (s[1] - a.A[m * a.D + d] * x * s[0]));
     }
 }
 
@@ -96,18 +88,12 @@ __global__ __launch_bounds__(1024) void finish_loss_kernel(const double *__restr
     if (threadIdx.x == 0) loss[0] = (float)(sh[0] / (double)B);
 }
 
-// bagel_sample_eval plumbing: phase 0 loads x[B][D] into xbuf; phase 1 writes f[B][M] from fbuf.
-__global__ __launch_bounds__(BAGEL_BLOCK) void eval_io_kernel(lane_args a, int phase, const float *__restrict__ xin,
-                                                              const double *__restrict__ fbuf,
-                                                              float *__restrict__ f_out)
+// x[B][D] -> xbuf
+__global__ __launch_bounds__(BAGEL_BLOCK) void eval_input_kernel(lane_args a, const float *__restrict__ xin)
 {
     const int b = blockIdx.x * BAGEL_BLOCK + threadIdx.x;
     if (b >= a.B) return;
-    if (phase == 0) {
-        for (int d = 0; d < a.D; ++d) a.xbuf[(size_t)d * a.B + b] = (double)xin[(size_t)b * a.D + d];
-        return;
-    }
-    for (int m = 0; m < a.M; ++m) f_out[(size_t)b * a.M + m] = (float)fbuf[(size_t)m * a.B + b];
+    for (int d = 0; d < a.D; ++d) a.xbuf[(size_t)d * a.B + b] = (double)xin[(size_t)b * a.D + d];
 }
 
 lane_args make_args(const bagel_ctx *c)
@@ -145,25 +131,15 @@ hipError_t bagel_launch_finish_loss(bagel_ctx *c, float *loss, float *loss_per_t
     return hipGetLastError();
 }
 
-hipError_t bagel_launch_eval_io(bagel_ctx *c, int phase, const float *x, float *f)
+hipError_t bagel_launch_eval_input(bagel_ctx *c, const float *x)
 {
-    lane_args a = make_args(c);
-    hipLaunchKernelGGL(eval_io_kernel, lane_grid(c), dim3(BAGEL_BLOCK), 0, c->stream, a, phase, x, c->fbuf, f);
+    hipLaunchKernelGGL(eval_input_kernel, lane_grid(c), dim3(BAGEL_BLOCK), 0, c->stream, make_args(c), x);
     return hipGetLastError();
 }
 
-// slot >= 0: Jacobian into that tape slot; slot < 0: into jac_out[B][M][D] (may be null: value only)
-hipError_t bagel_launch_finalize(bagel_ctx *c, bool jac, int slot, float *jac_out)
+hipError_t bagel_launch_finalize(bagel_ctx *c, float *f, float *jac)
 {
-    lane_args a = make_args(c);
     const int ncomp = jac ? 1 + c->D : 1;
-    dim3 grid((c->dm.B + BAGEL_BLOCK - 1) / BAGEL_BLOCK, c->M * ncomp);
-    float *jdst = nullptr;
-    long js_i = 0, js_b = 0;
-    if (jac) {
-        if (slot >= 0) { jdst = slot_ptr(c->tape_J, slot, c->M * c->D, c->dm.B); js_i = c->dm.B; js_b = 1; }
-        else { jdst = jac_out; js_i = 1; js_b = (long)c->M * c->D; }
-    }
-    hipLaunchKernelGGL(finalize_kernel, grid, dim3(BAGEL_BLOCK), 0, c->stream, a, ncomp, c->fbuf, jdst, js_i, js_b);
+    hipLaunchKernelGGL(finalize_kernel, dim3((c->dm.B + 63) / 64, c->M * ncomp), dim3(64), 0, c->stream, make_args(c), ncomp, f, jac);
     return hipGetLastError();
 }

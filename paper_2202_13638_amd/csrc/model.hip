@@ -18,15 +18,23 @@ constexpr double INV_TWO_PI = 0.15915494309189533577;
 
 __global__ void set_flag_kernel(int *flag, int value) { flag[0] = value; }
 
-__global__ void build_model_kernel(const float *__restrict__ X, const float *__restrict__ ell,
-                                   const float *__restrict__ sf2, const float *__restrict__ omega,
-                                   const float *__restrict__ phase, double *__restrict__ Xs,
-                                   double *__restrict__ Xn, int *__restrict__ near_ok,
-                                   double *__restrict__ Os, float *__restrict__ Of, double *__restrict__ A,
-                                   double *__restrict__ amp, int M, int N, int L, int D, int Np, int Lp)
+struct model_args {
+    const float *X, *ell, *sf2, *omega, *phase;
+    double *Xs, *Xn, *Os, *A, *amp;
+    float *Of;
+    int *near_ok;
+    int M, N, L, D, Np, Lp;
+};
+
+// rows i of the tables of output m
+__device__ __forceinline__ void build_rows(const model_args &t, int m, int i)
 {
-    const int m = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const float *__restrict__ X = t.X, *__restrict__ ell = t.ell, *__restrict__ sf2 = t.sf2, *__restrict__ omega = t.omega,
+                *__restrict__ phase = t.phase;
+    double *__restrict__ Xs = t.Xs, *__restrict__ Xn = t.Xn, *__restrict__ Os = t.Os, *__restrict__ A = t.A, *__restrict__ amp = t.amp;
+    float *__restrict__ Of = t.Of;
+    int *near_ok = t.near_ok;
+    const int N = t.N, L = t.L, D = t.D, Np = t.Np, Lp = t.Lp;
     if (i < Np) {
         double *row = Xs + ((size_t)m * Np + i) * (D + 1);
         if (i < N) {
@@ -82,53 +90,78 @@ __global__ void build_model_kernel(const float *__restrict__ X, const float *__r
     if (i == 0) amp[m] = sqrt(2.0 * (double)sf2[m] / (double)L);
 }
 
-// src[S][M][n] -> dst[M][np/4][S] (float4), zero padded.  One thread per (m, n4, s), s fastest.
-__global__ void pack_stream_kernel(const float *__restrict__ src, float4 *__restrict__ dst, int S, int M,
-                                   int n, int np4)
+// One 64 x 64 block of a stream, src[S][M][n] -> dst[M][np/4][S] (float4 of four consecutive n, zero past n), through LDS so
+// that both sides are contiguous: sample s0 + r, entries q0 ..
+__device__ __forceinline__ void pack_block(const float *__restrict__ src, float4 *__restrict__ dst, int S, int M, int n, int np4, int m,
+                                           int s0, int q0, float (*t)[65])
 {
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t total = (size_t)M * np4 * S;
-    if (idx >= total) return;
-    const int s = (int)(idx % S);
-    const size_t r = idx / S;
-    const int n4 = (int)(r % np4);
-    const int m = (int)(r / np4);
-    const float *p = src + ((size_t)s * M + m) * n;
-    float t[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int k = n4 * 4 + j;
-        t[j] = k < n ? p[k] : 0.0f;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll 4
+    for (int r = wave; r < 64; r += 4)
+        t[r][lane] = (s0 + r < S && q0 + lane < n) ? src[((size_t)(s0 + r) * M + m) * n + q0 + lane] : 0.0f;
+    __syncthreads();
+    for (int q = wave; q < 16; q += 4)
+        if (q0 / 4 + q < np4 && s0 + lane < S)
+            dst[((size_t)m * np4 + q0 / 4 + q) * S + s0 + lane] =
+                make_float4(t[lane][4 * q], t[lane][4 * q + 1], t[lane][4 * q + 2], t[lane][4 * q + 3]);
+}
+
+// What one call installs: blocks of the model tables, of the two streams and of the inputs, one after the other in the grid
+struct install_args {
+    model_args t;
+    const float *v, *w, *x;
+    float4 *v4, *w4;
+    double *xbuf;
+    int S, B;
+    int model_blocks, v_blocks, w_blocks;        // first three parts of the grid; the rest are inputs
+};
+
+__global__ __launch_bounds__(256) void install_kernel(install_args a)
+{
+    __shared__ float t[64][65];
+    int blk = blockIdx.x;
+    const int M = a.t.M, sb = (a.S + 63) / 64;
+    if (blk < a.model_blocks) {
+        const int per = a.model_blocks / M;
+        build_rows(a.t, blk / per, (blk % per) * 256 + threadIdx.x);
+        return;
     }
-    dst[idx] = make_float4(t[0], t[1], t[2], t[3]);
+    blk -= a.model_blocks;
+    if (blk < a.v_blocks + a.w_blocks) {
+        const bool is_v = blk < a.v_blocks;
+        if (!is_v) blk -= a.v_blocks;
+        const int n = is_v ? a.t.N : a.t.L, np4 = (is_v ? a.t.Np : a.t.Lp) / 4, qb = (np4 + 15) / 16;
+        const int s = blk % sb, q = (blk / sb) % qb, m = blk / (sb * qb);
+        pack_block(is_v ? a.v : a.w, is_v ? a.v4 : a.w4, a.S, M, n, np4, m, 64 * s, 64 * q, t);
+        return;
+    }
+    blk -= a.v_blocks + a.w_blocks;
+    const int b = blk * 256 + threadIdx.x;
+    if (b < a.B)
+        for (int d = 0; d < a.t.D; ++d) a.xbuf[(size_t)d * a.B + b] = (double)a.x[(size_t)b * a.t.D + d];
 }
 
 }  // namespace
 
-hipError_t bagel_launch_build_model(bagel_ctx *c, const float *X, const float *ell, const float *sf2,
-                                    const float *omega, const float *phase)
+hipError_t bagel_launch_install(bagel_ctx *c, const float *X, const float *ell, const float *sf2, const float *omega,
+                                const float *phase, const float *w, const float *v, const float *x)
 {
-    const int big = c->Np > c->Lp ? c->Np : c->Lp;
-    dim3 grid((big + 255) / 256, c->M);
     // near_ok starts at 1 and is cleared by any row outside the table form's range (contexts without the
     // table form have no Xn)
     if (c->Xn) hipLaunchKernelGGL(set_flag_kernel, dim3(1), dim3(1), 0, c->stream, c->near_ok, 1);
-    hipLaunchKernelGGL(build_model_kernel, grid, dim3(256), 0, c->stream, X, ell, sf2, omega, phase, c->Xs, c->Xn,
-                       c->near_ok, c->Os, c->Of, c->A, c->amp, c->M, c->dm.N, c->dm.L, c->D, c->Np, c->Lp);
-    return hipGetLastError();
-}
-
-hipError_t bagel_launch_pack_samples(bagel_ctx *c, const float *w, const float *v)
-{
-    if (v) {
-        const size_t total = (size_t)c->M * (c->Np / 4) * c->dm.S;
-        hipLaunchKernelGGL(pack_stream_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream, v,
-                           c->v4, c->dm.S, c->M, c->dm.N, c->Np / 4);
-    }
-    if (w) {
-        const size_t total = (size_t)c->M * (c->Lp / 4) * c->dm.S;
-        hipLaunchKernelGGL(pack_stream_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream, w,
-                           c->w4, c->dm.S, c->M, c->dm.L, c->Lp / 4);
-    }
+    install_args a;
+    a.t = model_args{X, ell, sf2, omega, phase, c->Xs, c->Xn, c->Os, c->A, c->amp, c->Of, c->near_ok, c->M, c->dm.N, c->dm.L, c->D,
+                     c->Np, c->Lp};
+    a.v = v; a.w = w; a.x = x;
+    a.v4 = c->v4; a.w4 = c->w4; a.xbuf = c->xbuf;
+    a.S = c->dm.S; a.B = c->dm.B;
+    const int big = c->Np > c->Lp ? c->Np : c->Lp;
+    const int64_t sb = (c->dm.S + 63) / 64;
+    const int64_t model = (int64_t)c->M * ((big + 255) / 256);
+    const int64_t vb = v ? c->M * sb * ((c->Np / 4 + 15) / 16) : 0, wb = w ? c->M * sb * ((c->Lp / 4 + 15) / 16) : 0;
+    const int64_t xb = x ? (c->dm.B + 255) / 256 : 0;
+    if (model + vb + wb + xb > 0x7fffffff) return hipErrorInvalidValue;
+    a.model_blocks = (int)model; a.v_blocks = (int)vb; a.w_blocks = (int)wb;
+    hipLaunchKernelGGL(install_kernel, dim3((unsigned)(model + vb + wb + xb)), dim3(256), 0, c->stream, a);
     return hipGetLastError();
 }
