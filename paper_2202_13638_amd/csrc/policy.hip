@@ -987,20 +987,32 @@ __global__ void pack_theta_kernel(const float *__restrict__ theta, float *__rest
 
 // ---- weight gradient GEMM ------------------------------------------------------------------
 // C[o][i] = sum_kk Dl[o][kk] * Hl[i][kk], kk = (slot, b); db[o] = sum_kk Dl[o][kk].
-// Wave (wr, wc) of a wrows x wcols wave grid (at most 4x4, sized to the layer so that no wave idles)
-// owns rows [64 wr, +64) x columns [64 wc, +64) as 2x2 MFMA tiles.
-template <bool FAST>
-__global__ __launch_bounds__(1024) void weight_grad_kernel(const float *__restrict__ Dl, const float *__restrict__ Hl,
-                                                           float *__restrict__ gsplit, int no, int ni, int B,
-                                                           int n_slots, int chunks_per_slot, int chunks_per_split,
-                                                           int w_off, int b_off, int P, int wcols)
+// Wave (wr, wc) of a layer's wrows x wcols wave grid (at most 4x4, sized to the layer so that no wave idles)
+// owns rows [64 wr, +64) x columns [64 wc, +64) as 2x2 MFMA tiles.  All layers that take this kernel share a launch
+// (blockIdx.y); blockIdx.x is the split of the contraction.
+struct wg_layer {
+    const float *Dl, *Hl;
+    int no, ni, w_off, b_off, wrows, wcols;
+};
+struct wg_layers {
+    wg_layer l[3];
+};
+
+// MAXW: waves per workgroup the launch is sized for; DEP: chunks of eight trajectories whose operands are in flight.  A
+// narrow policy has one wave per compute unit and layer here, so the kernel is a chain of trips to memory: DEP = 4
+// (one chunk ahead before: 56 us per layer and launch at 64-64, 1024 trajectories, 200 steps, and a launch per layer).
+template <bool FAST, int MAXW, int DEP>
+__global__ __launch_bounds__(64 * MAXW) void weight_grad_kernel(wg_layers ls, float *__restrict__ gsplit, int B, int n_slots,
+                                                                int chunks_per_slot, int chunks_per_split, int P)
 {
+    const wg_layer L = ls.l[blockIdx.y];
+    const int no = L.no, ni = L.ni;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave / wcols, wc = wave - wr * wcols;   // the workgroup has wrows x wcols waves
+    const int wr = wave / L.wcols, wc = wave - wr * L.wcols;
     const int cl = lane & 31, hf = lane >> 5;
-    const int o_base = blockIdx.y * 256 + wr * 64, i_base = blockIdx.z * 256 + wc * 64;
-    if (o_base >= no || i_base >= ni) return;   // whole wave has nothing to do (no barriers in this kernel)
+    const int o_base = wr * 64, i_base = wc * 64;
+    if (wr >= L.wrows) return;                  // whole wave has nothing to do (no barriers in this kernel)
     const bool fa_on[2] = {true, o_base + 32 < no};
     const bool fb_on[2] = {true, i_base + 32 < ni};
     const int total_chunks = n_slots * chunks_per_slot;
@@ -1018,10 +1030,52 @@ __global__ __launch_bounds__(1024) void weight_grad_kernel(const float *__restri
     const int orow[2] = {o_base + cl, o_base + 32 + cl};
     const int irow[2] = {i_base + cl, i_base + 32 + cl};
     // rows past the end are clamped: they feed accumulator rows / columns that are never stored
-    const int oc[2] = {min(orow[0], no - 1), min(orow[1], no - 1)};
-    const int ic[2] = {min(irow[0], ni - 1), min(irow[1], ni - 1)};
+    const size_t oc[2] = {(size_t)min(orow[0], no - 1) * B, (size_t)min(orow[1], no - 1) * B};
+    const size_t ic[2] = {(size_t)min(irow[0], ni - 1) * B, (size_t)min(irow[1], ni - 1) * B};
 
-    auto mfma_chunk = [&](const float4 *a4, const float4 *b4) {
+    // position of the next chunk to request (a request past the end repeats the last chunk) and of the next to use
+    int rc = c_begin, r_pos = c_begin % chunks_per_slot, u_pos = r_pos;
+    const float *Ds = L.Dl + (size_t)(c_begin / chunks_per_slot) * no * B, *Hs = L.Hl + (size_t)(c_begin / chunks_per_slot) * ni * B;
+    auto request = [&](float4 (&a4)[2], float4 (&b4)[2]) {
+        const int bb = r_pos * 8 + 4 * hf;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            if (FAST) {                          // B % 8 == 0: every chunk is full and 16-byte aligned
+                a4[f] = *reinterpret_cast<const float4 *>(Ds + oc[f] + bb);
+                b4[f] = *reinterpret_cast<const float4 *>(Hs + ic[f] + bb);
+            } else {
+                float ta[4], tb[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int k = min(bb + e, B - 1);
+                    ta[e] = Ds[oc[f] + k];
+                    tb[e] = Hs[ic[f] + k];
+                }
+                a4[f] = make_float4(ta[0], ta[1], ta[2], ta[3]);
+                b4[f] = make_float4(tb[0], tb[1], tb[2], tb[3]);
+            }
+        }
+        if (rc + 1 < c_end) {
+            ++rc;
+            if (++r_pos == chunks_per_slot) {
+                r_pos = 0;
+                Ds += (size_t)no * B;
+                Hs += (size_t)ni * B;
+            }
+        }
+    };
+    auto use = [&](float4 (&a4)[2], float4 (&b4)[2]) {
+        if (!FAST) {                             // trajectories past the end count as zero
+            const int bb = u_pos * 8 + 4 * hf;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                a4[f].x = bb < B ? a4[f].x : 0.0f; a4[f].y = bb + 1 < B ? a4[f].y : 0.0f;
+                a4[f].z = bb + 2 < B ? a4[f].z : 0.0f; a4[f].w = bb + 3 < B ? a4[f].w : 0.0f;
+                b4[f].x = bb < B ? b4[f].x : 0.0f; b4[f].y = bb + 1 < B ? b4[f].y : 0.0f;
+                b4[f].z = bb + 2 < B ? b4[f].z : 0.0f; b4[f].w = bb + 3 < B ? b4[f].w : 0.0f;
+            }
+            if (++u_pos == chunks_per_slot) u_pos = 0;
+        }
 #pragma unroll
         for (int f = 0; f < 2; ++f) bsum[f] += (a4[f].x + a4[f].y) + (a4[f].z + a4[f].w);
 #pragma unroll
@@ -1038,47 +1092,21 @@ __global__ __launch_bounds__(1024) void weight_grad_kernel(const float *__restri
         }
     };
 
-    if (FAST) {
-        // B % 8 == 0: every chunk is full and 16-byte aligned; loads are unconditional and the operands
-        // of chunk c+1 are requested before the MFMAs of chunk c issue
-        auto load_chunk = [&](int c, float4 *a4, float4 *b4) {
-            const int slot = c / chunks_per_slot;
-            const int bb = (c - slot * chunks_per_slot) * 8 + 4 * hf;
+    if (c_begin < c_end) {
+        float4 a4[DEP][2], b4[DEP][2];
 #pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                a4[f] = *reinterpret_cast<const float4 *>(Dl + ((size_t)slot * no + oc[f]) * B + bb);
-                b4[f] = *reinterpret_cast<const float4 *>(Hl + ((size_t)slot * ni + ic[f]) * B + bb);
+        for (int e = 0; e < DEP; ++e) request(a4[e], b4[e]);
+        int c = c_begin;
+        for (; c + DEP <= c_end; c += DEP) {
+#pragma unroll
+            for (int e = 0; e < DEP; ++e) {
+                use(a4[e], b4[e]);
+                request(a4[e], b4[e]);
             }
-        };
-        float4 a4[2], b4[2], an[2], bn[2];
-        if (c_begin < c_end) load_chunk(c_begin, a4, b4);
-        for (int c = c_begin; c < c_end; ++c) {
-            load_chunk(c + 1 < c_end ? c + 1 : c, an, bn);
-            mfma_chunk(a4, b4);
-#pragma unroll
-            for (int f = 0; f < 2; ++f) { a4[f] = an[f]; b4[f] = bn[f]; }
         }
-    } else {
-        for (int c = c_begin; c < c_end; ++c) {
-            const int slot = c / chunks_per_slot;
-            const int bb = (c - slot * chunks_per_slot) * 8 + 4 * hf;
-            float4 a4[2], b4[2];
 #pragma unroll
-            for (int f = 0; f < 2; ++f) {
-                const float *ar = Dl + ((size_t)slot * no + oc[f]) * B;
-                const float *br = Hl + ((size_t)slot * ni + ic[f]) * B;
-                float ta[4], tb[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool ok = bb + e < B;
-                    ta[e] = ok ? ar[bb + e] : 0.0f;
-                    tb[e] = ok ? br[bb + e] : 0.0f;
-                }
-                a4[f] = make_float4(ta[0], ta[1], ta[2], ta[3]);
-                b4[f] = make_float4(tb[0], tb[1], tb[2], tb[3]);
-            }
-            mfma_chunk(a4, b4);
-        }
+        for (int e = 0; e < DEP; ++e)
+            if (c + e < c_end) use(a4[e], b4[e]);
     }
     float *g = gsplit + (size_t)blockIdx.x * P;
 #pragma unroll
@@ -1089,13 +1117,13 @@ __global__ __launch_bounds__(1024) void weight_grad_kernel(const float *__restri
             for (int r = 0; r < 16; ++r) {
                 const int o = o_base + x * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
                 const int i = i_base + y * 32 + cl;
-                if (o < no && i < ni) g[w_off + (size_t)o * ni + i] = acc[x][y][r];
+                if (o < no && i < ni) g[L.w_off + (size_t)o * ni + i] = acc[x][y][r];
             }
-    if (blockIdx.z == 0 && wc == 0) {
+    if (wc == 0) {
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
             const float tot = bsum[f] + __shfl_xor(bsum[f], 32);
-            if (hf == 0 && orow[f] < no) g[b_off + orow[f]] = tot;
+            if (hf == 0 && orow[f] < no) g[L.b_off + orow[f]] = tot;
         }
     }
 }
@@ -1453,6 +1481,8 @@ hipError_t bagel_launch_weight_grad(bagel_ctx *c, int n_slots, bool accumulate, 
     const int ksplit = total < c->ksplit ? total : c->ksplit;
     const int per = (total + ksplit - 1) / ksplit;
     const int nz = (total + per - 1) / per;
+    wg_layers ls = {};
+    int n_direct = 0, waves = 1;
     for (int l = 0; l < c->n_layers; ++l) {
         const int no = c->width[l + 1], ni = c->width[l];
         if (B % WG_KC == 0 && no <= 256 && ni <= 256) {
@@ -1473,16 +1503,20 @@ hipError_t bagel_launch_weight_grad(bagel_ctx *c, int n_slots, bool accumulate, 
             if (e != hipSuccess) return e;
             if (done) continue;
         }
-        dim3 grid(nz, (no + 255) / 256, (ni + 255) / 256);
-        const int wrows = no >= 256 ? 4 : (no + 63) / 64, wcols = ni >= 256 ? 4 : (ni + 63) / 64;
-        if (B % 8 == 0)
-            hipLaunchKernelGGL(weight_grad_kernel<true>, grid, dim3(64 * wrows * wcols), 0, c->stream, c->tape_d[l],
-                               c->tape_h[l], c->gsplit, no, ni, B, n_slots, chunks_per_slot, per, c->w_off[l],
-                               c->b_off[l], c->P, wcols);
-        else
-            hipLaunchKernelGGL(weight_grad_kernel<false>, grid, dim3(64 * wrows * wcols), 0, c->stream, c->tape_d[l],
-                               c->tape_h[l], c->gsplit, no, ni, B, n_slots, chunks_per_slot, per, c->w_off[l],
-                               c->b_off[l], c->P, wcols);
+        wg_layer &q = ls.l[n_direct++];
+        q = wg_layer{c->tape_d[l], c->tape_h[l], no, ni, c->w_off[l], c->b_off[l], (no + 63) / 64, (ni + 63) / 64};
+        if (q.wrows * q.wcols > waves) waves = q.wrows * q.wcols;
+    }
+    if (n_direct > 0) {
+        const dim3 grid(nz, n_direct), block(64 * waves);
+#define WG(fast, maxw, dep)                                                                                                    \
+    hipLaunchKernelGGL((weight_grad_kernel<fast, maxw, dep>), grid, block, 0, c->stream, ls, c->gsplit, B, n_slots, chunks_per_slot, \
+                       per, c->P)
+        if (waves <= 4 && B % 8 == 0) WG(true, 4, 4);
+        else if (waves <= 4) WG(false, 4, 4);
+        else if (B % 8 == 0) WG(true, 16, 2);
+        else WG(false, 16, 1);
+#undef WG
     }
     hipLaunchKernelGGL(grad_reduce_kernel, dim3((c->P + 63) / 64), dim3(256), 0, c->stream, c->gsplit, c->gacc, c->P,
                        nz, accumulate, grad_theta);
