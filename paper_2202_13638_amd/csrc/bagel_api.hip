@@ -170,9 +170,8 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         ALLOC(c->tape_a_set[set], T * dims->d_a * Bz);
     }
     use_tape_set(c, 0);
-    if (c->p16) {
-        ALLOC(c->wpack16, (size_t)c->pack16_floats);
-    } else {
+    if (c->p16) { ALLOC(c->wpack16, (size_t)c->pack16_floats); }
+    if (c->p16 == 0 || c->p16 == 3) {        // (3: the backward sweep is that of policy.hip)
         ALLOC(c->wpad_f, (size_t)wf_total);
         ALLOC(c->wpad_b, (size_t)wb_total);
     }
@@ -448,7 +447,8 @@ extern "C" int bagel_profile_read(bagel_ctx *c, double *kernel_ms, int *launches
 static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape)
 {
     if (c->p16) {
-        const hipError_t e = bagel_launch_pack_theta16(c, theta);
+        hipError_t e = bagel_launch_pack_theta16(c, theta);
+        if (e == hipSuccess && tape && c->p16 == 3) e = bagel_launch_pack_theta(c, theta);     // for backward_sweep
         return e == hipSuccess ? bagel_launch_start16(c, s0, goals, states, tape) : e;
     }
     const hipError_t e = bagel_launch_pack_theta(c, theta);
@@ -457,7 +457,8 @@ static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s
 
 static hipError_t backward_sweep(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
 {
-    return c->p16 ? bagel_launch_backward_sweep16(c, t_lo, t_hi, goals, grad_s0) : bagel_launch_backward_sweep(c, t_lo, t_hi, goals, grad_s0);
+    return c->p16 == 1 || c->p16 == 2 ? bagel_launch_backward_sweep16(c, t_lo, t_hi, goals, grad_s0)
+                                      : bagel_launch_backward_sweep(c, t_lo, t_hi, goals, grad_s0);
 }
 
 // Forward steps 0 .. H-1 from the state in xbuf and the policy input in tape slot 0.  jac: the sample

@@ -15,7 +15,7 @@
 //     A lane's four results of a tile are then its operands of the next contraction over those 16 units, in the order
 //     they are needed: one 16-byte LDS write and reads of [trajectory][tile][4 g + r].
 //   - The output layer (forward) and the input layer (backward) have one row tile: wave w takes slice w of them.
-// Instances: 4 waves of one tile (hidden widths <= 64), 8 of one (<= 128), 8 of two (<= 256).
+// Instances: 4 waves of one tile (hidden widths <= 64), 8 of one (<= 128), 8 of two (<= 256; not the backward sweep).
 #include "bagel_internal.h"
 
 namespace {
@@ -486,6 +486,9 @@ __global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args 
 // As backward_sweep_kernel of policy.hip: the steps t_hi-1 .. t_lo of 16 trajectories per workgroup.  What a step reads from
 // the tapes is requested two steps ahead, into the registers that held the values of the step just done with them
 // (two sets, the loop body handles two steps), so that no value is copied and nothing waits for a load it does not need.
+// For widths up to 128.  Above, the 128 registers of middle weights leave too few for two steps of tape values: an instance
+// kept 400 bytes a lane in scratch, and gradients came out different from run to run when only its workgroup order was
+// changed.  The sweep of policy.hip, in registers, serves those policies.
 struct sweep16_args {
     int B, nl, ds, da, dg, D, M, H, t_hi, t_lo;
     int width[4];
@@ -836,7 +839,6 @@ hipError_t bagel_launch_backward_sweep16(bagel_ctx *c, int t_lo, int t_hi, const
     a.tape_J = c->tape_J + (per_segment ? (size_t)t_lo * c->M * c->D * c->dm.B : 0);
     a.goals = goals; a.lam = c->lam; a.grad_s0 = grad_s0;
     if (c->p16 == 1) launch_sweep<4, 1>(c, a);
-    else if (c->p16 == 2) launch_sweep<8, 1>(c, a);
-    else launch_sweep<8, 2>(c, a);
+    else launch_sweep<8, 1>(c, a);
     return hipGetLastError();
 }
