@@ -122,12 +122,12 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         delete c;
         CREATE_FAIL(BAGEL_EINVAL, "bagel_create: %s", msg);
     }
-    bagel_plan_policy(c);
     const int B = dims->B, M = c->M, D = c->D;
 
     const int K = dims->ckpt_interval;
     const int H = dims->H;
     c->T_tape = (K > 0 && K < H) ? K : H;
+    bagel_plan_policy(c);
     c->ksplit = bagel_env_int("BAGEL_KSPLIT", 256);
     int wf_total = 0, wb_total = 0;
     for (int l = 0; l < c->n_layers; ++l) {
@@ -444,12 +444,13 @@ extern "C" int bagel_profile_read(bagel_ctx *c, double *kernel_ms, int *launches
 }
 
 // Packed weights, initial state and policy input; with the kernels of policy16.hip also the policy of step 0
-static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape)
+static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape,
+                                bool acts)
 {
     if (c->p16) {
         hipError_t e = bagel_launch_pack_theta16(c, theta);
         if (e == hipSuccess && tape && c->p16 == 3) e = bagel_launch_pack_theta(c, theta);     // for backward_sweep
-        return e == hipSuccess ? bagel_launch_start16(c, s0, goals, states, tape) : e;
+        return e == hipSuccess ? bagel_launch_start16(c, s0, goals, states, tape, acts) : e;
     }
     const hipError_t e = bagel_launch_pack_theta(c, theta);
     return e == hipSuccess ? bagel_launch_init_state(c, s0, goals, states, tape) : e;
@@ -481,9 +482,9 @@ static int run_forward(bagel_ctx *c, bool jac, bool acts, bool write_tape_s, con
         float *prev_jac = (jac && !posterior && t > 0) ? c->tape_J + (size_t)(t - 1) * jslot : nullptr;
         BAGEL_HIP(c, gp_step_timed(c, jac, posterior ? c->cur_xi + (size_t)t * c->dm.B * c->M : nullptr, prev_jac));
         if (c->p16)
-            BAGEL_HIP(c, bagel_launch_step_tail16(c, t, t, next_slot, jac, write_tape_s, goals, states_out, posterior));
+            BAGEL_HIP(c, bagel_launch_step_tail16(c, t, t, next_slot, jac, acts, write_tape_s, goals, states_out, posterior));
         else
-            BAGEL_HIP(c, bagel_launch_step_tail(c, t, t, next_slot, jac, true, write_tape_s, theta, goals, states_out,
+            BAGEL_HIP(c, bagel_launch_step_tail(c, t, t, next_slot, jac, acts, true, write_tape_s, theta, goals, states_out,
                                                 posterior));
         double *tx = c->xbuf; c->xbuf = c->xbuf_alt; c->xbuf_alt = tx;
         double *tp = c->part; c->part = c->part_alt; c->part_alt = tp;
@@ -507,7 +508,7 @@ static int rollout_loss_impl(bagel_ctx *c, const char *who, const float *theta, 
     if (posterior ? !c->post_prepared : !c->prepared)
         BAGEL_FAIL(c, BAGEL_ENOTPREPARED, "%s: %s", who, posterior ? "no posterior cache installed" : "no samples installed");
     c->cur_xi = posterior ? xi : nullptr;
-    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, false));
+    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, false, false));
     const int rc = run_forward(c, false, false, false, theta, goals, states);
     if (rc != BAGEL_OK) return rc;
     BAGEL_HIP(c, bagel_launch_finish_loss(c, loss, loss_per_traj));
@@ -540,7 +541,7 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
     const int H = c->dm.H, K = c->T_tape;
     const bool ckpt = K < H;
     int rc;
-    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, true));
+    BAGEL_HIP(c, start_rollout(c, theta, s0, goals, states, true, !ckpt));
     // One forward pass with Jacobians.  Without checkpointing it also keeps the policy's activations.
     rc = run_forward(c, true, !ckpt, true, theta, goals, states);
     if (rc != BAGEL_OK) return rc;

@@ -171,7 +171,8 @@ hipError_t bagel_launch_policy_forward(bagel_ctx *ctx, int slot, const float *th
 // next_slot < 0).  The caller swaps xbuf / xbuf_alt and part / part_alt afterwards.  The Jacobian sums
 // are not touched (bagel_launch_gp_step / bagel_launch_jac_reduce), except with direct: ctx->part
 // then holds final values [m][1+D][B], whose Jacobian goes to tape slot `slot` here if jac.
-hipError_t bagel_launch_step_tail(bagel_ctx *ctx, int t, int slot, int next_slot, bool jac, bool add_cost,
+// acts: the policy's activations are kept in their tape (otherwise nobody reads them).
+hipError_t bagel_launch_step_tail(bagel_ctx *ctx, int t, int slot, int next_slot, bool jac, bool acts, bool add_cost,
                                   bool write_tape_s, const float *theta, const float *goals,
                                   float *states_out, bool direct);
 // activation tape of steps t0 .. t1-1 (slots 0 .. t1-t0-1) rebuilt from the kept states
@@ -183,14 +184,15 @@ hipError_t bagel_launch_adam(bagel_ctx *ctx, float *theta, const float *grad, fl
                              double beta1, double beta2, double eps, double corr1, double corr2);
 
 // ---- policy16.hip (contexts with p16 != 0) -----------------------------------------------
-// sets p16 and pack16_floats from the widths and the batch
+// sets p16 and pack16_floats from the widths, the batch and the tape length
 void bagel_plan_policy(bagel_ctx *ctx);
 hipError_t bagel_launch_pack_theta16(bagel_ctx *ctx, const float *theta);
 // start of a rollout: state from s0, tapes, zero cost, policy of step 0 into tape slot 0
-hipError_t bagel_launch_start16(bagel_ctx *ctx, const float *s0, const float *goals, float *states_out, bool tape);
+// (acts: the policy's activations are kept in their tape)
+hipError_t bagel_launch_start16(bagel_ctx *ctx, const float *s0, const float *goals, float *states_out, bool tape, bool acts);
 // the same roles as bagel_launch_step_tail, _policy_replay and _backward_sweep
-hipError_t bagel_launch_step_tail16(bagel_ctx *ctx, int t, int slot, int next_slot, bool jac, bool write_tape_s, const float *goals,
-                                    float *states_out, bool direct);
+hipError_t bagel_launch_step_tail16(bagel_ctx *ctx, int t, int slot, int next_slot, bool jac, bool acts, bool write_tape_s,
+                                    const float *goals, float *states_out, bool direct);
 hipError_t bagel_launch_policy_replay16(bagel_ctx *ctx, int t0, int t1, const float *goals);
 hipError_t bagel_launch_backward_sweep16(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
 

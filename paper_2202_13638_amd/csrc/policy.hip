@@ -50,6 +50,7 @@ struct policy_args {
     float *h[3];          // tape slots of the layer inputs
     float *a_slot;        // [d_a][B]
     double *xbuf;         // [D][B]
+    int keep;             // 0: nobody reads the tapes of this step (forward pass alone, checkpointing)
 };
 
 // How the 8 waves share a layer with `rows` output rows and padded contraction length kp: wave =
@@ -307,7 +308,7 @@ __device__ __forceinline__ void layer_epilogue(const policy_args &a, size_t slot
 {
     const int nj = a.width[l + 1];
     const int b = b0 + c;
-    const bool live = b < a.B;
+    const bool live = b < a.B, keep = live && a.keep;
     const int jb = row_u + 4 * hf;
     const unsigned lane_off = ((unsigned)(4 * hf) * (unsigned)a.B + (unsigned)b) * 4u;
     const float4 bias4 = *reinterpret_cast<const float4 *>(bias + jb);      // entries past nj are not used
@@ -320,7 +321,7 @@ __device__ __forceinline__ void layer_epilogue(const policy_args &a, size_t slot
             const bool on = jb + e < nj;
             const float hv = on ? tanh_fast(z4[e] + bz[e]) : 0.0f;
             out[e] = hv;
-            if (live && on) *at_byte(hrow + (size_t)e * a.B, lane_off) = hv;
+            if (keep && on) *at_byte(hrow + (size_t)e * a.B, lane_off) = hv;
         }
         act4[(jb >> 2) * PL + c] = make_float4(out[0], out[1], out[2], out[3]);
     } else {
@@ -334,7 +335,7 @@ __device__ __forceinline__ void layer_epilogue(const policy_args &a, size_t slot
                     act_v = tanh_fast(z);
                     act_out = a.act_bound * act_v;
                 }
-                a.a_slot[(slot * nj + j) * a.B + b] = act_v;
+                if (a.keep) a.a_slot[(slot * nj + j) * a.B + b] = act_v;
                 if (write_x) a.xbuf[(size_t)(a.ds + j) * a.B + b] = (double)act_out;
             }
         }
@@ -606,7 +607,7 @@ __global__ __launch_bounds__(PW * 64) void step_tail_kernel(tail_args r, policy_
         if (r.do_policy) {
             act1[((row >> 2) * PL + bl) * 4 + (row & 3)] = hin;
             act1[(((row + 16) >> 2) * PL + bl) * 4 + (row & 3)] = 0.0f;
-            if (liveq && row < d_in) a.h[0][(size_t)row * B + bq] = hin;
+            if (liveq && a.keep && row < d_in) a.h[0][(size_t)row * B + bq] = hin;
         }
     }
     if (r.do_policy) stash_biases(a, bias_r, biasS);
@@ -1356,6 +1357,7 @@ policy_args make_pargs(const bagel_ctx *c, int slot)
     for (int l = 0; l < 3; ++l) a.h[l] = (l < c->n_layers) ? c->tape_h[l] + (size_t)slot * c->width[l] * B : nullptr;
     a.a_slot = c->tape_a + (size_t)slot * c->dm.d_a * B;
     a.xbuf = c->xbuf;
+    a.keep = 1;
     a.theta = nullptr;
     a.Wp = c->wpad_f;
     return a;
@@ -1384,7 +1386,7 @@ hipError_t bagel_launch_policy_forward(bagel_ctx *c, int slot, const float *thet
     return hipGetLastError();
 }
 
-hipError_t bagel_launch_step_tail(bagel_ctx *c, int t, int slot, int next_slot, bool jac, bool add_cost,
+hipError_t bagel_launch_step_tail(bagel_ctx *c, int t, int slot, int next_slot, bool jac, bool acts, bool add_cost,
                                   bool write_tape_s, const float *theta, const float *goals, float *states_out,
                                   bool direct)
 {
@@ -1408,6 +1410,7 @@ hipError_t bagel_launch_step_tail(bagel_ctx *c, int t, int slot, int next_slot, 
     policy_args a = make_pargs(c, has_next ? next_slot : 0);
     a.theta = theta;
     a.xbuf = c->xbuf_alt;              // the action of step t+1 joins s_{t+1}
+    a.keep = acts ? 1 : 0;
     hipLaunchKernelGGL(step_tail_kernel, dim3((c->dm.B + PL - 1) / PL), dim3(PW * 64), 0, c->stream, r, a);
     return hipGetLastError();
 }

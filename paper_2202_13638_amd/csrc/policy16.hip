@@ -52,7 +52,18 @@ struct policy16_args {
     const float *pack;                       // packed weights of this pass
     float *h[3];                             // slot 0 of the tapes of the layer inputs
     float *a_slot;                           // slot 0: [d_a][B]
+    int keep;                                // 0: nobody reads the tapes of this step (forward pass alone, checkpointing)
 };
+
+// The trajectories of a workgroup.  Workgroups go to the eight chiplets in turn; a line of a tape row holds two tiles of
+// 16 trajectories, so neighbouring tiles are given to workgroups of one chiplet: its L2 then sees whole lines.  With this
+// and without activations that nobody reads (policy16_args::keep), forward passes at 256-256, B = 4096 took 57.7 instead of 68.4
+// us per step; gradient calls at 64-64, B = 2048, 53.3 instead of 54.2.
+__device__ __forceinline__ int first_trajectory()
+{
+    const int n = gridDim.x, x = blockIdx.x & 7, q = n >> 3, r = n & 7;
+    return (x * q + min(x, r) + ((int)blockIdx.x >> 3)) * PL;
+}
 
 // Offsets inside the packed weights, in floats (see pack_theta16_kernel)
 struct pack16 {
@@ -235,6 +246,7 @@ __device__ __forceinline__ void policy16_layers(const policy16_args &a, const pa
 {
     constexpr int TT = NW * NT, AS = shape16<NW, NT>::AS;
     const int j = lane & 15, g = lane >> 4;
+    const bool keep = live && a.keep;
     f4v h[NT];
     float in[4];
 #pragma unroll
@@ -249,7 +261,7 @@ __device__ __forceinline__ void policy16_layers(const policy16_args &a, const pa
             for (int r = 0; r < 4; ++r) {
                 const int u = u0 + unit16(0, r);
                 h[t][r] = u < n ? tanh_fast(h[t][r] + bias[t][r]) : 0.0f;
-                if (live && u < n) dst[(size_t)unit16(0, r) * a.B] = h[t][r];
+                if (keep && u < n) dst[(size_t)unit16(0, r) * a.B] = h[t][r];
             }
             *reinterpret_cast<f4v *>(out + j * AS + 16 * (wave * NT + t) + 4 * g) = h[t];
         }
@@ -290,7 +302,7 @@ __device__ __forceinline__ void finish_action(const policy16_args &a, const pack
         out = a.act_bound * v;
     }
     if (live) {
-        a.a_slot[(slot * a.da + o) * a.B + b] = v;
+        if (a.keep) a.a_slot[(slot * a.da + o) * a.B + b] = v;
         if (x) x[(size_t)(a.ds + o) * a.B + b] = (double)out;
     }
 }
@@ -339,7 +351,7 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
     __shared__ double fS[TAIL_GROUPS][PL], sS[8][PL];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const int b0 = blockIdx.x * PL;
+    const int b0 = first_trajectory();
     const bool live = b0 + bl < a.B;         // (trajectory bl is also lane % 16: the same for the matrix phases)
     const int b = live ? b0 + bl : a.B - 1;
     const int B = a.B, ds = a.ds, d_in = a.width[0];
@@ -420,7 +432,7 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
             hin = g_in;
         }
         h0[bl * HS + row] = hin;
-        if (r.do_policy && live && row < d_in) a.h[0][(r.slot * d_in + row) * B + b] = hin;
+        if (r.do_policy && live && a.keep && row < d_in) a.h[0][(r.slot * d_in + row) * B + b] = hin;
     }
     if (r.s0 && row == 0 && live) r.lpt[b] = 0.0;
     __syncthreads();
@@ -457,8 +469,9 @@ __global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args 
     __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const bool live = blockIdx.x * PL + bl < a.B;
-    const int b = live ? blockIdx.x * PL + bl : a.B - 1;
+    const int b0 = first_trajectory();
+    const bool live = b0 + bl < a.B;
+    const int b = live ? b0 + bl : a.B - 1;
     const int B = a.B, ds = a.ds, d_in = a.width[0];
     forward_weights<NW, NT> f;
     load_weights(f, a.pack, p, wave, lane);
@@ -544,8 +557,9 @@ __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4, ug = (g & 1) << 2 | g >> 1;       // unit16(g, r) = ug + unit16(0, r)
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const bool live = blockIdx.x * PL + bl < a.B;
-    const int b = live ? blockIdx.x * PL + bl : a.B - 1;
+    const int b0 = first_trajectory();
+    const bool live = b0 + bl < a.B;
+    const int b = live ? b0 + bl : a.B - 1;
     const int last = a.nl - 1;
     const size_t B = a.B;
     const int n_top = a.width[last];
@@ -709,9 +723,10 @@ __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args 
     }
 }
 
-policy16_args make_policy(const bagel_ctx *c)
+policy16_args make_policy(const bagel_ctx *c, bool keep)
 {
     policy16_args a;
+    a.keep = keep ? 1 : 0;
     a.B = c->dm.B; a.nl = c->n_layers; a.ds = c->dm.d_s; a.da = c->dm.d_a;
     for (int i = 0; i < 4; ++i) a.width[i] = c->width[i];
     a.act_bound = c->dm.act_bound;
@@ -722,17 +737,17 @@ policy16_args make_policy(const bagel_ctx *c)
 }
 
 template <int NW, int NT>
-void launch_tail(bagel_ctx *c, const tail16_args &r)
+void launch_tail(bagel_ctx *c, const tail16_args &r, bool keep)
 {
-    hipLaunchKernelGGL((step_tail16_kernel<NW, NT>), dim3((c->dm.B + PL - 1) / PL), dim3(64 * NW), 0, c->stream, r, make_policy(c),
-                       make_pack(c));
+    hipLaunchKernelGGL((step_tail16_kernel<NW, NT>), dim3((c->dm.B + PL - 1) / PL), dim3(64 * NW), 0, c->stream, r,
+                       make_policy(c, keep), make_pack(c));
 }
 
-hipError_t launch_tail(bagel_ctx *c, const tail16_args &r)
+hipError_t launch_tail(bagel_ctx *c, const tail16_args &r, bool keep)
 {
-    if (c->p16 == 1) launch_tail<4, 1>(c, r);
-    else if (c->p16 == 2) launch_tail<8, 1>(c, r);
-    else launch_tail<8, 2>(c, r);
+    if (c->p16 == 1) launch_tail<4, 1>(c, r, keep);
+    else if (c->p16 == 2) launch_tail<8, 1>(c, r, keep);
+    else launch_tail<8, 2>(c, r, keep);
     return hipGetLastError();
 }
 
@@ -748,18 +763,21 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 
 }  // namespace
 
-// Which policy kernels the context uses: 0 those of policy.hip, 1 .. 3 the instances here.  Measured per step of a gradient
-// call, policy.hip / here (N = 2048, L = 1024 unless said): hidden 64-64 at B = 256 (N = 512) 22.4 / 13.5 us, B = 2048 46.5 / 37.6,
-// B = 8192 111 / 105; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102; 256-256 at B = 1024 55.5 / 43.3, B = 2048 66.9 / 57.4.
-// Wider policies on larger batches fill the chip with 32 trajectories per workgroup, and fetching the weights twice as
-// often costs what the shorter chain gives: forward passes at 128-128, B = 8192 (N = 4096) 104 / 119, at 256-256, B = 4096 with
-// 16 trajectories per sample 64.7 / 68.5.
+// Which policy kernels the context uses: 0 those of policy.hip, 1 .. 3 the instances here (3: not the backward sweep).
+// Measured per step of a gradient call, policy.hip / here (N = 2048, L = 1024 unless said): hidden 64-64 at B = 256 (N = 512)
+// 22.4 / 13.5 us, B = 2048 46.5 / 37.6, B = 8192 111 / 105; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102, at B = 8192
+// 188 / 183; 256-256 at B = 1024 55.6 / 48.0, B = 2048 67.1 / 61.0 (checkpointed 71.5 / 66.9), B = 4096 (N = 4096) 131.7 /
+// 128.4, forward pass with 16 trajectories per sample there 64.0 / 57.7.  Wider policies on larger batches fill the chip with
+// 32 trajectories per workgroup, and fetching the weights twice as often costs what the shorter chain gives: forward and
+// backward pass at 256-256, B = 8192 (N = 8192) 580 / 601, checkpointed (N = 4096) 244 / 260, and already at B = 4096
+// checkpointed 64.2 / 64.6 ms a call of 500 steps.
 void bagel_plan_policy(bagel_ctx *c)
 {
     int w = 0;
     for (int l = 1; l < c->n_layers; ++l) w = c->width[l] > w ? c->width[l] : w;
     c->p16 = w <= 64 ? 1 : (w <= 128 ? 2 : 3);
-    if ((c->p16 == 3 && c->dm.B > 2048) || (c->p16 == 2 && c->dm.B > 4096)) c->p16 = 0;
+    const int most = c->p16 == 3 ? (c->T_tape < c->dm.H ? 2048 : 4096) : 8192;
+    if (c->p16 != 1 && c->dm.B > most) c->p16 = 0;
     c->pack16_floats = c->p16 ? make_pack(c).total() : 0;
 }
 
@@ -772,7 +790,7 @@ hipError_t bagel_launch_pack_theta16(bagel_ctx *c, const float *theta)
     return hipGetLastError();
 }
 
-hipError_t bagel_launch_start16(bagel_ctx *c, const float *s0, const float *goals, float *states_out, bool tape)
+hipError_t bagel_launch_start16(bagel_ctx *c, const float *s0, const float *goals, float *states_out, bool tape, bool acts)
 {
     tail16_args r = {};
     r.D = c->D; r.M = c->M; r.dg = c->dm.d_g;
@@ -781,11 +799,11 @@ hipError_t bagel_launch_start16(bagel_ctx *c, const float *s0, const float *goal
     r.tape_s_next = tape ? c->tape_s : nullptr;
     r.states_out_next = states_out;
     r.goals_next = goals; r.s0 = s0;
-    return launch_tail(c, r);
+    return launch_tail(c, r, acts);
 }
 
-hipError_t bagel_launch_step_tail16(bagel_ctx *c, int t, int slot, int next_slot, bool jac, bool write_tape_s, const float *goals,
-                                    float *states_out, bool direct)
+hipError_t bagel_launch_step_tail16(bagel_ctx *c, int t, int slot, int next_slot, bool jac, bool acts, bool write_tape_s,
+                                    const float *goals, float *states_out, bool direct)
 {
     const size_t B = c->dm.B;
     const bool has_next = t + 1 < c->dm.H && next_slot >= 0;
@@ -804,7 +822,7 @@ hipError_t bagel_launch_step_tail16(bagel_ctx *c, int t, int slot, int next_slot
     r.goals_next = has_next ? goals + (size_t)(t + 1) * B * c->dm.d_g : nullptr;
     r.jdst = (jac && direct) ? c->tape_J + (size_t)slot * c->M * c->D * B : nullptr;
     r.slot = has_next ? (size_t)next_slot : 0;
-    return launch_tail(c, r);
+    return launch_tail(c, r, acts);
 }
 
 hipError_t bagel_launch_policy_replay16(bagel_ctx *c, int t0, int t1, const float *goals)
@@ -812,7 +830,7 @@ hipError_t bagel_launch_policy_replay16(bagel_ctx *c, int t0, int t1, const floa
     replay16_args r;
     r.tape_s = c->tape_s; r.goals = goals; r.t0 = t0; r.dg = c->dm.d_g; r.n_slots = t1 - t0; r.per = 5;
     const dim3 grid((c->dm.B + PL - 1) / PL, (t1 - t0 + r.per - 1) / r.per);
-    const policy16_args a = make_policy(c);
+    const policy16_args a = make_policy(c, true);
     const pack16 p = make_pack(c);
     if (c->p16 == 1) hipLaunchKernelGGL((policy_replay16_kernel<4, 1>), grid, dim3(256), 0, c->stream, r, a, p);
     else if (c->p16 == 2) hipLaunchKernelGGL((policy_replay16_kernel<8, 1>), grid, dim3(512), 0, c->stream, r, a, p);
