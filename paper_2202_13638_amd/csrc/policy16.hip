@@ -532,8 +532,11 @@ __device__ __forceinline__ double add_cost_gradient16(const sweep16_args &a, dou
     double r[DG], e = 0.0;
 #pragma unroll
     for (int j = 0; j < DG; ++j) {
-        r[j] = j < a.dg ? (double)sv[j] - (double)gv[j] : 0.0;
-        e += (double)a.q[j] * r[j] * r[j];                                 // (absent components add +0.0)
+        r[j] = 0.0;
+        if (j < a.dg) {                                                    // (what q holds past d_g is the caller's: not used)
+            r[j] = (double)sv[j] - (double)gv[j];
+            e += (double)a.q[j] * r[j] * r[j];
+        }
     }
     double factor = 2.0;
     if (a.cost_kind == 1) {

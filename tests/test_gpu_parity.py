@@ -481,6 +481,30 @@ def test_repeated_calls_are_bitwise_reproducible():
         np.testing.assert_array_equal(a[k], b[k])
 
 
+@pytest.mark.parametrize("hidden", [(16,), (100, 37), (200,)])
+@pytest.mark.parametrize("d_g", [1, 3])
+@pytest.mark.parametrize("ckpt", [0, 3])
+def test_cost_weights_past_the_goal_dimension_are_not_used(hidden, d_g, ckpt, monkeypatch):
+    """q has one entry per goal component; what a caller leaves in the rest of the array must not reach any output."""
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("qpad", 18, 4, 1, d_g, 50, 40, 40, 7, hidden, 1.0, "sinusoid", "steps", ckpt, 0.5, 1e-3)
+    inp = synth.make_inputs(cfg)
+    v = np.random.default_rng(7).standard_normal((cfg.B, cfg.M, cfg.N)).astype(np.float32)
+    plain = harness.gpu_rollout(cfg, inp, v, cost_kind=1, sigma_r=0.7)
+    make = binding.dims_from_config
+    for rest in (float("nan"), float("inf")):
+        def with_rest(*args, **kw):
+            dims = make(*args, **kw)
+            for j in range(dims.d_g, 8):
+                dims.q[j] = rest
+            return dims
+        monkeypatch.setattr(binding, "dims_from_config", with_rest)
+        got = harness.gpu_rollout(cfg, inp, v, cost_kind=1, sigma_r=0.7)
+        for k in ("states", "loss_per_traj", "grad_theta", "grad_s0"):
+            assert np.isfinite(plain[k]).all()
+            np.testing.assert_array_equal(got[k], plain[k])
+
+
 # ------------------------------------------------------------------ prepare
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("name,kw", [("tiny", {}), ("small", dict(B=48)), ("ragged", {}), ("one-point", {}),
