@@ -517,7 +517,7 @@ struct sweep16_args {
     float *grad_s0;
 };
 
-// MM, DG: at least M and d_g (rounded up to 4 or 8, 2 or 8)
+// MM, DG: at least M and d_g (rounded up to 4 or 8, 2 or 8); ALL: M = MM
 template <int NT, int MM, int DG>
 struct sweep16_tape {
     float J[MM], th;                         // rows d < D: J[m][d]; actions: tanh output of the bounded action
@@ -547,7 +547,7 @@ __device__ __forceinline__ double add_cost_gradient16(const sweep16_args &a, dou
     return lam;
 }
 
-template <int NW, int NT, int MM, int DG>
+template <int NW, int NT, int MM, int DG, bool ALL>
 __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args a, pack16 p)
 {
     using S = shape16<NW, NT>;
@@ -647,7 +647,13 @@ __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args 
         if (row < a.D) {
             double u = 0.0;
 #pragma unroll
-            for (int m = 0; m < MM; ++m) u += (double)s.J[m] * lamS[m][bl];
+            for (int m = 0; m < MM; ++m) {
+                float Jm = s.J[m];
+                // past M: a duplicate, which may be infinite.  (An instance without this where M = MM: in all of them it made
+                // a gradient call at 64-64, B = 256 take 1387 us instead of 1376.)
+                if (!ALL) Jm = __int_as_float(__float_as_int(Jm) & ((m - a.M) >> 31));
+                u += (double)Jm * lamS[m][bl];
+            }
             if (row < a.ds) {
                 us = u;
             } else {
@@ -756,9 +762,13 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 {
     const dim3 grid((c->dm.B + PL - 1) / PL), block(64 * NW);
     const pack16 p = make_pack(c);
-    if (a.M <= 4 && a.dg <= 2) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 4, 2>), grid, block, 0, c->stream, a, p);
-    else if (a.dg <= 2) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 8, 2>), grid, block, 0, c->stream, a, p);
-    else hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, 8, 8>), grid, block, 0, c->stream, a, p);
+#define SWEEP(mm, dgm)                                                                                                       \
+    if (a.M == mm) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, mm, dgm, true>), grid, block, 0, c->stream, a, p);     \
+    else hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, mm, dgm, false>), grid, block, 0, c->stream, a, p)
+    if (a.M <= 4 && a.dg <= 2) { SWEEP(4, 2); }
+    else if (a.dg <= 2) { SWEEP(8, 2); }
+    else { SWEEP(8, 8); }
+#undef SWEEP
 }
 
 }  // namespace

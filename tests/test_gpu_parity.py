@@ -505,6 +505,41 @@ def test_cost_weights_past_the_goal_dimension_are_not_used(hidden, d_g, ckpt, mo
             np.testing.assert_array_equal(got[k], plain[k])
 
 
+@pytest.mark.parametrize("d_s,d_g", [(3, 1), (6, 2), (5, 3)])
+@pytest.mark.parametrize("hidden", [(16,), (100, 37), (200,)])
+def test_infinite_jacobian_entry_of_the_last_output(d_s, d_g, hidden):
+    """A model so steep that d f_m / d x_0 of the last output m overflows float32 while the state stays finite: with one
+    step, x_0 off the only training point, zero actions and nothing else that depends on x, the adjoint of s_0 is lam_m
+    times that infinity in component 0, zero in the components no state depends on, and lam_m alone in component m."""
+    import torch
+    from paper_2202_13638_amd import binding
+    B, m, step = 40, d_s - 1, 1e-4
+    dims = binding.make_dims(d_s=d_s, d_a=1, d_g=d_g, N=1, L=1, S=B, B=B, H=1, hidden=hidden, tracked=[m] + list(range(d_g - 1)))
+    ctx = binding.Bagel(dims)
+    X = torch.zeros((1, d_s + 1), device="cuda")
+    X[0, 0] = step
+    ell = torch.ones((d_s, d_s + 1), device="cuda")
+    ell[:, 0] = step
+    v = torch.zeros((B, d_s, 1), device="cuda")
+    v[:, m] = 1e35                                        # J = 1e35 exp(-1/2) / 1e-4 = 6e38
+    one = torch.ones(d_s, device="cuda")
+    ctx.bagel_set_samples(X, ell, one, torch.zeros((d_s, 1, d_s + 1), device="cuda"), torch.zeros((d_s, 1), device="cuda"),
+                          torch.zeros((B, d_s, 1), device="cuda"), v)
+    states = torch.full((2, B, d_s), float("nan"), device="cuda")
+    gs0 = torch.full((B, d_s), float("nan"), device="cuda")
+    loss, gth = torch.zeros(1, device="cuda"), torch.zeros(ctx.P, device="cuda")
+    ctx.bagel_rollout_loss_grad(torch.zeros(ctx.P, device="cuda"), torch.zeros((B, d_s), device="cuda"),
+                                torch.zeros((1, B, d_g), device="cuda"), loss, gth, None, states, gs0)
+    torch.cuda.synchronize()
+    ctx.close()
+    s1 = states[1, :, m].cpu().numpy()
+    np.testing.assert_allclose(s1, 1e35 * np.exp(-0.5), rtol=1e-6)
+    want = np.zeros((B, d_s))
+    want[:, m] = 2.0 * s1 / B
+    want[:, 0] = np.inf
+    np.testing.assert_allclose(gs0.cpu().numpy(), want, rtol=1e-6)
+
+
 # ------------------------------------------------------------------ prepare
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("name,kw", [("tiny", {}), ("small", dict(B=48)), ("ragged", {}), ("one-point", {}),
