@@ -55,6 +55,7 @@
  *   BAGEL_TARGET_WGS       number of workgroups the default unit sizes aim for (default 4096)
  *   BAGEL_EXP_TABLE        1: always the general form of the kernel-row loop, 2: always the table form,
  *                          unset: by launch size
+ *   BAGEL_POLICY_TILE      16 or 32: trajectories per workgroup of the policy kernels; unset: by widths and batch
  *   BAGEL_KSPLIT           split of the weight-gradient contraction (default 256)
  */
 #ifndef BAGEL_H

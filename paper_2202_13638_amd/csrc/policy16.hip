@@ -787,7 +787,8 @@ void bagel_plan_policy(bagel_ctx *c)
     for (int l = 1; l < c->n_layers; ++l) w = c->width[l] > w ? c->width[l] : w;
     c->p16 = w <= 64 ? 1 : (w <= 128 ? 2 : 3);
     const int most = c->p16 == 3 ? (c->T_tape < c->dm.H ? 2048 : 4096) : 8192;
-    if (c->p16 != 1 && c->dm.B > most) c->p16 = 0;
+    const int tile = bagel_env_int("BAGEL_POLICY_TILE", 0);                // 16 or 32: always that one, otherwise by size
+    if (tile == 32 || (tile != 16 && c->p16 != 1 && c->dm.B > most)) c->p16 = 0;
     c->pack16_floats = c->p16 ? make_pack(c).total() : 0;
 }
 

@@ -382,6 +382,28 @@ def test_policy_kernels_agree_bit_for_bit(hidden, B, ckpt, monkeypatch):
     np.testing.assert_array_equal(one["grad_s0"], 2.0 * both["grad_s0"][:B])
 
 
+@pytest.mark.parametrize("hidden", [(16,), (64, 64), (8, 8), (33, 5), (100, 37), (128, 128), (65,), (200, 136), (256, 256), (129,)])
+@pytest.mark.parametrize("sh", [dict(d_s=4, d_a=1, d_g=1), dict(d_s=6, d_a=2, d_g=2), dict(d_s=2, d_a=3, d_g=2), dict(d_s=8, d_a=8, d_g=8)])
+def test_policy_kernels_of_both_widths_agree_and_repeat(hidden, sh, monkeypatch):
+    """Every instance of the policy kernels: 16 and 32 trajectories per workgroup give the same bits in every output, the
+    weight gradient included, and so does a second call, with whole and with ragged tiles, with and without checkpointing."""
+    monkeypatch.setenv("BAGEL_EXP_TABLE", "1")
+    for B, ckpt in [(96, 0), (96, 3), (71, 0), (71, 3)]:
+        kind = dict(cost_kind=1, sigma_r=0.7) if B == 71 else {}
+        cfg = synth.Config("p1632", 19, sh["d_s"], sh["d_a"], sh["d_g"], 40, 24, B, 7, hidden, 0.7 if ckpt else 0.0, "sinusoid",
+                           "steps", ckpt, 0.05, 1e-3)
+        inp = synth.make_inputs(cfg)
+        v = np.random.default_rng(3).standard_normal((B, cfg.M, cfg.N)).astype(np.float32)
+        runs = []
+        for tile in ("16", "16", "32", "32"):
+            monkeypatch.setenv("BAGEL_POLICY_TILE", tile)
+            runs.append(harness.gpu_rollout(cfg, inp, v, **kind))
+        for k in ("states", "loss_per_traj", "grad_theta", "grad_s0"):
+            assert np.isfinite(runs[0][k]).all()
+            for r in runs[1:]:
+                np.testing.assert_array_equal(r[k], runs[0][k], err_msg=f"B={B} ckpt={ckpt} {k}")
+
+
 def test_rollout_with_table_exp2(monkeypatch):
     """The exp2 form of large launches, forced at a size the oracle finishes in seconds."""
     monkeypatch.setenv("BAGEL_EXP_TABLE", EXP2_FORMS["table"])
