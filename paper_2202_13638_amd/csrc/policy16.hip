@@ -775,7 +775,8 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 
 // Which policy kernels the context uses: 0 those of policy.hip, 1 .. 3 the instances here (3: not the backward sweep).
 // Measured per step of a gradient call, policy.hip / here (N = 2048, L = 1024 unless said): hidden 64-64 at B = 256 (N = 512)
-// 22.4 / 13.5 us, B = 2048 46.5 / 37.6, B = 8192 111 / 105; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102, at B = 8192
+// 22.4 / 13.5 us, B = 2048 46.5 / 37.6, B = 8192 109 / 100, B = 32768 406 / 377, B = 65536 (16 to a sample) 678 / 614; one layer of
+// 16 at B = 8192 100 / 96, B = 65536 630 / 583; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102, at B = 8192
 // 188 / 183; 256-256 at B = 1024 55.6 / 48.0, B = 2048 67.1 / 61.0 (checkpointed 71.5 / 66.9), B = 4096 (N = 4096) 131.7 /
 // 128.4, forward pass with 16 trajectories per sample there 64.0 / 57.7.  Wider policies on larger batches fill the chip with
 // 32 trajectories per workgroup, and fetching the weights twice as often costs what the shorter chain gives: forward and
