@@ -188,7 +188,8 @@ int bagel_rollout_loss_grad(bagel_ctx *ctx, const float *theta, const float *s0,
  *
  * bagel_prepare_posterior: alpha_m = K_hat_m^-1 y_m and K_hat_m^-1 for every output, float64, kept in
  * the context (the first call allocates 8 M (Np^2 + Np B (1 + (1+D)/32)) bytes, Np and B rounded up to 64:
- * K_hat^-1, the kernel rows of a step and the per-tile sums of its moments).
+ * K_hat^-1, the kernel rows of a step and the per-tile sums of its moments) and needs two Np x Np float64 matrices per
+ * output of the set-up work space.
  * Arrays as in bagel_prepare_samples.  Synchronises the stream.  Errors: EINVAL, ENOMEM, ENOTPD, EHIP.
  *
  * bagel_posterior_rollout_loss / _grad: as bagel_rollout_loss / bagel_rollout_loss_grad, with
@@ -240,7 +241,7 @@ int bagel_optimize(bagel_ctx *ctx, float *theta, float *adam_m, float *adam_v, c
  * with respect to the logarithms of the hyper-parameters of eq. (4):
  *   log_hyp[M][D+2] = (log l_1 .. log l_D, log alpha^2, log sigma_n^2) per output.
  * X[N][D], y[M][N] as in bagel_prepare_samples; lml[M]; grad[M][D+2] or NULL.  Float64 inside.
- * Set-up work: needs four Np x Np float64 matrices per output (set-up work space, see bagel_create; the outputs
+ * Set-up work: needs three Np x Np float64 matrices per output (set-up work space, see bagel_create; the outputs
  * in several passes if the memory for all cannot be had) and synchronises the stream.
  * Errors: EINVAL, ENOMEM, ENOTPD, EHIP.
  *

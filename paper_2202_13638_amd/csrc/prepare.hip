@@ -13,7 +13,8 @@
 //   K  the upper triangle of K_hat (whole 64 x 64 blocks), updated in place while it is factored;
 //   U  the factor, K_hat = U^T U (L = U^T), block rows written as they are finished; with `mirror` also L below;
 //   W  L^-1 (lower), V = W^T = U^-1 (upper): the 64 x 64 diagonal blocks come out of the factorisation of the
-//      diagonal block, larger blocks from them level by level (triangular_inverse).
+//      diagonal block, larger blocks from them level by level (triangular_inverse).  Where whole inverses are formed V
+//      takes the place of K (inverse_bytes).
 // With U, V and W at hand every product has its contraction index as the row of both operands (f64_tile.h).
 //
 // Factorisation (struct solver): recursive halving with products as deep as half the range down to ranges of
@@ -1127,17 +1128,30 @@ done:
     return rc;
 }
 
-// K, U, V, W [Np][Np], diagonal and two vectors per output: the work space of an inverse
-static size_t inverse_bytes(int Np) { return 4 * arena_round((size_t)Np * Np * 8) + 3 * arena_round((size_t)Np * 8); }
+// The work space of an inverse: U, W and, unless it has a place elsewhere, K [Np][Np], diagonal and two vectors per output.
+// V takes the place of K, block by block: V's diagonal block k is written when K's is done with (chol_step_kernel keeps the
+// next one in LDS, the products of the recursion touch later ranges only), its blocks above the diagonal after the
+// factorisation, and T (inverse_level_kernel) has the blocks below.
+static size_t inverse_bytes(int Np, bool with_K)
+{
+    return (with_K ? 3 : 2) * arena_round((size_t)Np * Np * 8) + 3 * arena_round((size_t)Np * 8);
+}
 
-static void inverse_carve(solver &s, arena_cursor &cur, int n_out, int Np, double **vec)
+// K, and with it V, of the outputs worked on
+static void inverse_place(solver &s, double *K)
+{
+    s.f.K = K;
+    s.f.sK = (size_t)s.f.Np * s.f.Np;
+    s.f.V = tri_matrix{K, (size_t)s.f.Np, s.f.sK};
+}
+
+static void inverse_carve(solver &s, arena_cursor &cur, int n_out, int Np, bool with_K, double **vec)
 {
     const size_t n = (size_t)n_out, nK = (size_t)Np * Np;
     s.nb = Np / NB;
     s.f.Np = Np;
-    s.f.K = cur.take<double>(n * nK); s.f.sK = nK;
+    if (with_K) inverse_place(s, cur.take<double>(n * nK));
     s.f.U = cur.take<double>(n * nK); s.f.sU = nK;
-    s.f.V = tri_matrix{cur.take<double>(n * nK), (size_t)Np, nK};
     s.f.W = tri_matrix{cur.take<double>(n * nK), (size_t)Np, nK};
     s.f.diag = cur.take<double>(n * Np);
     *vec = cur.take<double>(2 * n * Np);
@@ -1170,18 +1184,19 @@ int bagel_prepare_posterior_impl(bagel_ctx *c, const float *X, const float *y, c
     int *flag = nullptr;
     double *vec = nullptr;
     float h_sf2[BAGEL_MAX_STATE];
-    P_HIP(setup_reserve(c, inverse_bytes(Np), arena_round(BAGEL_MAX_STATE * sizeof(int)), &sc, &n_out));
+    P_HIP(setup_reserve(c, inverse_bytes(Np, false), arena_round(BAGEL_MAX_STATE * sizeof(int)), &sc, &n_out));
     {
         arena_cursor cur{sc->arena};
         flag = cur.take<int>(BAGEL_MAX_STATE);
         s.st = st;
-        inverse_carve(s, cur, n_out, Np, &vec);
+        inverse_carve(s, cur, n_out, Np, false, &vec);
     }
     P_HIP(hipMemcpyAsync(h_sf2, sf2, M * sizeof(float), hipMemcpyDeviceToHost, st));
     hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, st, flag, BAGEL_MAX_STATE);
     for (int m0 = 0; m0 < M; m0 += n_out) {
         s.outputs = M - m0 < n_out ? M - m0 : n_out;
         s.f.flag = flag + m0;
+        inverse_place(s, c->post_Kinv + (size_t)m0 * Np * Np);     // (K and V are done with when K_hat^-1 is written)
         build_and_factor(s, X, h, N, D, m0);
         s.triangular_inverse(s.nb);
         inverse_vectors(s, y, N, m0, vec, c->post_alpha + (size_t)m0 * Np);
@@ -1235,14 +1250,14 @@ int bagel_hyper_impl(bagel_ctx *c, const float *X, const float *y, float *log_hy
     int *flag = nullptr;
     float *gneg = nullptr;
     double *vec = nullptr, *partial = nullptr;
-    P_HIP(setup_reserve(c, inverse_bytes(Np) + arena_round((size_t)tiles * H2 * 8),
+    P_HIP(setup_reserve(c, inverse_bytes(Np, true) + arena_round((size_t)tiles * H2 * 8),
                         arena_round(BAGEL_MAX_STATE * sizeof(int)) + arena_round((size_t)M * H2 * sizeof(float)), &sc, &n_out));
     {
         arena_cursor cur{sc->arena};
         flag = cur.take<int>(BAGEL_MAX_STATE);
         gneg = cur.take<float>((size_t)M * H2);
         s.st = st;
-        inverse_carve(s, cur, n_out, Np, &vec);
+        inverse_carve(s, cur, n_out, Np, true, &vec);
         partial = cur.take<double>((size_t)n_out * tiles * H2);
     }
     hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, st, flag, BAGEL_MAX_STATE);

@@ -617,6 +617,27 @@ def test_prepare_blocking(N, L, S):
     assert np.abs(got["v"] - v64).max() <= 5e-7 * np.abs(v64).max()
 
 
+def test_setup_work_space_of_an_inverse():
+    """Marginal likelihood: three Np x Np float64 matrices per output; posterior cache: two, beside K_hat^-1 itself.  (Vectors,
+    sums and alignment come to less than a tenth of a matrix at this size.)"""
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("ws", 16, 4, 1, 1, 1000, 16, 4, 2, (4,), 0.0, "sinusoid", "const", 0, 0.6, 1e-3)
+    inp = synth.make_inputs(cfg)
+    g = harness.to_gpu(inp)
+    import torch
+    lh = torch.log(torch.cat([g["lengthscale"], g["signal_var"][:, None], g["noise_var"][:, None]], 1)).contiguous()
+    matrix = 8 * 1024 * 1024 * cfg.M
+    for call, matrices in (("hyper", 3), ("posterior", 3)):        # the second: two, and K_hat^-1
+        ctx = binding.Bagel(binding.dims_from_config(cfg))
+        before = ctx.workspace_bytes()
+        if call == "hyper":
+            ctx.bagel_hyper_lml_grad(g["X"], g["y"], lh, torch.empty(cfg.M, device="cuda"))
+        else:
+            ctx.bagel_prepare_posterior(g["X"], g["y"], g["lengthscale"], g["signal_var"], g["noise_var"])
+        assert matrices * matrix < ctx.workspace_bytes() - before < (matrices + 0.2) * matrix, call
+        ctx.close()
+
+
 def test_setup_work_space_is_made_once_and_kept():
     """The set-up calls share one work space: a second pass over them allocates nothing and gives the same bits."""
     import torch
