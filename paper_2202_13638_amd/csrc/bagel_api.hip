@@ -129,6 +129,7 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     c->T_tape = (K > 0 && K < H) ? K : H;
     bagel_plan_policy(c);
     c->ksplit = bagel_env_int("BAGEL_KSPLIT", 256);
+    c->setup_outputs = bagel_env_int("BAGEL_SETUP_OUTPUTS", BAGEL_MAX_STATE);
     int wf_total = 0, wb_total = 0;
     for (int l = 0; l < c->n_layers; ++l) {
         const int no = c->width[l + 1], ni = c->width[l];

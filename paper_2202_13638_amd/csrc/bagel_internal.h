@@ -90,6 +90,7 @@ struct bagel_ctx {
 
     // ---- set-up calls (prepare.hip): float64 work space, made by the first of them ----------------
     void *setup;
+    int setup_outputs;           // most outputs worked on at once
 
     // ---- measurement hooks -------------------------------------------------------------------
     int prof_every, prof_seen, prof_used;

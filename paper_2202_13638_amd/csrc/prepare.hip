@@ -945,7 +945,7 @@ constexpr size_t ARENA_ALIGN = 256;
 size_t arena_round(size_t bytes) { return (bytes + ARENA_ALIGN - 1) / ARENA_ALIGN * ARENA_ALIGN; }
 
 // At least shared_bytes + n * output_bytes of device memory, n = number of outputs worked on by one launch: all
-// of them, fewer if the memory for that many cannot be had (one must fit).  The stream is idle when the arena is
+// of them (at most setup_outputs), fewer if the memory for that many cannot be had (one must fit).  The stream is idle when the arena is
 // replaced: every set-up call ends with a synchronisation.
 hipError_t setup_reserve(bagel_ctx *c, size_t output_bytes, size_t shared_bytes, setup_scratch **out, int *n_outputs)
 {
@@ -964,7 +964,7 @@ hipError_t setup_reserve(bagel_ctx *c, size_t output_bytes, size_t shared_bytes,
     }
     output_bytes = arena_round(output_bytes);
     shared_bytes = arena_round(shared_bytes);
-    const size_t M = (size_t)c->M;
+    const size_t M = (size_t)(c->M < c->setup_outputs ? c->M : c->setup_outputs);
     auto fit = [&]() { return sc->arena_bytes < shared_bytes ? (size_t)0 : (sc->arena_bytes - shared_bytes) / output_bytes; };
     if (fit() < M && !(sc->limited && fit() >= 1)) {
         (void)hipStreamSynchronize(c->stream);

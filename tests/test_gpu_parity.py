@@ -638,6 +638,53 @@ def test_setup_work_space_of_an_inverse():
         ctx.close()
 
 
+@pytest.mark.parametrize("at_once", [1, 2, 4])
+def test_setup_calls_in_several_passes(at_once, monkeypatch):
+    """With work space for fewer outputs than there are (five here) the set-up calls take them in several passes, the last
+    one possibly smaller: the same bits as all at once, from a smaller work space, and a failing output is named as such."""
+    import torch
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("sp", 16, 5, 1, 1, 300, 70, 66, 3, (8,), 1.0, "sinusoid", "steps", 0, 0.6, 1e-3)
+    inp = synth.make_inputs(cfg)
+    g = harness.to_gpu(inp)
+    xi = torch.from_numpy(np.random.default_rng(1).standard_normal((cfg.H, cfg.B, cfg.M)).astype(np.float32)).cuda()
+    lh = torch.log(torch.cat([g["lengthscale"], g["signal_var"][:, None], g["noise_var"][:, None]], 1)).contiguous()
+
+    def run():
+        ctx = binding.Bagel(binding.dims_from_config(cfg))
+        v = torch.empty((cfg.B, cfg.M, cfg.N), device="cuda")
+        ctx.bagel_prepare_samples(g["X"], g["y"], g["lengthscale"], g["signal_var"], g["noise_var"], g["omega"], g["phase"],
+                                  g["w"], g["eps"], v)
+        lml, grad = torch.empty(cfg.M, device="cuda"), torch.empty((cfg.M, cfg.D + 2), device="cuda")
+        ctx.bagel_hyper_lml_grad(g["X"], g["y"], lh, lml, grad)
+        fit, hist = lh.clone(), torch.empty((2, cfg.M), device="cuda")
+        ctx.bagel_hyper_fit(g["X"], g["y"], fit, torch.zeros_like(lh), torch.zeros_like(lh), 2, hist)
+        held = ctx.workspace_bytes()
+        ctx.bagel_prepare_posterior(g["X"], g["y"], g["lengthscale"], g["signal_var"], g["noise_var"])
+        loss, gth = torch.empty(1, device="cuda"), torch.empty(ctx.P, device="cuda")
+        states = torch.empty((cfg.H + 1, cfg.B, cfg.d_s), device="cuda")
+        ctx.bagel_posterior_rollout_loss_grad(g["theta"], g["s0"], g["goals"], xi, loss, gth, None, states)
+        twice = g["X"].clone()
+        twice[1] = twice[0]                                # K of the fourth output is singular: two equal points, no noise
+        noise = g["noise_var"].clone()
+        noise[3] = 0.0
+        with pytest.raises(binding.BagelError) as err:
+            ctx.bagel_prepare_samples(twice, g["y"], g["lengthscale"], g["signal_var"], noise, g["omega"], g["phase"], g["w"],
+                                      g["eps"], None)
+        assert err.value.code == binding.ENOTPD and "output 3" in str(err.value)
+        torch.cuda.synchronize()
+        ctx.close()
+        return [t.cpu().numpy() for t in (v, lml, grad, fit, hist, gth, states)], held
+
+    whole, held_whole = run()
+    monkeypatch.setenv("BAGEL_SETUP_OUTPUTS", str(at_once))
+    parts, held_parts = run()
+    assert all(np.isfinite(t).all() for t in whole)
+    for a, b in zip(whole, parts):
+        np.testing.assert_array_equal(a, b)
+    assert held_parts < held_whole
+
+
 def test_setup_work_space_is_made_once_and_kept():
     """The set-up calls share one work space: a second pass over them allocates nothing and gives the same bits."""
     import torch
