@@ -627,19 +627,31 @@ extern "C" int bagel_prepare_posterior(bagel_ctx *c, const float *X, const float
     if (!c->post_Kinv) {
         c->post_Np = (c->dm.N + 63) / 64 * 64;
         const size_t Np = (size_t)c->post_Np, B = (size_t)c->dm.B, M = (size_t)c->M;
-        hipError_t e = dev_alloc(c, &c->post_alpha, M * Np);
-        if (e == hipSuccess) e = dev_alloc(c, &c->post_Kinv, M * Np * Np);
-        if (e == hipSuccess) e = dev_alloc(c, &c->post_Kx, M * Np * ((B + 63) / 64 * 64));
-        if (e == hipSuccess) e = dev_alloc(c, &c->post_sums, M * (Np / 64) * 2 * (1 + (size_t)c->D) * B);
-        if (e != hipSuccess) {
+        auto allocate = [&]() {
+            const int64_t bytes = c->bytes;
+            hipError_t e = dev_alloc(c, &c->post_alpha, M * Np);
+            if (e == hipSuccess) e = dev_alloc(c, &c->post_Kinv, M * Np * Np);
+            if (e == hipSuccess) e = dev_alloc(c, &c->post_Kx, M * Np * ((B + 63) / 64 * 64));
+            if (e == hipSuccess) e = dev_alloc(c, &c->post_sums, M * (Np / 64) * 2 * (1 + (size_t)c->D) * B);
+            if (e == hipSuccess) return true;
             void *ptrs[] = {c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
             for (void *p : ptrs)
                 if (p) (void)hipFree(p);
             c->post_alpha = c->post_Kinv = c->post_Kx = c->post_sums = nullptr;
+            c->bytes = bytes;
             (void)hipGetLastError();
+            return false;
+        };
+        bool done = allocate();
+        if (!done && c->setup) {
+            // an earlier set-up call's work space may be what is in the way: give it back (nothing uses it after such a call's
+            // final synchronisation) and let the call below make its own
+            bagel_release_setup(c);
+            done = allocate();
+        }
+        if (!done)
             BAGEL_FAIL(c, BAGEL_ENOMEM, "bagel_prepare_posterior: device allocation failed (%zu bytes for K_hat^-1)",
                        M * Np * Np * sizeof(double));
-        }
     }
     // the scaled training inputs the kernel rows are computed from (the feature tables are left alone)
     BAGEL_HIP(c, bagel_launch_install(c, X, lengthscale, signal_var, nullptr, nullptr, nullptr, nullptr, nullptr));

@@ -685,6 +685,39 @@ def test_setup_calls_in_several_passes(at_once, monkeypatch):
     assert held_parts < held_whole
 
 
+def test_posterior_cache_when_the_kept_work_space_leaves_no_room():
+    """The work space that an earlier set-up call left in the context must not keep the posterior cache from being allocated:
+    with less memory free than the cache needs, but enough once the work space is given back, the call succeeds."""
+    import torch
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("pr", 16, 2, 1, 1, 8192, 64, 64, 2, (4,), 0.0, "sinusoid", "const", 0, 0.6, 1e-3)
+    inp = synth.make_inputs(cfg)
+    g = harness.to_gpu(inp)
+    matrix = 8 * cfg.N * cfg.N
+    ctx = binding.Bagel(binding.dims_from_config(cfg))
+    lh = torch.log(torch.cat([g["lengthscale"], g["signal_var"][:, None], g["noise_var"][:, None]], 1)).contiguous()
+    lml = torch.empty(cfg.M, device="cuda")
+    ctx.bagel_hyper_lml_grad(g["X"], g["y"], lh, lml)                          # work space: six matrices
+    torch.cuda.synchronize()
+    before = ctx.workspace_bytes()
+    torch.cuda.empty_cache()
+    free, fill = torch.cuda.mem_get_info()[0], []
+    while free > matrix * 3 // 2:                                              # leave one and a half; the cache needs two
+        take = min(free - matrix * 3 // 2, 32 << 30) // (2 << 20) * (2 << 20)
+        if take <= 0:
+            break
+        fill.append(torch.empty(take, dtype=torch.uint8, device="cuda"))
+        free = torch.cuda.mem_get_info()[0]
+    try:
+        ctx.bagel_prepare_posterior(g["X"], g["y"], g["lengthscale"], g["signal_var"], g["noise_var"])
+        torch.cuda.synchronize()
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    assert ctx.workspace_bytes() < before + 3 * matrix
+    ctx.close()
+
+
 def test_setup_work_space_is_made_once_and_kept():
     """The set-up calls share one work space: a second pass over them allocates nothing and gives the same bits."""
     import torch
