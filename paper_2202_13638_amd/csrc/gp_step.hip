@@ -40,8 +40,10 @@ namespace {
 #ifndef BAGEL_MIN_WAVES
 #define BAGEL_MIN_WAVES(D) ((D) <= 8 ? 8 : ((D) <= 11 ? 5 : 4))
 #endif
-// launches without the table form have at most four waves per SIMD
-#define BAGEL_MIN_WAVES_SMALL(D) ((D) <= 6 ? 4 : 3)
+// Launches without the table form have at most four waves per SIMD.  The loops in pairs need more than the 128 registers of
+// four from D = 6 on: held to them, D = 6 kept three in scratch memory (N = 512, L = 512, 100 trajectories: 8.8 us a launch,
+// 8.5 with three waves; N = 2200, L = 1024, 200 trajectories: 11.8 and 11.6)
+#define BAGEL_MIN_WAVES_SMALL(D) ((D) <= 5 ? 4 : 3)
 #ifndef BAGEL_SAME_ROWS
 #define BAGEL_SAME_ROWS 0      // timing experiment only: every work unit reads the first unit's rows
 #endif
