@@ -777,8 +777,10 @@ __global__ __launch_bounds__(256) void hyper_lml_kernel(const double *__restrict
 // dK/dlog l_d = K (x_d - x'_d)^2 / l_d^2, dK/dlog alpha^2 = K, dK_hat/dlog sigma_n^2 = sigma_n^2 I).  The tile of
 // K_hat^-1 is formed here and never written: only these sums of it are needed.  Tiles off the diagonal count
 // twice.  The sums are added over a lane's entries, the lanes (fixed butterfly) and the four waves in order.
+// Three workgroups per compute unit as long as the sums fit their 168 registers: beyond D = 13 they do not, and D = 16 kept 93
+// in scratch memory (a call at N = 2048, 8 outputs: 2930 us, 2620 with two workgroups).
 template <int D>
-__global__ __launch_bounds__(256, 3) void hyper_grad_tiles_kernel(const float *__restrict__ X, const float *__restrict__ log_hyp,
+__global__ __launch_bounds__(256, D <= 13 ? 3 : 2) void hyper_grad_tiles_kernel(const float *__restrict__ X, const float *__restrict__ log_hyp,
                                                                   tri_matrix W, const double *__restrict__ alpha,
                                                                   double *__restrict__ partial, int N, int Np, int m0)
 {
