@@ -41,7 +41,11 @@ struct shape {
 // reach 256, 512, 1024, 1536, ... (what is left over after a pass of 512 is not spread one per unit); one of 64 x 64
 // takes a quarter of that time and balances by itself, at 5 % less speed.  Measured on the posterior step, 64 against
 // 128 (N, B, outputs): 512 tiles (2048, 1024, 4) 556 / 529 us; 256 tiles (2048, 512, 4) 321 / 311, (4096, 512, 2) 577 / 563;
-// 384 tiles (2048, 768, 4) 440 / 520; 768 tiles (4000, 500, 6) 1580 / 1944; 64 tiles (1024, 256, 4) 89 / 178.
+// 384 tiles (2048, 768, 4) 440 / 520; 768 tiles (4000, 500, 6) 1580 / 1944; 64 tiles (1024, 256, 4) 89 / 178.  256 and 512 are
+// one and two per compute unit of an MI355X.  The products of the set-up calls, shorter ones among them, go by the same line;
+// a set-up of samples (N, L, S, outputs) by it, with 64 and with 128 throughout: (8192, 4096, 8192, 6) 173 / 179 / 178 ms;
+// (4096, 2048, 4096, 4) 17.5 / 17.4 / 18.0; (2048, 1024, 4096, 4) 5.12 / 4.96 / 5.35; (4096, 1024, 512, 3) 5.14 / 4.92 / 7.97;
+// (1024, 1024, 1024, 4) 0.96 / 0.95 / 1.42.
 inline bool whole_passes(long tiles)
 {
     if (tiles <= 256) return 100 * tiles >= 95 * 256;
@@ -66,7 +70,9 @@ __device__ __forceinline__ lane_pos lane_position()
     return lane_pos{(wave >> 1) * (T / 2) + 2 * (lane >> 4), (wave & 1) * (T / 2) + 2 * (lane & 15)};
 }
 
-// lane i's 16 bytes at base + off go to LDS byte address lds + 16 i (base and lds are wave-uniform)
+// lane i's 16 bytes at base + off go to LDS byte address lds + 16 i (base and lds are wave-uniform).  M0 cannot be named as
+// clobbered: it is a reserved register, in which the compiler keeps nothing (it would write it right before an
+// instruction of its own that reads it; the kernels that call this have none).
 __device__ __forceinline__ void load_row_to_lds(const double *base, unsigned off, unsigned lds)
 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" : : "v"(off), "s"(lds), "s"(base) : "memory");

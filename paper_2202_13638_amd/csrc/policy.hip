@@ -1153,7 +1153,7 @@ constexpr int WG_KC = 32;              // contraction indices per tile
 // fragment reads of the current one: the compiler orders every LDS read after all outstanding loads
 // of this kind, whichever part of LDS they fill.  No register is written, so nothing the compiler
 // allocates depends on the load's completion; the caller waits (vmcnt) before the barrier that
-// publishes the tile.  M0 carries the LDS address; the kernel that calls this uses M0 for nothing else.
+// publishes the tile.  M0 carries the LDS address (see load_row_to_lds in f64_tile.h).
 __device__ __forceinline__ void load_16_bytes_per_lane_to_lds(const float *g, unsigned lds_addr)
 {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_addr) : "memory");
