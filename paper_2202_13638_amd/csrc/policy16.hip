@@ -190,6 +190,14 @@ __device__ __forceinline__ void load_weights(forward_weights<NW, NT> &f, const f
     }
 }
 
+// The ten wait states that the results of v_mfma_f32_16x16x4 want before anything but a matrix instruction reads them.  The compiler
+// places them by itself, but counts wrongly where a result is used behind a branch and again where the branch joins: it takes the
+// longer way round for both.  With two tiles the end of a slice below compiled into that: the last rows of the second tile were
+// read four or five wait states after the instruction, and a backward sweep built that way gave other gradients from run to
+// run.  tests/test_matrix_wait_states.py follows every path of the compiled kernels.  (No cost: 256-256, B = 1024, N = 2048
+// 46.2 us per step with and without.)
+__device__ __forceinline__ void matrix_results_ready(f4v &a, f4v &b) { asm volatile("s_nop 7\n\ts_nop 1" : "+v"(a), "+v"(b)); }
+
 // One contraction over the blocks of a wide layer for the wave's NT tiles: w[t][kb] the weights, act the operands, n inputs,
 // sl blocks per slice; slices are added up in order
 template <int NT, int TT, int AS>
@@ -209,6 +217,7 @@ __device__ __forceinline__ void contract_wide(f4v (&z)[NT], const f4v (&w)[NT][T
             for (int s = 0; s < 4; ++s)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) acc[t] = mfma16(w[t][kb][s], x[s], acc[t]);
+            if constexpr (NT == 2) matrix_results_ready(acc[0], acc[1]);
             if (--left == 0 || 16 * (kb + 1) >= n) {                       // end of a slice (wave-uniform)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
@@ -499,9 +508,8 @@ __global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args 
 // As backward_sweep_kernel of policy.hip: the steps t_hi-1 .. t_lo of 16 trajectories per workgroup.  What a step reads from
 // the tapes is requested two steps ahead, into the registers that held the values of the step just done with them
 // (two sets, the loop body handles two steps), so that no value is copied and nothing waits for a load it does not need.
-// For widths up to 128.  Above, the 128 registers of middle weights leave too few for two steps of tape values: an instance
-// kept 400 bytes a lane in scratch, and gradients came out different from run to run when only its workgroup order was
-// changed.  The sweep of policy.hip, in registers, serves those policies.
+// For widths up to 128.  Above, the 128 registers of middle weights leave too few for two steps of tape values (an instance
+// kept 400 bytes a lane in scratch memory); the sweep of policy.hip, in registers, serves those policies.
 struct sweep16_args {
     int B, nl, ds, da, dg, D, M, H, t_hi, t_lo;
     int width[4];
