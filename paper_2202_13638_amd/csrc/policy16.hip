@@ -525,7 +525,7 @@ struct sweep16_args {
     float *grad_s0;
 };
 
-// MM, DG: at least M and d_g (rounded up to 4 or 8, 2 or 8); ALL: M = MM
+// MM, DG: at least M and d_g (rounded up to 2, 3, 4, 6 or 8, 2 or 8); ALL: M = MM
 template <int NT, int MM, int DG>
 struct sweep16_tape {
     float J[MM], th;                         // rows d < D: J[m][d]; actions: tanh output of the bounded action
@@ -657,8 +657,9 @@ __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args 
 #pragma unroll
             for (int m = 0; m < MM; ++m) {
                 float Jm = s.J[m];
-                // past M: a duplicate, which may be infinite.  (An instance without this where M = MM: in all of them it made
-                // a gradient call at 64-64, B = 256 take 1387 us instead of 1376.)
+                // past M: a duplicate, which may be infinite.  (Instances without this where M = MM: it made a gradient call at
+                // 64-64, M = 4, B = 256 take 1387 us instead of 1376, and calls with M = 2, B = 20, N = 858 2796 instead of 2768,
+                // or 2707 with a register set of two.)
                 if (!ALL) Jm = __int_as_float(__float_as_int(Jm) & ((m - a.M) >> 31));
                 u += (double)Jm * lamS[m][bl];
             }
@@ -770,12 +771,22 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 {
     const dim3 grid((c->dm.B + PL - 1) / PL), block(64 * NW);
     const pack16 p = make_pack(c);
-#define SWEEP(mm, dgm)                                                                                                       \
-    if (a.M == mm) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, mm, dgm, true>), grid, block, 0, c->stream, a, p);     \
-    else hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, mm, dgm, false>), grid, block, 0, c->stream, a, p)
-    if (a.M <= 4 && a.dg <= 2) { SWEEP(4, 2); }
-    else if (a.dg <= 2) { SWEEP(8, 2); }
-    else { SWEEP(8, 8); }
+#define SWEEP(mm, dgm, all) hipLaunchKernelGGL((backward_sweep16_kernel<NW, NT, mm, dgm, all>), grid, block, 0, c->stream, a, p)
+    if (a.dg > 2) {
+        if (a.M == 8) SWEEP(8, 8, true);
+        else SWEEP(8, 8, false);
+        return;
+    }
+    switch (a.M) {
+    case 1: SWEEP(2, 2, false); break;
+    case 2: SWEEP(2, 2, true); break;
+    case 3: SWEEP(3, 2, true); break;
+    case 4: SWEEP(4, 2, true); break;
+    case 5: SWEEP(6, 2, false); break;
+    case 6: SWEEP(6, 2, true); break;
+    case 7: SWEEP(8, 2, false); break;
+    default: SWEEP(8, 2, true); break;
+    }
 #undef SWEEP
 }
 

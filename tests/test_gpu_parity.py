@@ -383,7 +383,9 @@ def test_policy_kernels_agree_bit_for_bit(hidden, B, ckpt, monkeypatch):
 
 
 @pytest.mark.parametrize("hidden", [(16,), (64, 64), (8, 8), (33, 5), (100, 37), (128, 128), (65,), (200, 136), (256, 256), (129,)])
-@pytest.mark.parametrize("sh", [dict(d_s=4, d_a=1, d_g=1), dict(d_s=6, d_a=2, d_g=2), dict(d_s=2, d_a=3, d_g=2), dict(d_s=8, d_a=8, d_g=8)])
+@pytest.mark.parametrize("sh", [dict(d_s=4, d_a=1, d_g=1), dict(d_s=6, d_a=2, d_g=2), dict(d_s=2, d_a=3, d_g=2), dict(d_s=8, d_a=8, d_g=8),
+                                dict(d_s=1, d_a=1, d_g=1), dict(d_s=3, d_a=1, d_g=2), dict(d_s=5, d_a=1, d_g=2), dict(d_s=7, d_a=2, d_g=1),
+                                dict(d_s=8, d_a=1, d_g=2), dict(d_s=4, d_a=1, d_g=3)])
 def test_policy_kernels_of_both_widths_agree_and_repeat(hidden, sh, monkeypatch):
     """Every instance of the policy kernels: 16 and 32 trajectories per workgroup give the same bits in every output, the
     weight gradient included, and so does a second call, with whole and with ragged tiles, with and without checkpointing."""
@@ -527,7 +529,7 @@ def test_cost_weights_past_the_goal_dimension_are_not_used(hidden, d_g, ckpt, mo
             np.testing.assert_array_equal(got[k], plain[k])
 
 
-@pytest.mark.parametrize("d_s,d_g", [(3, 1), (6, 2), (5, 3)])
+@pytest.mark.parametrize("d_s,d_g", [(3, 1), (6, 2), (5, 3), (1, 1), (5, 2), (7, 1)])
 @pytest.mark.parametrize("hidden", [(16,), (100, 37), (200,)])
 def test_infinite_jacobian_entry_of_the_last_output(d_s, d_g, hidden):
     """A model so steep that d f_m / d x_0 of the last output m overflows float32 while the state stays finite: with one
