@@ -56,6 +56,8 @@
  *   BAGEL_EXP_TABLE        1: always the general form of the kernel-row loop, 2: always the table form,
  *                          unset: by launch size
  *   BAGEL_POLICY_TILE      16 or 32: trajectories per workgroup of the policy kernels; unset: by widths and batch
+ *   BAGEL_ROLLOUT          1: rollouts always step by step, 2: with one workgroup per trajectory wherever a trajectory's share
+ *                          of the model fits a compute unit, unset: by batch size (same results to the last bit)
  *   BAGEL_SETUP_OUTPUTS    most GP outputs a set-up call works on at once; fewer need less work space (default: all)
  *   BAGEL_KSPLIT           split of the weight-gradient contraction (default 256)
  */

@@ -80,7 +80,8 @@ static void free_all(bagel_ctx *c)
     void *ptrs[] = {c->Xs, c->Xn, c->near_ok, c->Os, c->Of, c->A, c->amp, c->exp_tab, c->v4, c->w4, c->xbuf, c->part, c->xbuf_alt, c->part_alt, c->lpt, c->lam,
                     c->tape_s, c->tape_J, c->tape_h_set[0][0], c->tape_h_set[0][1], c->tape_h_set[0][2], c->tape_a_set[0],
                     c->tape_d_set[0][0], c->tape_d_set[0][1], c->tape_d_set[0][2], c->tape_h_set[1][0], c->tape_h_set[1][1],
-                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums};
+                    c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums,
+                    c->xall, c->part_all};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -100,6 +101,26 @@ static void destroy_side(bagel_ctx *c)
     for (hipEvent_t *ev : evs)
         if (*ev) { (void)hipEventDestroy(*ev); *ev = nullptr; }
     if (c->side) { (void)hipStreamDestroy(c->side); c->side = nullptr; }
+}
+
+// What rollouts with one workgroup per trajectory need beside the rest; where that does not fit, they are done step by step.
+static void plan_rollout_buffers(bagel_ctx *c)
+{
+    // the Jacobians of as many steps at a time as have 64 MB of sums (that fills the chip, and the sums stay on it)
+    const size_t B = (size_t)c->dm.B, H = (size_t)c->dm.H, per_step = (size_t)c->groups * (1 + c->D) * B;
+    const size_t most = ((size_t)64 << 20) / (per_step * sizeof(double));
+    c->rollout_steps = (int)(most < 1 ? 1 : (most < H ? most : H));
+    const int64_t bytes = c->bytes;
+    hipError_t e = dev_alloc(c, &c->xall, H * c->D * B);
+    if (e == hipSuccess) e = dev_alloc(c, &c->part_all, (size_t)c->rollout_steps * per_step);
+    if (e == hipSuccess) e = bagel_raise_rollout_lds(c);
+    if (e == hipSuccess) return;
+    if (c->xall) (void)hipFree(c->xall);
+    if (c->part_all) (void)hipFree(c->part_all);
+    c->xall = c->part_all = nullptr;
+    c->bytes = bytes;
+    c->rollout = false;
+    (void)hipGetLastError();
 }
 
 extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_stream)
@@ -128,6 +149,7 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     const int H = dims->H;
     c->T_tape = (K > 0 && K < H) ? K : H;
     bagel_plan_policy(c);
+    bagel_plan_rollout(c);
     c->ksplit = bagel_env_int("BAGEL_KSPLIT", 256);
     c->setup_outputs = bagel_env_int("BAGEL_SETUP_OUTPUTS", BAGEL_MAX_STATE);
     int wf_total = 0, wb_total = 0;
@@ -180,6 +202,7 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     ALLOC(c->gacc, (size_t)c->P);
     ALLOC(c->gtheta, (size_t)c->P);
 #undef ALLOC
+    if (e == hipSuccess && c->rollout) plan_rollout_buffers(c);
     if (e == hipSuccess) {
         // table of the sample-evaluation kernel's table form: -2^(i/256), high word lowered by i << 12
         uint64_t tab[256];
@@ -444,10 +467,17 @@ extern "C" int bagel_profile_read(bagel_ctx *c, double *kernel_ms, int *launches
     return BAGEL_OK;
 }
 
-// Packed weights, initial state and policy input; with the kernels of policy16.hip also the policy of step 0
+// One launch for the whole forward pass (rollout.hip)?  Not while single sample evaluations are being timed.
+static bool whole_rollout(const bagel_ctx *c) { return c->rollout && !c->cur_xi && c->prof_every == 0; }
+
+// Packed weights, initial state and policy input (and all that follows, with one launch for the whole forward pass); with the kernels of policy16.hip also the policy of step 0
 static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape,
                                 bool acts)
 {
+    if (whole_rollout(c)) {
+        const hipError_t e = tape ? bagel_launch_pack_theta16(c, theta) : hipSuccess;   // (for the backward pass)
+        return e == hipSuccess ? bagel_launch_rollout(c, theta, s0, goals, states, tape, acts) : e;
+    }
     if (c->p16) {
         hipError_t e = bagel_launch_pack_theta16(c, theta);
         if (e == hipSuccess && tape && c->p16 == 3) e = bagel_launch_pack_theta(c, theta);     // for backward_sweep
@@ -473,6 +503,10 @@ static hipError_t backward_sweep(bagel_ctx *c, int t_lo, int t_hi, const float *
 static int run_forward(bagel_ctx *c, bool jac, bool acts, bool write_tape_s, const float *theta, const float *goals,
                        float *states_out)
 {
+    if (whole_rollout(c)) {                  // (start_rollout has run it)
+        if (jac) BAGEL_HIP(c, bagel_launch_gp_steps(c));
+        return BAGEL_OK;
+    }
     const int H = c->dm.H;
     const bool posterior = c->cur_xi != nullptr;
     const size_t jslot = (size_t)c->M * c->D * c->dm.B;

@@ -40,6 +40,12 @@ struct bagel_ctx {
     float4 *v4;                  // [M][Np/4][S]: four consecutive training points of one sample
     float4 *w4;                  // [M][Lp/4][S]
 
+    // rollouts with one workgroup per trajectory (rollout.hip; null for contexts without)
+    bool rollout;
+    int rollout_steps;           // steps whose Jacobians are computed in one launch
+    double *xall;                // [D][H][B]: inputs of all steps
+    double *part_all;            // [groups][1+D][rollout_steps B]
+
     // ---- per-step workspace (lane = trajectory, arrays are [component][B]) ---------------
     double *xbuf;                // [D][B]   GP input of the current step; rows 0..d_s-1 are the state (float64)
     double *part;                // [groups][1+D][B] partial sums of the current step
@@ -148,6 +154,9 @@ hipError_t bagel_launch_gp_step(bagel_ctx *ctx, bool jac, float *prev_jac);
 // The Jacobian sums in ctx->part (evaluated at ctx->xbuf) added up into jdst[M][D][B], on their own.
 hipError_t bagel_launch_jac_reduce(bagel_ctx *ctx, float *jdst);
 
+// The Jacobians of all steps of a rollout by rollout.hip, at the inputs it left in ctx->xall, into the Jacobian tape.
+hipError_t bagel_launch_gp_steps(bagel_ctx *ctx);
+
 // ---- model.hip ---------------------------------------------------------------------------
 // The model tables (omega null: without the feature tables) and, where given, the streams w and v and the inputs x of one
 // evaluation, in one launch
@@ -196,6 +205,13 @@ hipError_t bagel_launch_step_tail16(bagel_ctx *ctx, int t, int slot, int next_sl
                                     const float *goals, float *states_out, bool direct);
 hipError_t bagel_launch_policy_replay16(bagel_ctx *ctx, int t0, int t1, const float *goals);
 hipError_t bagel_launch_backward_sweep16(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
+
+// ---- rollout.hip (contexts with rollout) ---------------------------------------------------
+// sets rollout from the sizes; the work decomposition and the policy kernels are planned before
+void bagel_plan_rollout(bagel_ctx *ctx);
+hipError_t bagel_raise_rollout_lds(bagel_ctx *ctx);
+// states, cost per trajectory, state tape and inputs of all steps (tape) and activation tape (acts) of a whole rollout
+hipError_t bagel_launch_rollout(bagel_ctx *ctx, const float *theta, const float *s0, const float *goals, float *states_out, bool tape, bool acts);
 
 // ---- posterior.hip ------------------------------------------------------------------------
 // mu + sqrt(var) xi and its Jacobian for every trajectory and output at xbuf, into ctx->part as

@@ -34,6 +34,7 @@
 #include <stdlib.h>
 
 #include "bagel_internal.h"
+#include "sample_math.h"
 
 namespace {
 
@@ -62,24 +63,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_descriptor(const float4
 __device__ __forceinline__ v4f stream_load(__amdgpu_buffer_rsrc_t desc, unsigned lane_off, unsigned row_off)
 {
     return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(desc, lane_off, row_off, 2));
-}
-
-// 2^t without a table: split off the integer part, evaluate 2^(f/2) for |f| <= 1/2 with a degree-7
-// polynomial and square it (relative error 4e-13), scale with ldexp.  Twelve vector instructions and
-// no LDS access.  c7 comes in a scalar and c6 in a vector register: the first Horner step is then a
-// single three-operand FMA (an FMA takes at most one scalar operand).
-__device__ __forceinline__ double exp2_poly(double t, double c7, double c6)
-{
-    const double n = rint(t);
-    const double f = t - n;                       // exact, |f| <= 1/2
-    double p = fma(c7, f, c6);
-    p = fma(p, f, 4.1667353769980764e-05);
-    p = fma(p, f, 0.0006011326659205452);
-    p = fma(p, f, 0.006938013583872582);
-    p = fma(p, f, 0.060056626759929704);
-    p = fma(p, f, 0.3465735902799663);
-    p = fma(p, f, 0.9999999999998426);
-    return ldexp(p * p, (int)n);
 }
 
 // End of a workgroup: waves 1-3 hand their sums (value u, Jacobian sums G) to wave 0 through LDS slots
@@ -128,21 +111,32 @@ __device__ __forceinline__ void combine_waves(double (*red)[RC][64], int wave, i
 // a rollout needs J, so this runs as M extra rows of workgroups (one per output) inside the NEXT step's
 // sample evaluation (or, after the last step, as a launch of its own).  256 threads: the four waves
 // share the D entries of the output.
+// Several steps of a rollout at once (STEPS below): B inputs are those of B / trajectories steps, x is [D][x_stride], and the Jacobians
+// go to [step][M][D][trajectories].
+struct several_steps {
+    int trajectories;
+    size_t x_stride;
+};
+
 struct jac_sums {
     const double *part;      // [groups][1+D][B]
     const double *x;         // [D][B] inputs the sums were evaluated at
     const double *A, *amp;   // [M][D], [M]
     float *jdst;             // [M][D][B]
+    several_steps several;
 };
 
 // W: loads in flight per sum (4 inside the large launches, which hide the trips and have few registers; 8 elsewhere)
-template <int W>
+template <int W, bool STEPS>
 __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
 {
     constexpr double LN2 = 0.69314718055994530942, TWO_PI = 6.28318530717958647693;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int b = tile * 64 + lane;
     if (b >= B) return;
+    const int T = STEPS ? j.several.trajectories : B, step = STEPS ? b / T : 0;
+    const size_t x_stride = STEPS ? j.several.x_stride : (size_t)B;
+    float *const jdst = j.jdst + (size_t)step * M * D * T + (b - step * T);
     const size_t stride = (size_t)(1 + D) * B;
     const double *pk = j.part + (size_t)(m * ngk) * stride + b;
     const double *pr = j.part + (size_t)(M * ngk + m * ngl) * stride + b;
@@ -151,7 +145,7 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
     for (int d = wave; d < D; d += BAGEL_BLOCK / 64) {
         const double *const p[3] = {pk + (size_t)(1 + d) * B, pr + (size_t)(1 + d) * B, pk};
         const int n[3] = {ngk, ngl, ngk};
-        const double xd = j.x[(size_t)d * B + b];
+        const double xd = j.x[(size_t)d * x_stride + b];
         double s[3];
         if (W < 8) {
             double one[1];
@@ -163,13 +157,14 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
         } else {
             bagel_sums_in_order<3, W>(p, n, stride, s);
         }
-        j.jdst[(size_t)(m * D + d) * B + b] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
+        jdst[(size_t)(m * D + d) * T] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
     }
 }
 
+template <bool STEPS>
 __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums j, int B, int D, int M, int ngk, int ngl)
 {
-    jacobian_tile<8>(j, blockIdx.x, blockIdx.y, B, D, M, ngk, ngl);
+    jacobian_tile<8, STEPS>(j, blockIdx.x, blockIdx.y, B, D, M, ngk, ngl);
 }
 
 // ---- the loops of small launches ------------------------------------------------------------------
@@ -188,29 +183,13 @@ __device__ __forceinline__ void load_row(double (&r)[D + 1], const double *__res
     for (int d = 0; d <= D; ++d) r[d] = src[d];
 }
 
-// 2^t of exp2_poly for two arguments side by side
-__device__ __forceinline__ void exp2_poly2(double t0, double t1, double c7, double c6, double &k0, double &k1)
-{
-    const double n0 = rint(t0), n1 = rint(t1);
-    const double f0 = t0 - n0, f1 = t1 - n1;
-    double p0 = fma(c7, f0, c6), p1 = fma(c7, f1, c6);
-    p0 = fma(p0, f0, 4.1667353769980764e-05); p1 = fma(p1, f1, 4.1667353769980764e-05);
-    p0 = fma(p0, f0, 0.0006011326659205452); p1 = fma(p1, f1, 0.0006011326659205452);
-    p0 = fma(p0, f0, 0.006938013583872582); p1 = fma(p1, f1, 0.006938013583872582);
-    p0 = fma(p0, f0, 0.060056626759929704); p1 = fma(p1, f1, 0.060056626759929704);
-    p0 = fma(p0, f0, 0.3465735902799663); p1 = fma(p1, f1, 0.3465735902799663);
-    p0 = fma(p0, f0, 0.9999999999998426); p1 = fma(p1, f1, 0.9999999999998426);
-    k0 = ldexp(p0 * p0, (int)n0);
-    k1 = ldexp(p1 * p1, (int)n1);
-}
-
 // n_iter float4 of training points (a multiple of 4) with rows from Xr and the stream vdesc: see the general loop
 template <int D, bool JAC>
 __device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, __amdgpu_buffer_rsrc_t vdesc, unsigned voff,
                                                  unsigned vstep, int n_iter, const double (&xs)[D], double qs, double &u, double (&G)[D])
 {
-    double ca = 1.192611307487823e-07, cb = 2.409383341728244e-06;
-    asm volatile("" : "+s"(ca), "+v"(cb));
+    exp2_coefficients ec;
+    asm volatile("" : "+s"(ec.c7), "+v"(ec.c6));
     const int last = n_iter - 1;
     auto pair = [&](const double (&r0)[D + 1], const double (&r1)[D + 1], double (&n0)[D + 1], double (&n1)[D + 1],
                     const double *__restrict__ next, float v0, float v1) {
@@ -224,7 +203,7 @@ __device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, 
             t1 = fma(xs[d], r1[d], t1);
         }
         double k0, k1;
-        exp2_poly2(t0, t1, ca, cb, k0, k1);
+        exp2_poly2(t0, t1, ec, k0, k1);
         const double vk0 = (double)v0 * k0, vk1 = (double)v1 * k1;
         u += vk0;
         u += vk1;
@@ -333,7 +312,7 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
 // The table form needs many workgroups per compute unit to pay: its LDS read shares a wait counter
 // with the scalar loads of the shared operands, so every look-up also waits for the operand rows
 // requested ahead; small launches take the general loop only.
-template <int D, bool JAC, bool NEAR>
+template <int D, bool JAC, bool NEAR, bool STEPS>
 __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEAR ? BAGEL_MIN_WAVES(D) : BAGEL_MIN_WAVES_SMALL(D), 8))) void gp_step_kernel(
     const double *__restrict__ Xs, const double *__restrict__ Xn, const double *__restrict__ Os,
     const float4 *__restrict__ Of, const double *__restrict__ A, const float4 *__restrict__ v4,
@@ -345,7 +324,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
     // M rows of workgroups past the work units: the previous step's Jacobian sums (see jacobian_tile).
     // (Placed first in the grid instead, they made the launch slower: 571 vs 556 us.)
     if ((int)blockIdx.y >= M * (((nck + 3) >> 2) + ((ncl + 3) >> 2))) {
-        jacobian_tile<NEAR ? 4 : 8>(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
+        jacobian_tile<NEAR ? 4 : 8, false>(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
                       (nck + 3) >> 2, (ncl + 3) >> 2);
         return;
     }
@@ -360,13 +339,13 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
     const int b_raw = blockIdx.x * 64 + lane;
     const bool live = b_raw < B;
     const int b = live ? b_raw : B - 1;
-    const int sidx = b / per_sample;
+    const int sidx = (STEPS ? b % prev.several.trajectories : b) / per_sample;
     const int group = blockIdx.y;                  // four consecutive units of one output and kind
     const int ngk = (nck + 3) >> 2, ngl = (ncl + 3) >> 2;
 
     double x[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) x[d] = xbuf[(size_t)d * B + b];
+    for (int d = 0; d < D; ++d) x[d] = xbuf[(size_t)d * (STEPS ? prev.several.x_stride : (size_t)B) + b];
 
     double *out = part + (size_t)group * (1 + D) * B + b;
 
@@ -492,8 +471,8 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
             if constexpr (!NEAR && D <= 8) {
                 if (n_iter > 0) kernel_row_pairs<D, JAC>(Xr, vdesc, voff, vstep, n_iter, xs, qs, u, G);
             } else {
-                double ca = 1.192611307487823e-07, cb = 2.409383341728244e-06;
-                asm volatile("" : "+s"(ca), "+v"(cb));
+                exp2_coefficients ec;
+                asm volatile("" : "+s"(ec.c7), "+v"(ec.c6));
                 // same pipeline as the table form: the next point's row is requested while this one is worked
                 // on, the stream one float4 ahead
                 const int last = n_iter - 1;
@@ -505,7 +484,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
                     double t = qs + rc[D];
     #pragma unroll
                     for (int d = 0; d < D; ++d) t = fma(xs[d], rc[d], t);
-                    const double k = exp2_poly(t, ca, cb);
+                    const double k = exp2_poly(t, ec);
                     const double vk = (double)vf * k;
                     u += vk;
                     if (JAC) {
@@ -682,8 +661,8 @@ void launch_variant(bagel_ctx *c, float *prev_jac)
 {
     dim3 grid((c->dm.B + 63) / 64, c->groups + (prev_jac ? c->M : 0));
     const int per_sample = c->dm.B / c->dm.S;
-    const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac};
-    hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,
+    const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac, {}};
+    hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR, false>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,
                        reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, c->xbuf, c->part, c->exp_tab,
                        c->near_ok, c->dm.B, c->dm.S, per_sample, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, prev);
 }
@@ -698,6 +677,20 @@ hipError_t launch_d(bagel_ctx *c, bool jac, float *prev_jac)
         if (jac) launch_variant<D, true, false>(c, prev_jac);
         else launch_variant<D, false, false>(c, prev_jac);
     }
+    return hipGetLastError();
+}
+
+// The Jacobians of the steps t0 .. t0 + steps - 1 of a rollout by rollout.hip (the same loops as step by step: the same bits)
+template <int D>
+hipError_t launch_steps(bagel_ctx *c, int t0, int steps)
+{
+    const int B = c->dm.B, n = steps * B;
+    const jac_sums j = {c->part_all, c->xall + (size_t)t0 * B, c->A, c->amp, c->tape_J + (size_t)t0 * c->M * c->D * B, {B, (size_t)c->dm.H * B}};
+    hipLaunchKernelGGL((gp_step_kernel<D, true, false, true>), dim3((n + 63) / 64, c->groups), dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn,
+                       c->Os, reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, j.x, c->part_all, c->exp_tab, c->near_ok, n,
+                       c->dm.S, B / c->dm.S, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, j);
+    hipLaunchKernelGGL(jac_reduce_kernel<true>, dim3((n + 63) / 64, c->M), dim3(BAGEL_BLOCK), 0, c->stream, j, n, D, c->M, (c->nck + 3) / 4,
+                       (c->ncl + 3) / 4);
     return hipGetLastError();
 }
 
@@ -775,8 +768,24 @@ hipError_t bagel_launch_gp_step(bagel_ctx *c, bool jac, float *prev_jac)
 
 hipError_t bagel_launch_jac_reduce(bagel_ctx *c, float *jdst)
 {
-    const jac_sums j = {c->part, c->xbuf, c->A, c->amp, jdst};
-    hipLaunchKernelGGL(jac_reduce_kernel, dim3((c->dm.B + 63) / 64, c->M), dim3(BAGEL_BLOCK), 0, c->stream, j, c->dm.B, c->D,
+    const jac_sums j = {c->part, c->xbuf, c->A, c->amp, jdst, {}};
+    hipLaunchKernelGGL(jac_reduce_kernel<false>, dim3((c->dm.B + 63) / 64, c->M), dim3(BAGEL_BLOCK), 0, c->stream, j, c->dm.B, c->D,
                        c->M, (c->nck + 3) / 4, (c->ncl + 3) / 4);
     return hipGetLastError();
+}
+
+hipError_t bagel_launch_gp_steps(bagel_ctx *c)
+{
+    const int H = c->dm.H;
+    for (int t0 = 0; t0 < H; t0 += c->rollout_steps) {
+        const int steps = t0 + c->rollout_steps < H ? c->rollout_steps : H - t0;
+        hipError_t e = hipErrorInvalidValue;
+        switch (c->D) {
+#define CASE(n) case n: e = launch_steps<n>(c, t0, steps); break;
+            CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
+#undef CASE
+        }
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }

@@ -1,0 +1,630 @@
+// The forward pass of a whole rollout in one launch, one workgroup per trajectory.
+//
+// With few trajectories a rollout is a chain of latencies: a sample evaluation spread over the chip and an end-of-step
+// kernel take two launches, four trips to memory and a hand-over between compute units for every step, whatever little
+// there is to compute.  Here a trajectory never leaves its compute unit: 512 threads hold the rows of the model tables and the
+// trajectory's weights v and w in registers for the whole horizon (the policy's weights in LDS), and a step is six barriers.
+// What bounds a step is the float64 arithmetic of one compute unit and what lies between the barriers.  A forward step of a gradient
+// call takes 3.1 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 3.0 at M = 2, N = 2200, L = 1024, 8-8,
+// B = 100 (13.2) and 1.5 at M = 2, N = 64, L = 256, 16, B = 16 (8.6); the Jacobians afterwards take 1.5, 0.5 and 0.5 us a step.
+//
+// Only values are computed here.  The Jacobians feed nothing but the backward pass, so they are computed afterwards for all
+// steps at once, where they fill the chip (bagel_launch_gp_steps): the exponentials are computed twice, which is cheaper than
+// a chain with D times more sums in it.
+//
+// Every number is formed in the order of gp_step.hip and policy16.hip, so states and costs have the same bits as a rollout by
+// those kernels: terms are computed by whichever thread has the operands and left in LDS, and one thread per work unit adds
+// them up in order; four units make a group sum, group sums are added as step_tail16_kernel adds them.
+#include <type_traits>
+
+#include "policy16.h"
+#include "sample_math.h"
+
+namespace {
+
+constexpr int NT = 512;                      // threads
+constexpr int NW = NT / 64;
+constexpr int MAX_SUMS = 512;                // group sums in LDS (a multiple of eight for every output and kind)
+constexpr int LDS_BYTES = 152 * 1024;        // what the launch may ask for beside the static arrays
+
+// Pairs of an output and a training point or feature go to the waves in chunks of 64, in turn.  A thread keeps the rows of
+// this many pairs, 2 (D + 1) + 1 registers each, in about 160 of its 256 registers.
+template <int D>
+constexpr int chunks_per_wave() { return 160 / (2 * D + 3) < 16 ? 160 / (2 * D + 3) : 16; }
+
+__device__ __forceinline__ double from_lane(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// A contraction runs through a block of 16 units as the matrix instructions of policy16.hip do: unit16(g, e) is at place 4 e + g.
+// Weights and activations lie in that order here, so that a chain reads four of each at a time.
+// Slices of 32 start nine groups apart, on banks of their own.
+__host__ __device__ constexpr int act_place(int unit)
+{
+    return (unit >> 5) * 36 + (unit & 0x18) + ((unit & 2) << 1 | (unit & 1) << 1 | (unit >> 2 & 1));
+}
+
+// a chain over one block: weights in steps of STRIDE groups
+template <int STRIDE>
+__device__ __forceinline__ float chain16(const f4v *w, const f4v *x, float acc)
+{
+    f4v a[4], h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[i] = w[i * STRIDE];
+        h[i] = x[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = fmaf(a[i][e], h[i][e], acc);
+    return acc;
+}
+
+// The policy's weights in LDS, in groups of four along a chain, zero past the layers' ends (what a zero weight adds changes no bit), so
+// that no lane needs a condition:
+//   hidden layer 1 [4][width], hidden layer 2 [4 blocks][lanes], output layer [2 * 4][32 lanes], biases [3][128] floats.
+// A long contraction is cut into slices that are added up in order, as in policy16.hip: at most four for up to 64 units, two for more.
+// Hidden layer 2 gives that many neighbouring lanes to a unit, one a slice, the output layer four to an action.
+template <bool WIDE>
+struct policy_weights {
+    static constexpr int W = WIDE ? 128 : 64, LANES = 256;
+    static constexpr int MID = 4 * W, LAST = MID + (WIDE ? 16 : 8) * LANES, BIAS = LAST + 8 * 32;      // in groups of four
+    static constexpr int FLOATS = 4 * BIAS + 3 * 128;
+};
+
+struct policy_shape {
+    int nl, width[4];
+    int fs;                                  // blocks per slice of hidden layer 2
+};
+
+struct rollout_args {
+    int B, S, per_sample, H, M, da, Np, Lp, nck, ncl;
+    int GS;                                  // room for the group sums of an output and kind
+    int KC, FC;                              // chunks of training points (per output whole ones) and of features
+    int d_in, dg, cost_kind, keep;
+    int w_off[3], b_off[3];
+    int tracked[8];
+    float q[8];
+    float act_bound, sigma_r;
+    float *tape_s, *states_out;              // null: not kept
+    float *h[3], *a_slot;                    // activation tapes (keep)
+    double *lpt;
+    double *xall;                            // [D][H][B], inputs of every step for the Jacobians, null: not kept
+};
+
+__device__ __forceinline__ double shuffle(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * lane, __double2hiint(v)), __builtin_amdgcn_ds_bpermute(4 * lane, __double2loint(v)));
+}
+
+// A wave's own LDS writes are seen by its later reads; this keeps the compiler from moving them
+__device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+template <int D, int CK, bool WIDE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void rollout_kernel(
+    rollout_args r, policy_shape p, const float *__restrict__ theta, const double *__restrict__ Xs, const double *__restrict__ Os,
+    const double *__restrict__ A, const double *__restrict__ amp, const float *__restrict__ v4, const float *__restrict__ w4,
+    const float *__restrict__ s0, const float *__restrict__ goals)
+{
+    constexpr int E = chunks_per_wave<D>();
+    constexpr int RS = CK + 2, CHUNK = 64 / CK * RS;                       // doubles per row and per chunk of terms
+    // terms: [KC 64 / CK][CK + 2] doubles of the kernel rows, then [FC 64 / CK][CK + 2] pairs (w, cos) of the features; policy weights
+    extern __shared__ __align__(16) double terms[];
+    __shared__ __align__(16) double gsum[MAX_SUMS], xS[16];
+    __shared__ double AS[8][D];              // -1/2 A
+    __shared__ float goalS[2][16], aS[8];    // goals of the next step and this one (lane M + j: entry M + j), action tape
+    __shared__ __align__(16) float act[2][144];
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups of one chiplet (they go to the eight in turn) take neighbouring trajectories: these share the lines of a tape row
+    int b;
+    {
+        const int n = gridDim.x, x = blockIdx.x & 7, q = n >> 3, rest = n & 7;
+        b = x * q + (x < rest ? x : rest) + ((int)blockIdx.x >> 3);
+    }
+    const int B = r.B, M = r.M, sample = b / r.per_sample;
+
+    // ---- what stays where it is for the whole horizon ---------------------------------------------------------------
+    double row[E][D + 1];
+    float weight[E];
+    // Chunks of points take slots 0, 1, ..., chunks of features E - 1, E - 2, ...: every slot index below is a constant
+    const int kchunks = (r.KC - wave + NW - 1) / NW, fchunks = (r.FC - (NW - 1 - wave) + NW - 1) / NW;
+    int m_of_chunk = 0;                      // lane i: the output of the wave's chunk i
+    {
+        const int per_m = r.KC / M;          // chunks per output
+        m_of_chunk = min((lane * NW + wave) / per_m, M - 1);
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+            const int c = i * NW + wave, cf = (E - 1 - i) * NW + (NW - 1 - wave);
+            const double *src = Xs;
+            const float *wsrc = nullptr;
+            if (i < kchunks) {
+                const int m = c / per_m, n = min((c - m * per_m) * 64 + lane, r.Np - 1);
+                src = Xs + ((size_t)m * r.Np + n) * (D + 1);
+                wsrc = v4 + ((size_t)(m * (r.Np / 4) + n / 4) * r.S + sample) * 4 + (n & 3);
+            } else if (E - 1 - i < fchunks) {
+                const int f = min(cf * 64 + lane, M * r.Lp - 1);
+                src = Os + (size_t)f * (D + 1);
+                wsrc = w4 + ((size_t)(f / 4) * r.S + sample) * 4 + (f & 3);
+            }
+#pragma unroll
+            for (int d = 0; d <= D; ++d) row[i][d] = src[d];
+            weight[i] = wsrc ? *wsrc : 0.0f;
+        }
+    }
+    // policy weights into LDS
+    using PW = policy_weights<WIDE>;
+    f4v *const w0 = reinterpret_cast<f4v *>(terms + (r.KC + r.FC) * CHUNK), *const w1 = w0 + PW::MID, *const w2 = w0 + PW::LAST;
+    float *const biases = reinterpret_cast<float *>(w0 + PW::BIAS);
+    // more than 64 units: two lanes a unit in hidden layer 2, otherwise four
+    const bool two = WIDE && p.width[2] > 64;
+    {
+        const int n0 = p.width[0], n1 = p.width[1], n2 = p.width[2], n_last = p.width[p.nl - 1];
+        auto load = [&](int l, bool live, int u, int k, int n_in) { return live && k < n_in ? theta[r.w_off[l] + u * n_in + k] : 0.0f; };
+        for (int e = tid; e < 4 * PW::W; e += NT) {
+            const int u = e % PW::W, c4 = e / PW::W;
+            f4v w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = load(0, u < n1, u, unit16(i, c4), n0);
+            w0[e] = w;
+        }
+        for (int e = tid; p.nl == 3 && e < 4 * p.fs * PW::LANES; e += NT) {
+            const int ln = e % PW::LANES, c4 = e / PW::LANES, u = ln >> (two ? 1 : 2), sl = ln & (two ? 1 : 3);
+            f4v w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = load(1, u < n2, u, 16 * (sl * p.fs + (c4 >> 2)) + unit16(i, c4 & 3), n1);
+            w1[e] = w;
+        }
+        if (tid < 8 * 32) {
+            const int ln = tid & 31, c4 = tid >> 5;
+            f4v w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = load(p.nl - 1, (ln >> 2) < r.da, ln >> 2, 16 * (2 * (ln & 3) + (c4 >> 2)) + unit16(i, c4 & 3), n_last);
+            w2[tid] = w;
+        }
+        if (tid < 3 * 128) {
+            const int l = tid >> 7, u = tid & 127;
+            const int n = l == 0 ? n1 : (l == 1 ? n2 : p.width[3]), off = l == 0 ? r.b_off[0] : (l == 1 ? r.b_off[1] : r.b_off[2]);
+            biases[tid] = l < p.nl && u < n ? theta[off + u] : 0.0f;
+        }
+        if (tid < 288) act[tid / 144][tid % 144] = 0.0f;
+        if (tid < MAX_SUMS) gsum[tid] = 0.0;                               // (group sums past an output's last are never written)
+        if (tid < M * D) AS[tid / D][tid % D] = -0.5 * A[tid];
+    }
+    // a layer that only the first wave has a part in needs no barrier after it
+    const int lanes1 = p.nl == 3 ? p.width[2] << (two ? 1 : 2) : 0;        // lanes of hidden layer 2
+    const bool barrier0 = p.width[1] > 64 || lanes1 > 64, barrier1 = lanes1 > 64;
+
+    int ml = min(lane, M - 1);
+    const double amp_lane = amp[ml];
+    const int my_term = (lane / CK) * RS + lane % CK, my_points = wave * CHUNK + my_term, my_features = (r.KC + NW - 1 - wave) * CHUNK + my_term;
+    // the work unit this thread adds up: kernel rows first, features from the next whole wave on.  Group sums of output m: the
+    // kernel rows' from (2 m) GS, the features' from (2 m + 1) GS on
+    int unit_at = 0, unit_to = 0;            // first term; group sum
+    bool unit_live;
+    const int ngk = (r.nck + 3) >> 2, ngl = (r.ncl + 3) >> 2, fbegin = (4 * M * ngk + 63) & ~63;
+    const bool wave_kernel = 64 * wave < fbegin, sum_wave = 64 * wave < fbegin + 4 * M * ngl;
+    {
+        const int u = wave_kernel ? tid : tid - fbegin, ng = wave_kernel ? ngk : ngl, nc = wave_kernel ? r.nck : r.ncl;
+        const int gr = u >> 2, m = gr / ng, g = gr - m * ng, c = 4 * g + (u & 3);
+        unit_live = m < M && c < nc;
+        if (unit_live) unit_at = wave_kernel ? (m * (r.KC / M * (64 / CK)) + c) * RS : r.KC * CHUNK + (m * nc + c) * RS;
+        unit_to = m < M ? (2 * m + (wave_kernel ? 0 : 1)) * r.GS + g : MAX_SUMS - 1;
+    }
+
+    // ---- state: lane m < M of every wave holds s_m, lanes M .. d_in - 1 the goal the policy sees ------------------------
+    double s = lane < M ? (double)s0[(size_t)b * M + ml] : 0.0;
+    // (zero past d_in).  Wave 7 fetches the goals two steps ahead and hands them to the others.
+    const bool goal_lane = lane >= M && lane < r.d_in;
+    float goal = goal_lane ? goals[(size_t)b * r.dg + lane - M] : 0.0f, goal_ahead = 0.0f;
+    if (wave == 7 && goal_lane && r.H > 1) goal_ahead = goals[(size_t)B * r.dg + (b * r.dg + lane - M)];
+    if (tid < 32) goalS[tid >> 4][tid & 15] = 0.0f;
+    double cost = 0.0;
+    exp2_coefficients ec;
+    asm volatile("" : "+v"(ec.c6));
+    __syncthreads();
+
+    int t = 0;
+    for (;;) {
+        // What is the same in every step (addresses, conditions, float64 copies of the weights) is formed again in every step: kept
+        // from before the loop, as it would be without this, it takes more registers than there are.
+        asm volatile("" : "+v"(tid), "+v"(lane), "+v"(ml));
+#pragma unroll
+        for (int i = 0; i < E; ++i) asm volatile("" : "+v"(weight[i]));
+        // ---- policy ----------------------------------------------------------------------------------------------------
+        const float hin = lane < M ? (float)s : goal;
+        if (64 * wave < p.width[1]) {
+            const float bias = biases[tid];
+            f4v w[2] = {w0[tid], w0[PW::W + tid]};
+            float z = 0.0f;
+            auto inputs = [&](int e) {
+                float x[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hin), unit16(i, e)));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) z = fmaf(w[e & 1][i], x[i], z);
+            };
+            inputs(0);
+            inputs(1);
+            if (r.d_in > 8) {
+                w[0] = w0[2 * PW::W + tid];
+                w[1] = w0[3 * PW::W + tid];
+                inputs(2);
+                inputs(3);
+            }
+            act[0][act_place(tid)] = tanh_fast(z + bias);
+        }
+        if (barrier0) __syncthreads();
+        else wave_sync();
+        if (p.nl == 3) {
+            if (64 * wave < lanes1) {
+                const int u = two ? tid >> 1 : tid >> 2, sl = two ? tid & 1 : tid & 3;
+                const float bias = biases[128 + u];
+                // (past the last slice the weights are zero: any operands will do)
+                const f4v *w = w1 + tid, *x = reinterpret_cast<const f4v *>(act[0]) + (two ? 9 * (p.fs >> 1) * sl : 9 * sl);
+                float z = chain16<PW::LANES>(w, x, 0.0f);
+                z = chain16<PW::LANES>(w + 4 * PW::LANES, x + 4, z);
+                if (WIDE && p.fs == 4) {
+                    z = chain16<PW::LANES>(w + 8 * PW::LANES, x + 9, z);
+                    z = chain16<PW::LANES>(w + 12 * PW::LANES, x + 13, z);
+                }
+                // slices in order: quad_perm broadcasts
+                const int zi = __float_as_int(z);
+                if (two) {
+                    z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xf5, 0xf, 0xf, true));
+                } else {
+                    z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0x55, 0xf, 0xf, true));
+                    if (p.width[1] > 64) {
+                        z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xaa, 0xf, 0xf, true));
+                        z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xff, 0xf, 0xf, true));
+                    }
+                }
+                if (sl == 0) act[1][act_place(u)] = tanh_fast(z + bias);
+            }
+            if (barrier1) __syncthreads();
+            else wave_sync();
+        }
+        if (wave == 0) {                     // actions: lane 4 o + slice
+            const int o = (lane & 31) >> 2, sl = lane & 3;
+            const f4v *w = w2 + (lane & 31), *x = reinterpret_cast<const f4v *>(act[p.nl - 2]) + 9 * sl;
+            const float bias = biases[128 * (p.nl - 1) + o];
+            float z = chain16<32>(w, x, 0.0f);
+            if (p.width[p.nl - 1] > 16) z = chain16<32>(w + 128, x + 4, z);
+            const int zi = __float_as_int(z);
+            z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0x55, 0xf, 0xf, true));
+            if (WIDE) {
+                z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xaa, 0xf, 0xf, true));
+                z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xff, 0xf, 0xf, true));
+            }
+            z += bias;
+            float a = z, out = z;
+            if (r.act_bound > 0.0f) {
+                a = tanh_fast(z);
+                out = r.act_bound * a;
+            }
+            if (lane < 4 * r.da && sl == 0) {
+                xS[M + o] = (double)out;
+                aS[o] = a;
+            }
+            if (lane < M) xS[lane] = s;
+        }
+        double Am[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) Am[d] = AS[ml][d];
+        __syncthreads();
+        const double xl = xS[lane & 15];
+        double x[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) x[d] = from_lane(xl, d);
+
+        // ---- terms of the kernel rows and features ---------------------------------------------------------------------
+        double q = 0.0;                      // lane m
+#pragma unroll
+        for (int d = 0; d < D; ++d) q = fma(Am[d] * x[d], x[d], q);
+        const unsigned far = (unsigned)__ballot(q < -131072.0);            // outputs whose kernel row is zero (see gp_step.hip)
+        {
+            int nk = kchunks, nf = fchunks;
+            asm volatile("" : "+s"(nk), "+s"(nf));
+            asm volatile("" : "+s"(ec.c7), "+s"(ec.c5), "+s"(ec.c4), "+s"(ec.c3), "+s"(ec.c2), "+s"(ec.c1), "+s"(ec.c0));
+            double *kout = terms + my_points, *fout = terms + my_features;
+            auto exponent = [&](int i) {
+                double e = from_lane(q, __builtin_amdgcn_readlane(m_of_chunk, i)) + row[i][D];
+#pragma unroll
+                for (int d = 0; d < D; ++d) e = fma(x[d], row[i][d], e);
+                return e;
+            };
+            auto point = [&](int i, double e) { kout[i * (NW * CHUNK)] = (double)weight[i] * exp2_poly(e, ec); };
+            auto phase = [&](int j) {
+                double z = x[0] * row[E - 1 - j][0];
+#pragma unroll
+                for (int d = 1; d < D; ++d) z = fma(x[d], row[E - 1 - j][d], z);
+                return z + row[E - 1 - j][D];
+            };
+            auto feature = [&](int j, double z) {
+                const float y = (float)__builtin_amdgcn_fract(z);
+                *reinterpret_cast<float2 *>(fout + j * (NW * CHUNK)) = make_float2(weight[E - 1 - j], __builtin_amdgcn_cosf(y));
+            };
+            // (nested, so that a wave leaves with one branch after its last chunk)
+            auto points = [&](auto self, auto slot) {
+                constexpr int i = decltype(slot)::value;
+                if constexpr (i < E) {
+                    if (i >= nk) return;
+                    if (i + 1 < E && i + 1 < nk) {
+                        const double e0 = exponent(i), e1 = exponent(i + 1);
+                        double k0, k1;
+                        exp2_poly2(e0, e1, ec, k0, k1);
+                        kout[i * (NW * CHUNK)] = (double)weight[i] * k0;
+                        kout[(i + 1) * (NW * CHUNK)] = (double)weight[i + 1] * k1;
+                        self(self, std::integral_constant<int, i + 2>{});
+                    } else {
+                        point(i, exponent(i));
+                    }
+                }
+            };
+            auto features = [&](auto self, auto slot) {
+                constexpr int j = decltype(slot)::value;
+                if constexpr (j < E) {
+                    if (j >= nf) return;
+                    if (j + 1 < E && j + 1 < nf) {
+                        const double z0 = phase(j), z1 = phase(j + 1);
+                        feature(j, z0);
+                        feature(j + 1, z1);
+                        self(self, std::integral_constant<int, j + 2>{});
+                    } else {
+                        feature(j, phase(j));
+                    }
+                }
+            };
+            if (__builtin_expect(far == 0, 1)) {
+                points(points, std::integral_constant<int, 0>{});
+            } else {
+                double outside = -3000.0;
+                asm volatile("" : "+s"(outside));
+#pragma unroll
+                for (int i = 0; i < E; ++i)
+                    if (i < nk) point(i, far >> __builtin_amdgcn_readlane(m_of_chunk, i) & 1 ? outside + row[i][D] : exponent(i));
+            }
+            features(features, std::integral_constant<int, 0>{});
+        }
+        __syncthreads();
+        // ---- sums of the work units, four of them to a group ---------------------------------------------------------
+        if (sum_wave) {
+            double sum = 0.0;
+            constexpr int N4 = CK / 8;       // batches of four reads, the next one under way while one is added up
+            if (wave_kernel) {
+                const double2 *t2 = reinterpret_cast<const double2 *>(terms + unit_at);
+                double2 a[2][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[0][i] = t2[i];
+#pragma unroll
+                for (int n = 0; n < N4; ++n) {
+                    if (n + 1 < N4) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) a[(n + 1) & 1][i] = t2[4 * n + 4 + i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        sum += a[n & 1][i].x;
+                        sum += a[n & 1][i].y;
+                    }
+                }
+            } else {
+                const f4v *t2 = reinterpret_cast<const f4v *>(terms + unit_at);
+                float pf = 0.0f;
+                f4v a[2][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[0][i] = t2[i];
+#pragma unroll
+                for (int n = 0; n < N4; ++n) {
+                    if (n + 1 < N4) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) a[(n + 1) & 1][i] = t2[4 * n + 4 + i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        pf = fmaf(a[n & 1][i][0], a[n & 1][i][1], pf);
+                        pf = fmaf(a[n & 1][i][2], a[n & 1][i][3], pf);
+                    }
+                }
+                sum = (double)pf;
+            }
+            if (!unit_live) sum = 0.0;
+            // quad broadcasts: the four units of the group in order
+            double tot = dpp_move<0x00>(sum) + dpp_move<0x55>(sum);
+            tot += dpp_move<0xaa>(sum);
+            tot += dpp_move<0xff>(sum);
+            if ((lane & 3) == 0) gsum[unit_to] = tot;
+        }
+        // ---- meanwhile, what is kept of this step (by the last waves, which mostly have no unit) --------------------------
+        if (wave == 7) {
+            const float f = (float)s;
+            if (lane < M) {
+                if (r.tape_s) (r.tape_s + (size_t)t * M * B)[lane * B + b] = f;
+                if (r.states_out) (r.states_out + (size_t)t * M * B)[b * M + lane] = f;
+            }
+            if (r.keep && lane < r.d_in) (r.h[0] + (size_t)t * r.d_in * B)[lane * B + b] = hin;
+            if (r.xall && lane < D) (r.xall + (size_t)t * B)[(size_t)lane * r.H * B + b] = xl;
+            if (lane < 16) goalS[(t + 1) & 1][lane] = goal_lane ? goal_ahead : 0.0f;
+            if (goal_lane && t + 2 < r.H) goal_ahead = load_pinned(goals + (size_t)(t + 2) * B * r.dg + (b * r.dg + lane - M));
+        }
+        if (wave == 4 && r.keep && lane < r.da) (r.a_slot + (size_t)t * r.da * B)[lane * B + b] = aS[lane];
+        if (r.keep && wave >= 5) {           // waves 5 and 6: activations
+#pragma unroll
+            for (int l = 0; l < 2; ++l)
+                if (l < p.nl - 1 && wave == 6 - l)
+                    for (int u = lane; u < p.width[l + 1]; u += 64)
+                        (r.h[l + 1] + (size_t)t * p.width[l + 1] * B)[u * B + b] = act[l][act_place(u)];
+        }
+        __syncthreads();
+        // ---- state s_{t+1}: lanes 2 m add up the kernel rows of output m, lanes 2 m + 1 its features (8 sums, then the rest: see
+        // step_tail16_kernel) ------------------------------------------------------------------------------------------
+        float goal_next;
+        {
+            goal_next = goalS[(t + 1) & 1][lane & 15];
+            const double2 *g2 = reinterpret_cast<const double2 *>(gsum + min(lane, 2 * M - 1) * r.GS);
+            double tot = 0.0, rest = 0.0;
+            for (int c0 = 0; c0 < r.GS; c0 += 8) {
+                double2 a[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[i] = g2[c0 / 2 + i];
+                double v = c0 > 0 ? rest : 0.0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v += a[i].x;
+                    v += a[i].y;
+                }
+                if (c0 > 0) rest = v;
+                else tot = v;
+            }
+            if ((lane & 1 ? ngl : ngk) > 8) tot = tot + rest;
+            const double k = shuffle(tot, 2 * ml), e = shuffle(tot, 2 * ml + 1);
+            s += amp_lane * e + k;
+        }
+        if (wave == 4) {                                                   // cost of s_{t+1} against goal t
+            double e = 0.0;
+            for (int j = 0; j < r.dg; ++j) {
+                const double gt = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(goal), M + j));
+                const double dlt = from_lane(s, r.tracked[j]) - gt;
+                e += (double)r.q[j] * dlt * dlt;
+            }
+            if (r.cost_kind == 1) {
+                const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
+                e = -exp(-e / (2.0 * sr2));
+            }
+            cost += e;
+        }
+        goal = lane < 16 ? goal_next : 0.0f;
+        if (++t == r.H) break;
+    }
+    if (wave == 7 && lane < M) {
+        const float f = (float)s;
+        if (r.tape_s) (r.tape_s + (size_t)t * M * B)[lane * B + b] = f;
+        if (r.states_out) (r.states_out + (size_t)t * M * B)[b * M + lane] = f;
+    }
+    if (wave == 4 && lane == 0) r.lpt[b] = cost;
+}
+
+int point_chunks(const bagel_ctx *c) { return c->M * ((c->Np + 63) / 64); }
+int feature_chunks(const bagel_ctx *c) { return (c->M * c->Lp + 63) / 64; }
+
+policy_shape shape(const bagel_ctx *c)
+{
+    policy_shape p = {};
+    p.nl = c->n_layers;
+    for (int i = 0; i < 4; ++i) p.width[i] = c->width[i];
+    p.fs = p.nl == 3 ? slice_blocks(p.width[2], p.width[1]) : 0;
+    return p;
+}
+
+size_t lds_bytes(const bagel_ctx *c)
+{
+    return sizeof(double) * (size_t)(point_chunks(c) + feature_chunks(c)) * (64 / c->CK) * (c->CK + 2) + sizeof(float) * (c->p16 == 2 ? policy_weights<true>::FLOATS : policy_weights<false>::FLOATS);
+}
+
+int sums_room(const bagel_ctx *c) { return ((c->nck > c->ncl ? c->nck : c->ncl) + 31) / 32 * 8; }
+
+template <int D>
+bool chunks_fit(const bagel_ctx *c)
+{
+    for (int w = 0; w < NW; ++w)
+        if ((point_chunks(c) - w + NW - 1) / NW + (feature_chunks(c) - (NW - 1 - w) + NW - 1) / NW > chunks_per_wave<D>()) return false;
+    return true;
+}
+
+template <int D, int CK, bool WIDE>
+hipError_t raise_lds(size_t lds)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(rollout_kernel<D, CK, WIDE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+}
+
+template <int D, int CK, bool WIDE>
+hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const float *s0, const float *goals)
+{
+    hipLaunchKernelGGL((rollout_kernel<D, CK, WIDE>), dim3(c->dm.B), dim3(NT), lds_bytes(c), c->stream, r, shape(c), theta, c->Xs, c->Os,
+                       c->A, c->amp, reinterpret_cast<const float *>(c->v4), reinterpret_cast<const float *>(c->w4), s0, goals);
+    return hipGetLastError();
+}
+
+// the instance f<D, CK, WIDE> for the context
+#define FOR_CONTEXT(c, f, ...) \
+    ((c)->CK == 32 ? ((c)->p16 == 2 ? f<D, 32, true>(__VA_ARGS__) : f<D, 32, false>(__VA_ARGS__)) \
+                   : ((c)->p16 == 2 ? f<D, 64, true>(__VA_ARGS__) : f<D, 64, false>(__VA_ARGS__)))
+template <int D>
+hipError_t raise_lds(const bagel_ctx *c) { return FOR_CONTEXT(c, raise_lds, LDS_BYTES); }
+template <int D>
+hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const float *s0, const float *goals)
+{
+    return FOR_CONTEXT(c, launch, c, r, theta, s0, goals);
+}
+
+#define ROLLOUT_INPUTS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+
+}  // namespace
+
+// Whether rollouts take one workgroup per trajectory: where the rows of all points and features fit the registers of a compute
+// unit (about 8000 pairs of an output and a point or feature at D = 3, 6000 at D = 5, 4000 at D = 8), the policy is one of up to 128
+// units (its weights lie in LDS) and three rounds of workgroups do (one workgroup per compute unit at a time).  Measured on
+// MI355X, 60 steps, a gradient call / a forward pass in us, step by step -> here: M = 2, N = 2200, L = 1024, 64-64 at B = 100
+// 959 -> 382 / 766 -> 198, B = 512 937 -> 681 / 729 -> 391, B = 768 1046 -> 947 / 773 -> 586, B = 1024 1085 -> 1203 / 868 -> 778;
+// M = 4, N = 512, L = 1024, 128-128 at B = 256 972 -> 508 / 711 -> 193, B = 640 1101 -> 1046 / 720 -> 558, B = 1024 1206 -> 1374 /
+// 768 -> 742; M = 6, d_a = 2, N = L = 256, 8-8 at B = 16 766 -> 272 / 640 -> 139, B = 768 912 -> 751 / 671 -> 415.
+void bagel_plan_rollout(bagel_ctx *c)
+{
+    c->rollout = false;
+    if (c->exp_table || !(c->p16 == 1 || c->p16 == 2)) return;
+    if (c->CK != c->CL || (c->CK != 32 && c->CK != 64)) return;
+    const int ngk = (c->nck + 3) / 4, ngl = (c->ncl + 3) / 4;
+    if (((4 * c->M * ngk + 63) & ~63) + 4 * c->M * ngl > NT) return;       // one work unit a thread
+    if (2 * c->M * sums_room(c) >= MAX_SUMS || lds_bytes(c) > LDS_BYTES) return;
+    const int want = bagel_env_int("BAGEL_ROLLOUT", 0);                    // 1: never, 2: wherever it fits, otherwise by size
+    if (want == 1 || (want != 2 && c->dm.B > 768)) return;
+    switch (c->D) {
+#define FITS(d) case d: c->rollout = chunks_fit<d>(c); break;
+        ROLLOUT_INPUTS(FITS)
+#undef FITS
+    }
+}
+
+hipError_t bagel_raise_rollout_lds(bagel_ctx *c)
+{
+    switch (c->D) {
+#define RAISE(d) case d: return raise_lds<d>(c);
+        ROLLOUT_INPUTS(RAISE)
+#undef RAISE
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t bagel_launch_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states_out, bool tape, bool acts)
+{
+    rollout_args r = {};
+    r.B = c->dm.B; r.S = c->dm.S; r.per_sample = c->dm.B / c->dm.S; r.H = c->dm.H; r.M = c->M; r.da = c->dm.d_a;
+    r.Np = c->Np; r.Lp = c->Lp; r.nck = c->nck; r.ncl = c->ncl; r.GS = sums_room(c);
+    r.KC = point_chunks(c); r.FC = feature_chunks(c);
+    r.d_in = c->d_in; r.dg = c->dm.d_g; r.cost_kind = c->dm.cost_kind; r.keep = acts ? 1 : 0;
+    for (int l = 0; l < 3; ++l) { r.w_off[l] = c->w_off[l]; r.b_off[l] = c->b_off[l]; }
+    for (int j = 0; j < 8; ++j) { r.tracked[j] = c->dm.tracked[j]; r.q[j] = c->dm.q[j]; }
+    r.act_bound = c->dm.act_bound; r.sigma_r = c->dm.sigma_r;
+    r.tape_s = tape ? c->tape_s : nullptr;
+    r.states_out = states_out;
+    for (int l = 0; l < 3; ++l) r.h[l] = l < c->n_layers ? c->tape_h[l] : nullptr;
+    r.a_slot = c->tape_a;
+    r.lpt = c->lpt;
+    r.xall = tape ? c->xall : nullptr;
+    switch (c->D) {
+#define LAUNCH(d) case d: return launch<d>(c, r, theta, s0, goals);
+        ROLLOUT_INPUTS(LAUNCH)
+#undef LAUNCH
+    }
+    return hipErrorInvalidValue;
+}

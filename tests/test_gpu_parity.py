@@ -406,6 +406,47 @@ def test_policy_kernels_of_both_widths_agree_and_repeat(hidden, sh, monkeypatch)
                 np.testing.assert_array_equal(r[k], runs[0][k], err_msg=f"B={B} ckpt={ckpt} {k}")
 
 
+# d_s, d_a, d_g, N, L, B, samples, H, hidden, bound, saturating, ckpt: the smallest sizes, whole and ragged tiles, both unit sizes, every
+# input dimension, one to four slices of a contraction, policy inputs past eight, shared samples, the most a compute unit holds
+ROLLOUTS = [(1, 1, 1, 1, 1, 1, 1, 1, (1,), 0.0, False, 0), (2, 1, 1, 65, 33, 3, 1, 2, (8, 8), 1.0, False, 0),
+            (2, 2, 2, 2048, 300, 5, 5, 4, (65,), 0.0, False, 0), (2, 2, 2, 300, 1000, 19, 19, 5, (128, 128), 0.7, False, 2),
+            (4, 1, 1, 512, 1024, 65, 65, 3, (64, 64), 0.0, False, 0), (4, 2, 3, 127, 96, 33, 11, 7, (100, 37), 0.8, True, 3),
+            (6, 1, 2, 129, 64, 17, 17, 6, (33, 5), 0.0, False, 4), (6, 2, 6, 256, 256, 16, 2, 5, (16,), 0.5, False, 0),
+            (4, 4, 1, 63, 200, 9, 9, 5, (37, 100), 0.0, True, 0), (1, 7, 1, 320, 31, 7, 7, 5, (80, 20), 0.6, False, 0),
+            (3, 2, 1, 96, 97, 40, 40, 5, (96, 96), 0.0, False, 0), (5, 1, 5, 31, 32, 12, 6, 9, (128, 30), 0.9, False, 4),
+            (2, 1, 2, 2200, 1024, 30, 30, 12, (8, 8), 1.0, False, 0), (7, 1, 7, 160, 100, 8, 8, 5, (120, 128), 0.0, False, 0)]
+
+
+@pytest.mark.parametrize("sh", ROLLOUTS)
+def test_rollout_with_one_workgroup_per_trajectory_gives_the_same_bits(sh, monkeypatch):
+    """A rollout step by step and with one workgroup per trajectory: every output of a gradient call and of a forward pass is the
+    same to the last bit, also for trajectories far outside the data, infinite or not a number."""
+    from paper_2202_13638_amd import binding
+    d_s, d_a, d_g, N, L, B, S, H, hidden, bound, saturating, ckpt = sh
+    cfg = synth.Config("wg1", 23, d_s, d_a, d_g, N, L, B, H, hidden, bound, "sinusoid", "steps", ckpt, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg, S=S) if S != B else synth.make_inputs(cfg)
+    kind = dict(cost_kind=1, sigma_r=0.7) if saturating else {}
+    v = (0.3 * np.random.default_rng(8).standard_normal((S, cfg.M, N))).astype(np.float32)
+    for scale in (1.0, 500.0):
+        if scale > 1.0:
+            # 500 length scales out for output 0 only; one trajectory infinite, one not a number
+            inp["lengthscale"][0] /= np.float32(scale)
+            if B > 2:
+                inp["s0"][1, 0], inp["s0"][2, -1] = np.inf, np.nan
+        runs, held = {}, {}
+        for env in ("1", "2"):
+            monkeypatch.setenv("BAGEL_ROLLOUT", env)
+            ctx = binding.Bagel(binding.dims_from_config(cfg, S=S, **kind))
+            held[env] = ctx.workspace_bytes()
+            ctx.close()
+            runs[env] = [harness.gpu_rollout(cfg, inp, v, S=S, grad=grad, **kind) for grad in (True, False)]
+        assert held["2"] > held["1"]                     # (the rollout has buffers of its own)
+        for a, b in zip(runs["1"], runs["2"]):
+            assert scale > 1.0 or np.isfinite(a["states"]).all()
+            for k in a:
+                np.testing.assert_array_equal(b[k], a[k], err_msg=f"{k} scale {scale}")
+
+
 def test_rollout_with_table_exp2(monkeypatch):
     """The exp2 form of large launches, forced at a size the oracle finishes in seconds."""
     monkeypatch.setenv("BAGEL_EXP_TABLE", EXP2_FORMS["table"])
