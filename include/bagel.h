@@ -58,6 +58,8 @@
  *   BAGEL_POLICY_TILE      16 or 32: trajectories per workgroup of the policy kernels; unset: by widths and batch
  *   BAGEL_ROLLOUT          1: rollouts always step by step, 2: with one workgroup per trajectory wherever a trajectory's share
  *                          of the model fits a compute unit, unset: by batch size (same results to the last bit)
+ *   BAGEL_BACKWARD         1: backward pass of narrow policies always by a sweep, 2: always with its steps side by side (up to two
+ *                          actions), unset: by size (by a sweep if BAGEL_POLICY_TILE is set)
  *   BAGEL_SETUP_OUTPUTS    most GP outputs a set-up call works on at once; fewer need less work space (default: all)
  *   BAGEL_KSPLIT           split of the weight-gradient contraction (default 256)
  */
@@ -97,7 +99,8 @@ typedef struct {
                                 time and recomputed segment by segment in the backward sweep from the kept
                                 states; the states and the Jacobians of the sample evaluation
                                 (d_s + d_s (d_s + d_a) floats per trajectory and step) are kept for the
-                                whole horizon.  Results are identical.  The per-segment tapes exist
+                                whole horizon.  Results are identical.  (Where a segment is small, K is
+                                rounded up to a multiple of at least 16 steps.)  The per-segment tapes exist
                                 twice, and the backward pass of a gradient call uses a second stream
                                 owned by the context beside the caller's (forked after the forward pass,
                                 joined before the call's last kernel is ordered on the caller's stream):

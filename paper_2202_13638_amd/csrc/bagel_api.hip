@@ -81,7 +81,7 @@ static void free_all(bagel_ctx *c)
                     c->tape_s, c->tape_J, c->tape_h_set[0][0], c->tape_h_set[0][1], c->tape_h_set[0][2], c->tape_a_set[0],
                     c->tape_d_set[0][0], c->tape_d_set[0][1], c->tape_d_set[0][2], c->tape_h_set[1][0], c->tape_h_set[1][1],
                     c->tape_h_set[1][2], c->tape_a_set[1], c->tape_d_set[1][0], c->tape_d_set[1][1], c->tape_d_set[1][2], c->wpack16, c->wpad_f, c->wpad_b, c->gsplit, c->gacc, c->gtheta, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums,
-                    c->xall, c->part_all};
+                    c->xall, c->part_all, c->adjoint_steps, c->lam_steps};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -103,24 +103,38 @@ static void destroy_side(bagel_ctx *c)
     if (c->side) { (void)hipStreamDestroy(c->side); c->side = nullptr; }
 }
 
-// What rollouts with one workgroup per trajectory need beside the rest; where that does not fit, they are done step by step.
-static void plan_rollout_buffers(bagel_ctx *c)
+// Two buffers of one way to do something; where they do not fit, *way becomes false and it is done the other way.
+static void alloc_or_drop(bagel_ctx *c, bool *way, double **p, size_t np, double **q, size_t nq)
 {
+    const int64_t bytes = c->bytes;
+    hipError_t e = dev_alloc(c, p, np);
+    if (e == hipSuccess) e = dev_alloc(c, q, nq);
+    if (e == hipSuccess) return;
+    if (*p) (void)hipFree(*p);
+    *p = *q = nullptr;
+    c->bytes = bytes;
+    *way = false;
+    (void)hipGetLastError();
+}
+
+static void alloc_backward_buffers(bagel_ctx *c)
+{
+    const size_t per_step = (size_t)c->dm.B * c->M, T = (size_t)c->T_tape;
+    alloc_or_drop(c, &c->backward_parallel, &c->adjoint_steps, (BAGEL_CHAIN_AHEAD + T) * per_step * (c->M + 1), &c->lam_steps, T * per_step);
+}
+
+static void alloc_rollout_buffers(bagel_ctx *c)
+{
+    if (bagel_raise_rollout_lds(c) != hipSuccess) {
+        c->rollout = false;
+        (void)hipGetLastError();
+        return;
+    }
     // the Jacobians of as many steps at a time as have 64 MB of sums (that fills the chip, and the sums stay on it)
     const size_t B = (size_t)c->dm.B, H = (size_t)c->dm.H, per_step = (size_t)c->groups * (1 + c->D) * B;
     const size_t most = ((size_t)64 << 20) / (per_step * sizeof(double));
     c->rollout_steps = (int)(most < 1 ? 1 : (most < H ? most : H));
-    const int64_t bytes = c->bytes;
-    hipError_t e = dev_alloc(c, &c->xall, H * c->D * B);
-    if (e == hipSuccess) e = dev_alloc(c, &c->part_all, (size_t)c->rollout_steps * per_step);
-    if (e == hipSuccess) e = bagel_raise_rollout_lds(c);
-    if (e == hipSuccess) return;
-    if (c->xall) (void)hipFree(c->xall);
-    if (c->part_all) (void)hipFree(c->part_all);
-    c->xall = c->part_all = nullptr;
-    c->bytes = bytes;
-    c->rollout = false;
-    (void)hipGetLastError();
+    alloc_or_drop(c, &c->rollout, &c->xall, H * c->D * B, &c->part_all, (size_t)c->rollout_steps * per_step);
 }
 
 extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_stream)
@@ -150,6 +164,13 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     c->T_tape = (K > 0 && K < H) ? K : H;
     bagel_plan_policy(c);
     bagel_plan_rollout(c);
+    bagel_plan_backward(c);
+    if (c->backward_parallel && c->T_tape < H && c->T_tape < BAGEL_SHORTEST_SEGMENT) {
+        // Short segments are put together: a few steps do not pay for their launches, and with these batches and policies a
+        // segment of this length is a few megabytes.
+        c->T_tape *= (BAGEL_SHORTEST_SEGMENT + K - 1) / K;
+        if (c->T_tape > H) c->T_tape = H;
+    }
     c->ksplit = bagel_env_int("BAGEL_KSPLIT", 256);
     c->setup_outputs = bagel_env_int("BAGEL_SETUP_OUTPUTS", BAGEL_MAX_STATE);
     int wf_total = 0, wb_total = 0;
@@ -202,7 +223,8 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     ALLOC(c->gacc, (size_t)c->P);
     ALLOC(c->gtheta, (size_t)c->P);
 #undef ALLOC
-    if (e == hipSuccess && c->rollout) plan_rollout_buffers(c);
+    if (e == hipSuccess && c->backward_parallel) alloc_backward_buffers(c);
+    if (e == hipSuccess && c->rollout) alloc_rollout_buffers(c);
     if (e == hipSuccess) {
         // table of the sample-evaluation kernel's table form: -2^(i/256), high word lowered by i << 12
         uint64_t tab[256];
@@ -489,6 +511,7 @@ static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s
 
 static hipError_t backward_sweep(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
 {
+    if (c->backward_parallel) return bagel_launch_backward_parallel(c, t_lo, t_hi, goals, grad_s0);
     return c->p16 == 1 || c->p16 == 2 ? bagel_launch_backward_sweep16(c, t_lo, t_hi, goals, grad_s0)
                                       : bagel_launch_backward_sweep(c, t_lo, t_hi, goals, grad_s0);
 }

@@ -78,6 +78,9 @@ struct bagel_ctx {
     int p16;                     // policy kernels: 0 policy.hip, 1 .. 3 an instance of policy16.hip
     int pack16_floats;
     float *wpack16;              // packed weights of policy16.hip
+    bool backward_parallel;      // backward pass by backward.hip instead of a sweep
+    double *adjoint_steps;       // [BAGEL_CHAIN_AHEAD + T][B][d_s][d_s + 1]: its linear map of a step (null without)
+    double *lam_steps;           // [T][B][d_s]: adjoints of the states of all steps
     float *gsplit;               // [ksplit][P] split-contraction partial weight gradients
     double *gacc;                // [P] gradient accumulated over segments
     float *gtheta;               // [P] gradient of the current iteration of bagel_optimize
@@ -103,6 +106,8 @@ struct bagel_ctx {
     hipEvent_t *prof_ev;         // 2 * BAGEL_PROF_MAX events, created on enable
 };
 #define BAGEL_PROF_MAX 4096
+#define BAGEL_CHAIN_AHEAD 16
+#define BAGEL_SHORTEST_SEGMENT 16       // steps of a checkpointed segment, with backward_parallel
 
 // K sums of n[k] terms p[k][0] + p[k][stride] + ... each added in order, W loads of every sum in flight at a time: the
 // sums of a step's work units are a chain of trips to memory, one per W terms.
@@ -205,6 +210,11 @@ hipError_t bagel_launch_step_tail16(bagel_ctx *ctx, int t, int slot, int next_sl
                                     const float *goals, float *states_out, bool direct);
 hipError_t bagel_launch_policy_replay16(bagel_ctx *ctx, int t0, int t1, const float *goals);
 hipError_t bagel_launch_backward_sweep16(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
+
+// ---- backward.hip (contexts with backward_parallel) -----------------------------------------
+void bagel_plan_backward(bagel_ctx *ctx);
+// the same role as bagel_launch_backward_sweep
+hipError_t bagel_launch_backward_parallel(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
 
 // ---- rollout.hip (contexts with rollout) ---------------------------------------------------
 // sets rollout from the sizes; the work decomposition and the policy kernels are planned before

@@ -21,6 +21,16 @@ __host__ __device__ inline int slice_blocks(int rows, int k)
 
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+constexpr int PL = 16;                       // trajectories per workgroup
+constexpr int HS = 20;                       // LDS row length of the policy input and the action adjoint
+
+template <int NW, int NT>
+struct shape16 {
+    static constexpr int TT = NW * NT;       // row tiles of a hidden layer
+    static constexpr int ROWS = 4 * NW;      // thread rows of 16 trajectories
+    static constexpr int AS = 16 * TT + 4;   // LDS row length of the activations: rows start 4 banks apart
+};
+
 // Offsets inside the packed weights, in floats (see pack_theta16_kernel)
 struct pack16 {
     int nl, TT, nsi, nsa;                    // nsi, nsa: instructions for a contraction over the inputs / actions
@@ -58,6 +68,79 @@ __device__ __forceinline__ double load_pinned(const double *p)
 {
     const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     return __longlong_as_double((long long)v);
+}
+
+// (p[0] + .. + p[7]) + (p[8] + p[9] + ...): the order in which step_tail_kernel adds n group sums
+template <class P>
+__device__ __forceinline__ double sum_groups16(P p, int n, size_t stride)
+{
+    double s = 0.0, rest = 0.0;
+    for (int c0 = 0; c0 < n; c0 += 8) {
+        double v[8], t = 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = c0 + u < n ? p[(size_t)(c0 + u) * stride] : 0.0;
+        if (c0 > 0) t = rest;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t += v[u];
+        if (c0 > 0) rest = t;
+        else s = t;
+    }
+    return n > 8 ? s + rest : s;
+}
+
+// The ten wait states that the results of v_mfma_f32_16x16x4 want before anything but a matrix instruction reads them.  The compiler
+// places them by itself, but counts wrongly where a result is used behind a branch and again where the branch joins: it takes the
+// longer way round for both.  With two tiles the end of a slice below compiled into that: the last rows of the second tile were
+// read four or five wait states after the instruction, and a backward sweep built that way gave other gradients from run to
+// run.  tests/test_matrix_wait_states.py follows every path of the compiled kernels.  (No cost: 256-256, B = 1024, N = 2048
+// 46.2 us per step with and without.)
+__device__ __forceinline__ void matrix_results_ready(f4v &a, f4v &b) { asm volatile("s_nop 7\n\ts_nop 1" : "+v"(a), "+v"(b)); }
+
+// One contraction over the blocks of a wide layer for the wave's NT tiles: w[t][kb] the weights, act the operands, n inputs,
+// sl blocks per slice; slices are added up in order
+template <int NT, int TT, int AS>
+__device__ __forceinline__ void contract_wide(f4v (&z)[NT], const f4v (&w)[NT][TT], const float *act, int lane, int n, int sl)
+{
+    const float *x0 = act + (lane & 15) * AS + 4 * (lane >> 4);
+    f4v acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) z[t] = acc[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    bool first = true;
+    int left = sl;
+#pragma unroll
+    for (int kb = 0; kb < TT; ++kb)
+        if (16 * kb < n) {
+            const f4v x = *reinterpret_cast<const f4v *>(x0 + 16 * kb);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = mfma16(w[t][kb][s], x[s], acc[t]);
+            if constexpr (NT == 2) matrix_results_ready(acc[0], acc[1]);
+            if (--left == 0 || 16 * (kb + 1) >= n) {                       // end of a slice (wave-uniform)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    z[t] = first ? acc[t] : z[t] + acc[t];
+                    acc[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+                first = false;
+                left = sl;
+            }
+        }
+}
+
+// Slice `wave` (two blocks) of a contraction with one row tile: operands from act
+template <int TT, int AS>
+__device__ __forceinline__ f4v contract_slice(const f4v (&w)[2], const float *act, int wave, int lane)
+{
+    const float *x0 = act + (lane & 15) * AS + 4 * (lane >> 4) + 32 * wave;
+    f4v acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const f4v x = *reinterpret_cast<const f4v *>(x0 + 16 * e);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = mfma16(w[e][s], x[s], acc);
+    }
+    return acc;
 }
 
 }  // namespace

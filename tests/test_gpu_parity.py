@@ -447,6 +447,36 @@ def test_rollout_with_one_workgroup_per_trajectory_gives_the_same_bits(sh, monke
                 np.testing.assert_array_equal(b[k], a[k], err_msg=f"{k} scale {scale}")
 
 
+# d_s, d_a, d_g, B, H, hidden, bound, saturating, ckpt: every number of outputs, both instances of the layers, one and two hidden
+# layers and actions, fewer steps than are requested ahead, as many, and one more, whole and ragged tiles and segments
+BACKWARDS = [(1, 1, 1, 1, 1, (1,), 0.0, False, 0), (2, 1, 2, 16, 16, (16,), 0.0, False, 0), (3, 2, 1, 5, 17, (64, 64), 0.7, False, 0),
+             (4, 1, 1, 19, 33, (33, 5), 0.0, True, 0), (5, 2, 5, 70, 13, (128, 128), 0.0, False, 5), (6, 1, 2, 33, 29, (100, 37), 0.9, True, 13),
+             (7, 2, 7, 17, 20, (65,), 0.5, False, 0), (8, 1, 8, 40, 11, (37, 100), 0.0, False, 0), (8, 2, 3, 16, 25, (8, 8), 1.0, False, 12)]
+
+
+@pytest.mark.parametrize("sh", BACKWARDS)
+def test_backward_pass_with_its_steps_side_by_side(sh, monkeypatch):
+    """The sweep and the backward pass with its steps side by side.  Both round the layers' adjoints to float32 in other places: up
+    to three contractions of 128 terms a step, about sqrt(384) roundings of 2^-24 adding at random, 1.2e-6 of a gradient; what
+    the forward pass returns is the same, and a second call gives the same bits."""
+    d_s, d_a, d_g, B, H, hidden, bound, saturating, ckpt = sh
+    cfg = synth.Config("bwd", 29, d_s, d_a, d_g, 40, 24, B, H, hidden, bound, "sinusoid", "steps", ckpt, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    kind = dict(cost_kind=1, sigma_r=0.7) if saturating else {}
+    v = (0.3 * np.random.default_rng(6).standard_normal((B, cfg.M, cfg.N))).astype(np.float32)
+    runs = []
+    for env in ("1", "2", "2"):
+        monkeypatch.setenv("BAGEL_BACKWARD", env)
+        runs.append(harness.gpu_rollout(cfg, inp, v, **kind))
+    sweep, one, again = runs
+    for k in ("loss", "states", "loss_per_traj"):
+        np.testing.assert_array_equal(one[k], sweep[k])
+    for k in ("grad_theta", "grad_s0"):
+        assert np.isfinite(one[k]).all()
+        np.testing.assert_array_equal(again[k], one[k])
+        assert np.linalg.norm(one[k] - sweep[k]) <= 1.2e-6 * np.linalg.norm(sweep[k]), k
+
+
 def test_rollout_with_table_exp2(monkeypatch):
     """The exp2 form of large launches, forced at a size the oracle finishes in seconds."""
     monkeypatch.setenv("BAGEL_EXP_TABLE", EXP2_FORMS["table"])
