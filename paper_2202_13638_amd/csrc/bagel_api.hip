@@ -496,10 +496,7 @@ static bool whole_rollout(const bagel_ctx *c) { return c->rollout && !c->cur_xi 
 static hipError_t start_rollout(bagel_ctx *c, const float *theta, const float *s0, const float *goals, float *states, bool tape,
                                 bool acts)
 {
-    if (whole_rollout(c)) {
-        const hipError_t e = tape ? bagel_launch_pack_theta16(c, theta) : hipSuccess;   // (for the backward pass)
-        return e == hipSuccess ? bagel_launch_rollout(c, theta, s0, goals, states, tape, acts) : e;
-    }
+    if (whole_rollout(c)) return bagel_launch_rollout(c, theta, s0, goals, states, tape, acts);
     if (c->p16) {
         hipError_t e = bagel_launch_pack_theta16(c, theta);
         if (e == hipSuccess && tape && c->p16 == 3) e = bagel_launch_pack_theta(c, theta);     // for backward_sweep
@@ -603,10 +600,10 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
     // One forward pass with Jacobians.  Without checkpointing it also keeps the policy's activations.
     rc = run_forward(c, true, !ckpt, true, theta, goals, states);
     if (rc != BAGEL_OK) return rc;
-    BAGEL_HIP(c, bagel_launch_finish_loss(c, loss, loss_per_traj));
+    const bagel_loss_args finish = {c->lpt, c->dm.B, loss, loss_per_traj};
     if (!ckpt) {
         BAGEL_HIP(c, backward_sweep(c, 0, H, goals, grad_s0));
-        BAGEL_HIP(c, bagel_launch_weight_grad(c, H, false, grad_theta));
+        BAGEL_HIP(c, bagel_launch_weight_grad(c, H, false, grad_theta, &finish));
         return BAGEL_OK;
     }
     // Checkpointed (Sec. IV-C): what is large, the activations and adjoints of the policy (about 4 KB
@@ -629,7 +626,7 @@ static int rollout_loss_grad_impl(bagel_ctx *c, const char *who, const float *th
         use_tape_set(c, seg & 1);
         c->stream = c->side;
         hipError_t r = replay ? (c->p16 ? bagel_launch_policy_replay16(c, t0, t1, goals) : bagel_launch_policy_replay(c, t0, t1, theta, goals))
-                              : bagel_launch_weight_grad(c, t1 - t0, seg != n_seg - 1, seg == 0 ? grad_theta : nullptr);
+                              : bagel_launch_weight_grad(c, t1 - t0, seg != n_seg - 1, seg == 0 ? grad_theta : nullptr, seg == 0 ? &finish : nullptr);
         c->stream = main_stream;
         if (r == hipSuccess && replay) r = hipEventRecord(c->ev_replay[seg & 1], c->side);
         return r;

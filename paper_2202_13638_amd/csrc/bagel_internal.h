@@ -133,6 +133,38 @@ __device__ __forceinline__ void bagel_sums_in_order(const double *const (&p)[K],
     }
 }
 
+// loss = (1/B) sum_b lpt[b], by one workgroup of 256 threads: 1024 sums over b, b + 1024, ..., added up in a fixed tree
+struct bagel_loss_args {
+    const double *lpt;
+    int B;
+    float *loss, *loss_per_traj;             // loss_per_traj may be null
+};
+__device__ __forceinline__ void bagel_finish_loss(const bagel_loss_args &a)
+{
+    __shared__ double sh[256];
+    const int tid = threadIdx.x;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int b0 = tid; b0 < a.B; b0 += 1024) {
+        double v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = b0 + 256 * k < a.B ? a.lpt[b0 + 256 * k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            acc[k] += v[k];
+            if (a.loss_per_traj && b0 + 256 * k < a.B) a.loss_per_traj[b0 + 256 * k] = (float)v[k];
+        }
+    }
+    acc[0] += acc[2];                        // (the tree's first two levels)
+    acc[1] += acc[3];
+    sh[tid] = acc[0] + acc[1];
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (tid < s) sh[tid] += sh[tid + s];
+        __syncthreads();
+    }
+    if (tid == 0) a.loss[0] = (float)(sh[0] / (double)a.B);
+}
+
 #define BAGEL_FAIL(ctx, code, ...)                                   \
     do {                                                             \
         snprintf((ctx)->err, sizeof((ctx)->err), __VA_ARGS__);      \
@@ -194,7 +226,8 @@ hipError_t bagel_launch_step_tail(bagel_ctx *ctx, int t, int slot, int next_slot
 hipError_t bagel_launch_policy_replay(bagel_ctx *ctx, int t0, int t1, const float *theta, const float *goals);
 // backward sweep over steps t_hi-1 .. t_lo (tape slot of step k is k - t_lo); grad_s0 is written when t_lo == 0
 hipError_t bagel_launch_backward_sweep(bagel_ctx *ctx, int t_lo, int t_hi, const float *goals, float *grad_s0);
-hipError_t bagel_launch_weight_grad(bagel_ctx *ctx, int n_slots, bool accumulate, float *grad_theta);
+// finish (not null): the loss as well, in the same launch
+hipError_t bagel_launch_weight_grad(bagel_ctx *ctx, int n_slots, bool accumulate, float *grad_theta, const bagel_loss_args *finish);
 hipError_t bagel_launch_adam(bagel_ctx *ctx, float *theta, const float *grad, float *m, float *v, int count, double lr,
                              double beta1, double beta2, double eps, double corr1, double corr2);
 
@@ -219,8 +252,11 @@ hipError_t bagel_launch_backward_parallel(bagel_ctx *ctx, int t_lo, int t_hi, co
 // ---- rollout.hip (contexts with rollout) ---------------------------------------------------
 // sets rollout from the sizes; the work decomposition and the policy kernels are planned before
 void bagel_plan_rollout(bagel_ctx *ctx);
+// whether a rollout with work units of `units` points and features may be one of these (from dm, D and M alone)
+bool bagel_rollout_rows_fit(const bagel_ctx *ctx, int units);
 hipError_t bagel_raise_rollout_lds(bagel_ctx *ctx);
-// states, cost per trajectory, state tape and inputs of all steps (tape) and activation tape (acts) of a whole rollout
+// states, cost per trajectory, state tape, inputs of all steps and packed weights for the backward pass (tape) and activation tape
+// (acts) of a whole rollout
 hipError_t bagel_launch_rollout(bagel_ctx *ctx, const float *theta, const float *s0, const float *goals, float *states_out, bool tape, bool acts);
 
 // ---- posterior.hip ------------------------------------------------------------------------

@@ -67,26 +67,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) void init_state_kernel(lane_args a, co
     a.lpt[b] = 0.0;
 }
 
-// loss = (1/B) sum_b lpt[b], summed in a fixed tree order by one workgroup
-__global__ __launch_bounds__(1024) void finish_loss_kernel(const double *__restrict__ lpt, int B,
-                                                           float *__restrict__ loss,
-                                                           float *__restrict__ loss_per_traj)
-{
-    __shared__ double sh[1024];
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < B; b += 1024) {
-        const double v = lpt[b];
-        acc += v;
-        if (loss_per_traj) loss_per_traj[b] = (float)v;
-    }
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) loss[0] = (float)(sh[0] / (double)B);
-}
+__global__ __launch_bounds__(256) void finish_loss_kernel(bagel_loss_args a) { bagel_finish_loss(a); }
 
 // x[B][D] -> xbuf
 __global__ __launch_bounds__(BAGEL_BLOCK) void eval_input_kernel(lane_args a, const float *__restrict__ xin)
@@ -127,7 +108,7 @@ hipError_t bagel_launch_init_state(bagel_ctx *c, const float *s0, const float *g
 
 hipError_t bagel_launch_finish_loss(bagel_ctx *c, float *loss, float *loss_per_traj)
 {
-    hipLaunchKernelGGL(finish_loss_kernel, dim3(1), dim3(1024), 0, c->stream, c->lpt, c->dm.B, loss, loss_per_traj);
+    hipLaunchKernelGGL(finish_loss_kernel, dim3(1), dim3(256), 0, c->stream, bagel_loss_args{c->lpt, c->dm.B, loss, loss_per_traj});
     return hipGetLastError();
 }
 

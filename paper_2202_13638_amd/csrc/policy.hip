@@ -1304,12 +1304,19 @@ __global__ __launch_bounds__(64 * WA * WB) void weight_grad_tiled_kernel(const f
 
 // gacc[p] (+)= sum_z gsplit[z][p]; optionally emit grad_theta = (float) gacc.  64 parameters per workgroup;
 // wave q adds the q-th quarter of the splits in z order, the four quarters are added in order.
+// finish.loss not null: the first workgroup adds up the loss instead (a launch of its own in front of the backward pass took 3 to 5 us).
 __global__ __launch_bounds__(256) void grad_reduce_kernel(const float *__restrict__ gsplit, double *__restrict__ gacc, int P,
-                                                          int ksplit, bool accumulate, float *__restrict__ grad_theta)
+                                                          int ksplit, bool accumulate, float *__restrict__ grad_theta,
+                                                          bagel_loss_args finish)
 {
     __shared__ double sh[4][64];
+    int block = blockIdx.x;
+    if (finish.loss && block-- == 0) {
+        bagel_finish_loss(finish);
+        return;
+    }
     const int lane = threadIdx.x & 63, quarter = threadIdx.x >> 6;
-    const int p = blockIdx.x * 64 + lane;
+    const int p = block * 64 + lane;
     const int per = (ksplit + 3) / 4;
     const int z0 = quarter * per, z1 = min(ksplit, z0 + per);
     double s = 0.0;
@@ -1476,7 +1483,7 @@ hipError_t launch_wg_tiled(bagel_ctx *c, int which, int nz, int l, int no, int n
 }
 }  // namespace
 
-hipError_t bagel_launch_weight_grad(bagel_ctx *c, int n_slots, bool accumulate, float *grad_theta)
+hipError_t bagel_launch_weight_grad(bagel_ctx *c, int n_slots, bool accumulate, float *grad_theta, const bagel_loss_args *finish)
 {
     const int B = c->dm.B;
     const int chunks_per_slot = (B + 7) / 8;
@@ -1521,7 +1528,7 @@ hipError_t bagel_launch_weight_grad(bagel_ctx *c, int n_slots, bool accumulate, 
         else WG(false, 16, 1);
 #undef WG
     }
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3((c->P + 63) / 64), dim3(256), 0, c->stream, c->gsplit, c->gacc, c->P,
-                       nz, accumulate, grad_theta);
+    hipLaunchKernelGGL(grad_reduce_kernel, dim3((c->P + 63) / 64 + (finish ? 1 : 0)), dim3(256), 0, c->stream, c->gsplit, c->gacc, c->P,
+                       nz, accumulate, grad_theta, finish ? *finish : bagel_loss_args{});
     return hipGetLastError();
 }

@@ -53,6 +53,75 @@ inline pack16 make_pack(const bagel_ctx *c)
                   slice_blocks(c->width[1], c->width[2])};
 }
 
+// theta -> the register contents of the lanes.  "tile t" = units 16 t .. of the layer that is produced, lane = 16 g + i
+// with i = 4 gi + ri, u = unit16(gi, ri):
+//   wide contraction   [t][kb][lane][s] = W(16 t + u, 16 kb + unit16(g, s))
+//   narrow contraction [t][s][lane]     = W(16 t + u, unit16(g, s))
+// with W(row, k) the layer's matrix (forward) or its transpose (backward), zero outside it.  Also the biases, padded.
+struct pack16_args {
+    pack16 p;
+    int width[4], w_off[3], b_off[3];
+    float *dst;
+};
+__device__ __forceinline__ void pack_theta16(const pack16_args &a, const float *__restrict__ theta, int idx)
+{
+    const pack16 &p = a.p;
+    if (idx >= p.total()) return;
+    const int (&width)[4] = a.width;
+    const int wo0 = a.w_off[0], wo1 = a.w_off[1], bo0 = a.b_off[0], bo1 = a.b_off[1];
+    const int last = p.nl - 1;
+    const int w_last = last == 2 ? a.w_off[2] : wo1, b_last = last == 2 ? a.b_off[2] : bo1;
+    const int n_last = width[last + 1], h_last = width[last];              // actions, units of the last hidden layer
+    float v = 0.0f;
+    auto wide = [&](int e, int &row, int &k, int kbs) {
+        const int s = e & 3, lane = (e >> 2) & 63, blk = e >> 8;
+        row = 16 * (blk / kbs) + unit16(lane >> 2 & 3, lane & 3);
+        k = 16 * (blk % kbs) + unit16(lane >> 4, s);
+    };
+    auto narrow = [&](int e, int &row, int &k, int ns) {
+        const int lane = e & 63, blk = e >> 6;
+        row = 16 * (blk / ns) + unit16(lane >> 2 & 3, lane & 3);
+        k = unit16(lane >> 4, blk % ns);
+    };
+    int r, k;
+    if (idx < p.f_mid()) {
+        narrow(idx - p.f_first(), r, k, p.nsi);
+        if (r < width[1] && k < width[0]) v = theta[wo0 + r * width[0] + k];
+    } else if (idx < p.f_last()) {
+        wide(idx - p.f_mid(), r, k, p.TT);
+        if (r < width[2] && k < width[1]) v = theta[wo1 + r * width[1] + k];
+    } else if (idx < p.bias(0)) {
+        wide(idx - p.f_last(), r, k, p.TT);
+        if (r < n_last && k < h_last) v = theta[w_last + r * h_last + k];
+    } else if (idx < p.b_top()) {
+        const int e = idx - p.bias(0), l = e / (16 * p.TT), q = e - l * 16 * p.TT;
+        const int u = (q & ~15) + unit16(q >> 2 & 3, q & 3);               // in the order of a lane's registers
+        if (l == 2) v = q < n_last ? theta[b_last + q] : 0.0f;             // the action's bias in the third place, plain
+        else if (l < last && u < width[l + 1]) v = theta[(l == 0 ? bo0 : bo1) + u];
+    } else if (idx < p.b_mid()) {
+        narrow(idx - p.b_top(), r, k, p.nsa);
+        if (r < h_last && k < n_last) v = theta[w_last + k * h_last + r];
+    } else if (idx < p.b_first()) {
+        wide(idx - p.b_mid(), r, k, p.TT);
+        if (r < width[1] && k < width[2]) v = theta[wo1 + k * width[1] + r];
+    } else {
+        wide(idx - p.b_first(), r, k, p.TT);
+        if (r < width[0] && k < width[1]) v = theta[wo0 + k * width[0] + r];
+    }
+    a.dst[idx] = v;
+}
+
+inline pack16_args make_pack_args(const bagel_ctx *c)
+{
+    pack16_args a = {make_pack(c), {}, {}, {}, c->wpack16};
+    for (int i = 0; i < 4; ++i) a.width[i] = c->width[i];
+    for (int l = 0; l < 3; ++l) {
+        a.w_off[l] = c->w_off[l];
+        a.b_off[l] = c->b_off[l];
+    }
+    return a;
+}
+
 // tanh in float32, 1 - 2 / (e^{2z} + 1): see policy.hip
 __device__ __forceinline__ float tanh_fast(float z)
 {

@@ -40,58 +40,9 @@ __device__ __forceinline__ int first_trajectory()
     return (x * q + min(x, r) + ((int)blockIdx.x >> 3)) * PL;
 }
 
-// theta -> the register contents of the lanes.  "tile t" = units 16 t .. of the layer that is produced, lane = 16 g + i
-// with i = 4 gi + ri, u = unit16(gi, ri):
-//   wide contraction   [t][kb][lane][s] = W(16 t + u, 16 kb + unit16(g, s))
-//   narrow contraction [t][s][lane]     = W(16 t + u, unit16(g, s))
-// with W(row, k) the layer's matrix (forward) or its transpose (backward), zero outside it.  Also the biases, padded.
-__global__ __launch_bounds__(256) void pack_theta16_kernel(const float *__restrict__ theta, float *__restrict__ dst, pack16 p, int w0,
-                                                           int w1, int w2, int w3, int wo0, int wo1, int wo2, int bo0, int bo1,
-                                                           int bo2)
+__global__ __launch_bounds__(256) void pack_theta16_kernel(pack16_args a, const float *__restrict__ theta)
 {
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= p.total()) return;
-    const int width[4] = {w0, w1, w2, w3};
-    const int last = p.nl - 1;
-    const int w_last = last == 2 ? wo2 : wo1, b_last = last == 2 ? bo2 : bo1;
-    const int n_last = width[last + 1], h_last = width[last];              // actions, units of the last hidden layer
-    float v = 0.0f;
-    auto wide = [&](int e, int &row, int &k, int kbs) {
-        const int s = e & 3, lane = (e >> 2) & 63, blk = e >> 8;
-        row = 16 * (blk / kbs) + unit16(lane >> 2 & 3, lane & 3);
-        k = 16 * (blk % kbs) + unit16(lane >> 4, s);
-    };
-    auto narrow = [&](int e, int &row, int &k, int ns) {
-        const int lane = e & 63, blk = e >> 6;
-        row = 16 * (blk / ns) + unit16(lane >> 2 & 3, lane & 3);
-        k = unit16(lane >> 4, blk % ns);
-    };
-    int r, k;
-    if (idx < p.f_mid()) {
-        narrow(idx - p.f_first(), r, k, p.nsi);
-        if (r < width[1] && k < width[0]) v = theta[wo0 + r * width[0] + k];
-    } else if (idx < p.f_last()) {
-        wide(idx - p.f_mid(), r, k, p.TT);
-        if (r < width[2] && k < width[1]) v = theta[wo1 + r * width[1] + k];
-    } else if (idx < p.bias(0)) {
-        wide(idx - p.f_last(), r, k, p.TT);
-        if (r < n_last && k < h_last) v = theta[w_last + r * h_last + k];
-    } else if (idx < p.b_top()) {
-        const int e = idx - p.bias(0), l = e / (16 * p.TT), q = e - l * 16 * p.TT;
-        const int u = (q & ~15) + unit16(q >> 2 & 3, q & 3);               // in the order of a lane's registers
-        if (l == 2) v = q < n_last ? theta[b_last + q] : 0.0f;             // the action's bias in the third place, plain
-        else if (l < last && u < width[l + 1]) v = theta[(l == 0 ? bo0 : bo1) + u];
-    } else if (idx < p.b_mid()) {
-        narrow(idx - p.b_top(), r, k, p.nsa);
-        if (r < h_last && k < n_last) v = theta[w_last + k * h_last + r];
-    } else if (idx < p.b_first()) {
-        wide(idx - p.b_mid(), r, k, p.TT);
-        if (r < width[1] && k < width[2]) v = theta[wo1 + k * width[1] + r];
-    } else {
-        wide(idx - p.b_first(), r, k, p.TT);
-        if (r < width[0] && k < width[1]) v = theta[wo0 + k * width[0] + r];
-    }
-    dst[idx] = v;
+    pack_theta16(a, theta, blockIdx.x * 256 + threadIdx.x);
 }
 
 // The weights of the forward pass a wave multiplies with
@@ -677,10 +628,8 @@ void bagel_plan_policy(bagel_ctx *c)
 
 hipError_t bagel_launch_pack_theta16(bagel_ctx *c, const float *theta)
 {
-    const pack16 p = make_pack(c);
-    hipLaunchKernelGGL(pack_theta16_kernel, dim3((p.total() + 255) / 256), dim3(256), 0, c->stream, theta, c->wpack16, p, c->width[0],
-                       c->width[1], c->width[2], c->width[3], c->w_off[0], c->w_off[1], c->w_off[2], c->b_off[0], c->b_off[1],
-                       c->b_off[2]);
+    const pack16_args a = make_pack_args(c);
+    hipLaunchKernelGGL(pack_theta16_kernel, dim3((a.p.total() + 255) / 256), dim3(256), 0, c->stream, a, theta);
     return hipGetLastError();
 }
 

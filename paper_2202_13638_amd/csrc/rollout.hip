@@ -100,6 +100,7 @@ struct rollout_args {
     float *h[3], *a_slot;                    // activation tapes (keep)
     double *lpt;
     double *xall;                            // [D][H][B], inputs of every step for the Jacobians, null: not kept
+    pack16_args pack;                        // for the workgroups past the trajectories
 };
 
 __device__ __forceinline__ double shuffle(double v, int lane)
@@ -124,12 +125,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     __shared__ double AS[8][D];              // -1/2 A
     __shared__ float goalS[2][16], aS[8];    // goals of the next step and this one (lane M + j: entry M + j), action tape
     __shared__ __align__(16) float act[2][144];
+    // Workgroups past the trajectories pack the weights for the backward pass (a launch of its own in front took 4.7 us)
+    if ((int)blockIdx.x >= r.B) {
+        pack_theta16(r.pack, theta, ((int)blockIdx.x - r.B) * NT + (int)threadIdx.x);
+        return;
+    }
     int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroups of one chiplet (they go to the eight in turn) take neighbouring trajectories: these share the lines of a tape row
     int b;
     {
-        const int n = gridDim.x, x = blockIdx.x & 7, q = n >> 3, rest = n & 7;
+        const int n = r.B, x = blockIdx.x & 7, q = n >> 3, rest = n & 7;
         b = x * q + (x < rest ? x : rest) + ((int)blockIdx.x >> 3);
     }
     const int B = r.B, M = r.M, sample = b / r.per_sample;
@@ -550,7 +556,7 @@ hipError_t raise_lds(size_t lds)
 template <int D, int CK, bool WIDE>
 hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const float *s0, const float *goals)
 {
-    hipLaunchKernelGGL((rollout_kernel<D, CK, WIDE>), dim3(c->dm.B), dim3(NT), lds_bytes(c), c->stream, r, shape(c), theta, c->Xs, c->Os,
+    hipLaunchKernelGGL((rollout_kernel<D, CK, WIDE>), dim3(c->dm.B + (r.pack.dst ? (r.pack.p.total() + NT - 1) / NT : 0)), dim3(NT), lds_bytes(c), c->stream, r, shape(c), theta, c->Xs, c->Os,
                        c->A, c->amp, reinterpret_cast<const float *>(c->v4), reinterpret_cast<const float *>(c->w4), s0, goals);
     return hipGetLastError();
 }
@@ -621,6 +627,7 @@ hipError_t bagel_launch_rollout(bagel_ctx *c, const float *theta, const float *s
     r.a_slot = c->tape_a;
     r.lpt = c->lpt;
     r.xall = tape ? c->xall : nullptr;
+    if (tape) r.pack = make_pack_args(c);
     switch (c->D) {
 #define LAUNCH(d) case d: return launch<d>(c, r, theta, s0, goals);
         ROLLOUT_INPUTS(LAUNCH)
