@@ -67,8 +67,8 @@ __device__ __forceinline__ v4f stream_load(__amdgpu_buffer_rsrc_t desc, unsigned
 
 // End of a workgroup: waves 1-3 hand their sums (value u, Jacobian sums G) to wave 0 through LDS slots
 // 0-2, wave 0 adds them in wave order and writes the group's partial sum.  in_lds: every wave, wave 0
-// included (slot 3), has already stored its sums (the feature units of a Jacobian launch).
-template <int D, bool JAC, int RC>
+// included (slot 3), has already stored its sums (the feature units of a Jacobian launch).  VALUE: with the value sum.
+template <int D, bool JAC, int RC, bool VALUE = true>
 __device__ __forceinline__ void combine_waves(double (*red)[RC][64], int wave, int lane, bool live, double *out, int B,
                                               bool in_lds, double u, double (&G)[D])
 {
@@ -82,20 +82,20 @@ __device__ __forceinline__ void combine_waves(double (*red)[RC][64], int wave, i
     __syncthreads();
     if (wave == 0) {
         if (in_lds) {
-            u = red[3][0][lane];
+            if (VALUE) u = red[3][0][lane];
 #pragma unroll
             for (int d = 0; d < D; ++d) G[d] = red[3][1 + d][lane];
         }
 #pragma unroll
         for (int w = 0; w < 3; ++w) {
-            u += red[w][0][lane];
+            if (VALUE) u += red[w][0][lane];
             if (JAC) {
 #pragma unroll
                 for (int d = 0; d < D; ++d) G[d] += red[w][1 + d][lane];
             }
         }
         if (live) {
-            out[0] = u;
+            if (VALUE) out[0] = u;
             if (JAC) {
 #pragma unroll
                 for (int d = 0; d < D; ++d) out[(size_t)(1 + d) * B] = G[d];
@@ -232,8 +232,10 @@ __device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, 
     }
 }
 
-// n_iter float4 of random features (a multiple of 4): see the feature loops of the kernel
-template <int D, bool JAC>
+// n_iter float4 of random features (a multiple of 4): see the feature loops of the kernel.  Without VALUE the Jacobian sums
+// alone: the steps of a rollout by rollout.hip have their values, and the cosines are a sixth of the work (100 steps, B = 256,
+// N = 512, L = 1024, D = 5: 133.9 us a launch without, 139.6 with them).
+template <int D, bool JAC, bool VALUE>
 __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __amdgpu_buffer_rsrc_t wdesc, unsigned woff, unsigned wstep,
                                               __amdgpu_buffer_rsrc_t odesc, unsigned ooff, unsigned ostep, int n_iter,
                                               const double (&x)[D], float &p, f4v (&acc)[(D + 3) / 4])
@@ -254,8 +256,10 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
         z0 += r0[D];
         z1 += r1[D];
         const float y0 = (float)__builtin_amdgcn_fract(z0), y1 = (float)__builtin_amdgcn_fract(z1);
-        p = fmaf(w0, __builtin_amdgcn_cosf(y0), p);
-        p = fmaf(w1, __builtin_amdgcn_cosf(y1), p);
+        if (VALUE) {
+            p = fmaf(w0, __builtin_amdgcn_cosf(y0), p);
+            p = fmaf(w1, __builtin_amdgcn_cosf(y1), p);
+        }
         if (JAC) {
             const float s0 = w0 * __builtin_amdgcn_sinf(y0), s1 = w1 * __builtin_amdgcn_sinf(y1);
 #pragma unroll
@@ -544,7 +548,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
 #pragma unroll
             for (int qd = 0; qd < NQ; ++qd) acc[qd] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
             if constexpr (!NEAR && D <= 8) {
-                if (n_iter > 0) feature_pairs<D, true>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc);
+                if (n_iter > 0) feature_pairs<D, true, !STEPS>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc);
             } else {
                 const int last = n_iter - 1;         // CL is a multiple of 16: two float4 per trip, no branch
                 auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
@@ -601,7 +605,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
             // every wave, wave 0 included, hands its sums over through LDS: that is also the transposition
             // from the accumulator layout (lane = column, register = trajectory) to lane = trajectory
             const int slot = (wave + 3) & 3;
-            red[slot][0][lane] = (double)p;
+            if (!STEPS) red[slot][0][lane] = (double)p;
 #pragma unroll
             for (int qd = 0; qd < NQ; ++qd) {
                 const int d = 4 * qd + (lane & 3);
@@ -611,7 +615,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
                 }
             }
             double u = 0.0, G[D];
-            combine_waves<D, JAC, RC>(red, wave, lane, live, out, B, true, u, G);
+            combine_waves<D, JAC, RC, !STEPS>(red, wave, lane, live, out, B, true, u, G);
         } else {
             if constexpr (!NEAR && D <= 8) {
                 f4v none[NQ];
