@@ -611,16 +611,16 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 // 22.4 / 13.5 us, B = 2048 46.5 / 37.6, B = 8192 109 / 100, B = 32768 406 / 377, B = 65536 (16 to a sample) 678 / 614; one layer of
 // 16 at B = 8192 100 / 96, B = 65536 630 / 583; 128-128 (N = 4096, L = 2048) at B = 4096 113 / 102, at B = 8192
 // 188 / 183; 256-256 at B = 1024 55.6 / 48.0, B = 2048 67.1 / 61.0 (checkpointed 71.5 / 66.9), B = 4096 (N = 4096) 131.7 /
-// 128.4, forward pass with 16 trajectories per sample there 64.0 / 57.7.  Wider policies on larger batches fill the chip with
-// 32 trajectories per workgroup, and fetching the weights twice as often costs what the shorter chain gives: forward and
-// backward pass at 256-256, B = 8192 (N = 8192) 580 / 601, checkpointed (N = 4096) 244 / 260, and already at B = 4096
-// checkpointed 64.2 / 64.6 ms a call of 500 steps.
+// 128.4 (checkpointed, 500 steps 127.1 / 123.2), forward pass with 16 trajectories per sample there 64.0 / 57.7.  Wider policies on
+// larger batches fill the chip with 32 trajectories per workgroup, and fetching the weights twice as often costs what the
+// shorter chain gives: N = 2048, B = 6144 256-256 118.0 / 120.4, 192-192 108.7 / 112.6, checkpointed 126.2 / 127.3 and 116.9 / 119.9,
+// B = 8192 checkpointed 157.0 / 160.1, 128-128 127.3 / 116.3.
 void bagel_plan_policy(bagel_ctx *c)
 {
     int w = 0;
     for (int l = 1; l < c->n_layers; ++l) w = c->width[l] > w ? c->width[l] : w;
     c->p16 = w <= 64 ? 1 : (w <= 128 ? 2 : 3);
-    const int most = c->p16 == 3 ? (c->T_tape < c->dm.H ? 2048 : 4096) : 8192;
+    const int most = c->p16 == 3 ? 4096 : 8192;
     const int tile = bagel_env_int("BAGEL_POLICY_TILE", 0);                // 16 or 32: always that one, otherwise by size
     if (tile == 32 || (tile != 16 && c->p16 != 1 && c->dm.B > most)) c->p16 = 0;
     c->pack16_floats = c->p16 ? make_pack(c).total() : 0;
