@@ -619,7 +619,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
         } else {
             if constexpr (!NEAR && D <= 8) {
                 f4v none[NQ];
-                if (n_iter > 0) feature_pairs<D, false>(Or, wdesc, woff, wstep, wdesc, 0u, 0u, n_iter, x, p, none);
+                if (n_iter > 0) feature_pairs<D, false, true>(Or, wdesc, woff, wstep, wdesc, 0u, 0u, n_iter, x, p, none);
             } else {
                 // value only: the same pipeline without the Jacobian sums
                 const int last = n_iter - 1;
@@ -708,6 +708,42 @@ int bagel_env_int(const char *name, int dflt)
     return v > 0 ? v : dflt;
 }
 
+// The units of a launch of few workgroups (fewer than 1024: all of them are on the chip at once, the point-by-point loops in pairs).
+// Its time is that of the fullest compute unit, or, where a compute unit has one or two workgroups, of the longest unit: a wave
+// alone on its SIMD waits for its own chain.  So the pair (CK, CL) is taken whose fullest compute unit, with the workgroups
+// dealt out in turn, has the least to do.  Costs are in instructions per lane: 2 D + 18 a point, 1.6 times the D + 9 + 4 ceil(D / 4) of a
+// feature (sines and cosines issue slower), 500 a workgroup, 40 a partial sum (the end-of-step kernel adds them up).  Fitted
+// to 17 problems timed at up to 87 pairs each (B = 100 .. 4096, N = 512 .. 8000, L = 256 .. 4096, D = 3 .. 8): the pair taken is on
+// average 2.8 % of a step from the best one, units of 32 or 64 were 13 % from it.  us a step of a gradient call, before and after:
+// M = 4, N = L = 2048, B = 1024 26.6 -> 24.6 (128 and 64 instead of 64 and 64), M = 3, N = 1533, L = 901, B = 777 21.7 -> 18.6 (48, 48),
+// M = 5, N = 4000, L = 2000, B = 640 36.6 -> 32.2 (128, 80), M = 4, N = 5000, L = 3000, B = 400 27.7 -> 25.4 (96, 64).
+static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *CL)
+{
+    const int sizes[] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
+    const int64_t tiles = (int64_t)M * ((B + 63) / 64), point = 2 * D + 18, feature5 = 8 * (D + 9 + 4 * ((D + 3) / 4));
+    int64_t least = INT64_MAX;
+    for (const int ck : sizes)
+        for (const int cl : sizes) {
+            if (cl > 2 * ck || ck > 4 * cl) continue;
+            const int64_t gk = ((N + ck - 1) / ck + 3) / 4, gl = ((L + cl - 1) / cl + 3) / 4, wk = tiles * gk, w = wk + tiles * gl;
+            if (w >= 1024) continue;
+            const int64_t tk = ck * point, tl = cl * feature5 / 5;
+            int64_t fullest = 0;             // the load changes only where a kind's last round ends
+            for (const int64_t cu : {(int64_t)0, wk & 255, w & 255}) {
+                const int64_t nk = (wk - cu + 255) / 256, n = (w - cu + 255) / 256, load = nk * (tk + 500) + (n - nk) * (tl + 500);
+                if (load > fullest) fullest = load;
+            }
+            const int64_t longest = tk > tl ? tk : tl;
+            if (fullest < longest * 14 / 5) fullest = longest * 14 / 5;
+            const int64_t cost = fullest + longest / 5 + 40 * M * (gk + gl);
+            if (cost < least) {
+                least = cost;
+                *CK = ck;
+                *CL = cl;
+            }
+        }
+}
+
 // Work decomposition of one sample evaluation (sets CK, CL, nck, ncl, Np, Lp, units, groups and the
 // exp2 form from dm, D, M); returns a message if the problem cannot be decomposed.
 const char *bagel_plan_sample_eval(bagel_ctx *c)
@@ -724,19 +760,20 @@ const char *bagel_plan_sample_eval(bagel_ctx *c)
     // ones for the features of a large problem: workgroups are dispatched in grid order, training-point
     // units first, so short feature units at the end fill the tail of the launch.  Measured on MI355X:
     // stress 0.650 ms per launch at (CK, CL) = (1024, 512), 0.628 ms at (1024, 256); the large-policy
-    // step 140.6 ms at (128, 64), 136.8 ms at (256, 64).
-    // A launch that stays under the target even with the smallest chunk has only a handful of waves per
-    // SIMD, and the longest of them sets its duration (measured: launch time grows in proportion to
-    // CK), so its units are kept short and alike: medium 10.7 ms per call at (128, 32), 9.7 ms at
-    // (64, 64); small 3.78 ms at (64, 32), 3.46 ms at (32, 32).  (Staging the operand rows through LDS
-    // and look-ahead loads of the stream changed nothing there: those launches are not latency-bound.)
+    // step 140.6 ms at (128, 64), 136.8 ms at (256, 64).  Features in units of 32 pay only where there are few of them: M = 4,
+    // N = L = 2048, B = 2048 44.1 us a step at (128, 32), 41.6 at (128, 64), N = L = 1024, B = 4096 46.8 and 43.3, N = 8192, L = 4096,
+    // B = 1024 58.4 and 56.4, but M = 3, N = 1024, L = 512, B = 8192 47.9 and 48.7.
     const bool small_launch = chunk == 32 && items / chunk < target;
-    const int ck_default = small_launch ? (N / chunk >= 64 ? 64 : 32)
-                                        : (N / chunk >= 32 ? 4 * chunk : (N / chunk >= 16 ? 2 * chunk : chunk));
-    const int cl_default = small_launch ? (N / chunk >= 64 ? 64 : 32)
-                                        : ((chunk >= 512 && L / chunk >= 8) ? chunk / 2 : chunk);
-    c->CK = bagel_env_int("BAGEL_CK", ck_default);
-    c->CL = bagel_env_int("BAGEL_CL", cl_default);
+    int ck = N / chunk >= 32 ? 4 * chunk : (N / chunk >= 16 ? 2 * chunk : chunk);
+    int cl = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : (chunk == 32 && L >= 1024 ? 64 : chunk);
+    if (small_launch) {
+        // equal units of 32 or 64 where a rollout may take one workgroup per trajectory (rollout.hip; whether it does depends on more,
+        // but results must not), the best pair otherwise
+        ck = cl = N / chunk >= 64 ? 64 : 32;
+        if (!bagel_rollout_rows_fit(c, ck)) small_launch_units(c->D, M, N, L, B, &ck, &cl);
+    }
+    c->CK = bagel_env_int("BAGEL_CK", ck);
+    c->CL = bagel_env_int("BAGEL_CL", cl);
     c->CK = (c->CK + 15) & ~15;       // the sample-evaluation loops take two or four float4 (eight or sixteen points) per trip
     c->CL = (c->CL + 15) & ~15;
     c->nck = (N + c->CK - 1) / c->CK;

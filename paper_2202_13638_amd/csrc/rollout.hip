@@ -520,8 +520,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     if (wave == 4 && lane == 0) r.lpt[b] = cost;
 }
 
-int point_chunks(const bagel_ctx *c) { return c->M * ((c->Np + 63) / 64); }
-int feature_chunks(const bagel_ctx *c) { return (c->M * c->Lp + 63) / 64; }
+#define ROLLOUT_INPUTS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+
+int point_chunks(int M, int Np) { return M * ((Np + 63) / 64); }
+int feature_chunks(int M, int Lp) { return (M * Lp + 63) / 64; }
+int point_chunks(const bagel_ctx *c) { return point_chunks(c->M, c->Np); }
+int feature_chunks(const bagel_ctx *c) { return feature_chunks(c->M, c->Lp); }
 
 policy_shape shape(const bagel_ctx *c)
 {
@@ -537,15 +541,32 @@ size_t lds_bytes(const bagel_ctx *c)
     return sizeof(double) * (size_t)(point_chunks(c) + feature_chunks(c)) * (64 / c->CK) * (c->CK + 2) + sizeof(float) * (c->p16 == 2 ? policy_weights<true>::FLOATS : policy_weights<false>::FLOATS);
 }
 
-int sums_room(const bagel_ctx *c) { return ((c->nck > c->ncl ? c->nck : c->ncl) + 31) / 32 * 8; }
+int sums_room(int nck, int ncl) { return ((nck > ncl ? nck : ncl) + 31) / 32 * 8; }
+int sums_room(const bagel_ctx *c) { return sums_room(c->nck, c->ncl); }
 
 template <int D>
-bool chunks_fit(const bagel_ctx *c)
+bool chunks_fit(int points, int features)
 {
     for (int w = 0; w < NW; ++w)
-        if ((point_chunks(c) - w + NW - 1) / NW + (feature_chunks(c) - (NW - 1 - w) + NW - 1) / NW > chunks_per_wave<D>()) return false;
+        if ((points - w + NW - 1) / NW + (features - (NW - 1 - w) + NW - 1) / NW > chunks_per_wave<D>()) return false;
     return true;
 }
+
+// the trips of a compute unit's registers and sums suffice for units of CK points and CK features
+bool rows_fit(const bagel_ctx *c, int CK)
+{
+    const int M = c->M, nck = (c->dm.N + CK - 1) / CK, ncl = (c->dm.L + CK - 1) / CK, ngk = (nck + 3) / 4, ngl = (ncl + 3) / 4;
+    if (((4 * M * ngk + 63) & ~63) + 4 * M * ngl > NT) return false;       // one work unit a thread
+    if (2 * M * sums_room(nck, ncl) >= MAX_SUMS) return false;
+    switch (c->D) {
+#define FITS(d) case d: return chunks_fit<d>(point_chunks(M, nck * CK), feature_chunks(M, ncl * CK));
+        ROLLOUT_INPUTS(FITS)
+#undef FITS
+    }
+    return false;
+}
+
+constexpr int MOST_TRAJECTORIES = 768;       // of a rollout with one workgroup each (see bagel_plan_rollout)
 
 template <int D, int CK, bool WIDE>
 hipError_t raise_lds(size_t lds)
@@ -573,8 +594,6 @@ hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const
     return FOR_CONTEXT(c, launch, c, r, theta, s0, goals);
 }
 
-#define ROLLOUT_INPUTS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
-
 }  // namespace
 
 // Whether rollouts take one workgroup per trajectory: where the rows of all points and features fit the registers of a compute
@@ -584,21 +603,19 @@ hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const
 // 959 -> 382 / 766 -> 198, B = 512 937 -> 681 / 729 -> 391, B = 768 1046 -> 947 / 773 -> 586, B = 1024 1085 -> 1203 / 868 -> 778;
 // M = 4, N = 512, L = 1024, 128-128 at B = 256 972 -> 508 / 711 -> 193, B = 640 1101 -> 1046 / 720 -> 558, B = 1024 1206 -> 1374 /
 // 768 -> 742; M = 6, d_a = 2, N = L = 256, 8-8 at B = 16 766 -> 272 / 640 -> 139, B = 768 912 -> 751 / 671 -> 415.
+bool bagel_rollout_rows_fit(const bagel_ctx *c, int units)
+{
+    return (c->dm.B <= MOST_TRAJECTORIES || bagel_env_int("BAGEL_ROLLOUT", 0) == 2) && rows_fit(c, units);
+}
+
 void bagel_plan_rollout(bagel_ctx *c)
 {
     c->rollout = false;
     if (c->exp_table || !(c->p16 == 1 || c->p16 == 2)) return;
     if (c->CK != c->CL || (c->CK != 32 && c->CK != 64)) return;
-    const int ngk = (c->nck + 3) / 4, ngl = (c->ncl + 3) / 4;
-    if (((4 * c->M * ngk + 63) & ~63) + 4 * c->M * ngl > NT) return;       // one work unit a thread
-    if (2 * c->M * sums_room(c) >= MAX_SUMS || lds_bytes(c) > LDS_BYTES) return;
+    if (!rows_fit(c, c->CK) || lds_bytes(c) > LDS_BYTES) return;
     const int want = bagel_env_int("BAGEL_ROLLOUT", 0);                    // 1: never, 2: wherever it fits, otherwise by size
-    if (want == 1 || (want != 2 && c->dm.B > 768)) return;
-    switch (c->D) {
-#define FITS(d) case d: c->rollout = chunks_fit<d>(c); break;
-        ROLLOUT_INPUTS(FITS)
-#undef FITS
-    }
+    c->rollout = want == 2 || (want != 1 && c->dm.B <= MOST_TRAJECTORIES);
 }
 
 hipError_t bagel_raise_rollout_lds(bagel_ctx *c)

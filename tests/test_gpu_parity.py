@@ -232,6 +232,15 @@ def test_sample_eval_unit_sizes(ck, cl, d_s, d_a, monkeypatch):
     _check_sample_eval(shape, x)
 
 
+@pytest.mark.parametrize("d_s,d_a,N,L,B,S", [(4, 1, 900, 1100, 1024, 64), (2, 1, 1300, 900, 2400, 48), (6, 2, 1000, 500, 1024, 64),
+                                             (5, 2, 544, 809, 3136, 56)])
+def test_sample_eval_units_by_size(d_s, d_a, N, L, B, S):
+    """Pairs of unit sizes that a launch of few workgroups takes by itself: (80, 64), (48, 80), (64, 32) and (160, 128), last units and
+    last workgroups partly filled."""
+    x = np.random.default_rng(N).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
+    _check_sample_eval(dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S), x)
+
+
 @pytest.mark.parametrize("form", list(EXP2_FORMS))
 def test_sample_eval_inputs_far_from_the_data(form, monkeypatch):
     """GP inputs hundreds of length scales away from every training point: the kernel row is zero
