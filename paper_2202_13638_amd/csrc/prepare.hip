@@ -483,21 +483,35 @@ __global__ __launch_bounds__(256) void chol_step_kernel(factor_args f, int k, in
 
 // ---- products -----------------------------------------------------------------------------------------------------
 // C (ni x nj) -= or = sum_k A[k][i] B[k][j] for every output (blockIdx.z); upper: tiles that lie below the diagonal
-// of C are left out.
+// of C are left out (ni <= nj), and the others are numbered row by row, the outputs of a tile one after the other (blockIdx.x).  Workgroups
+// go to the eight chiplets in turn: with a grid of all tiles, a chiplet had whole columns and so up to 1.4 times its share
+// of the tiles (16 x 16 tiles of 64, K = 1024, four outputs: 167 us, 104 so).
 struct gemm_args {
     const double *A, *B;
     double *C;
     size_t lda, ldb, ldc, sA, sB, sC;
     int ni, nj, K;
-    int subtract, upper;
+    int subtract, upper, outputs;            // outputs: set by gemm()
 };
+
+template <int T>
+__device__ __forceinline__ void upper_tile(const gemm_args &g, int &i, int &j, int &o)
+{
+    const int columns = (g.nj + T - 1) / T;
+    int t = blockIdx.x / g.outputs, row = 0;
+    o = blockIdx.x - t * g.outputs;
+    while (t >= columns - row) t -= columns - row++;
+    i = row;
+    j = row + t;
+}
 
 template <int T>
 __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_kernel(gemm_args g)
 {
     __shared__ __align__(16) double lds[f64_tile::shape<T>::LDS_DOUBLES];
-    const int i0 = blockIdx.y * T, j0 = blockIdx.x * T, o = blockIdx.z;
-    if (g.upper && j0 + T <= i0) return;
+    int ti = blockIdx.y, tj = blockIdx.x, o = blockIdx.z;
+    if (g.upper) upper_tile<T>(g, ti, tj, o);
+    const int i0 = ti * T, j0 = tj * T;
     f64_tile::accumulators<T> acc;
     f64_tile::clear(acc);
     f64_tile::product<T>(acc, lds, i0, j0, g.ni, g.nj, g.K, g.A + o * g.sA, g.lda, g.B + o * g.sB, g.ldb);
@@ -523,15 +537,21 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 3) void gemm_kernel(gemm_args g
             }
 }
 
-void gemm(hipStream_t st, int outputs, const gemm_args &g)
+template <int T>
+void launch_gemm(hipStream_t st, const gemm_args &g, long ti, long tj)
+{
+    const dim3 grid = g.upper ? dim3((ti * tj - ti * (ti - 1) / 2) * g.outputs) : dim3(tj, ti, g.outputs);
+    hipLaunchKernelGGL(gemm_kernel<T>, grid, dim3(256), 0, st, g);
+}
+
+void gemm(hipStream_t st, int outputs, gemm_args g)
 {
     if (g.ni <= 0 || g.nj <= 0 || g.K <= 0) return;
+    g.outputs = outputs;
     const long ti = (g.ni + 127) / 128, tj = (g.nj + 127) / 128;
     const long tiles = outputs * (g.upper ? ti * tj - ti * (ti - 1) / 2 : ti * tj);
-    if (f64_tile::whole_passes(tiles))
-        hipLaunchKernelGGL(gemm_kernel<128>, dim3(tj, ti, outputs), dim3(256), 0, st, g);
-    else
-        hipLaunchKernelGGL(gemm_kernel<64>, dim3((g.nj + 63) / 64, (g.ni + 63) / 64, outputs), dim3(256), 0, st, g);
+    if (f64_tile::whole_passes(tiles)) launch_gemm<128>(st, g, ti, tj);
+    else launch_gemm<64>(st, g, (g.ni + 63) / 64, (g.nj + 63) / 64);
 }
 
 // ---- inverse of the factor -----------------------------------------------------------------------------------------
@@ -539,8 +559,10 @@ void gemm(hipStream_t st, int outputs, const gemm_args &g)
 // shorter), with U = [U11 U12; 0 U22], V = U^-1, W = V^T and the diagonal blocks of V and W known,
 //   first launch   T[j][i] = sum_c U12[c][j] W11[c][i]            (T = (W11 ... )^T, c >= i)
 //   second launch  W21[j][i] = - sum_c V22[c][j] T[c][i] = V12[i][j]  (c <= j)
-// blockIdx.z = output * pairs + pair; T goes to the lower triangle of K.  Every level is two launches for all pairs and
-// outputs: log2(N / 64) of them instead of a chain of N / 64 block solves.
+// blockIdx.y = output * pairs + pair; T goes to the lower triangle of K.  Every level is two launches for all pairs and
+// outputs: log2(N / 64) of them instead of a chain of N / 64 block solves.  The sums differ in length: blockIdx.z counts from
+// the longest to the shortest, so that these fill the end of the launch and every chiplet has some of each (top level
+// of N = 2048, four outputs: 134 and 110 us for the two, 81 and 84 so).
 struct level_args {
     const double *U;
     double *T;
@@ -553,10 +575,11 @@ template <bool SECOND>
 __global__ __launch_bounds__(256, 3) void inverse_level_kernel(level_args a)
 {
     __shared__ __align__(16) double lds[f64_tile::shape<64>::LDS_DOUBLES];
-    const int o = blockIdx.z / a.pairs, p = blockIdx.z - o * a.pairs;
+    const int o = blockIdx.y / a.pairs, p = blockIdx.y - o * a.pairs;
     const int r1 = 2 * p * a.h * NB, r2 = r1 + a.h * NB;                     // first rows of the two blocks
     const int n2 = min(a.h * NB, a.Np - r2);
-    const int j0 = blockIdx.y * NB, i0 = blockIdx.x * NB;                    // row of block 2, column of block 1
+    // row of block 2 and column of block 1: the first product is the longer the smaller i0, the second the larger j0
+    const int j0 = NB * (SECOND ? a.h - 1 - (int)blockIdx.z : (int)blockIdx.x), i0 = NB * (SECOND ? blockIdx.x : blockIdx.z);
     if (j0 >= n2) return;
     const size_t Np = a.Np;
     f64_tile::accumulators<64> acc;
@@ -635,7 +658,7 @@ struct solver {
         for (int h = 1; h < size && h < nb; h *= 2) {
             const int pairs = (nb + h - 1) / (2 * h);
             level_args a = {f.U, f.K, f.sU, f.sK, f.V, f.W, f.Np, h, pairs};
-            const dim3 grid(h, h, outputs * pairs);
+            const dim3 grid(h, outputs * pairs, h);
             hipLaunchKernelGGL(inverse_level_kernel<false>, grid, dim3(256), 0, st, a);
             hipLaunchKernelGGL(inverse_level_kernel<true>, grid, dim3(256), 0, st, a);
         }
