@@ -743,13 +743,13 @@ __device__ __forceinline__ void inverse_tile(f64_tile::accumulators<64> &acc, do
     f64_tile::product<64>(acc, lds, NB * bi, NB * bj, Np, Np, Np - NB * bi, Wk, W.ld, Wk, W.ld);
 }
 
-// K_hat^-1, both triangles (the posterior cache)
-__global__ __launch_bounds__(256, 3) void inverse_store_kernel(tri_matrix W, double *__restrict__ Kinv, int Np)
+// K_hat^-1, both triangles (the posterior cache); the outputs of a tile one after the other (see hyper_grad_tiles_kernel)
+__global__ __launch_bounds__(256, 3) void inverse_store_kernel(tri_matrix W, double *__restrict__ Kinv, int Np, int outputs)
 {
     __shared__ __align__(16) double lds[f64_tile::shape<64>::LDS_DOUBLES];
-    const int o = blockIdx.y;
+    const int tile = blockIdx.x / outputs, o = blockIdx.x - tile * outputs;
     int bi, bj;
-    lower_tile(blockIdx.x, bi, bj);
+    lower_tile(tile, bi, bj);
     f64_tile::accumulators<64> acc;
     inverse_tile(acc, lds, W, o, Np, bi, bj);
     const f64_tile::lane_pos pos = f64_tile::lane_position<64>();
@@ -800,19 +800,21 @@ __global__ __launch_bounds__(256) void hyper_lml_kernel(const double *__restrict
 // dK/dlog l_d = K (x_d - x'_d)^2 / l_d^2, dK/dlog alpha^2 = K, dK_hat/dlog sigma_n^2 = sigma_n^2 I).  The tile of
 // K_hat^-1 is formed here and never written: only these sums of it are needed.  Tiles off the diagonal count
 // twice.  The sums are added over a lane's entries, the lanes (fixed butterfly) and the four waves in order.
+// The outputs of a tile come one after the other, so that the longest sums of all outputs are started first and the launch ends
+// with the shortest (N = 2048, four outputs: output after output 270 us, so 238).
 // Three workgroups per compute unit as long as the sums fit their 168 registers: beyond D = 13 they do not, and D = 16 kept 93
 // in scratch memory (a call at N = 2048, 8 outputs: 2930 us, 2620 with two workgroups).
 template <int D>
 __global__ __launch_bounds__(256, D <= 13 ? 3 : 2) void hyper_grad_tiles_kernel(const float *__restrict__ X, const float *__restrict__ log_hyp,
                                                                   tri_matrix W, const double *__restrict__ alpha,
-                                                                  double *__restrict__ partial, int N, int Np, int m0)
+                                                                  double *__restrict__ partial, int N, int Np, int m0, int outputs)
 {
     constexpr int LQ = NB + 1, NEED = NB * LQ + 2 * NB * (D + 1) + 4 * (D + 2);
     constexpr int HAVE = f64_tile::shape<64>::LDS_DOUBLES;
     __shared__ __align__(16) double lds[NEED > HAVE ? NEED : HAVE];
-    const int o = blockIdx.y;
+    const int tile = blockIdx.x / outputs, o = blockIdx.x - tile * outputs;
     int bi, bj;
-    lower_tile(blockIdx.x, bi, bj);
+    lower_tile(tile, bi, bj);
     f64_tile::accumulators<64> acc;
     inverse_tile(acc, lds, W, o, Np, bi, bj);
     // the tile, and inputs and alpha of its rows and columns, into the LDS the product is done with: thread = column
@@ -875,7 +877,7 @@ __global__ __launch_bounds__(256, D <= 13 ? 3 : 2) void hyper_grad_tiles_kernel(
     const int c = threadIdx.x;
     if (c < D + 2) {
         const double tot = ((sums[c] + sums[(D + 2) + c]) + sums[2 * (D + 2) + c]) + sums[3 * (D + 2) + c];
-        partial[((size_t)o * gridDim.x + blockIdx.x) * (D + 2) + c] = bi == bj ? tot : 2.0 * tot;
+        partial[((size_t)o * (gridDim.x / outputs) + tile) * (D + 2) + c] = bi == bj ? tot : 2.0 * tot;
     }
 }
 
@@ -1225,8 +1227,8 @@ int bagel_prepare_posterior_impl(bagel_ctx *c, const float *X, const float *y, c
         build_and_factor(s, X, h, N, D, m0);
         s.triangular_inverse(s.nb);
         inverse_vectors(s, y, N, m0, vec, c->post_alpha + (size_t)m0 * Np);
-        hipLaunchKernelGGL(inverse_store_kernel, dim3(s.nb * (s.nb + 1) / 2, s.outputs), dim3(256), 0, st, s.f.W,
-                           c->post_Kinv + (size_t)m0 * Np * Np, Np);
+        hipLaunchKernelGGL(inverse_store_kernel, dim3(s.nb * (s.nb + 1) / 2 * s.outputs), dim3(256), 0, st, s.f.W,
+                           c->post_Kinv + (size_t)m0 * Np * Np, Np, s.outputs);
         P_HIP(hipGetLastError());
     }
     P_HIP(read_flags(st, flag, M, &bad, &pivot));
@@ -1243,12 +1245,12 @@ done:
 static void launch_hyper_grad(const solver &s, int D, const float *X, const float *log_hyp, const double *alpha, double *partial,
                               int N, int m0)
 {
-    const dim3 grid(s.nb * (s.nb + 1) / 2, s.outputs);
+    const dim3 grid(s.nb * (s.nb + 1) / 2 * s.outputs);
     switch (D) {
 #define CASE(n)                                                                                                                \
     case n:                                                                                                                    \
         hipLaunchKernelGGL(hyper_grad_tiles_kernel<n>, grid, dim3(256), 0, s.st, X, log_hyp, s.f.W, alpha, partial, N, \
-                           s.f.Np, m0);                                                                                        \
+                           s.f.Np, m0, s.outputs);                                                                             \
         break;
         CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8) CASE(9) CASE(10) CASE(11) CASE(12)
         CASE(13) CASE(14) CASE(15) CASE(16)
