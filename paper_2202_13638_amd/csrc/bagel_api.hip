@@ -153,7 +153,7 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
     layer_layout(dims, c->width, c->w_off, c->b_off, &c->P);
     c->stream = (hipStream_t)hip_stream;
 
-    if (const char *msg = bagel_plan_sample_eval(c)) {     // msg is a string literal: it outlives c
+    if (const char *msg = bagel_plan_sample_eval(c, false)) {     // msg is a string literal: it outlives c
         delete c;
         CREATE_FAIL(BAGEL_EINVAL, "bagel_create: %s", msg);
     }
@@ -365,7 +365,7 @@ static int64_t static_scratch_bytes(const bagel_dims *dims)
     c.dm = *dims;
     c.D = dims->d_s + dims->d_a;
     c.M = dims->d_s;
-    if (bagel_plan_sample_eval(&c)) return BAGEL_EINVAL;
+    if (bagel_plan_sample_eval(&c, true)) return BAGEL_EINVAL;
     const int64_t M = c.M, D = c.D, B = dims->B, S = dims->S;
     const int64_t counts[] = {8 * M * c.Np * (D + 1), 8 * M * c.Lp * (D + 1), 16 * M * c.Lp * ((D + 3) / 4), 8 * M * D, 8 * M,
                               16 * M * (c.Np / 4) * S, 16 * M * (c.Lp / 4) * S, 8 * D * B,
@@ -400,7 +400,7 @@ extern "C" int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream
     c.D = dims->d_s + dims->d_a;
     c.M = dims->d_s;
     c.stream = (hipStream_t)hip_stream;
-    (void)bagel_plan_sample_eval(&c);             // cannot fail: static_scratch_bytes has planned the same dims
+    (void)bagel_plan_sample_eval(&c, true);             // cannot fail: static_scratch_bytes has planned the same dims
     c.exp_table = false;                    // the table form of exp2 reads a table this call does not have
     const size_t M = c.M, D = c.D, B = dims->B, S = dims->S;
     size_t off = 0;

@@ -745,8 +745,9 @@ static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *
 }
 
 // Work decomposition of one sample evaluation (sets CK, CL, nck, ncl, Np, Lp, units, groups and the
-// exp2 form from dm, D, M); returns a message if the problem cannot be decomposed.
-const char *bagel_plan_sample_eval(bagel_ctx *c)
+// exp2 form from dm, D, M); returns a message if the problem cannot be decomposed.  plain: without what the unit sizes of small
+// launches and of features were refined by (bagel_sample_eval_static, whose fixed scratch array decides which sizes it takes).
+const char *bagel_plan_sample_eval(bagel_ctx *c, bool plain)
 {
     // work decomposition of one sample evaluation: power-of-two chunk of training points / features
     const bagel_dims *dims = &c->dm;
@@ -765,12 +766,12 @@ const char *bagel_plan_sample_eval(bagel_ctx *c)
     // B = 1024 58.4 and 56.4, but M = 3, N = 1024, L = 512, B = 8192 47.9 and 48.7.
     const bool small_launch = chunk == 32 && items / chunk < target;
     int ck = N / chunk >= 32 ? 4 * chunk : (N / chunk >= 16 ? 2 * chunk : chunk);
-    int cl = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : (chunk == 32 && L >= 1024 ? 64 : chunk);
+    int cl = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : (chunk == 32 && L >= 1024 && !plain ? 64 : chunk);
     if (small_launch) {
         // equal units of 32 or 64 where a rollout may take one workgroup per trajectory (rollout.hip; whether it does depends on more,
         // but results must not), the best pair otherwise
         ck = cl = N / chunk >= 64 ? 64 : 32;
-        if (!bagel_rollout_rows_fit(c, ck)) small_launch_units(c->D, M, N, L, B, &ck, &cl);
+        if (!plain && !bagel_rollout_rows_fit(c, ck)) small_launch_units(c->D, M, N, L, B, &ck, &cl);
     }
     c->CK = bagel_env_int("BAGEL_CK", ck);
     c->CL = bagel_env_int("BAGEL_CL", cl);
