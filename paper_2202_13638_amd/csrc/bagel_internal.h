@@ -21,6 +21,7 @@ struct bagel_ctx {
     char err[512];
     int64_t bytes;
 
+    void *arena;                 // the one allocation of the buffers made by bagel_create
     // ---- model, internal layout --------------------------------------------------------
     int Np, Lp;                  // N and L rounded up to a whole number of chunks
     int CK, CL;                  // training points / features per work unit (multiples of 16)
