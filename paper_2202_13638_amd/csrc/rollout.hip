@@ -3,8 +3,8 @@
 // With few trajectories a rollout is a chain of latencies: a sample evaluation spread over the chip and an end-of-step
 // kernel take two launches, four trips to memory and a hand-over between compute units for every step, whatever little
 // there is to compute.  Here a trajectory never leaves its compute unit: 512 threads hold the rows of the model tables and the
-// trajectory's weights v and w in registers for the whole horizon (the policy's weights in LDS), and a step is six barriers.
-// What bounds a step is the float64 arithmetic of one compute unit and what lies between the barriers.  A forward step of a gradient
+// trajectory's weights v and w in registers for the whole horizon (the policy's weights in LDS), and a step is three to five
+// barriers.  What bounds it is the float64 arithmetic of one compute unit and what lies between the barriers.  A forward step of a gradient
 // call takes 3.1 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 3.0 at M = 2, N = 2200, L = 1024, 8-8,
 // B = 100 (13.2) and 1.5 at M = 2, N = 64, L = 256, 16, B = 16 (8.6); the Jacobians afterwards take 1.5, 0.5 and 0.5 us a step.
 //
@@ -70,8 +70,9 @@ __device__ __forceinline__ float chain16(const f4v *w, const f4v *x, float acc)
     return acc;
 }
 
-// The policy's weights in LDS, in groups of four along a chain, zero past the layers' ends (what a zero weight adds changes no bit), so
-// that no lane needs a condition:
+// The policy's weights in LDS, in groups of four along a chain, zero past the layers' ends, so that a chain needs no condition.  What a
+// zero weight adds changes no bit as long as its operand is finite: activations of units that do not exist stay zero (an infinite goal
+// saturates the units there are, and zero times infinity would make the others not a number).
 //   hidden layer 1 [4][width], hidden layer 2 [4 blocks][lanes], output layer [2 * 4][32 lanes], biases [3][128] floats.
 // A long contraction is cut into slices that are added up in order, as in policy16.hip: at most four for up to 64 units, two for more.
 // Hidden layer 2 gives that many neighbouring lanes to a unit, one a slice, the output layer four to an action.
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 inputs(2);
                 inputs(3);
             }
-            act[0][act_place(tid)] = tanh_fast(z + bias);
+            if (tid < p.width[1]) act[0][act_place(tid)] = tanh_fast(z + bias);
         }
         if (barrier0) __syncthreads();
         else wave_sync();
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             if (64 * wave < lanes1) {
                 const int u = two ? tid >> 1 : tid >> 2, sl = two ? tid & 1 : tid & 3;
                 const float bias = biases[128 + u];
-                // (past the last slice the weights are zero: any operands will do)
+                // (past the last slice the weights are zero: operands of any place will do, as one that is not a number is in every unit's chain)
                 const f4v *w = w1 + tid, *x = reinterpret_cast<const f4v *>(act[0]) + (two ? 9 * (p.fs >> 1) * sl : 9 * sl);
                 float z = chain16<PW::LANES>(w, x, 0.0f);
                 z = chain16<PW::LANES>(w + 4 * PW::LANES, x + 4, z);
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                         z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xff, 0xf, 0xf, true));
                     }
                 }
-                if (sl == 0) act[1][act_place(u)] = tanh_fast(z + bias);
+                if (sl == 0 && u < p.width[2]) act[1][act_place(u)] = tanh_fast(z + bias);
             }
             if (barrier1) __syncthreads();
             else wave_sync();

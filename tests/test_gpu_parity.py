@@ -456,6 +456,24 @@ def test_rollout_with_one_workgroup_per_trajectory_gives_the_same_bits(sh, monke
                 np.testing.assert_array_equal(b[k], a[k], err_msg=f"{k} scale {scale}")
 
 
+@pytest.mark.parametrize("hidden", [(16,), (8, 8), (33, 5), (64, 64), (65,), (100, 37), (80, 20), (128, 30)])
+def test_rollout_with_an_infinite_goal_gives_the_same_bits(hidden, monkeypatch):
+    """One component of one trajectory's goal is infinite for a step: its policy units saturate, the action and every later state are
+    finite, and so is the saturating cost, step by step and with one workgroup per trajectory."""
+    cfg = synth.Config("wginf", 31, 3, 1, 2, 70, 90, 6, 7, hidden, 0.8, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    inp["goals"][1, 2, 1], inp["goals"][3, 4, 0] = np.inf, -np.inf
+    v = (0.3 * np.random.default_rng(9).standard_normal((cfg.B, cfg.M, cfg.N))).astype(np.float32)
+    runs = []
+    for env in ("1", "2"):
+        monkeypatch.setenv("BAGEL_ROLLOUT", env)
+        runs.append([harness.gpu_rollout(cfg, inp, v, grad=grad, cost_kind=1, sigma_r=0.7) for grad in (True, False)])
+    for a, b in zip(*runs):
+        assert np.isfinite(a["states"]).all() and np.isfinite(a["loss_per_traj"]).all()
+        for k in a:
+            np.testing.assert_array_equal(b[k], a[k], err_msg=k)
+
+
 # d_s, d_a, d_g, B, H, hidden, bound, saturating, ckpt: every number of outputs, both instances of the layers, one and two hidden
 # layers and actions, fewer steps than are requested ahead, as many, and one more, whole and ragged tiles and segments
 BACKWARDS = [(1, 1, 1, 1, 1, (1,), 0.0, False, 0), (2, 1, 2, 16, 16, (16,), 0.0, False, 0), (3, 2, 1, 5, 17, (64, 64), 0.7, False, 0),
