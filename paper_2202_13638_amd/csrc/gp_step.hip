@@ -708,7 +708,8 @@ int bagel_env_int(const char *name, int dflt)
     return v > 0 ? v : dflt;
 }
 
-// The units of a launch of few workgroups (fewer than 1024: all of them are on the chip at once, the point-by-point loops in pairs).
+// The units of a launch of few workgroups (fewer than 1024: all of them are on the chip at once).  *CK = *CL: the equal units of 32 or 64 that
+// stay where the following does not apply.
 // Its time is that of the fullest compute unit, or, where a compute unit has one or two workgroups, of the longest unit: a wave
 // alone on its SIMD waits for its own chain.  So the pair (CK, CL) is taken whose fullest compute unit, with the workgroups
 // dealt out in turn, has the least to do.  Costs are in instructions per lane: 2 D + 18 a point, 1.6 times the D + 9 + 4 ceil(D / 4) of a
@@ -717,10 +718,17 @@ int bagel_env_int(const char *name, int dflt)
 // average 2.8 % of a step from the best one, units of 32 or 64 were 13 % from it.  us a step of a gradient call, before and after:
 // M = 4, N = L = 2048, B = 1024 26.6 -> 24.6 (128 and 64 instead of 64 and 64), M = 3, N = 1533, L = 901, B = 777 21.7 -> 18.6 (48, 48),
 // M = 5, N = 4000, L = 2000, B = 640 36.6 -> 32.2 (128, 80), M = 4, N = 5000, L = 3000, B = 400 27.7 -> 25.4 (96, 64).
+// Past eight inputs the loops do not take points in pairs, and the pairs of sizes pay where equal units make a launch of 321 to 2047
+// workgroups (25 problems with D = 9 .. 16: 0.97 to 1.25 times as fast, 1.05 on average), not outside (11 others: 0.86 to 1.01; above, equal
+// units make launches of the table form: M = 8, D = 16, N = L = 1024, B = 1024 54.7 us at (32, 32), 58.1 at (128, 64)).
 static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *CL)
 {
     const int sizes[] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
     const int64_t tiles = (int64_t)M * ((B + 63) / 64), point = 2 * D + 18, feature5 = 8 * (D + 9 + 4 * ((D + 3) / 4));
+    if (D > 8) {
+        const int64_t equal = tiles * (((N + *CK - 1) / *CK + 3) / 4 + ((L + *CL - 1) / *CL + 3) / 4);
+        if (equal <= 320 || equal >= 2048) return;
+    }
     int64_t least = INT64_MAX;
     for (const int ck : sizes)
         for (const int cl : sizes) {
@@ -763,7 +771,7 @@ const char *bagel_plan_sample_eval(bagel_ctx *c, bool plain)
     // stress 0.650 ms per launch at (CK, CL) = (1024, 512), 0.628 ms at (1024, 256); the large-policy
     // step 140.6 ms at (128, 64), 136.8 ms at (256, 64).  Features in units of 32 pay only where there are few of them: M = 4,
     // N = L = 2048, B = 2048 44.1 us a step at (128, 32), 41.6 at (128, 64), N = L = 1024, B = 4096 46.8 and 43.3, N = 8192, L = 4096,
-    // B = 1024 58.4 and 56.4, but M = 3, N = 1024, L = 512, B = 8192 47.9 and 48.7.
+    // B = 1024 58.4 and 56.4, M = 6, D = 9, N = 1024, L = 1500, B = 2560 64.4 and 60.1, but M = 3, N = 1024, L = 512, B = 8192 47.9 and 48.7.
     const bool small_launch = chunk == 32 && items / chunk < target;
     int ck = N / chunk >= 32 ? 4 * chunk : (N / chunk >= 16 ? 2 * chunk : chunk);
     int cl = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : (chunk == 32 && L >= 1024 && !plain ? 64 : chunk);

@@ -241,6 +241,20 @@ def test_sample_eval_units_by_size(d_s, d_a, N, L, B, S):
     _check_sample_eval(dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S), x)
 
 
+@pytest.mark.parametrize("d_s,d_a,N,L,B,S,ck,cl", [(8, 8, 1024, 1024, 1024, 64, 32, 32), (6, 5, 3966, 380, 72, 18, 64, 64),
+                                                   (8, 1, 323, 805, 2408, 56, 32, 32), (5, 4, 900, 1300, 700, 100, 48, 48)])
+def test_sample_eval_units_of_more_than_eight_inputs(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
+    """Past eight inputs a small launch takes a pair of unit sizes only between the launches for which equal units are the better ones:
+    the same bits as with the sizes given."""
+    shape = dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S)
+    x = np.random.default_rng(N + L).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
+    by_size = _check_sample_eval(shape, x)
+    monkeypatch.setenv("BAGEL_CK", str(ck))
+    monkeypatch.setenv("BAGEL_CL", str(cl))
+    for a, b in zip(by_size, _check_sample_eval(shape, x)):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("form", list(EXP2_FORMS))
 def test_sample_eval_inputs_far_from_the_data(form, monkeypatch):
     """GP inputs hundreds of length scales away from every training point: the kernel row is zero
@@ -281,6 +295,7 @@ def _check_sample_eval(shape, x):
     assert np.abs(f - fr).max() <= 2e-6 * max(1.0, np.abs(fr).max())
     assert np.abs(J - Jr).max() <= 1e-5 * max(1.0, np.abs(Jr).max())
     np.testing.assert_array_equal(f, f_only)      # the value does not depend on asking for the Jacobian
+    return f, J
 
 
 # ------------------------------------------------------------------ variants of the rollout
