@@ -33,6 +33,8 @@
 // [0, 1) and only then rounded to float32 for the hardware sin / cos (which take revolutions).
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "bagel_internal.h"
 #include "sample_math.h"
 
@@ -111,32 +113,37 @@ __device__ __forceinline__ void combine_waves(double (*red)[RC][64], int wave, i
 // a rollout needs J, so this runs as M extra rows of workgroups (one per output) inside the NEXT step's
 // sample evaluation (or, after the last step, as a launch of its own).  256 threads: the four waves
 // share the D entries of the output.
-// Several steps of a rollout at once (STEPS below): B inputs are those of B / trajectories steps, x is [D][x_stride], and the Jacobians
-// go to [step][M][D][trajectories].
-struct several_steps {
-    int trajectories;
-    size_t x_stride;
-};
-
 struct jac_sums {
     const double *part;      // [groups][1+D][B]
     const double *x;         // [D][B] inputs the sums were evaluated at
     const double *A, *amp;   // [M][D], [M]
     float *jdst;             // [M][D][B]
-    several_steps several;
 };
+// Several steps of a rollout at once: B inputs are those of B / trajectories steps, x is [D][x_stride], and the Jacobians go to
+// [step][M][D][trajectories].  (An argument type of its own: with these two in every launch
+// a call of bagel_sample_eval_static, N = 512, B = 256, took 18.53 us instead of 18.45.)
+struct jac_sums_of_steps : jac_sums {
+    int trajectories;
+    size_t x_stride;
+};
+template <bool STEPS>
+using jac_sums_arg = std::conditional_t<STEPS, jac_sums_of_steps, jac_sums>;
 
 // W: loads in flight per sum (4 inside the large launches, which hide the trips and have few registers; 8 elsewhere)
 template <int W, bool STEPS>
-__device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
+__device__ __forceinline__ void jacobian_tile(const jac_sums_arg<STEPS> &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
 {
     constexpr double LN2 = 0.69314718055994530942, TWO_PI = 6.28318530717958647693;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int b = tile * 64 + lane;
     if (b >= B) return;
-    const int T = STEPS ? j.several.trajectories : B, step = STEPS ? b / T : 0;
-    const size_t x_stride = STEPS ? j.several.x_stride : (size_t)B;
-    float *const jdst = j.jdst + (size_t)step * M * D * T + (b - step * T);
+    int T = B;
+    size_t x_stride = B, at = b;
+    if constexpr (STEPS) {
+        T = j.trajectories;
+        x_stride = j.x_stride;
+        at = (size_t)(b / T) * M * D * T + b % T;
+    }
     const size_t stride = (size_t)(1 + D) * B;
     const double *pk = j.part + (size_t)(m * ngk) * stride + b;
     const double *pr = j.part + (size_t)(M * ngk + m * ngl) * stride + b;
@@ -157,12 +164,12 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums &j, int tile, int m
         } else {
             bagel_sums_in_order<3, W>(p, n, stride, s);
         }
-        jdst[(size_t)(m * D + d) * T] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
+        j.jdst[(size_t)(m * D + d) * T + at] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
     }
 }
 
 template <bool STEPS>
-__global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums j, int B, int D, int M, int ngk, int ngl)
+__global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums_arg<STEPS> j, int B, int D, int M, int ngk, int ngl)
 {
     jacobian_tile<8, STEPS>(j, blockIdx.x, blockIdx.y, B, D, M, ngk, ngl);
 }
@@ -323,7 +330,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
     const float4 *__restrict__ w4,
     const double *__restrict__ xbuf, double *__restrict__ part, const double *__restrict__ exp_tab,
     const int *__restrict__ near_ok, int B, int S, int per_sample, int Np, int Lp, int CK, int CL, int nck, int ncl,
-    int M, jac_sums prev)
+    int M, jac_sums_arg<STEPS> prev)
 {
     // M rows of workgroups past the work units: the previous step's Jacobian sums (see jacobian_tile).
     // (Placed first in the grid instead, they made the launch slower: 571 vs 556 us.)
@@ -343,13 +350,19 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
     const int b_raw = blockIdx.x * 64 + lane;
     const bool live = b_raw < B;
     const int b = live ? b_raw : B - 1;
-    const int sidx = (STEPS ? b % prev.several.trajectories : b) / per_sample;
+    int trajectory = b;
+    size_t x_stride = B;
+    if constexpr (STEPS) {
+        trajectory = b % prev.trajectories;
+        x_stride = prev.x_stride;
+    }
+    const int sidx = trajectory / per_sample;
     const int group = blockIdx.y;                  // four consecutive units of one output and kind
     const int ngk = (nck + 3) >> 2, ngl = (ncl + 3) >> 2;
 
     double x[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) x[d] = xbuf[(size_t)d * (STEPS ? prev.several.x_stride : (size_t)B) + b];
+    for (int d = 0; d < D; ++d) x[d] = xbuf[d * x_stride + b];
 
     double *out = part + (size_t)group * (1 + D) * B + b;
 
@@ -665,7 +678,7 @@ void launch_variant(bagel_ctx *c, float *prev_jac)
 {
     dim3 grid((c->dm.B + 63) / 64, c->groups + (prev_jac ? c->M : 0));
     const int per_sample = c->dm.B / c->dm.S;
-    const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac, {}};
+    const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac};
     hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR, false>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,
                        reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, c->xbuf, c->part, c->exp_tab,
                        c->near_ok, c->dm.B, c->dm.S, per_sample, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, prev);
@@ -689,7 +702,7 @@ template <int D>
 hipError_t launch_steps(bagel_ctx *c, int t0, int steps)
 {
     const int B = c->dm.B, n = steps * B;
-    const jac_sums j = {c->part_all, c->xall + (size_t)t0 * B, c->A, c->amp, c->tape_J + (size_t)t0 * c->M * c->D * B, {B, (size_t)c->dm.H * B}};
+    const jac_sums_of_steps j = {{c->part_all, c->xall + (size_t)t0 * B, c->A, c->amp, c->tape_J + (size_t)t0 * c->M * c->D * B}, B, (size_t)c->dm.H * B};
     hipLaunchKernelGGL((gp_step_kernel<D, true, false, true>), dim3((n + 63) / 64, c->groups), dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn,
                        c->Os, reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, j.x, c->part_all, c->exp_tab, c->near_ok, n,
                        c->dm.S, B / c->dm.S, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, j);
@@ -823,7 +836,7 @@ hipError_t bagel_launch_gp_step(bagel_ctx *c, bool jac, float *prev_jac)
 
 hipError_t bagel_launch_jac_reduce(bagel_ctx *c, float *jdst)
 {
-    const jac_sums j = {c->part, c->xbuf, c->A, c->amp, jdst, {}};
+    const jac_sums j = {c->part, c->xbuf, c->A, c->amp, jdst};
     hipLaunchKernelGGL(jac_reduce_kernel<false>, dim3((c->dm.B + 63) / 64, c->M), dim3(BAGEL_BLOCK), 0, c->stream, j, c->dm.B, c->D,
                        c->M, (c->nck + 3) / 4, (c->ncl + 3) / 4);
     return hipGetLastError();
