@@ -239,13 +239,20 @@ __device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, 
     }
 }
 
+// A feature unit adds up its features in float32, in one chain per sum, and the units' sums are added up in float64.  The error of a
+// chain grows as the square root of its length, so where units are longer for speed alone (bagel_ctx::feature_chains) a chain ends, and its
+// sum goes to float64, every 32 features.  (Error of f and its Jacobian against 64 bits, D = 8, L = 4096, units of 128: 2.4e-7 and 2.3e-7 in
+// one chain a unit, 1.4e-7 and 1.5e-7 in chains of 32, as with units of 32; a step of a gradient call, M = 4, D = 5, N = 1024, B = 1500 44.9 and
+// 45.7 us, 50.6 with units of 32.  CHAINS instances of the kernel, so that the launches without them keep their code.)
+constexpr int CHAIN = 32 / 4;                // float4
+
 // n_iter float4 of random features (a multiple of 4): see the feature loops of the kernel.  Without VALUE the Jacobian sums
 // alone: the steps of a rollout by rollout.hip have their values, and the cosines are a sixth of the work (100 steps, B = 256,
 // N = 512, L = 1024, D = 5: 133.9 us a launch without, 139.6 with them).
-template <int D, bool JAC, bool VALUE>
+template <int D, bool JAC, bool VALUE, bool CHAINS, class F>
 __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __amdgpu_buffer_rsrc_t wdesc, unsigned woff, unsigned wstep,
                                               __amdgpu_buffer_rsrc_t odesc, unsigned ooff, unsigned ostep, int n_iter,
-                                              const double (&x)[D], float &p, f4v (&acc)[(D + 3) / 4])
+                                              const double (&x)[D], float &p, f4v (&acc)[(D + 3) / 4], F end_chain)
 {
     constexpr int NQ = (D + 3) / 4;
     const int last = n_iter - 1;
@@ -299,6 +306,7 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
             pair(b0, b1, a0, a1, l4 + i < last ? r + 4 * (D + 1) : Or, wb[i].z, wb[i].w, bq[i & 1], 2);
             wb[i] = stream_load(wdesc, woff, (unsigned)(l4 + 4 + i < last ? l4 + 4 + i : last) * wstep);
         }
+        if (CHAINS && (l4 + 4) % CHAIN == 0 && l4 + 4 < n_iter) end_chain();
     }
 }
 
@@ -323,7 +331,7 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
 // The table form needs many workgroups per compute unit to pay: its LDS read shares a wait counter
 // with the scalar loads of the shared operands, so every look-up also waits for the operand rows
 // requested ahead; small launches take the general loop only.
-template <int D, bool JAC, bool NEAR, bool STEPS>
+template <int D, bool JAC, bool NEAR, bool STEPS, bool CHAINS>
 __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEAR ? BAGEL_MIN_WAVES(D) : BAGEL_MIN_WAVES_SMALL(D), 8))) void gp_step_kernel(
     const double *__restrict__ Xs, const double *__restrict__ Xn, const double *__restrict__ Os,
     const float4 *__restrict__ Of, const double *__restrict__ A, const float4 *__restrict__ v4,
@@ -541,6 +549,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
             stream_descriptor(w4 + ((size_t)m * (Lp / 4) + (size_t)c * (CL / 4)) * S, (size_t)(CL / 4) * wstep);
         const unsigned woff = (unsigned)sidx * (unsigned)sizeof(float4);
         float p = 0.0f;
+        double p_chains = 0.0;                     // of the chains that have ended (CHAINS)
         if (JAC) {
             // The Jacobian sums of the feature part, G[b][d] = sum_l (w_l sin z_l) omega_ld, tolerate
             // float32 (no cancellation: w has random signs), so they run on the matrix cores as rank-1
@@ -560,8 +569,34 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
             f4v acc[NQ];
 #pragma unroll
             for (int qd = 0; qd < NQ; ++qd) acc[qd] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+            // the wave's sums so far in float64, where the end of the unit hands them over
+            auto add_to_lds = [&](bool first) {
+#pragma unroll
+                for (int qd = 0; qd < NQ; ++qd) {
+                    const int d = 4 * qd + (lane & 3);
+                    if (d < D) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            double &sum = red[((threadIdx.x >> 6) + 3) & 3][1 + d][(lane & ~3) + i];
+                            sum = first ? 0.0 : sum + (double)acc[qd][i];
+                        }
+                    }
+                }
+            };
+            auto end_chain = [&]() {
+                p_chains += (double)p;
+                p = 0.0f;
+                add_to_lds(false);
+#pragma unroll
+                for (int qd = 0; qd < NQ; ++qd) acc[qd] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+            };
+            if (CHAINS) add_to_lds(true);
             if constexpr (!NEAR && D <= 8) {
-                if (n_iter > 0) feature_pairs<D, true, !STEPS>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc);
+                if constexpr (CHAINS) {
+                    if (n_iter > 0) feature_pairs<D, true, true, true>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc, end_chain);
+                } else {
+                    if (n_iter > 0) feature_pairs<D, true, !STEPS, false>(Or, wdesc, woff, wstep, odesc, ooff, ostep, n_iter, x, p, acc, [] {});
+                }
             } else {
                 const int last = n_iter - 1;         // CL is a multiple of 16: two float4 per trip, no branch
                 auto one_feature = [&](const double (&rc)[D + 1], double (&rn)[D + 1], const double *__restrict__ next,
@@ -613,26 +648,36 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
                 for (int l4 = 0; l4 < n_iter; l4 += 2) {
                     four_features(wa, l4, wb, l4 + 1);
                     four_features(wb, l4 + 1, wa, l4 + 2 < last ? l4 + 2 : last);
+                    // (D = 16 without the table form, every eight features: a condition takes scalar registers that the rows leave no room for)
+                    if (CHAINS && ((D == 16 && !NEAR) || ((l4 + 2) % CHAIN == 0 && l4 + 2 < n_iter))) end_chain();
                 }
             }
             // every wave, wave 0 included, hands its sums over through LDS: that is also the transposition
             // from the accumulator layout (lane = column, register = trajectory) to lane = trajectory
             const int slot = (wave + 3) & 3;
-            if (!STEPS) red[slot][0][lane] = (double)p;
+            if (!STEPS) red[slot][0][lane] = CHAINS ? p_chains + (double)p : (double)p;
+            if constexpr (CHAINS) {
+                add_to_lds(false);
+            } else {
 #pragma unroll
-            for (int qd = 0; qd < NQ; ++qd) {
-                const int d = 4 * qd + (lane & 3);
-                if (d < D) {
+                for (int qd = 0; qd < NQ; ++qd) {
+                    const int d = 4 * qd + (lane & 3);
+                    if (d < D) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) red[slot][1 + d][(lane & ~3) + i] = (double)acc[qd][i];
+                        for (int i = 0; i < 4; ++i) red[slot][1 + d][(lane & ~3) + i] = (double)acc[qd][i];
+                    }
                 }
             }
             double u = 0.0, G[D];
             combine_waves<D, JAC, RC, !STEPS>(red, wave, lane, live, out, B, true, u, G);
         } else {
+            auto end_chain = [&]() {
+                p_chains += (double)p;
+                p = 0.0f;
+            };
             if constexpr (!NEAR && D <= 8) {
                 f4v none[NQ];
-                if (n_iter > 0) feature_pairs<D, false, true>(Or, wdesc, woff, wstep, wdesc, 0u, 0u, n_iter, x, p, none);
+                if (n_iter > 0) feature_pairs<D, false, true, CHAINS>(Or, wdesc, woff, wstep, wdesc, 0u, 0u, n_iter, x, p, none, end_chain);
             } else {
                 // value only: the same pipeline without the Jacobian sums
                 const int last = n_iter - 1;
@@ -665,35 +710,43 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
                     four_features(wa, l4);
                     wa = stream_load(wdesc, woff, (unsigned)(l4 + 2 < last ? l4 + 2 : last) * wstep);
                     four_features(wb, l4 + 1);
+                    if (CHAINS && (l4 + 2) % CHAIN == 0 && l4 + 2 < n_iter) end_chain();
                 }
             }
-            double u = (double)p, G[D];
+            double u = CHAINS ? p_chains + (double)p : (double)p, G[D];
             combine_waves<D, JAC, RC>(red, wave, lane, live, out, B, false, u, G);
         }
     }
 }
 
-template <int D, bool JAC, bool NEAR>
+template <int D, bool JAC, bool NEAR, bool CHAINS>
 void launch_variant(bagel_ctx *c, float *prev_jac)
 {
     dim3 grid((c->dm.B + 63) / 64, c->groups + (prev_jac ? c->M : 0));
     const int per_sample = c->dm.B / c->dm.S;
     const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac};
-    hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR, false>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,
+    hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR, false, CHAINS>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,
                        reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, c->xbuf, c->part, c->exp_tab,
                        c->near_ok, c->dm.B, c->dm.S, per_sample, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, prev);
+}
+
+template <int D, bool JAC>
+void launch_variant(bagel_ctx *c, float *prev_jac)
+{
+    if (c->exp_table) {
+        if (c->feature_chains) launch_variant<D, JAC, true, true>(c, prev_jac);
+        else launch_variant<D, JAC, true, false>(c, prev_jac);
+    } else {
+        if (c->feature_chains) launch_variant<D, JAC, false, true>(c, prev_jac);
+        else launch_variant<D, JAC, false, false>(c, prev_jac);
+    }
 }
 
 template <int D>
 hipError_t launch_d(bagel_ctx *c, bool jac, float *prev_jac)
 {
-    if (c->exp_table) {
-        if (jac) launch_variant<D, true, true>(c, prev_jac);
-        else launch_variant<D, false, true>(c, prev_jac);
-    } else {
-        if (jac) launch_variant<D, true, false>(c, prev_jac);
-        else launch_variant<D, false, false>(c, prev_jac);
-    }
+    if (jac) launch_variant<D, true>(c, prev_jac);
+    else launch_variant<D, false>(c, prev_jac);
     return hipGetLastError();
 }
 
@@ -703,7 +756,7 @@ hipError_t launch_steps(bagel_ctx *c, int t0, int steps)
 {
     const int B = c->dm.B, n = steps * B;
     const jac_sums_of_steps j = {{c->part_all, c->xall + (size_t)t0 * B, c->A, c->amp, c->tape_J + (size_t)t0 * c->M * c->D * B}, B, (size_t)c->dm.H * B};
-    hipLaunchKernelGGL((gp_step_kernel<D, true, false, true>), dim3((n + 63) / 64, c->groups), dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn,
+    hipLaunchKernelGGL((gp_step_kernel<D, true, false, true, false>), dim3((n + 63) / 64, c->groups), dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn,
                        c->Os, reinterpret_cast<const float4 *>(c->Of), c->A, c->v4, c->w4, j.x, c->part_all, c->exp_tab, c->near_ok, n,
                        c->dm.S, B / c->dm.S, c->Np, c->Lp, c->CK, c->CL, c->nck, c->ncl, c->M, j);
     hipLaunchKernelGGL(jac_reduce_kernel<true>, dim3((n + 63) / 64, c->M), dim3(BAGEL_BLOCK), 0, c->stream, j, n, D, c->M, (c->nck + 3) / 4,
@@ -736,8 +789,9 @@ int bagel_env_int(const char *name, int dflt)
 // they are faster (1.02, 0.90 to 1.14): M = 2, D = 6, N = 3099, L = 3486, B = 224 23.5 us a step at (32, 32), 21.3 at (48, 48), 20.3 at (64, 64);
 // M = 6, D = 7, N = 2274, L = 1213, B = 200 1.05 times as fast at (64, 48) as at (64, 64).
 // Past eight inputs the loops do not take points in pairs, and the pairs of sizes pay where equal units make a launch of 321 to 2047
-// workgroups (25 problems with D = 9 .. 16: 0.97 to 1.25 times as fast, 1.05 on average), not outside (11 others: 0.86 to 1.01; above, equal
-// units make launches of the table form: M = 8, D = 16, N = L = 1024, B = 1024 54.7 us at (32, 32), 58.1 at (128, 64)).
+// workgroups (23 problems with D = 9 .. 14: 0.97 to 1.25 times as fast, 1.05 on average), not outside (11 others: 0.86 to 1.01; above, equal
+// units make launches of the table form: M = 8, D = 16, N = L = 1024, B = 1024 54.7 us at (32, 32), 58.1 at (128, 64)), and not for 16 inputs,
+// whose float32 chains cost what they give (M = 8, N = 468, L = 1747, B = 592 43.2 us at (32, 32), 44.7 at (64, 64)).
 static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *CL)
 {
     const int sizes[] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
@@ -745,7 +799,7 @@ static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *
     const int equal = *CL, least_cl = D <= 8 && equal == 64 ? 48 : 32;
     if (D > 8) {
         const int64_t w = tiles * (((N + equal - 1) / equal + 3) / 4 + ((L + equal - 1) / equal + 3) / 4);
-        if (w <= 320 || w >= 2048) return;
+        if (w <= 320 || w >= 2048 || D == 16) return;
     }
     int64_t least = INT64_MAX;
     for (const int ck : sizes)
@@ -792,15 +846,17 @@ const char *bagel_plan_sample_eval(bagel_ctx *c, bool plain)
     // B = 1024 58.4 and 56.4, M = 6, D = 9, N = 1024, L = 1500, B = 2560 64.4 and 60.1, but M = 3, N = 1024, L = 512, B = 8192 47.9 and 48.7.
     const bool small_launch = chunk == 32 && items / chunk < target;
     int ck = N / chunk >= 32 ? 4 * chunk : (N / chunk >= 16 ? 2 * chunk : chunk);
-    int cl = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : (chunk == 32 && L >= 1024 && !plain ? 64 : chunk);
+    int chain = (chunk >= 512 && L / chunk >= 8) ? chunk / 2 : chunk;       // longest float32 sum of features
+    int cl = chunk == 32 && L >= 1024 && !plain ? 64 : chain;
     if (small_launch) {
         // equal units of 32 or 64 where a rollout may take one workgroup per trajectory (rollout.hip; whether it does depends on more,
         // but results must not), the best pair otherwise
-        ck = cl = N / chunk >= 64 ? 64 : 32;
+        ck = cl = chain = N / chunk >= 64 ? 64 : 32;
         if (!plain && !bagel_rollout_rows_fit(c, ck)) small_launch_units(c->D, M, N, L, B, &ck, &cl);
     }
     c->CK = bagel_env_int("BAGEL_CK", ck);
     c->CL = bagel_env_int("BAGEL_CL", cl);
+    c->feature_chains = c->CL == cl && cl > chain;
     c->CK = (c->CK + 15) & ~15;       // the sample-evaluation loops take two or four float4 (eight or sixteen points) per trip
     c->CL = (c->CL + 15) & ~15;
     c->nck = (N + c->CK - 1) / c->CK;

@@ -613,7 +613,7 @@ void bagel_plan_rollout(bagel_ctx *c)
 {
     c->rollout = false;
     if (c->exp_table || !(c->p16 == 1 || c->p16 == 2)) return;
-    if (c->CK != c->CL || (c->CK != 32 && c->CK != 64)) return;
+    if (c->CK != c->CL || (c->CK != 32 && c->CK != 64) || c->feature_chains) return;
     if (!rows_fit(c, c->CK) || lds_bytes(c) > LDS_BYTES) return;
     const int want = bagel_env_int("BAGEL_ROLLOUT", 0);                    // 1: never, 2: wherever it fits, otherwise by size
     c->rollout = want == 2 || (want != 1 && c->dm.B <= MOST_TRAJECTORIES);

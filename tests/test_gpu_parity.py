@@ -242,7 +242,7 @@ def test_sample_eval_units_by_size(d_s, d_a, N, L, B, S):
 
 
 @pytest.mark.parametrize("d_s,d_a,N,L,B,S,ck,cl", [(8, 8, 1024, 1024, 1024, 64, 32, 32), (6, 5, 3966, 380, 72, 18, 64, 64),
-                                                   (8, 1, 323, 805, 2408, 56, 32, 32), (5, 4, 900, 1300, 700, 100, 48, 48)])
+                                                   (8, 1, 323, 805, 2408, 56, 32, 32), (5, 4, 900, 1300, 700, 100, 48, 48), (8, 8, 468, 1747, 592, 37, 32, 32)])
 def test_sample_eval_units_of_more_than_eight_inputs(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
     """Past eight inputs a small launch takes a pair of unit sizes only between the launches for which equal units are the better ones:
     the same bits as with the sizes given."""
@@ -265,6 +265,24 @@ def _check_units_taken(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("d_s,d_a,N,L,B,S", [(6, 2, 1024, 4096, 1024, 64), (3, 1, 1000, 3000, 1500, 75), (6, 2, 1024, 1100, 2752, 43), (6, 3, 1024, 1500, 2560, 64),
+                                             (8, 4, 2048, 1024, 2048, 64)])
+def test_sample_eval_feature_sums_of_long_units(d_s, d_a, N, L, B, S, monkeypatch):
+    """Feature units of 64 and 128, small launches and large ones, points in pairs and one by one: the sums are in float32 over 32
+    features at most, so that they have the bits of units of 32 (float64 sums of the same float32 sums in another order: a bit in 2^29
+    differs)."""
+    shape = dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S)
+    x = np.random.default_rng(N + L).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
+    _check_sample_eval(shape, x)
+    for form in EXP2_FORMS.values():
+        monkeypatch.setenv("BAGEL_EXP_TABLE", form)
+        monkeypatch.delenv("BAGEL_CL", raising=False)
+        by_size = _sample_eval(shape, x)
+        monkeypatch.setenv("BAGEL_CL", "32")
+        for a, b in zip(by_size, _sample_eval(shape, x)):
+            assert np.count_nonzero(a != b) <= 2
+
+
 @pytest.mark.parametrize("form", list(EXP2_FORMS))
 def test_sample_eval_inputs_far_from_the_data(form, monkeypatch):
     """GP inputs hundreds of length scales away from every training point: the kernel row is zero
@@ -279,14 +297,18 @@ def test_sample_eval_inputs_far_from_the_data(form, monkeypatch):
     _check_sample_eval(shape, x)
 
 
-def _check_sample_eval(shape, x):
-    import torch
-    from paper_2202_13638_amd import binding
+def _sample_eval_case(shape):
     cfg = synth.Config("e", 11, shape["d_s"], shape["d_a"], 1, shape["N"], shape["L"], shape["B"], 2, (4,), 0.0,
                        "sinusoid", "const", 0, 0.7, 1e-3)
     inp = synth.make_inputs(cfg, S=shape["S"])
     dm = oracle.dims_from_config(cfg, S=shape["S"])
-    v32 = oracle.prepare_samples(dm, inp).astype(np.float32)
+    return cfg, inp, dm, oracle.prepare_samples(dm, inp).astype(np.float32)
+
+
+def _sample_eval(shape, x, case=None):
+    import torch
+    from paper_2202_13638_amd import binding
+    cfg, inp, dm, v32 = case or _sample_eval_case(shape)
     ctx = binding.Bagel(binding.dims_from_config(cfg, S=shape["S"]))
     g = harness.to_gpu(inp)
     ctx.bagel_set_samples(g["X"], g["lengthscale"], g["signal_var"], g["omega"], g["phase"], g["w"],
@@ -297,14 +319,20 @@ def _check_sample_eval(shape, x):
     ctx.bagel_sample_eval(torch.from_numpy(x).cuda(), f, J)
     ctx.bagel_sample_eval(torch.from_numpy(x).cuda(), f_only, None)
     torch.cuda.synchronize()
-    f, J, f_only = f.cpu().numpy(), J.cpu().numpy(), f_only.cpu().numpy()
+    ctx.close()
+    np.testing.assert_array_equal(f.cpu().numpy(), f_only.cpu().numpy())      # the value does not depend on asking for the Jacobian
+    return f.cpu().numpy(), J.cpu().numpy()
+
+
+def _check_sample_eval(shape, x):
+    case = cfg, inp, dm, v32 = _sample_eval_case(shape)
+    f, J = _sample_eval(shape, x, case)
     per = cfg.B // shape["S"]
     fr = np.zeros((cfg.B, cfg.M)); Jr = np.zeros((cfg.B, cfg.M, cfg.D))
     for b in range(cfg.B):
         fr[b], Jr[b] = oracle.sample_eval(dm, inp, inp["w"][b // per], v32[b // per], x[b])
     assert np.abs(f - fr).max() <= 2e-6 * max(1.0, np.abs(fr).max())
     assert np.abs(J - Jr).max() <= 1e-5 * max(1.0, np.abs(Jr).max())
-    np.testing.assert_array_equal(f, f_only)      # the value does not depend on asking for the Jacobian
     return f, J
 
 
