@@ -269,7 +269,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 inputs(2);
                 inputs(3);
             }
-            if (tid < p.width[1]) act[0][act_place(tid)] = tanh_fast(z + bias);
+            act[0][act_place(tid)] = tid < p.width[1] ? tanh_fast(z + bias) : 0.0f;
         }
         if (barrier0) __syncthreads();
         else wave_sync();
