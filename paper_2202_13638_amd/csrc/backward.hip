@@ -303,8 +303,10 @@ void bagel_plan_backward(bagel_ctx *c)
                                          c->dm.B <= (c->dm.d_a == 1 ? 1024 : 768));
 }
 
-hipError_t bagel_launch_backward_parallel(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
+// The steps t_hi - 1 .. t_lo, at most backward_steps of them, of a segment that begins with the step t_seg
+static hipError_t launch_steps(bagel_ctx *c, int t_seg, int t_lo, int t_hi, const float *goals, float *grad_s0)
 {
+    const size_t slot = (size_t)(t_lo - t_seg) * c->dm.B;
     double *const steps = c->adjoint_steps + (size_t)CHAIN_AHEAD * c->dm.B * c->M * (c->M + 1);
     layers_args a = {};
     a.B = c->dm.B; a.nl = c->n_layers; a.ds = c->dm.d_s; a.da = c->dm.d_a; a.dg = c->dm.d_g; a.H = c->dm.H; a.t_lo = t_lo;
@@ -313,14 +315,13 @@ hipError_t bagel_launch_backward_parallel(bagel_ctx *c, int t_lo, int t_hi, cons
     for (int i = 0; i < 4; ++i) a.width[i] = c->width[i];
     a.sigma_r = c->dm.sigma_r; a.cost_kind = c->dm.cost_kind;
     for (int l = 0; l < 3; ++l) {
-        a.tape_h[l] = l < c->n_layers ? c->tape_h[l] : nullptr;
-        a.tape_d[l] = l < c->n_layers ? c->tape_d[l] : nullptr;
+        a.tape_h[l] = l < c->n_layers ? c->tape_h[l] + slot * c->width[l] : nullptr;
+        a.tape_d[l] = l < c->n_layers ? c->tape_d[l] + slot * c->width[l + 1] : nullptr;
     }
     a.M = c->M; a.D = c->D; a.act_bound = c->dm.act_bound;
     a.pack = c->wpack16;
-    a.tape_s = c->tape_s; a.tape_a = c->tape_a; a.goals = goals; a.steps = steps; a.lam = c->lam_steps;
-    // the Jacobian tape spans the whole horizon when the activation tape is kept per segment
-    a.tape_J = c->tape_J + (c->T_tape < c->dm.H ? (size_t)t_lo * c->M * c->D * c->dm.B : 0);
+    a.tape_s = c->tape_s; a.tape_a = c->tape_a + slot * c->dm.d_a; a.goals = goals; a.steps = steps; a.lam = c->lam_steps;
+    a.tape_J = c->tape_J + (size_t)t_lo * c->M * c->D * c->dm.B;           // (spans the whole horizon)
     chain_args k = {};
     for (int j = 0; j < 8; ++j) {
         a.tracked[j] = k.tracked[j] = c->dm.tracked[j];
@@ -347,4 +348,14 @@ hipError_t bagel_launch_backward_parallel(bagel_ctx *c, int t_lo, int t_hi, cons
     if (c->p16 == 1) launch_layers<4, true>(c, a);
     else launch_layers<8, true>(c, a);
     return hipGetLastError();
+}
+
+hipError_t bagel_launch_backward_parallel(bagel_ctx *c, int t_lo, int t_hi, const float *goals, float *grad_s0)
+{
+    for (int hi = t_hi; hi > t_lo; hi -= c->backward_steps) {
+        const int lo = hi - c->backward_steps > t_lo ? hi - c->backward_steps : t_lo;
+        const hipError_t e = launch_steps(c, t_lo, lo, hi, goals, grad_s0);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }

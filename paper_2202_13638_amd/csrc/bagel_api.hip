@@ -77,8 +77,8 @@ static hipError_t dev_alloc(bagel_ctx *c, T **p, size_t count)
 
 static void free_all(bagel_ctx *c)
 {
-    // (xall and adjoint_steps: with part_all and lam_steps behind them)
-    void *ptrs[] = {c->arena, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums, c->xall, c->adjoint_steps};
+    // (xall: with part_all behind it)
+    void *ptrs[] = {c->arena, c->post_alpha, c->post_Kinv, c->post_Kx, c->post_sums, c->xall};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
 }
@@ -132,24 +132,7 @@ static void destroy_side(bagel_ctx *c)
     if (c->side) { (void)hipStreamDestroy(c->side); c->side = nullptr; }
 }
 
-// Two buffers of one way to do something; where they do not fit, *way becomes false and it is done the other way.
-static void alloc_or_drop(bagel_ctx *c, bool *way, double **p, size_t np, double **q, size_t nq)
-{
-    arena_plan plan;
-    void *base;
-    plan.add(p, np);
-    plan.add(q, nq);
-    if (plan.allocate(c, &base) == hipSuccess) return;
-    *way = false;
-    (void)hipGetLastError();
-}
-
-static void alloc_backward_buffers(bagel_ctx *c)
-{
-    const size_t per_step = (size_t)c->dm.B * c->M, T = (size_t)c->T_tape;
-    alloc_or_drop(c, &c->backward_parallel, &c->adjoint_steps, (BAGEL_CHAIN_AHEAD + T) * per_step * (c->M + 1), &c->lam_steps, T * per_step);
-}
-
+// Where the buffers of rollout.hip do not fit the rollouts go step by step: the same results.
 static void alloc_rollout_buffers(bagel_ctx *c)
 {
     if (bagel_raise_rollout_lds(c) != hipSuccess) {
@@ -161,7 +144,13 @@ static void alloc_rollout_buffers(bagel_ctx *c)
     const size_t B = (size_t)c->dm.B, H = (size_t)c->dm.H, per_step = (size_t)c->groups * (1 + c->D) * B;
     const size_t most = ((size_t)64 << 20) / (per_step * sizeof(double));
     c->rollout_steps = (int)(most < 1 ? 1 : (most < H ? most : H));
-    alloc_or_drop(c, &c->rollout, &c->xall, H * c->D * B, &c->part_all, (size_t)c->rollout_steps * per_step);
+    arena_plan plan;
+    void *base;
+    plan.add(&c->xall, H * c->D * B);
+    plan.add(&c->part_all, (size_t)c->rollout_steps * per_step);
+    if (plan.allocate(c, &base) == hipSuccess) return;
+    c->rollout = false;
+    (void)hipGetLastError();
 }
 
 extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_stream)
@@ -197,6 +186,12 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         // segment of this length is a few megabytes.
         c->T_tape *= (BAGEL_SHORTEST_SEGMENT + K - 1) / K;
         if (c->T_tape > H) c->T_tape = H;
+    }
+    if (c->backward_parallel) {
+        // as many steps side by side as have 64 MB of maps and adjoints (that fills the chip, and a long horizon does not take as much again
+        // as its tape).  Part of the context like the tape, not given up where memory is short: a sweep's gradients have other bits.
+        const size_t most = ((size_t)64 << 20) / ((size_t)B * M * (M + 2) * sizeof(double));
+        c->backward_steps = (int)(most < 1 ? 1 : (most < (size_t)c->T_tape ? most : c->T_tape));
     }
     c->ksplit = bagel_env_int("BAGEL_KSPLIT", 256);
     c->setup_outputs = bagel_env_int("BAGEL_SETUP_OUTPUTS", BAGEL_MAX_STATE);
@@ -245,13 +240,16 @@ extern "C" int bagel_create(bagel_ctx **out, const bagel_dims *dims, void *hip_s
         ALLOC(c->wpad_f, (size_t)wf_total);
         ALLOC(c->wpad_b, (size_t)wb_total);
     }
+    if (c->backward_parallel) {
+        ALLOC(c->adjoint_steps, (BAGEL_CHAIN_AHEAD + (size_t)c->backward_steps) * Bz * M * (M + 1));
+        ALLOC(c->lam_steps, (size_t)c->backward_steps * Bz * M);
+    }
     ALLOC(c->gsplit, (size_t)c->ksplit * c->P);
     ALLOC(c->gacc, (size_t)c->P);
     ALLOC(c->gtheta, (size_t)c->P);
 #undef ALLOC
     e = plan.allocate(c, &c->arena);
     use_tape_set(c, 0);
-    if (e == hipSuccess && c->backward_parallel) alloc_backward_buffers(c);
     if (e == hipSuccess && c->rollout) alloc_rollout_buffers(c);
     if (e == hipSuccess) {
         // table of the sample-evaluation kernel's table form: -2^(i/256), high word lowered by i << 12

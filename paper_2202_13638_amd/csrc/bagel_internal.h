@@ -81,8 +81,9 @@ struct bagel_ctx {
     int pack16_floats;
     float *wpack16;              // packed weights of policy16.hip
     bool backward_parallel;      // backward pass by backward.hip instead of a sweep
+    int backward_steps;          // steps taken side by side: T
     double *adjoint_steps;       // [BAGEL_CHAIN_AHEAD + T][B][d_s][d_s + 1]: its linear map of a step (null without)
-    double *lam_steps;           // [T][B][d_s]: adjoints of the states of all steps
+    double *lam_steps;           // [T][B][d_s]: adjoints of the states of these steps
     float *gsplit;               // [ksplit][P] split-contraction partial weight gradients
     double *gacc;                // [P] gradient accumulated over segments
     float *gtheta;               // [P] gradient of the current iteration of bagel_optimize

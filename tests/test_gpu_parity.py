@@ -557,6 +557,36 @@ def test_backward_pass_with_its_steps_side_by_side(sh, monkeypatch):
         assert np.linalg.norm(one[k] - sweep[k]) <= 1.2e-6 * np.linalg.norm(sweep[k]), k
 
 
+def test_backward_pass_of_more_steps_than_are_taken_at_once(monkeypatch):
+    """64 MB of linear maps and adjoints are 102 steps of 1024 trajectories and eight outputs: horizons and segments in several parts, the
+    last ones short.  Checkpointed or not the states' adjoints are the same bits; against the sweep the bound is that of the test above,
+    three times (the square root of 250 / 29 steps) as large."""
+    cfg = synth.Config("bwdlong", 29, 8, 1, 2, 40, 24, 1024, 250, (33, 16), 0.5, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg, S=32)
+    v = (0.3 * np.random.default_rng(6).standard_normal((32, cfg.M, cfg.N))).astype(np.float32)
+    whole, parts = [harness.gpu_rollout(cfg, inp, v, S=32, ckpt_interval=k) for k in (0, 120)]
+    monkeypatch.setenv("BAGEL_BACKWARD", "1")
+    sweep = harness.gpu_rollout(cfg, inp, v, S=32)
+    for k in ("states", "loss_per_traj", "grad_s0"):
+        assert np.isfinite(whole[k]).all()
+        np.testing.assert_array_equal(parts[k], whole[k], err_msg=k)
+    assert np.linalg.norm(parts["grad_theta"] - whole["grad_theta"]) <= 1e-6 * np.linalg.norm(whole["grad_theta"])
+    for k in ("grad_theta", "grad_s0"):
+        assert np.linalg.norm(whole[k] - sweep[k]) <= 3.6e-6 * np.linalg.norm(sweep[k]), k
+
+
+def test_backward_pass_buffers_do_not_grow_with_the_horizon(monkeypatch):
+    """Steps side by side take 64 MB, beside the steps requested ahead and what fills up allocations, however long the horizon."""
+    from paper_2202_13638_amd import binding
+    held = {}
+    for env in ("1", "2"):
+        monkeypatch.setenv("BAGEL_BACKWARD", env)
+        ctx = binding.Bagel(binding.make_dims(d_s=8, d_a=1, d_g=1, N=10, L=10, S=1, B=256, H=2000, hidden=(8,)))
+        held[env] = ctx.workspace_bytes()
+        ctx.close()
+    assert 60 << 20 < held["2"] - held["1"] < 68 << 20
+
+
 def test_rollout_with_table_exp2(monkeypatch):
     """The exp2 form of large launches, forced at a size the oracle finishes in seconds."""
     monkeypatch.setenv("BAGEL_EXP_TABLE", EXP2_FORMS["table"])
