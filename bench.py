@@ -14,7 +14,9 @@ Prints ONE JSON line, with
                library's stream.
   roofline     the dominant kernel (sample evaluation with Jacobian, one launch per rollout step):
                algorithmic flops per launch / average launch duration measured with HIP events on
-               the library's stream during the timed steps, against the float64 vector peak; hbm_frac is
+               the library's stream in calls of their own after the timed steps (the hook that times launches
+               makes rollouts of few trajectories take the step-by-step route, which other calls do not),
+               against the float64 vector peak; share_of_step is the share of these calls; hbm_frac is
                the algorithmic bytes of the same launch against 8 TB/s; traffic is the counter reading
                stored in profiles/ if that profile was taken from the kernel sources as they are now,
                else null.
@@ -154,7 +156,7 @@ def main():
                          "hyper-parameters) on the workload's training set, outside the timed region")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true", help="skip the forward-only and inner-loop figures")
-    ap.add_argument("--profile-every", type=int, default=8, help="time every n-th sample-evaluation launch")
+    ap.add_argument("--profile-every", type=int, default=8, help="time every n-th sample-evaluation launch of the calls after the timed ones")
     ap.add_argument("--ckpt", type=int, default=None, help="override ckpt_interval")
     ap.add_argument("--trajectories-per-sample", type=int, default=1,
                     help="supplementary runs: G trajectories share one function sample (S = B / G)")
@@ -217,7 +219,6 @@ def main():
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    ctx.bagel_profile_enable(args.profile_every)
     # every call between two events on the stream the library launches on (torch's current stream)
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(args.steps + 1)]
     t0 = time.perf_counter()
@@ -229,6 +230,14 @@ def main():
     elapsed = time.perf_counter() - t0
     call_ms = sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(args.steps))
     median_ms = call_ms[len(call_ms) // 2] if len(call_ms) % 2 else 0.5 * (call_ms[len(call_ms) // 2 - 1] + call_ms[len(call_ms) // 2])
+    # launch times, in calls of their own: about 128 timed launches
+    n_hook = min(args.steps, -(-128 * args.profile_every // cfg.H)) if args.profile_every > 0 else 0
+    ctx.bagel_profile_enable(args.profile_every)
+    t0 = time.perf_counter()
+    for _ in range(n_hook):
+        step()
+    torch.cuda.synchronize()
+    hook_s = time.perf_counter() - t0
     k_ms, k_n = ctx.bagel_profile_read()
     ctx.bagel_profile_enable(0)
     if not os.environ.get("BAGEL_BENCH_TIMING_ONLY"):      # timing experiments with deliberately wrong operands
@@ -276,7 +285,7 @@ def main():
                      "algorithmic_bytes_per_launch": None if posterior else algorithmic_bytes_per_launch(cfg, S),
                      "avg_launch_ms": avg_ms, "timed_launches": k_n,
                      "flops_per_launch": flops_launch,
-                     "share_of_step": (avg_ms * cfg.H) / (1e3 * elapsed / args.steps)},
+                     "share_of_step": (avg_ms * cfg.H) / (1e3 * hook_s / n_hook) if n_hook else None},
     }
     r = out["roofline"]
     # the kernel's lower bound is the larger of its arithmetic time and its streaming time

@@ -298,7 +298,9 @@ int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream, const flo
  * `every`-th launch of the sample-evaluation kernel inside the rollout calls (for the posterior
  * sampler: the launches of one step, all outputs) is bracketed by
  * HIP events on the context's stream (at most 4096 timed launches between two reads; further
- * ones are skipped).  bagel_profile_read synchronises the stream, returns the summed elapsed
+ * ones are skipped).  While the hook is on, rollouts of few trajectories, which otherwise are one launch
+ * without such launches in it, go step by step: the same results, but not the time of a call without
+ * the hook.  bagel_profile_read synchronises the stream, returns the summed elapsed
  * milliseconds and the number of timed launches since the last read, and resets both.
  * Errors: EINVAL, EHIP.
  */

@@ -527,6 +527,30 @@ def test_rollout_with_an_infinite_goal_gives_the_same_bits(hidden, monkeypatch):
             np.testing.assert_array_equal(b[k], a[k], err_msg=k)
 
 
+def test_measurement_hook_gives_the_same_bits():
+    """With the hook on, rollouts that are one launch go step by step, and their sample evaluations are timed."""
+    import torch
+    from paper_2202_13638_amd import binding
+    cfg = _cfg("tiny")
+    inp = synth.make_inputs(cfg)
+    g = harness.to_gpu(inp)
+    ctx = binding.Bagel(binding.dims_from_config(cfg))
+    ctx.bagel_prepare_samples(g["X"], g["y"], g["lengthscale"], g["signal_var"], g["noise_var"], g["omega"], g["phase"], g["w"], g["eps"], None)
+    runs = []
+    for every in (0, 1, 0):
+        ctx.bagel_profile_enable(every)
+        outs = [torch.full(sh, float("nan"), device="cuda")
+                for sh in [(1,), (ctx.P,), (cfg.B,), (cfg.H + 1, cfg.B, cfg.d_s), (cfg.B, cfg.d_s)]]
+        ctx.bagel_rollout_loss_grad(g["theta"], g["s0"], g["goals"], *outs)
+        ms, launches = ctx.bagel_profile_read()
+        assert launches == every * cfg.H and (ms > 0) == (every > 0)
+        runs.append(outs)
+    ctx.close()
+    for outs in runs[1:]:
+        for a, b in zip(runs[0], outs):
+            assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
 # d_s, d_a, d_g, B, H, hidden, bound, saturating, ckpt: every number of outputs, both instances of the layers, one and two hidden
 # layers and actions, fewer steps than are requested ahead, as many, and one more, whole and ragged tiles and segments
 BACKWARDS = [(1, 1, 1, 1, 1, (1,), 0.0, False, 0), (2, 1, 2, 16, 16, (16,), 0.0, False, 0), (3, 2, 1, 5, 17, (64, 64), 0.7, False, 0),
