@@ -57,7 +57,7 @@
  *                          unset: by launch size
  *   BAGEL_POLICY_TILE      16 or 32: trajectories per workgroup of the policy kernels; unset: by widths and batch
  *   BAGEL_ROLLOUT          1: rollouts always step by step, 2: with one workgroup per trajectory wherever a trajectory's share
- *                          of the model fits a compute unit, unset: by batch size (same results to the last bit for up to 768
+ *                          of the model fits a compute unit, unset: by batch size and horizon (same results to the last bit for up to 768
  *                          trajectories; above, the work units differ)
  *   BAGEL_BACKWARD         1: backward pass of narrow policies always by a sweep, 2: always with its steps side by side (up to two
  *                          actions), unset: by size (by a sweep if BAGEL_POLICY_TILE is set)

@@ -604,6 +604,10 @@ hipError_t launch(bagel_ctx *c, const rollout_args &r, const float *theta, const
 // 959 -> 382 / 766 -> 198, B = 512 937 -> 681 / 729 -> 391, B = 768 1046 -> 947 / 773 -> 586, B = 1024 1085 -> 1203 / 868 -> 778;
 // M = 4, N = 512, L = 1024, 128-128 at B = 256 972 -> 508 / 711 -> 193, B = 640 1101 -> 1046 / 720 -> 558, B = 1024 1206 -> 1374 /
 // 768 -> 742; M = 6, d_a = 2, N = L = 256, 8-8 at B = 16 766 -> 272 / 640 -> 139, B = 768 912 -> 751 / 671 -> 415.
+// A round begins with reading the model and the weights into a compute unit, which a few steps do not pay for: five steps for every round
+// after the first.  Eight models, calls step by step / here, gradient and forward: one round, H = 1 0.95 .. 1.22 and 1.00 .. 1.46; two
+// rounds, H = 1 0.71 .. 1.06 and 0.62 .. 1.08, H = 2 0.84 .. 1.28 and 0.86 .. 1.80, H = 4 1.00 .. 1.53 and 1.16 .. 2.17; three rounds, H = 4
+// 0.81 .. 1.25 and 0.87 .. 1.59, H = 8 0.91 .. 1.50 and 1.07 .. 1.87, H = 11 0.97 .. 1.56 and 1.16 .. 2.10.
 bool bagel_rollout_rows_fit(const bagel_ctx *c, int units)
 {
     return (c->dm.B <= MOST_TRAJECTORIES || bagel_env_int("BAGEL_ROLLOUT", 0) == 2) && rows_fit(c, units);
@@ -616,7 +620,7 @@ void bagel_plan_rollout(bagel_ctx *c)
     if (c->CK != c->CL || (c->CK != 32 && c->CK != 64) || c->feature_chains) return;
     if (!rows_fit(c, c->CK) || lds_bytes(c) > LDS_BYTES) return;
     const int want = bagel_env_int("BAGEL_ROLLOUT", 0);                    // 1: never, 2: wherever it fits, otherwise by size
-    c->rollout = want == 2 || (want != 1 && c->dm.B <= MOST_TRAJECTORIES);
+    c->rollout = want == 2 || (want != 1 && c->dm.B <= MOST_TRAJECTORIES && c->dm.H >= 5 * ((c->dm.B - 1) / 256));
 }
 
 hipError_t bagel_raise_rollout_lds(bagel_ctx *c)

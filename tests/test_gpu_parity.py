@@ -530,6 +530,20 @@ def test_rollout_with_an_infinite_goal_gives_the_same_bits(hidden, monkeypatch):
             np.testing.assert_array_equal(b[k], a[k], err_msg=k)
 
 
+@pytest.mark.parametrize("B,H,one_launch", [(256, 1, True), (257, 4, False), (257, 5, True), (768, 9, False), (768, 10, True), (769, 50, False)])
+def test_rollouts_of_several_rounds_and_few_steps_go_step_by_step(B, H, one_launch, monkeypatch):
+    """One workgroup per trajectory, which reads the model first, takes five steps for every round of 256 workgroups after the first to
+    pay (seen from the buffers such a context has)."""
+    from paper_2202_13638_amd import binding
+    held = []
+    for env in ("1", ""):
+        monkeypatch.setenv("BAGEL_ROLLOUT", env)
+        ctx = binding.Bagel(binding.make_dims(d_s=2, d_a=1, d_g=1, N=64, L=128, S=1, B=B, H=H, hidden=(8,)))
+        held.append(ctx.workspace_bytes())
+        ctx.close()
+    assert (held[1] > held[0]) == one_launch
+
+
 def test_measurement_hook_gives_the_same_bits():
     """With the hook on, rollouts that are one launch go step by step, and their sample evaluations are timed."""
     import torch
