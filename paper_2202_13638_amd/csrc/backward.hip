@@ -293,6 +293,7 @@ void launch_layers(bagel_ctx *c, const layers_args &a)
 //   M = 6, d_a = 2, 64-64, B = 256: 16 steps 114 / 93, 8 steps 77 / 72, 4 steps 54 / 57;
 //   64 steps in segments of 32 408 / 311, of 16 443 / 370, of 8 520 / 501; one layer of 64: of 16 335 / 313, of 8 406 / 409
 //   (segments shorter than 16 steps are put together, see bagel_create).
+// With two actions, which are two passes through the layers, the line lies where 128-128 no longer gains; narrower policies still do at 1024.
 void bagel_plan_backward(bagel_ctx *c)
 {
     const int want = bagel_env_int("BAGEL_BACKWARD", 0);                   // 1: sweep, 2: steps side by side, otherwise by size

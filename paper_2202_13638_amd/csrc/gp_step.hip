@@ -868,8 +868,9 @@ const char *bagel_plan_sample_eval(bagel_ctx *c, bool plain)
     // The table form of the kernel-row loop (gp_step.hip) pays once the launch has a few workgroups per
     // compute unit; below that its extra set-up per workgroup (the table copy) and the wait counter its
     // LDS read shares with the scalar loads cost more than its five fewer instructions per training point
-    // save.  Measured on MI355X, table vs general form, per launch: stress (4608 workgroups) 0.561 vs
-    // 0.60 ms; large policy (3072) 83.7 vs 86.4 us; medium (1280) 20.9 vs 22.4 us; small (192) 9.6 vs 9.2 us.
+    // save.  Measured on MI355X, table vs general form, per launch: stress (4608 workgroups) 583 vs 655 us; large policy (3072) 85.1 vs 97.6;
+    // M = 4, N = L = 2048, B = 2048 (1536) 34.9 vs 38.9; the same at B = 1400 in units of 64 (1408) 28.3 vs 29.5, at B = 1024 (1024)
+    // 22.5 vs 22.0, and in units of 128 and 64 (768) 23.6 vs 21.3; small (192) 9.5 vs 8.5.
     {
         const int64_t wgs = (int64_t)((B + 63) / 64) * c->groups;
         const int tab = bagel_env_int("BAGEL_EXP_TABLE", 0);         // 1: off, 2: on, otherwise by launch size
