@@ -784,10 +784,6 @@ int bagel_env_int(const char *name, int dflt)
 // average 2.8 % of a step from the best one, units of 32 or 64 were 13 % from it.  us a step of a gradient call, before and after:
 // M = 4, N = L = 2048, B = 1024 26.6 -> 24.6 (128 and 64 instead of 64 and 64), M = 3, N = 1533, L = 901, B = 777 21.7 -> 18.6 (48, 48),
 // M = 5, N = 4000, L = 2000, B = 640 36.6 -> 32.2 (128, 80), M = 4, N = 5000, L = 3000, B = 400 27.7 -> 25.4 (96, 64).
-// Feature units of 32, two trips of the loop, are not taken where equal units would be 64 (N >= 2048), whatever the model says: in 48 such
-// problems with up to 700 workgroups the pairs with them were slower than equal units on average (0.99 times as fast, 0.83 to 1.15), without
-// they are faster (1.02, 0.90 to 1.14): M = 2, D = 6, N = 3099, L = 3486, B = 224 23.5 us a step at (32, 32), 21.3 at (48, 48), 20.3 at (64, 64);
-// M = 6, D = 7, N = 2274, L = 1213, B = 200 1.05 times as fast at (64, 48) as at (64, 64).
 // Past eight inputs the loops do not take points in pairs, and the pairs of sizes pay where equal units make a launch of 321 to 2047
 // workgroups (23 problems with D = 9 .. 14: 0.97 to 1.25 times as fast, 1.05 on average), not outside (11 others: 0.86 to 1.01; above, equal
 // units make launches of the table form: M = 8, D = 16, N = L = 1024, B = 1024 54.7 us at (32, 32), 58.1 at (128, 64)), and not for 16 inputs,
@@ -796,15 +792,14 @@ static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *
 {
     const int sizes[] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
     const int64_t tiles = (int64_t)M * ((B + 63) / 64), point = 2 * D + 18, feature5 = 8 * (D + 9 + 4 * ((D + 3) / 4));
-    const int equal = *CL, least_cl = D <= 8 && equal == 64 ? 48 : 32;
     if (D > 8) {
-        const int64_t w = tiles * (((N + equal - 1) / equal + 3) / 4 + ((L + equal - 1) / equal + 3) / 4);
-        if (w <= 320 || w >= 2048 || D == 16) return;
+        const int64_t equal = tiles * (((N + *CK - 1) / *CK + 3) / 4 + ((L + *CL - 1) / *CL + 3) / 4);
+        if (equal <= 320 || equal >= 2048 || D == 16) return;
     }
     int64_t least = INT64_MAX;
     for (const int ck : sizes)
         for (const int cl : sizes) {
-            if (cl < least_cl || cl > 2 * ck || ck > 4 * cl) continue;
+            if (cl > 2 * ck || ck > 4 * cl) continue;
             const int64_t gk = ((N + ck - 1) / ck + 3) / 4, gl = ((L + cl - 1) / cl + 3) / 4, wk = tiles * gk, w = wk + tiles * gl;
             if (w >= 1024) continue;
             const int64_t tk = ck * point, tl = cl * feature5 / 5;

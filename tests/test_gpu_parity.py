@@ -246,16 +246,6 @@ def test_sample_eval_units_by_size(d_s, d_a, N, L, B, S):
 def test_sample_eval_units_of_more_than_eight_inputs(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
     """Past eight inputs a small launch takes a pair of unit sizes only between the launches for which equal units are the better ones:
     the same bits as with the sizes given."""
-    _check_units_taken(d_s, d_a, N, L, B, S, ck, cl, monkeypatch)
-
-
-@pytest.mark.parametrize("d_s,d_a,N,L,B,S,ck,cl", [(2, 4, 3099, 3486, 224, 28, 48, 48), (6, 1, 3129, 418, 216, 27, 64, 48)])
-def test_sample_eval_feature_units_of_many_training_points(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
-    """From 2048 training points on no small launch with points in pairs takes its features in units of 32."""
-    _check_units_taken(d_s, d_a, N, L, B, S, ck, cl, monkeypatch)
-
-
-def _check_units_taken(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
     shape = dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S)
     x = np.random.default_rng(N + L).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
     by_size = _check_sample_eval(shape, x)
