@@ -112,7 +112,10 @@ __device__ __forceinline__ void combine_waves(double (*red)[RC][64], int wave, i
 // result goes to a slot of the Jacobian tape, jdst[M][D][B] (float32).  Nothing on the critical path of
 // a rollout needs J, so this runs as M extra rows of workgroups (one per output) inside the NEXT step's
 // sample evaluation (or, after the last step, as a launch of its own).  256 threads: the four waves
-// share the D entries of the output.
+// share the D entries of the output.  SPLIT: four entries to a workgroup, one a wave, ceil(D / 4) rows per output: in a small launch
+// with many training points and few outputs a wave's trips to memory, one for every W groups of an entry (about 0.8 us each), are
+// longer than the evaluation beside them.  us a step of a gradient call, unsplit and split: M = 2, D = 5, N = 3212, L = 4149,
+// B = 96 23.2 -> 19.5, M = 3, D = 5, N = 6177, L = 439, B = 32 20.5 -> 17.0; 31 problems with D = 5 .. 8 and N >= 2048 1.07 times as fast.
 struct jac_sums {
     const double *part;      // [groups][1+D][B]
     const double *x;         // [D][B] inputs the sums were evaluated at
@@ -130,13 +133,15 @@ template <bool STEPS>
 using jac_sums_arg = std::conditional_t<STEPS, jac_sums_of_steps, jac_sums>;
 
 // W: loads in flight per sum (4 inside the large launches, which hide the trips and have few registers; 8 elsewhere)
-template <int W, bool STEPS>
-__device__ __forceinline__ void jacobian_tile(const jac_sums_arg<STEPS> &j, int tile, int m, int B, int D, int M, int ngk, int ngl)
+template <int W, bool STEPS, bool SPLIT = false>
+__device__ __forceinline__ void jacobian_tile(const jac_sums_arg<STEPS> &j, int tile, int row, int B, int D, int M, int ngk, int ngl)
 {
     constexpr double LN2 = 0.69314718055994530942, TWO_PI = 6.28318530717958647693;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int b = tile * 64 + lane;
     if (b >= B) return;
+    // (the same division signed and unsigned: with the other one D = 5 and D = 8 reserve scratch memory that no instruction uses)
+    const int parts = SPLIT ? (D + 3) / 4 : 1, m = D == 8 ? row / parts : (int)((unsigned)row / (unsigned)parts), part = row - m * parts;
     int T = B;
     size_t x_stride = B, at = b;
     if constexpr (STEPS) {
@@ -149,7 +154,7 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums_arg<STEPS> &j, int 
     const double *pr = j.part + (size_t)(M * ngk + m * ngl) * stride + b;
     double u[1];
     if (W < 8) bagel_sums_in_order<1, W>({pk}, {ngk}, stride, u);      // (fewer registers: the value sum on its own first)
-    for (int d = wave; d < D; d += BAGEL_BLOCK / 64) {
+    for (int d = 4 * part + wave; d < D; d += SPLIT ? BAGEL_MAX_D : 4) {
         const double *const p[3] = {pk + (size_t)(1 + d) * B, pr + (size_t)(1 + d) * B, pk};
         const int n[3] = {ngk, ngl, ngk};
         const double xd = j.x[(size_t)d * x_stride + b];
@@ -167,6 +172,8 @@ __device__ __forceinline__ void jacobian_tile(const jac_sums_arg<STEPS> &j, int 
         j.jdst[(size_t)(m * D + d) * T + at] = (float)(-j.amp[m] * TWO_PI * s[1] + LN2 * (s[0] - j.A[m * D + d] * xd * s[2]));
     }
 }
+
+constexpr bool split_jacobian(int D, bool jac, bool near, bool steps) { return D > 4 && jac && !near && !steps; }
 
 template <bool STEPS>
 __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums_arg<STEPS> j, int B, int D, int M, int ngk, int ngl)
@@ -340,10 +347,11 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
     const int *__restrict__ near_ok, int B, int S, int per_sample, int Np, int Lp, int CK, int CL, int nck, int ncl,
     int M, jac_sums_arg<STEPS> prev)
 {
-    // M rows of workgroups past the work units: the previous step's Jacobian sums (see jacobian_tile).
+    // Rows of workgroups past the work units: the previous step's Jacobian sums (see jacobian_tile).
     // (Placed first in the grid instead, they made the launch slower: 571 vs 556 us.)
+    constexpr bool SPLIT = split_jacobian(D, JAC, NEAR, STEPS);
     if ((int)blockIdx.y >= M * (((nck + 3) >> 2) + ((ncl + 3) >> 2))) {
-        jacobian_tile<NEAR ? 4 : 8, false>(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
+        jacobian_tile<NEAR ? 4 : 8, false, SPLIT>(prev, blockIdx.x, (int)blockIdx.y - M * (((nck + 3) >> 2) + ((ncl + 3) >> 2)), B, D, M,
                       (nck + 3) >> 2, (ncl + 3) >> 2);
         return;
     }
@@ -722,7 +730,7 @@ __global__ __launch_bounds__(BAGEL_BLOCK) __attribute__((amdgpu_waves_per_eu(NEA
 template <int D, bool JAC, bool NEAR, bool CHAINS>
 void launch_variant(bagel_ctx *c, float *prev_jac)
 {
-    dim3 grid((c->dm.B + 63) / 64, c->groups + (prev_jac ? c->M : 0));
+    dim3 grid((c->dm.B + 63) / 64, c->groups + (prev_jac ? c->M * (split_jacobian(D, JAC, NEAR, false) ? (D + 3) / 4 : 1) : 0));
     const int per_sample = c->dm.B / c->dm.S;
     const jac_sums prev = {c->part_alt, c->xbuf_alt, c->A, c->amp, prev_jac};
     hipLaunchKernelGGL((gp_step_kernel<D, JAC, NEAR, false, CHAINS>), grid, dim3(BAGEL_BLOCK), 0, c->stream, c->Xs, c->Xn, c->Os,

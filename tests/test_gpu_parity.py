@@ -220,6 +220,18 @@ def test_sample_eval_every_input_dimension(D, monkeypatch):
         _check_sample_eval(shape, x)
 
 
+@pytest.mark.parametrize("D", range(4, 17))
+def test_gradient_step_by_step_every_input_dimension(D, monkeypatch):
+    """The Jacobian sums of a step, added up beside the next step's evaluation by one to four workgroups per output: against the
+    oracle, with several groups of partial sums and a tile of trajectories that is not full."""
+    monkeypatch.setenv("BAGEL_ROLLOUT", "1")
+    d_s = (D + 1) // 2
+    cfg = synth.Config("jac", 33, d_s, D - d_s, 1, 300 + D, 150 + D, 70, 4, (8,), 1.0, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    ref = harness.oracle_reference(cfg, inp)
+    harness.assert_parity(ref, harness.gpu_rollout(cfg, inp, ref["v32"]), label=f"step by step/D{D}")
+
+
 @pytest.mark.parametrize("ck,cl", [(16, 16), (48, 16), (16, 80), (32, 48), (100, 33)])
 @pytest.mark.parametrize("d_s,d_a", [(1, 1), (4, 1), (6, 2), (6, 3)])
 def test_sample_eval_unit_sizes(ck, cl, d_s, d_a, monkeypatch):
