@@ -792,6 +792,12 @@ int bagel_env_int(const char *name, int dflt)
 // average 2.8 % of a step from the best one, units of 32 or 64 were 13 % from it.  us a step of a gradient call, before and after:
 // M = 4, N = L = 2048, B = 1024 26.6 -> 24.6 (128 and 64 instead of 64 and 64), M = 3, N = 1533, L = 901, B = 777 21.7 -> 18.6 (48, 48),
 // M = 5, N = 4000, L = 2000, B = 640 36.6 -> 32.2 (128, 80), M = 4, N = 5000, L = 3000, B = 400 27.7 -> 25.4 (96, 64).
+// Where equal units make 1024 workgroups or more they have the table form, which suits launches with much to do for the training points, values
+// alone above all, and they are a candidate like the pairs: 8 instructions a point less, no round of workgroups to fill, 4000 to begin
+// with.  (D = 3 .. 8, N = 256 .. 6000, L = 256 .. 4096, 746 such problems: the pairs are 1.04 times as fast in gradient calls and 0.98 times in
+// forward passes over all of them, but 0.96 and 0.91 times over the 92 that this leaves with equal units, of which 5 and 4 would be more than 2 %
+// faster with pairs.  us a step, pair and equal: M = 6, D = 8, N = 437, L = 864, B = 2729 46.1 and 40.2, forward 32.2 and 28.4;
+// M = 4, D = 6, N = 1585, L = 398, B = 3342 49.2 and 44.6, 35.4 and 31.7; M = 2, D = 3, N = 3209, L = 323, B = 4078 43.0 and 40.8, 34.8 and 30.5.)
 // Past eight inputs the loops do not take points in pairs, and the pairs of sizes pay where equal units make a launch of 321 to 2047
 // workgroups (23 problems with D = 9 .. 14: 0.97 to 1.25 times as fast, 1.05 on average), not outside (11 others: 0.86 to 1.01; above, equal
 // units make launches of the table form: M = 8, D = 16, N = L = 1024, B = 1024 54.7 us at (32, 32), 58.1 at (128, 64)), and not for 16 inputs,
@@ -800,11 +806,13 @@ static void small_launch_units(int D, int M, int N, int L, int B, int *CK, int *
 {
     const int sizes[] = {32, 48, 64, 80, 96, 128, 160, 192, 256};
     const int64_t tiles = (int64_t)M * ((B + 63) / 64), point = 2 * D + 18, feature5 = 8 * (D + 9 + 4 * ((D + 3) / 4));
-    if (D > 8) {
-        const int64_t equal = tiles * (((N + *CK - 1) / *CK + 3) / 4 + ((L + *CL - 1) / *CL + 3) / 4);
-        if (equal <= 320 || equal >= 2048 || D == 16) return;
-    }
     int64_t least = INT64_MAX;
+    {
+        const int64_t gk = ((N + *CK - 1) / *CK + 3) / 4, gl = ((L + *CL - 1) / *CL + 3) / 4, wk = tiles * gk, w = wk + tiles * gl;
+        if (D > 8 && (w <= 320 || w >= 2048 || D == 16)) return;
+        if (D <= 8 && w >= 1024)
+            least = (wk * (*CK * (point - 8) + 100) + (w - wk) * (*CL * feature5 / 5 + 100)) / 256 + 4000 + 40 * M * (gk + gl);
+    }
     for (const int ck : sizes)
         for (const int cl : sizes) {
             if (cl > 2 * ck || ck > 4 * cl) continue;

@@ -253,6 +253,27 @@ def test_sample_eval_units_by_size(d_s, d_a, N, L, B, S):
     _check_sample_eval(dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S), x)
 
 
+@pytest.mark.parametrize("d_s,d_a,N,L,B,S,taken,other", [(6, 2, 437, 864, 2728, 44, (32, 32), (128, 128)), (2, 1, 3209, 323, 4080, 40, (64, 64), (192, 96)),
+                                                         (5, 2, 256, 758, 5740, 41, (32, 32), (96, 192)), (4, 1, 2048, 2048, 1024, 32, (128, 64), (64, 64)),
+                                                         (3, 1, 2025, 589, 834, 139, (64, 48), (32, 32))])
+def test_sample_eval_equal_units_of_the_table_form(d_s, d_a, N, L, B, S, taken, other, monkeypatch):
+    """Equal units that make a launch of 1024 workgroups or more, which has the table form, are weighed against the pairs of launches without
+    it (seen from the buffers: partial sums and padding)."""
+    from paper_2202_13638_amd import binding
+    held = []
+    for ck, cl in (("", ""), taken, other):
+        monkeypatch.setenv("BAGEL_CK", str(ck))
+        monkeypatch.setenv("BAGEL_CL", str(cl))
+        ctx = binding.Bagel(binding.make_dims(d_s=d_s, d_a=d_a, d_g=1, N=N, L=L, S=S, B=B, H=2, hidden=(8,)))
+        held.append(ctx.workspace_bytes())
+        ctx.close()
+    assert held[0] == held[1] != held[2]
+    monkeypatch.delenv("BAGEL_CK")
+    monkeypatch.delenv("BAGEL_CL")
+    x = np.random.default_rng(N + L).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
+    _check_sample_eval(dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S), x)
+
+
 @pytest.mark.parametrize("d_s,d_a,N,L,B,S,ck,cl", [(8, 8, 1024, 1024, 1024, 64, 32, 32), (6, 5, 3966, 380, 72, 18, 64, 64),
                                                    (8, 1, 323, 805, 2408, 56, 32, 32), (5, 4, 900, 1300, 700, 100, 48, 48), (8, 8, 468, 1747, 592, 37, 32, 32)])
 def test_sample_eval_units_of_more_than_eight_inputs(d_s, d_a, N, L, B, S, ck, cl, monkeypatch):
