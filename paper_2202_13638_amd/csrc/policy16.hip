@@ -614,13 +614,17 @@ void launch_sweep(bagel_ctx *c, const sweep16_args &a)
 // 128.4 (checkpointed, 500 steps 127.1 / 123.2), forward pass with 16 trajectories per sample there 64.0 / 57.7.  Wider policies on
 // larger batches fill the chip with 32 trajectories per workgroup, and fetching the weights twice as often costs what the
 // shorter chain gives: N = 2048, B = 6144 256-256 118.0 / 120.4, 192-192 108.7 / 112.6, checkpointed 126.2 / 127.3 and 116.9 / 119.9,
-// B = 8192 checkpointed 157.0 / 160.1, 128-128 127.3 / 116.3.
+// B = 8192 checkpointed 157.0 / 160.1, 128-128 127.3 / 116.3.  Above 2048 trajectories, checkpointed, 130 policies with one layer of 129 to 256
+// units (H = 40): a second layer of up to 64 behind it 0.90 .. 0.99 times as fast as policy.hip (0.97 on average; 254-25 0.91, 139-50
+// 0.99), of 65 to 128 1.00 on average, the narrow layer first 1.01 .. 1.10, two wide ones 1.02 .. 1.11, one layer 1.04 .. 1.15; not checkpointed,
+// up to 64 behind it, 0.97 .. 1.02.  So the second layer sets the limit when checkpointed; both kernels give the same bits.
 void bagel_plan_policy(bagel_ctx *c)
 {
     int w = 0;
     for (int l = 1; l < c->n_layers; ++l) w = c->width[l] > w ? c->width[l] : w;
     c->p16 = w <= 64 ? 1 : (w <= 128 ? 2 : 3);
-    const int most = c->p16 == 3 ? 4096 : 8192;
+    const bool narrow_second = c->n_layers == 3 && c->width[2] <= 64;
+    const int most = c->p16 == 3 ? (narrow_second && c->T_tape < c->dm.H ? 2048 : 4096) : 8192;
     const int tile = bagel_env_int("BAGEL_POLICY_TILE", 0);                // 16 or 32: always that one, otherwise by size
     if (tile == 32 || (tile != 16 && c->p16 != 1 && c->dm.B > most)) c->p16 = 0;
     c->pack16_floats = c->p16 ? make_pack(c).total() : 0;

@@ -567,6 +567,28 @@ def test_rollouts_of_several_rounds_and_few_steps_go_step_by_step(B, H, one_laun
     assert (held[1] > held[0]) == one_launch
 
 
+@pytest.mark.parametrize("B,hidden,ckpt,tile", [(2048, (130, 64), 3, "16"), (2049, (130, 64), 3, "32"), (2049, (130, 64), 0, "16"), (2049, (130, 65), 3, "16"),
+                                                (2049, (64, 130), 3, "16"), (2049, (130,), 3, "16"), (4097, (130, 65), 3, "32")])
+def test_wide_policies_trajectories_per_workgroup(B, hidden, ckpt, tile, monkeypatch):
+    """A narrow second layer behind a wide one takes 32 trajectories per workgroup from 2049 on when checkpointed (seen from the packed
+    weights), with the same bits as 16."""
+    from paper_2202_13638_amd import binding
+    cfg = synth.Config("tile", 37, 2, 1, 1, 40, 30, B, 8, hidden, 0.6, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg, S=1)
+    v = (0.3 * np.random.default_rng(7).standard_normal((1, cfg.M, cfg.N))).astype(np.float32)
+    held, runs = {}, []
+    for env in ("", "16", "32"):
+        monkeypatch.setenv("BAGEL_POLICY_TILE", env)
+        ctx = binding.Bagel(binding.dims_from_config(cfg, S=1, ckpt_interval=ckpt))
+        held[env] = ctx.workspace_bytes()
+        ctx.close()
+        runs.append(harness.gpu_rollout(cfg, inp, v, S=1, ckpt_interval=ckpt))
+    assert held["16"] > held["32"] and held[""] == held[tile]
+    for got in runs[1:]:
+        for k in got:
+            np.testing.assert_array_equal(got[k], runs[0][k], err_msg=k)
+
+
 def test_measurement_hook_gives_the_same_bits():
     """With the hook on, rollouts that are one launch go step by step, and their sample evaluations are timed."""
     import torch
