@@ -186,10 +186,22 @@ __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums_arg<ST
 // waits for: its chain of dependent float64 operations (8 cycles each, where independent ones issue every 5),
 // the trip of its operand row through the scalar cache, the stream.  So points (features) are worked on in pairs,
 // rows are requested a pair ahead, the stream four float4 ahead (into the registers just used: CK and CL are
-// multiples of 16), the matrix-core operands of the features four features ahead.  Every sum keeps the order of the
+// multiples of 16).  Every sum keeps the order of the
 // point-by-point loops.  A launch at N = 2200, L = 1024, 100 trajectories, D = 3 takes 9.1 -> 7.8 us, at N = 512, L = 1024, 256
 // trajectories, D = 5 6.4 -> 5.9 us.  For D > 8 two pairs of rows do not fit the scalar registers: those stay with
 // the point-by-point loops.
+//
+// What a wave then still waits for is the order of its loads.  Scalar loads return in any order, so a wait for one is a wait for
+// all: the rows of this pair are waited for (rows_arrived) before those of the next are requested, not after.  Vector loads
+// return in order, so the matrix-core operands, which hit in cache, come after the stream's float4 requested before them:
+// they are requested three float4 ahead, behind a request that has had as long.  Us a launch, before -> now: M = 4, N = L = 2048, B = 1024
+// 19.1 -> 18.1 (its 67 MB of streams alone take 11.5), M = 3, N = 1533, L = 901, B = 777 10.4 -> 9.8.
+__device__ __forceinline__ void rows_arrived()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);        // lgkmcnt(0) alone
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int D>
 __device__ __forceinline__ void load_row(double (&r)[D + 1], const double *__restrict__ src)
 {
@@ -207,6 +219,7 @@ __device__ __forceinline__ void kernel_row_pairs(const double *__restrict__ Xr, 
     const int last = n_iter - 1;
     auto pair = [&](const double (&r0)[D + 1], const double (&r1)[D + 1], double (&n0)[D + 1], double (&n1)[D + 1],
                     const double *__restrict__ next, float v0, float v1) {
+        rows_arrived();
         load_row<D>(n0, next);
         load_row<D>(n1, next + (D + 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -265,6 +278,7 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
     const int last = n_iter - 1;
     auto pair = [&](const double (&r0)[D + 1], const double (&r1)[D + 1], double (&n0)[D + 1], double (&n1)[D + 1],
                     const double *__restrict__ next, float w0, float w1, const v4f (&bq)[NQ], int j) {
+        rows_arrived();
         load_row<D>(n0, next);
         load_row<D>(n1, next + (D + 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -290,7 +304,7 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    v4f wb[4], bq[2][NQ];
+    v4f wb[4], bq[4][NQ];
     auto operands = [&](v4f (&b)[NQ], int l4) {
         if (JAC) {
 #pragma unroll
@@ -298,9 +312,11 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
                 b[qd] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(odesc, ooff + 16u * qd, (unsigned)l4 * ostep, 0));
         }
     };
-    operands(bq[0], 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) wb[i] = stream_load(wdesc, woff, (unsigned)i * wstep);
+    for (int i = 0; i < 4; ++i) {
+        wb[i] = stream_load(wdesc, woff, (unsigned)i * wstep);
+        if (i < 3) operands(bq[i], i);
+    }
     double a0[D + 1], a1[D + 1], b0[D + 1], b1[D + 1];
     load_row<D>(a0, Or);
     load_row<D>(a1, Or + (D + 1));
@@ -308,9 +324,9 @@ __device__ __forceinline__ void feature_pairs(const double *__restrict__ Or, __a
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const double *__restrict__ r = Or + (size_t)((l4 + i) * 4) * (D + 1);
-            operands(bq[(i + 1) & 1], l4 + i < last ? l4 + i + 1 : last);
-            pair(a0, a1, b0, b1, r + 2 * (D + 1), wb[i].x, wb[i].y, bq[i & 1], 0);
-            pair(b0, b1, a0, a1, l4 + i < last ? r + 4 * (D + 1) : Or, wb[i].z, wb[i].w, bq[i & 1], 2);
+            operands(bq[(i + 3) & 3], l4 + i + 3 < last ? l4 + i + 3 : last);
+            pair(a0, a1, b0, b1, r + 2 * (D + 1), wb[i].x, wb[i].y, bq[i], 0);
+            pair(b0, b1, a0, a1, l4 + i < last ? r + 4 * (D + 1) : Or, wb[i].z, wb[i].w, bq[i], 2);
             wb[i] = stream_load(wdesc, woff, (unsigned)(l4 + 4 + i < last ? l4 + 4 + i : last) * wstep);
         }
         if (CHAINS && (l4 + 4) % CHAIN == 0 && l4 + 4 < n_iter) end_chain();
