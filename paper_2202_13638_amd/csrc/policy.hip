@@ -29,6 +29,7 @@
 // narrow ones (weight_grad_kernel).  The contraction range is split over workgroups in a fixed way
 // and the partial results are added in a fixed order, so the gradient is bitwise reproducible.
 #include "bagel_internal.h"
+#include "sample_math.h"
 #include <type_traits>
 
 namespace {
@@ -622,7 +623,7 @@ __global__ __launch_bounds__(PW * 64) void step_tail_kernel(tail_args r, policy_
             }
         if (r.cost_kind == 1) {
             const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
-            e = -exp(-e / (2.0 * sr2));
+            e = -cost_exp(-e / (2.0 * sr2));
         }
         r.lpt[bq] = lp_in + e;
     }

@@ -17,6 +17,7 @@
 //   - The output layer (forward) and the input layer (backward) have one row tile: wave w takes slice w of them.
 // Instances: 4 waves of one tile (hidden widths <= 64), 8 of one (<= 128), 8 of two (<= 256; not the backward sweep).
 #include "policy16.h"
+#include "sample_math.h"
 
 namespace {
 
@@ -270,7 +271,7 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
             }
         if (r.cost_kind == 1) {
             const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
-            e = -exp(-e / (2.0 * sr2));
+            e = -cost_exp(-e / (2.0 * sr2));
         }
         r.lpt[b] = lp_in + e;
     }

@@ -5,8 +5,12 @@
 // there is to compute.  Here a trajectory never leaves its compute unit: 512 threads hold the rows of the model tables and the
 // trajectory's weights v and w in registers for the whole horizon (the policy's weights in LDS), and a step is three to five
 // barriers.  What bounds it is the float64 arithmetic of one compute unit and what lies between the barriers.  A forward step of a gradient
-// call takes 3.1 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 3.0 at M = 2, N = 2200, L = 1024, 8-8,
-// B = 100 (13.2) and 1.5 at M = 2, N = 64, L = 256, 16, B = 16 (8.6); the Jacobians afterwards take 1.5, 0.5 and 0.5 us a step.
+// call takes 2.7 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 2.8 at M = 2, N = 2200, L = 1024, 8-8,
+// B = 100 (13.2) and 1.3 at M = 2, N = 64, L = 256, 16, B = 16 (8.6); the Jacobians afterwards take 1.5, 0.5 and 0.5 us a step.
+// Of a step of the first of them (6200 cycles) the policy and the state take 3000, one wave after the other with one contraction each,
+// the terms 2300 (float64 instructions of two waves a SIMD, about 5 cycles each) and their sums 650 (a chain of dependent additions).
+// What is off that chain, the tapes, the goals ahead and the cost, belongs to waves that wait anyway.  (3.1, 3.0 and 1.5 us a step while
+// addresses were formed anew for every store, 1400 cycles of one wave, and the waits for the rows stood inside the loop.)
 //
 // Only values are computed here.  The Jacobians feed nothing but the backward pass, so they are computed afterwards for all
 // steps at once, where they fill the chip (bagel_launch_gp_steps): the exponentials are computed twice, which is cheaper than
@@ -53,20 +57,29 @@ __host__ __device__ constexpr int act_place(int unit)
     return (unit >> 5) * 36 + (unit & 0x18) + ((unit & 2) << 1 | (unit & 1) << 1 | (unit >> 2 & 1));
 }
 
-// a chain over one block: weights in steps of STRIDE groups
+// a chain over one block: weights in steps of STRIDE groups, requested ahead (they do not depend on the layer before)
 template <int STRIDE>
-__device__ __forceinline__ float chain16(const f4v *w, const f4v *x, float acc)
+__device__ __forceinline__ void load16(f4v (&a)[4], const f4v *w, bool there = true)
 {
-    f4v a[4], h[4];
+    if (there) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        a[i] = w[i * STRIDE];
-        h[i] = x[i];
+        for (int i = 0; i < 4; ++i) a[i] = w[i * STRIDE];
+    } else {
+        // (not used; without a value of any kind here the registers of the step before would be kept)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(a[i]));
     }
+}
+__device__ __forceinline__ float chain16(const f4v (&a)[4], const f4v *x, float acc)
+{
+    f4v h[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) h[i] = x[i];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc = fmaf(a[i][e], h[i][e], acc);
+    __builtin_amdgcn_sched_barrier(0);       // (the operands of the next block in the registers of this one's)
     return acc;
 }
 
@@ -75,7 +88,8 @@ __device__ __forceinline__ float chain16(const f4v *w, const f4v *x, float acc)
 // saturates the units there are, and zero times infinity would make the others not a number).
 //   hidden layer 1 [4][width], hidden layer 2 [4 blocks][lanes], output layer [2 * 4][32 lanes], biases [3][128] floats.
 // A long contraction is cut into slices that are added up in order, as in policy16.hip: at most four for up to 64 units, two for more.
-// Hidden layer 2 gives that many neighbouring lanes to a unit, one a slice, the output layer four to an action.
+// Hidden layer 2 gives two or four neighbouring lanes to a unit, one a slice (lanes for slices that are not there would read weights as
+// the others do, and the layer is bound by reading them), the output layer four to an action.
 template <bool WIDE>
 struct policy_weights {
     static constexpr int W = WIDE ? 128 : 64, LANES = 256;
@@ -112,6 +126,14 @@ __device__ __forceinline__ double shuffle(double v, int lane)
 // A wave's own LDS writes are seen by its later reads; this keeps the compiler from moving them
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
+// What a step leaves behind, as floats in one place: a lane that stores one of them to a tape knows its place
+struct step_values {
+    double x[16];                            // inputs of the sample evaluation
+    float act[2][144];
+    float hin[16];                           // policy input
+    float a[8];                              // action tape
+};
+
 template <int D, int CK, bool WIDE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void rollout_kernel(
     rollout_args r, policy_shape p, const float *__restrict__ theta, const double *__restrict__ Xs, const double *__restrict__ Os,
@@ -122,10 +144,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     constexpr int RS = CK + 2, CHUNK = 64 / CK * RS;                       // doubles per row and per chunk of terms
     // terms: [KC 64 / CK][CK + 2] doubles of the kernel rows, then [FC 64 / CK][CK + 2] pairs (w, cos) of the features; policy weights
     extern __shared__ __align__(16) double terms[];
-    __shared__ __align__(16) double gsum[MAX_SUMS], xS[16];
+    __shared__ __align__(16) double gsum[MAX_SUMS];
     __shared__ double AS[8][D];              // -1/2 A
-    __shared__ float goalS[2][16], aS[8];    // goals of the next step and this one (lane M + j: entry M + j), action tape
-    __shared__ __align__(16) float act[2][144];
+    __shared__ float goalS[2][16];           // goals of the next step and this one (lane M + j: entry M + j)
+    __shared__ __align__(16) step_values sv;
     // Workgroups past the trajectories pack the weights for the backward pass (a launch of its own in front took 4.7 us)
     if ((int)blockIdx.x >= r.B) {
         pack_theta16(r.pack, theta, ((int)blockIdx.x - r.B) * NT + (int)threadIdx.x);
@@ -173,8 +195,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     using PW = policy_weights<WIDE>;
     f4v *const w0 = reinterpret_cast<f4v *>(terms + (r.KC + r.FC) * CHUNK), *const w1 = w0 + PW::MID, *const w2 = w0 + PW::LAST;
     float *const biases = reinterpret_cast<float *>(w0 + PW::BIAS);
-    // more than 64 units: two lanes a unit in hidden layer 2, otherwise four
-    const bool two = WIDE && p.width[2] > 64;
+    // lanes a unit of hidden layer 2, one a slice: two for up to 64 inputs or more than 64 units, otherwise four
+    const bool two = !WIDE || p.width[1] <= 64 || p.width[2] > 64;
     {
         const int n0 = p.width[0], n1 = p.width[1], n2 = p.width[2], n_last = p.width[p.nl - 1];
         auto load = [&](int l, bool live, int u, int k, int n_in) { return live && k < n_in ? theta[r.w_off[l] + u * n_in + k] : 0.0f; };
@@ -204,12 +226,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const int n = l == 0 ? n1 : (l == 1 ? n2 : p.width[3]), off = l == 0 ? r.b_off[0] : (l == 1 ? r.b_off[1] : r.b_off[2]);
             biases[tid] = l < p.nl && u < n ? theta[off + u] : 0.0f;
         }
-        if (tid < 288) act[tid / 144][tid % 144] = 0.0f;
+        if (tid < 288) sv.act[tid / 144][tid % 144] = 0.0f;
         if (tid < MAX_SUMS) gsum[tid] = 0.0;                               // (group sums past an output's last are never written)
         if (tid < M * D) AS[tid / D][tid % D] = -0.5 * A[tid];
     }
     // a layer that only the first wave has a part in needs no barrier after it
     const int lanes1 = p.nl == 3 ? p.width[2] << (two ? 1 : 2) : 0;        // lanes of hidden layer 2
+    const int blocks1 = p.width[1] > 16 ? 2 : 1, blocks2 = p.width[p.nl - 1] > 16 ? 2 : 1;     // blocks of 16 inputs of a slice, at least
     const bool barrier0 = p.width[1] > 64 || lanes1 > 64, barrier1 = lanes1 > 64;
 
     int ml = min(lane, M - 1);
@@ -229,17 +252,76 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         unit_to = m < M ? (2 * m + (wave_kernel ? 0 : 1)) * r.GS + g : MAX_SUMS - 1;
     }
 
+    // ---- what is kept of a step: one value a lane (two of a layer of more than 64 units), by waves 5 to 7 --------------------
+    // keep_at: place in sv (-1: none), keep_to: where it goes in this step, keep_stride: floats from step to step.  (Formed from the
+    // arguments in every step instead, addresses and conditions took these waves 1400 cycles, and the others waited.)
+    int keep_at = -1, keep_more = 0, keep_stride = 0;
+    float *keep_to = nullptr;
+    const float *const svf = reinterpret_cast<const float *>(&sv);
+    constexpr int AT_ACT = 32, AT_HIN = AT_ACT + 288, AT_A = AT_HIN + 16;
+    {
+        auto keep = [&](bool mine, float *base, size_t offset, int stride, int at) {
+            if (mine && base) {
+                keep_to = base + offset;
+                keep_stride = stride;
+                keep_at = at;
+            }
+        };
+        const size_t Bz = (size_t)B;
+        if (wave == 7) {
+            const int j = lane & 15;
+            keep(lane < M, r.tape_s, lane * Bz + b, M * B, AT_HIN + lane);
+            keep(lane >= 8 && lane < 8 + M, r.states_out, (size_t)b * M + lane - 8, M * B, AT_HIN + lane - 8);
+            keep(lane >= 16 && lane < 16 + r.d_in && r.keep, r.h[0], j * Bz + b, r.d_in * B, AT_HIN + j);
+            keep(lane >= 32 && lane < 32 + 2 * D, reinterpret_cast<float *>(r.xall), 2 * ((j >> 1) * (size_t)r.H * Bz + b) + (j & 1), 2 * B, j);
+            keep(lane >= 48 && lane < 48 + r.da && r.keep, r.a_slot, j * Bz + b, r.da * B, AT_A + j);
+        }
+        if (wave == 5 || wave == 6) {
+            const int l = 6 - wave;          // wave 6: hidden layer 1
+            if (l < p.nl - 1 && r.keep) {
+                const int n = l == 0 ? p.width[1] : p.width[2];
+                keep(lane < n, l == 0 ? r.h[1] : r.h[2], lane * Bz + b, n * B, AT_ACT + 144 * l + act_place(lane));
+                keep_more = n - 64;
+            }
+        }
+    }
+
     // ---- state: lane m < M of every wave holds s_m, lanes M .. d_in - 1 the goal the policy sees ------------------------
     double s = lane < M ? (double)s0[(size_t)b * M + ml] : 0.0;
-    // (zero past d_in).  Wave 7 fetches the goals two steps ahead and hands them to the others.
+    // (zero past d_in).  Wave 4 fetches the goals two steps ahead and hands them to the others.
     const bool goal_lane = lane >= M && lane < r.d_in;
     float goal = goal_lane ? goals[(size_t)b * r.dg + lane - M] : 0.0f, goal_ahead = 0.0f;
-    if (wave == 7 && goal_lane && r.H > 1) goal_ahead = goals[(size_t)B * r.dg + (b * r.dg + lane - M)];
-    if (tid < 32) goalS[tid >> 4][tid & 15] = 0.0f;
+    if (wave == 4) {
+        keep_to = const_cast<float *>(goals) + (size_t)b * r.dg + lane - M;    // (only read through)
+        keep_stride = B * r.dg;
+        if (goal_lane && r.H > 1) goal_ahead = keep_to[(size_t)keep_stride];
+        keep_to += 2 * (size_t)keep_stride;
+    }
+    if (tid < 16) {
+        goalS[0][tid] = goal;
+        goalS[1][tid] = 0.0f;
+    }
+    const int H = r.H, dg = r.dg, da = r.da, GS = r.GS;
+    const float act_bound = r.act_bound;
+    const bool saturating = r.cost_kind == 1;
+    // cost of state s against the goals the policy saw before it (against[M + j]: goal j), by wave 4.  Lane j: tracked state j
+    const int cost_lane = r.tracked[min(lane, dg - 1)];
+    const double cost_q = (double)r.q[min(lane, dg - 1)];
     double cost = 0.0;
+    auto add_cost = [&](const float *against) {
+        const double dlt = shuffle(s, cost_lane) - (double)against[M + min(lane, dg - 1)], term = cost_q * dlt * dlt;
+        double e = 0.0;
+        for (int i = 0; i < dg; ++i) e += from_lane(term, i);
+        if (saturating) {
+            const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
+            e = -cost_exp(-e / (2.0 * sr2));
+        }
+        cost += e;
+    };
     exp2_coefficients ec;
     asm volatile("" : "+v"(ec.c6));
     __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0f70);      // (vmcnt(0): inside the loop the waits for the rows above would be waits for its stores)
 
     int t = 0;
     for (;;) {
@@ -269,21 +351,32 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 inputs(2);
                 inputs(3);
             }
-            act[0][act_place(tid)] = tid < p.width[1] ? tanh_fast(z + bias) : 0.0f;
+            sv.act[0][act_place(tid)] = tid < p.width[1] ? tanh_fast(z + bias) : 0.0f;
         }
-        if (barrier0) __syncthreads();
-        else wave_sync();
+        if (wave == 7 && lane < 16) sv.hin[lane] = hin;
         if (p.nl == 3) {
-            if (64 * wave < lanes1) {
-                const int u = two ? tid >> 1 : tid >> 2, sl = two ? tid & 1 : tid & 3;
+            const int u = two ? tid >> 1 : tid >> 2, sl = two ? tid & 1 : tid & 3;
+            auto arrive = [&] {              // (each wave at one of the two places below)
+                if (barrier0) __syncthreads();
+                else wave_sync();
+            };
+            if (64 * wave >= lanes1) {
+                arrive();
+            } else {
+                f4v wa[4], wb[4];
+                load16<PW::LANES>(wa, w1 + tid);
                 const float bias = biases[128 + u];
+                arrive();
+                load16<PW::LANES>(wb, w1 + 4 * PW::LANES + tid, blocks1 > 1);
                 // (past the last slice the weights are zero: operands of any place will do, as one that is not a number is in every unit's chain)
-                const f4v *w = w1 + tid, *x = reinterpret_cast<const f4v *>(act[0]) + (two ? 9 * (p.fs >> 1) * sl : 9 * sl);
-                float z = chain16<PW::LANES>(w, x, 0.0f);
-                z = chain16<PW::LANES>(w + 4 * PW::LANES, x + 4, z);
+                const f4v *x = reinterpret_cast<const f4v *>(sv.act[0]) + (two ? 9 * (p.fs >> 1) * sl : 9 * sl);
+                float z = chain16(wa, x, 0.0f);
+                if (blocks1 > 1) z = chain16(wb, x + 4, z);
                 if (WIDE && p.fs == 4) {
-                    z = chain16<PW::LANES>(w + 8 * PW::LANES, x + 9, z);
-                    z = chain16<PW::LANES>(w + 12 * PW::LANES, x + 13, z);
+                    load16<PW::LANES>(wa, w1 + 8 * PW::LANES + tid);
+                    z = chain16(wa, x + 9, z);
+                    load16<PW::LANES>(wb, w1 + 12 * PW::LANES + tid);
+                    z = chain16(wb, x + 13, z);
                 }
                 // slices in order: quad_perm broadcasts
                 const int zi = __float_as_int(z);
@@ -291,22 +384,26 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xf5, 0xf, 0xf, true));
                 } else {
                     z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0x55, 0xf, 0xf, true));
-                    if (p.width[1] > 64) {
-                        z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xaa, 0xf, 0xf, true));
-                        z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xff, 0xf, 0xf, true));
-                    }
+                    z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xaa, 0xf, 0xf, true));
+                    z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0xff, 0xf, 0xf, true));
                 }
-                if (sl == 0 && u < p.width[2]) act[1][act_place(u)] = tanh_fast(z + bias);
+                if (sl == 0 && u < p.width[2]) sv.act[1][act_place(u)] = tanh_fast(z + bias);
             }
-            if (barrier1) __syncthreads();
-            else wave_sync();
         }
+        auto arrive = [&] {
+            if (p.nl == 3 ? barrier1 : barrier0) __syncthreads();
+            else wave_sync();
+        };
         if (wave == 0) {                     // actions: lane 4 o + slice
             const int o = (lane & 31) >> 2, sl = lane & 3;
-            const f4v *w = w2 + (lane & 31), *x = reinterpret_cast<const f4v *>(act[p.nl - 2]) + 9 * sl;
+            f4v wa[4], wb[4];
+            load16<32>(wa, w2 + (lane & 31));
             const float bias = biases[128 * (p.nl - 1) + o];
-            float z = chain16<32>(w, x, 0.0f);
-            if (p.width[p.nl - 1] > 16) z = chain16<32>(w + 128, x + 4, z);
+            arrive();
+            load16<32>(wb, w2 + 128 + (lane & 31), blocks2 > 1);
+            const f4v *x = reinterpret_cast<const f4v *>(sv.act[p.nl - 2]) + 9 * sl;
+            float z = chain16(wa, x, 0.0f);
+            if (blocks2 > 1) z = chain16(wb, x + 4, z);
             const int zi = __float_as_int(z);
             z += __int_as_float(__builtin_amdgcn_update_dpp(0, zi, 0x55, 0xf, 0xf, true));
             if (WIDE) {
@@ -315,21 +412,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             }
             z += bias;
             float a = z, out = z;
-            if (r.act_bound > 0.0f) {
+            if (act_bound > 0.0f) {
                 a = tanh_fast(z);
-                out = r.act_bound * a;
+                out = act_bound * a;
             }
-            if (lane < 4 * r.da && sl == 0) {
-                xS[M + o] = (double)out;
-                aS[o] = a;
+            if (lane < 4 * da && sl == 0) {
+                sv.x[M + o] = (double)out;
+                sv.a[o] = a;
             }
-            if (lane < M) xS[lane] = s;
+            if (lane < M) sv.x[lane] = s;
+        } else {
+            arrive();
+            if (wave == 4 && t > 0) add_cost(goalS[(t - 1) & 1]);
         }
         double Am[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) Am[d] = AS[ml][d];
         __syncthreads();
-        const double xl = xS[lane & 15];
+        const double xl = sv.x[lane & 15];
         double x[D];
 #pragma unroll
         for (int d = 0; d < D; ++d) x[d] = from_lane(xl, d);
@@ -344,8 +444,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             asm volatile("" : "+s"(nk), "+s"(nf));
             asm volatile("" : "+s"(ec.c7), "+s"(ec.c5), "+s"(ec.c4), "+s"(ec.c3), "+s"(ec.c2), "+s"(ec.c1), "+s"(ec.c0));
             double *kout = terms + my_points, *fout = terms + my_features;
+            const double q_of_chunk = shuffle(q, m_of_chunk);              // lane i: of chunk i
             auto exponent = [&](int i) {
-                double e = from_lane(q, __builtin_amdgcn_readlane(m_of_chunk, i)) + row[i][D];
+                double e = from_lane(q_of_chunk, i) + row[i][D];
 #pragma unroll
                 for (int d = 0; d < D; ++d) e = fma(x[d], row[i][d], e);
                 return e;
@@ -392,6 +493,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     }
                 }
             };
+            features(features, std::integral_constant<int, 0>{});
             if (__builtin_expect(far == 0, 1)) {
                 points(points, std::integral_constant<int, 0>{});
             } else {
@@ -401,7 +503,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 for (int i = 0; i < E; ++i)
                     if (i < nk) point(i, far >> __builtin_amdgcn_readlane(m_of_chunk, i) & 1 ? outside + row[i][D] : exponent(i));
             }
-            features(features, std::integral_constant<int, 0>{});
         }
         __syncthreads();
         // ---- sums of the work units, four of them to a group ---------------------------------------------------------
@@ -452,25 +553,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             tot += dpp_move<0xff>(sum);
             if ((lane & 3) == 0) gsum[unit_to] = tot;
         }
-        // ---- meanwhile, what is kept of this step (by the last waves, which mostly have no unit) --------------------------
-        if (wave == 7) {
-            const float f = (float)s;
-            if (lane < M) {
-                if (r.tape_s) (r.tape_s + (size_t)t * M * B)[lane * B + b] = f;
-                if (r.states_out) (r.states_out + (size_t)t * M * B)[b * M + lane] = f;
+        // ---- meanwhile, what is kept of this step and the goals ahead (by the last waves, which mostly have no unit) -------------
+        if (wave >= 4) {
+            if (wave == 4) {
+                if (lane < 16) goalS[(t + 1) & 1][lane] = goal_lane ? goal_ahead : 0.0f;
+                if (goal_lane && t + 2 < H) goal_ahead = load_pinned(keep_to);
+            } else {
+                if (keep_at >= 0) *keep_to = svf[keep_at];
+                if (WIDE && lane < keep_more) keep_to[64 * (size_t)B] = svf[keep_at + 72];
             }
-            if (r.keep && lane < r.d_in) (r.h[0] + (size_t)t * r.d_in * B)[lane * B + b] = hin;
-            if (r.xall && lane < D) (r.xall + (size_t)t * B)[(size_t)lane * r.H * B + b] = xl;
-            if (lane < 16) goalS[(t + 1) & 1][lane] = goal_lane ? goal_ahead : 0.0f;
-            if (goal_lane && t + 2 < r.H) goal_ahead = load_pinned(goals + (size_t)(t + 2) * B * r.dg + (b * r.dg + lane - M));
-        }
-        if (wave == 4 && r.keep && lane < r.da) (r.a_slot + (size_t)t * r.da * B)[lane * B + b] = aS[lane];
-        if (r.keep && wave >= 5) {           // waves 5 and 6: activations
-#pragma unroll
-            for (int l = 0; l < 2; ++l)
-                if (l < p.nl - 1 && wave == 6 - l)
-                    for (int u = lane; u < p.width[l + 1]; u += 64)
-                        (r.h[l + 1] + (size_t)t * p.width[l + 1] * B)[u * B + b] = act[l][act_place(u)];
+            keep_to += keep_stride;
         }
         __syncthreads();
         // ---- state s_{t+1}: lanes 2 m add up the kernel rows of output m, lanes 2 m + 1 its features (8 sums, then the rest: see
@@ -478,9 +570,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         float goal_next;
         {
             goal_next = goalS[(t + 1) & 1][lane & 15];
-            const double2 *g2 = reinterpret_cast<const double2 *>(gsum + min(lane, 2 * M - 1) * r.GS);
+            const double2 *g2 = reinterpret_cast<const double2 *>(gsum + min(lane, 2 * M - 1) * GS);
             double tot = 0.0, rest = 0.0;
-            for (int c0 = 0; c0 < r.GS; c0 += 8) {
+            for (int c0 = 0; c0 < GS; c0 += 8) {
                 double2 a[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) a[i] = g2[c0 / 2 + i];
@@ -497,28 +589,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const double k = shuffle(tot, 2 * ml), e = shuffle(tot, 2 * ml + 1);
             s += amp_lane * e + k;
         }
-        if (wave == 4) {                                                   // cost of s_{t+1} against goal t
-            double e = 0.0;
-            for (int j = 0; j < r.dg; ++j) {
-                const double gt = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(goal), M + j));
-                const double dlt = from_lane(s, r.tracked[j]) - gt;
-                e += (double)r.q[j] * dlt * dlt;
-            }
-            if (r.cost_kind == 1) {
-                const double sr2 = (double)r.sigma_r * (double)r.sigma_r;
-                e = -exp(-e / (2.0 * sr2));
-            }
-            cost += e;
-        }
         goal = lane < 16 ? goal_next : 0.0f;
-        if (++t == r.H) break;
+        if (++t == H) break;
     }
     if (wave == 7 && lane < M) {
         const float f = (float)s;
         if (r.tape_s) (r.tape_s + (size_t)t * M * B)[lane * B + b] = f;
         if (r.states_out) (r.states_out + (size_t)t * M * B)[b * M + lane] = f;
     }
-    if (wave == 4 && lane == 0) r.lpt[b] = cost;
+    if (wave == 4) {
+        add_cost(goalS[(t - 1) & 1]);
+        if (lane == 0) r.lpt[b] = cost;
+    }
 }
 
 #define ROLLOUT_INPUTS(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)

@@ -1,5 +1,5 @@
-// The exponential of the kernel row, shared by the sample evaluation (gp_step.hip) and the rollout with one workgroup per
-// trajectory (rollout.hip), which must give the same bits.
+// Exponentials shared by kernels that must give the same bits: that of the kernel row by the sample evaluation (gp_step.hip) and the rollout
+// with one workgroup per trajectory (rollout.hip), that of the cost by all end-of-step kernels.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,6 +43,26 @@ __device__ __forceinline__ void exp2_poly2(double t0, double t1, const exp2_coef
     p0 = fma(p0, f0, c.c0); p1 = fma(p1, f1, c.c0);
     k0 = ldexp(p0 * p0, (int)n0);
     k1 = ldexp(p1 * p1, (int)n1);
+}
+
+// exp(x) for the saturating cost (x <= 0; relative error 1.4e-16 down to x = -700): x = n log 2 + r with log 2 in two parts, and the Taylor
+// polynomial of degree 13 in r.  The compiler keeps the constants of the library's function, 19 vector registers, from step to step of
+// rollout.hip, where the rows need them; here they are scalars, and made anew.
+__device__ __forceinline__ double cost_exp(double x)
+{
+    double c[14] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800,
+                    1.0 / 479001600, 1.0 / 6227020800.0};
+    double log2e = 1.4426950408889634, hi = -0x1.62e42fefa0000p-1, lo = -0x1.cf79abc9e3b3ap-40;
+    asm volatile("" : "+s"(log2e), "+s"(hi), "+s"(lo));
+#pragma unroll
+    for (int k = 2; k < 14; ++k) asm volatile("" : "+s"(c[k]));
+    const double n = rint(x * log2e);
+    double r = fma(n, hi, x);
+    r = fma(n, lo, r);
+    double p = c[13];
+#pragma unroll
+    for (int k = 12; k >= 0; --k) p = fma(p, r, c[k]);
+    return x < -746.0 ? 0.0 : ldexp(p, (int)n);
 }
 
 }  // namespace
