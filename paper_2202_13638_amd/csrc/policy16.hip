@@ -35,9 +35,9 @@ struct policy16_args {
 // 16 trajectories, so neighbouring tiles are given to workgroups of one chiplet: its L2 then sees whole lines.  With this
 // and without activations that nobody reads (policy16_args::keep), forward passes at 256-256, B = 4096 took 57.7 instead of 68.4
 // us per step; gradient calls at 64-64, B = 2048, 53.3 instead of 54.2.
-__device__ __forceinline__ int first_trajectory()
+__device__ __forceinline__ int first_trajectory(int B)
 {
-    const int n = gridDim.x, x = blockIdx.x & 7, q = n >> 3, r = n & 7;
+    const int n = (B + PL - 1) / PL, x = blockIdx.x & 7, q = n >> 3, r = n & 7;
     return (x * q + min(x, r) + ((int)blockIdx.x >> 3)) * PL;
 }
 
@@ -53,28 +53,35 @@ struct forward_weights {
     f4v mid[NT][NW * NT], last[2], bias0[NT], bias1[NT];      // last: the two blocks of slice `wave`
 };
 
+// those of the narrow layers and the biases; blocks kb0 .. kb1 - 1 of the middle layer
 template <int NW, int NT>
-__device__ __forceinline__ void load_weights(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane)
+__device__ __forceinline__ void load_narrow(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane)
 {
     constexpr int TT = NW * NT;
-    const f4v *mid = reinterpret_cast<const f4v *>(pack + p.f_mid()) + lane;
-    const f4v *last = reinterpret_cast<const f4v *>(pack + p.f_last()) + lane;
-    const int g = lane >> 4;
+    // (a scalar base and the lane, unsigned: the load adds them itself)
+    const unsigned ul = lane, g = ul >> 4;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int tile = wave * NT + t;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) f.first[t][s] = pack[p.f_first() + (tile * p.nsi + min(s, p.nsi - 1)) * 64 + lane];
-        f.bias0[t] = *reinterpret_cast<const f4v *>(pack + p.bias(0) + 16 * tile + 4 * g);
-        f.bias1[t] = *reinterpret_cast<const f4v *>(pack + p.bias(1) + 16 * tile + 4 * g);
+        for (int s = 0; s < 4; ++s) f.first[t][s] = (pack + p.f_first() + (tile * p.nsi + min(s, p.nsi - 1)) * 64)[ul];
+        f.bias0[t] = reinterpret_cast<const f4v *>(pack + p.bias(0) + 16 * tile)[g];
+        f.bias1[t] = reinterpret_cast<const f4v *>(pack + p.bias(1) + 16 * tile)[g];
     }
 #pragma unroll
-    for (int e = 0; e < 2; ++e) f.last[e] = last[min(2 * wave + e, TT - 1) * 64];
+    for (int e = 0; e < 2; ++e) f.last[e] = reinterpret_cast<const f4v *>(pack + p.f_last() + min(2 * wave + e, TT - 1) * 256)[ul];
+}
+template <int NW, int NT>
+__device__ __forceinline__ void load_middle(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane, int kb0, int kb1)
+{
+    constexpr int TT = NW * NT;
+    const unsigned ul = lane;
     if (p.nl == 3) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int kb = 0; kb < TT; ++kb) f.mid[t][kb] = mid[((wave * NT + t) * TT + kb) * 64];
+            for (int kb = 0; kb < TT; ++kb)
+                if (kb >= kb0 && kb < kb1) f.mid[t][kb] = reinterpret_cast<const f4v *>(pack + p.f_mid() + ((wave * NT + t) * TT + kb) * 256)[ul];
     }
 }
 
@@ -167,30 +174,51 @@ struct tail16_args {
 
 constexpr int TAIL_GROUPS = 128;             // value sums of a trajectory that are staged in LDS
 
-template <int NW, int NT>
+// What a step waits for is trips to memory one after the other, so everything is requested before anything waits: the arguments
+// (they come from memory as well, and the compiler would fetch each where it is first used, a trip of 300 to 700 cycles a time), what is
+// summed, the weights of the narrow layers and half of a wide middle layer's.  The rest of that comes while the first layer is worked
+// on: all of it at once, 256 KB for a compute unit, held up the waves that were to write their sums to LDS.  No load stands
+// in a branch of its own: where paths join, the compiler waits for what one of them has requested.
+// What is kept of the state, and the cost, come last, beside the action.  (us a launch, before and now: 64-64, B = 1024 6.1 and 5.0, 100-37,
+// B = 777 7.0 and 6.0, 256-256, B = 4096 14.6 and 13.6, of which the matrix instructions take 3.4.)
+// the value of the lane 16 further on, in the even rows of 16 lanes
+__device__ __forceinline__ double next_row(double v)
+{
+    unsigned a = __double2loint(v), b = __double2hiint(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap(a, a, false, false), hi = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    return __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+enum tail_mode { TAIL_SUMS, TAIL_DIRECT, TAIL_START };                     // part: groups' sums, final values; s0 instead
+
+template <int NW, int NT, int MODE>
 __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, policy16_args a, pack16 p)
 {
     using S = shape16<NW, NT>;
+    constexpr int TT = NW * NT, TT_AHEAD = NT == 2 ? TT / 2 : TT;          // blocks of the middle layer requested at the start
     __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
     __shared__ double fS[TAIL_GROUPS][PL], sS[8][PL];
+    asm volatile("" ::"s"(r.x_cur), "s"(r.part), "s"(r.amp), "s"(r.goals_t), "s"(r.goals_next), "s"(r.lpt), "s"(r.x_next), "s"(r.tape_s_next),
+                 "s"(r.states_out_next), "s"(a.pack), "s"(a.h[0]), "s"(a.h[1]), "s"(a.h[2]), "s"(r.slot), "s"(r.D), "s"(r.M), "s"(r.dg), "s"(r.ngk),
+                 "s"(r.ngl), "s"(r.do_policy), "s"(a.B), "s"(a.ds), "s"(a.width[0]), "s"(a.keep), "s"(p.nl), "s"(p.nsi), "s"(p.fs));
+    asm volatile("" ::"s"(a.width[1]), "s"(a.width[2]), "s"(a.width[3]), "s"(a.da), "s"(a.act_bound), "s"(a.a_slot), "s"(r.cost_kind));
+    p.TT = TT;                               // (not an argument to wait for)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const int b0 = first_trajectory();
+    const int b0 = first_trajectory(a.B);
     const bool live = b0 + bl < a.B;         // (trajectory bl is also lane % 16: the same for the matrix phases)
     const int b = live ? b0 + bl : a.B - 1;
     const int B = a.B, ds = a.ds, d_in = a.width[0];
 
-    // Everything that comes from memory is requested before anything waits, the values needed first first.
-    double x_in = 0.0, lp_in = 0.0;
-    float g_in = 0.0f, gt_in[8], bias_in = 0.0f;
-    const bool cost_row = !r.s0 && row == S::ROWS - 1;
-    if (row < ds) x_in = r.s0 ? (double)r.s0[(size_t)b * ds + row] : r.x_cur[(size_t)row * B + b];
-    else if (row < d_in && r.goals_next) g_in = r.goals_next[(size_t)b * r.dg + (row - ds)];
-    if (cost_row) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) gt_in[j] = j < r.dg ? r.goals_t[(size_t)b * r.dg + j] : 0.0f;
-        lp_in = r.lpt[b];
-    }
+    // Thread row 2 m has state m and its kernel rows' sums, row 2 m + 1 its features' sums and goal m.
+    const int m = row >> 1, ms = min(m, ds - 1);
+    const bool even = (row & 1) == 0;
+    double x_in;
+    if constexpr (MODE == TAIL_START) x_in = (double)load_pinned(r.s0 + (size_t)b * ds + ms);
+    else x_in = load_pinned(r.x_cur + (size_t)ms * B + b);
+    const float *const goals = MODE == TAIL_START || r.goals_next ? r.goals_next : r.goals_t;      // (after the last step any will do)
+    const float g_in = load_pinned(goals + (size_t)b * r.dg + min(m, r.dg - 1));
+    const double amp_in = MODE == TAIL_SUMS ? load_pinned(r.amp + ms) : 0.0;
     // The groups' value sums are fetched by all threads, a few each, and added up from LDS in the order of policy.hip (the
     // first eight, then the rest); more than fit there are added up by one thread row per sum.
     const size_t stride = (size_t)(1 + r.D) * B;
@@ -198,69 +226,79 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
     const bool staged = groups <= TAIL_GROUPS;
     constexpr int PER = TAIL_GROUPS / S::ROWS;
     double v[PER];
-    if (r.s0) {
-    } else if (r.direct) {
-        for (int qi = row; qi < r.M * r.ncomp; qi += S::ROWS) {
-            const int m = qi / r.ncomp, comp = qi - m * r.ncomp;
-            const double val = r.part[(size_t)m * stride + (size_t)comp * B + b];
-            if (comp == 0) fS[m][bl] = val;
-            else if (live) r.jdst[(size_t)(m * r.D + comp - 1) * B + b] = (float)val;
-        }
-    } else if (staged) {
+    if constexpr (MODE == TAIL_SUMS) {
+        if (staged) {
 #pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (u * S::ROWS < groups) v[u] = load_pinned(r.part + (size_t)min(row + u * S::ROWS, groups - 1) * stride + b);
+            for (int u = 0; u < PER; ++u)
+                if (u * S::ROWS < groups) v[u] = load_pinned(r.part + (size_t)min(row + u * S::ROWS, groups - 1) * stride + b);
+        }
+    }
+    const bool cost_row = MODE != TAIL_START && row == S::ROWS - 1;
+    float gt_in[8];
+    double lp_in = 0.0;
+    if (MODE != TAIL_START && wave == NW - 1) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) gt_in[j] = load_pinned(r.goals_t + (size_t)b * r.dg + min(j, r.dg - 1));
+        lp_in = load_pinned(r.lpt + b);
     }
     forward_weights<NW, NT> f;
+    float bias_in = 0.0f;
     if (r.do_policy) {
-        load_weights(f, a.pack, p, wave, lane);
+        load_narrow(f, a.pack, p, wave, lane);
         bias_in = a.pack[p.bias(2) + min(row, 7)];
+        load_middle(f, a.pack, p, wave, lane, 0, TT_AHEAD);
     }
-    if (!r.s0 && !r.direct) {
+    if constexpr (MODE == TAIL_DIRECT) {
+        for (int qi = row; qi < r.M * r.ncomp; qi += S::ROWS) {
+            const int mq = qi / r.ncomp, comp = qi - mq * r.ncomp;
+            const double val = r.part[(size_t)mq * stride + (size_t)comp * B + b];
+            if (comp == 0) fS[mq][bl] = val;
+            else if (live) r.jdst[(size_t)(mq * r.D + comp - 1) * B + b] = (float)val;
+        }
+    }
+    if constexpr (MODE == TAIL_SUMS) {
         if (staged) {
 #pragma unroll
             for (int u = 0; u < PER; ++u)
                 if (u * S::ROWS < groups) fS[min(row + u * S::ROWS, TAIL_GROUPS - 1)][bl] = v[u];
-        } else if (row < 2 * r.M) {
-            const bool kernel = row < r.M;
-            fS[row][bl] = sum_groups16(r.part + (size_t)(kernel ? row * r.ngk : r.M * r.ngk + (row - r.M) * r.ngl) * stride + b,
-                                       kernel ? r.ngk : r.ngl, stride);
         }
     }
-    __syncthreads();
+    if constexpr (MODE != TAIL_START) __syncthreads();
     if (row < 16) {
-        float hin = 0.0f;
-        if (row < ds) {
-            double s = x_in;
-            if (r.direct) {
-                s += fS[row][bl];
-            } else if (!r.s0) {
-                double k, e;
-                if (staged) {
-                    k = sum_groups16(&fS[row * r.ngk][bl], r.ngk, PL);
-                    e = sum_groups16(&fS[r.M * r.ngk + row * r.ngl][bl], r.ngl, PL);
-                } else {
-                    k = fS[row][bl];
-                    e = fS[r.M + row][bl];
-                }
-                s += r.amp[row] * e + k;
+        double s = x_in;
+        if constexpr (MODE == TAIL_DIRECT) s += fS[ms][bl];
+        if constexpr (MODE == TAIL_SUMS) {
+            double sum = 0.0;
+            if (m < ds) {
+                const int n = even ? r.ngk : r.ngl, first = even ? m * r.ngk : r.M * r.ngk + m * r.ngl;
+                sum = staged ? sum_groups16(&fS[first][bl], n, PL) : sum_groups16(r.part + (size_t)first * stride + b, n, stride);
             }
-            sS[row][bl] = s;
-            hin = (float)s;
-            if (live) {
-                r.x_next[(size_t)row * B + b] = s;
-                if (r.tape_s_next) r.tape_s_next[(size_t)row * B + b] = hin;
-                if (r.states_out_next) r.states_out_next[(size_t)b * ds + row] = hin;
-            }
-        } else if (row < d_in) {
-            hin = g_in;
+            s += amp_in * next_row(sum) + sum;
         }
-        h0[bl * HS + row] = hin;
-        if (r.do_policy && live && a.keep && row < d_in) a.h[0][(r.slot * d_in + row) * B + b] = hin;
+        const float hin = even ? (float)s : g_in;
+        if (even && m < ds) sS[m][bl] = s;
+        if (m < (even ? ds : r.dg)) h0[bl * HS + (even ? m : ds + m)] = hin;
+        if (row >= d_in) h0[bl * HS + row] = 0.0f;
     }
-    if (r.s0 && row == 0 && live) r.lpt[b] = 0.0;
+    if (MODE == TAIL_START && row == 0 && live) r.lpt[b] = 0.0;
     __syncthreads();
-    if (r.do_policy) policy16_layers<NW, NT>(a, p, f, r.slot, wave, lane, b, live, h0, act, red);
+    if (TT_AHEAD < TT && r.do_policy) load_middle(f, a.pack, p, wave, lane, TT_AHEAD, TT);
+    if (r.do_policy) {
+        policy16_layers<NW, NT>(a, p, f, r.slot, wave, lane, b, live, h0, act, red);
+        __syncthreads();
+        if (row < a.da) finish_action(a, p, r.slot, row, bl, b, live, red, bias_in, r.x_next);
+    }
+    // what is kept of the state and the policy's input, and the cost, by the waves that have no action to finish
+    if (row >= 4 && live)
+        for (int i = row - 4; i < d_in; i += S::ROWS - 4) {
+            const float hin = h0[bl * HS + i];
+            if (r.do_policy && a.keep) a.h[0][(r.slot * d_in + i) * B + b] = hin;
+            if (i < ds) {
+                r.x_next[(size_t)i * B + b] = sS[i][bl];
+                if (r.tape_s_next) r.tape_s_next[(size_t)i * B + b] = hin;
+                if (r.states_out_next) r.states_out_next[(size_t)b * ds + i] = hin;
+            }
+        }
     if (cost_row && live) {
         double e = 0.0;
 #pragma unroll
@@ -275,9 +313,6 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
         }
         r.lpt[b] = lp_in + e;
     }
-    if (!r.do_policy) return;
-    __syncthreads();
-    if (row < a.da) finish_action(a, p, r.slot, row, bl, b, live, red, bias_in, r.x_next);
 }
 
 // ---- activation tape of the steps t0 .. t0 + n_slots - 1 rebuilt from the kept states (see policy_replay_kernel) --------
@@ -293,12 +328,13 @@ __global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args 
     __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const int b0 = first_trajectory();
+    const int b0 = first_trajectory(a.B);
     const bool live = b0 + bl < a.B;
     const int b = live ? b0 + bl : a.B - 1;
     const int B = a.B, ds = a.ds, d_in = a.width[0];
     forward_weights<NW, NT> f;
-    load_weights(f, a.pack, p, wave, lane);
+    load_narrow(f, a.pack, p, wave, lane);
+    load_middle(f, a.pack, p, wave, lane, 0, NW * NT);
     const float bias = a.pack[p.bias(2) + min(row, 7)];
     const int s_end = min(r.n_slots, (int)(blockIdx.y + 1) * r.per);
     auto input = [&](int sl) {
@@ -380,7 +416,7 @@ __global__ __launch_bounds__(64 * NW) void backward_sweep16_kernel(sweep16_args 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4, ug = (g & 1) << 2 | g >> 1;       // unit16(g, r) = ug + unit16(0, r)
     const int bl = tid & (PL - 1), row = tid >> 4;
-    const int b0 = first_trajectory();
+    const int b0 = first_trajectory(a.B);
     const bool live = b0 + bl < a.B;
     const int b = live ? b0 + bl : a.B - 1;
     const int last = a.nl - 1;
@@ -569,8 +605,12 @@ policy16_args make_policy(const bagel_ctx *c, bool keep)
 template <int NW, int NT>
 void launch_tail(bagel_ctx *c, const tail16_args &r, bool keep)
 {
-    hipLaunchKernelGGL((step_tail16_kernel<NW, NT>), dim3((c->dm.B + PL - 1) / PL), dim3(64 * NW), 0, c->stream, r,
-                       make_policy(c, keep), make_pack(c));
+    const dim3 grid((c->dm.B + PL - 1) / PL), block(64 * NW);
+    const policy16_args a = make_policy(c, keep);
+    const pack16 p = make_pack(c);
+    if (r.s0) hipLaunchKernelGGL((step_tail16_kernel<NW, NT, TAIL_START>), grid, block, 0, c->stream, r, a, p);
+    else if (r.direct) hipLaunchKernelGGL((step_tail16_kernel<NW, NT, TAIL_DIRECT>), grid, block, 0, c->stream, r, a, p);
+    else hipLaunchKernelGGL((step_tail16_kernel<NW, NT, TAIL_SUMS>), grid, block, 0, c->stream, r, a, p);
 }
 
 hipError_t launch_tail(bagel_ctx *c, const tail16_args &r, bool keep)
