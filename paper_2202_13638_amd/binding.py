@@ -129,17 +129,22 @@ def bagel_num_params(dims: Dims) -> int:
     return int(load().bagel_num_params(C.byref(dims)))
 
 
+_Tensor = _float32 = None        # torch's, looked up once: a call checks up to eleven tensors
+
+
 def _ptr(t, shape, name, optional=False):
-    import torch
+    global _Tensor, _float32
     if t is None:
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.float32 or not t.is_contiguous():
+    if _Tensor is None:
+        from torch import Tensor as _Tensor, float32 as _float32
+    if not isinstance(t, _Tensor) or not t.is_cuda or t.dtype is not _float32 or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous float32 tensor on the GPU")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def bagel_sample_eval_static(dims: Dims, X, lengthscale, signal_var, omega, phase, w, v, x, f, jac=None, stream=None):

@@ -382,17 +382,10 @@ static unsigned char *scratch_base(hipError_t *err)
     return g_scratch_ptr[dev];
 }
 
-// bytes of the static array a call with these dims uses, or BAGEL_EINVAL
-static int64_t static_scratch_bytes(const bagel_dims *dims)
+// bytes of the static array a call uses whose work units are planned in c
+static int64_t static_scratch_bytes(const bagel_ctx &c)
 {
-    if (!dims || check_dims(dims)) return BAGEL_EINVAL;
-    bagel_ctx c;
-    memset(&c, 0, sizeof(c));
-    c.dm = *dims;
-    c.D = dims->d_s + dims->d_a;
-    c.M = dims->d_s;
-    if (bagel_plan_sample_eval(&c, true)) return BAGEL_EINVAL;
-    const int64_t M = c.M, D = c.D, B = dims->B, S = dims->S;
+    const int64_t M = c.M, D = c.D, B = c.dm.B, S = c.dm.S;
     const int64_t counts[] = {8 * M * c.Np * (D + 1), 8 * M * c.Lp * (D + 1), 16 * M * c.Lp * ((D + 3) / 4), 8 * M * D, 8 * M,
                               16 * M * (c.Np / 4) * S, 16 * M * (c.Lp / 4) * S, 8 * D * B,
                               8 * (int64_t)c.groups * (1 + D) * B, 8 * M * B};     // (the last is not used any more: what fits stays as documented)
@@ -410,15 +403,6 @@ extern "C" int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream
     if (const char *msg = check_dims(dims)) CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: %s", msg);
     if (!X || !lengthscale || !signal_var || !omega || !phase || !w || !v || !x || !f)
         CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: null argument");
-    const int64_t need = static_scratch_bytes(dims);
-    if (need < 0) CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: too many work units for these sizes");
-    if (need > (int64_t)BAGEL_STATIC_SCRATCH_BYTES)
-        CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: these sizes need %lld bytes of scratch, the static buffer holds %lld",
-                    (long long)need, (long long)BAGEL_STATIC_SCRATCH_BYTES);
-    hipError_t e = hipSuccess;
-    unsigned char *base = scratch_base(&e);
-    if (!base) CREATE_FAIL(BAGEL_EHIP, "bagel_sample_eval_static: address of the static buffer: %s", hipGetErrorString(e));
-
     // a context on the host stack whose device pointers are carved out of the static array
     bagel_ctx c;
     memset(&c, 0, sizeof(c));
@@ -426,8 +410,16 @@ extern "C" int bagel_sample_eval_static(const bagel_dims *dims, void *hip_stream
     c.D = dims->d_s + dims->d_a;
     c.M = dims->d_s;
     c.stream = (hipStream_t)hip_stream;
-    (void)bagel_plan_sample_eval(&c, true);             // cannot fail: static_scratch_bytes has planned the same dims
+    if (bagel_plan_sample_eval(&c, true)) CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: too many work units for these sizes");
     c.exp_table = false;                    // the table form of exp2 reads a table this call does not have
+    const int64_t need = static_scratch_bytes(c);
+    if (need > (int64_t)BAGEL_STATIC_SCRATCH_BYTES)
+        CREATE_FAIL(BAGEL_EINVAL, "bagel_sample_eval_static: these sizes need %lld bytes of scratch, the static buffer holds %lld",
+                    (long long)need, (long long)BAGEL_STATIC_SCRATCH_BYTES);
+    hipError_t e = hipSuccess;
+    unsigned char *base = scratch_base(&e);
+    if (!base) CREATE_FAIL(BAGEL_EHIP, "bagel_sample_eval_static: address of the static buffer: %s", hipGetErrorString(e));
+
     const size_t M = c.M, D = c.D, B = dims->B, S = dims->S;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
