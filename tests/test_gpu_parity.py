@@ -193,6 +193,14 @@ def test_sample_eval_value_and_jacobian(shape):
     _check_sample_eval(shape, x)
 
 
+@pytest.mark.parametrize("d_s,d_a,N,L,S,B", [(1, 1, 1, 1, 1, 1), (2, 2, 1, 65, 64, 64), (5, 3, 65, 1, 65, 65), (3, 2, 256, 257, 1, 3),
+                                             (8, 1, 257, 256, 33, 66)])
+def test_sample_eval_edges_of_the_installed_blocks(d_s, d_a, N, L, S, B):
+    """Model rows are installed in blocks of 256 and the sample streams in blocks of 64 x 64: one row, whole blocks, one row past them."""
+    x = np.random.default_rng(6).uniform(-1.2, 1.2, (B, d_s + d_a)).astype(np.float32)
+    _check_sample_eval(dict(d_s=d_s, d_a=d_a, N=N, L=L, B=B, S=S), x)
+
+
 # the library picks the form of its float64 exp2 by launch size (polynomial on small launches, table
 # look-up on large ones); BAGEL_EXP_TABLE = 1 / 2 forces one, so that both are checked at test sizes
 EXP2_FORMS = {"polynomial": "1", "table": "2"}
@@ -611,6 +619,21 @@ def test_measurement_hook_gives_the_same_bits():
     for outs in runs[1:]:
         for a, b in zip(runs[0], outs):
             assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+# all 16 thread rows with a state or a goal, in every instance of the layers; more groups of sums (144) than are staged; no policy to
+# follow; one hidden layer; a middle layer of more, as many and fewer blocks than are requested at the start
+@pytest.mark.parametrize("d_s,d_a,d_g,N,L,H,hidden,unit", [(8, 8, 8, 40, 30, 3, (8,), ""), (8, 1, 8, 600, 500, 3, (64, 64), "16"),
+                                                           (8, 1, 8, 70, 50, 3, (100, 128), ""), (8, 2, 8, 70, 50, 3, (256, 256), ""),
+                                                           (3, 1, 2, 40, 30, 3, (128, 250), ""), (1, 1, 1, 40, 30, 1, (130, 65), "")])
+def test_end_of_step_rows_and_groups(d_s, d_a, d_g, N, L, H, hidden, unit, monkeypatch):
+    monkeypatch.setenv("BAGEL_ROLLOUT", "1")
+    monkeypatch.setenv("BAGEL_CK", unit)
+    monkeypatch.setenv("BAGEL_CL", unit)
+    cfg = synth.Config("tail", 41, d_s, d_a, d_g, N, L, 19, H, hidden, 0.8, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    ref = harness.oracle_reference(cfg, inp)
+    harness.assert_parity(ref, harness.gpu_rollout(cfg, inp, ref["v32"]), label=f"end of step/{d_s}-{d_g}-{hidden}")
 
 
 # d_s, d_a, d_g, B, H, hidden, bound, saturating, ckpt: every number of outputs, both instances of the layers, one and two hidden
