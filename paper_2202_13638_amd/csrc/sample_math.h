@@ -45,23 +45,25 @@ __device__ __forceinline__ void exp2_poly2(double t0, double t1, const exp2_coef
     k1 = ldexp(p1 * p1, (int)n1);
 }
 
-// exp(x) for the saturating cost (x <= 0; relative error 1.4e-16 down to x = -700): x = n log 2 + r with log 2 in two parts, and the Taylor
-// polynomial of degree 13 in r.  The compiler keeps the constants of the library's function, 19 vector registers, from step to step of
+// exp(x) for the saturating cost (x <= 0): x = n log 2 + r with log 2 in two parts, and the Taylor polynomial of degree 13 in r, with what
+// r and 1 + r are rounded by added at the end.  Largest and mean square relative error over two million x, own and the library's:
+// 1.11e-16 and 4.7e-17, 1.34e-16 and 4.9e-17.  The compiler keeps the constants of the library's function, 19 vector registers, from step to step of
 // rollout.hip, where the rows need them; here they are scalars, and made anew.
 __device__ __forceinline__ double cost_exp(double x)
 {
-    double c[14] = {1.0, 1.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800,
+    double c[14] = {0.0, 0.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800,
                     1.0 / 479001600, 1.0 / 6227020800.0};
     double log2e = 1.4426950408889634, hi = -0x1.62e42fefa0000p-1, lo = -0x1.cf79abc9e3b3ap-40;
     asm volatile("" : "+s"(log2e), "+s"(hi), "+s"(lo));
 #pragma unroll
     for (int k = 2; k < 14; ++k) asm volatile("" : "+s"(c[k]));
     const double n = rint(x * log2e);
-    double r = fma(n, hi, x);
-    r = fma(n, lo, r);
+    const double r0 = fma(n, hi, x), r = fma(n, lo, r0), dr = fma(n, lo, r0 - r);
     double p = c[13];
 #pragma unroll
-    for (int k = 12; k >= 0; --k) p = fma(p, r, c[k]);
+    for (int k = 12; k >= 2; --k) p = fma(p, r, c[k]);
+    const double t = 1.0 + r;
+    p = t + fma(r * r, p, ((1.0 - t) + r) + dr);
     return x < -746.0 ? 0.0 : ldexp(p, (int)n);
 }
 
