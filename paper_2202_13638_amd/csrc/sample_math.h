@@ -45,26 +45,42 @@ __device__ __forceinline__ void exp2_poly2(double t0, double t1, const exp2_coef
     k1 = ldexp(p1 * p1, (int)n1);
 }
 
-// exp(x) for the saturating cost (x <= 0): x = n log 2 + r with log 2 in two parts, and the Taylor polynomial of degree 13 in r, with what
-// r and 1 + r are rounded by added at the end.  Largest and mean square relative error over two million x, own and the library's:
-// 1.11e-16 and 4.7e-17, 1.34e-16 and 4.9e-17.  The compiler keeps the constants of the library's function, 19 vector registers, from step to step of
-// rollout.hip, where the rows need them; here they are scalars, and made anew.
-__device__ __forceinline__ double cost_exp(double x)
+// exp(x) for the saturating cost: x = n log 2 + r with log 2 in two parts, and the Taylor polynomial of degree 13 in r, with what
+// r and 1 + r are rounded by added at the end.  A negative cost weight makes x positive, without a bound where a trajectory diverges: x is held
+// to the range past whose ends the result is 0 or infinite, as nothing is left of r for a large n (not a number stays so).
+// Largest and root mean square relative error, x from -708 to 709 (ten ranges of 0.2 million): 1.11e-16 and 4.7e-17, the library's 1.37e-16 and
+// 4.9e-17.  The compiler keeps the constants of the library's function, 19 vector registers, from step to step of
+// rollout.hip, where the rows need them; here they are scalars, and made anew where each is used (with all of them made ahead of the chain others
+// had to make room: a saturating launch of rollout.hip took 823 instead of 795 us at B = 100, N = 2200, H = 300 and 293 instead of 283 at B = 256,
+// N = 512, H = 100).  The end-of-step kernels take as long with the library's function (saturating, 60-60, B = 777: 4.83 us, 100-37 6.1, 256-256,
+// B = 4096 14.9; policy.hip at 100-37 11.2): they have this one for the same bits.
+__host__ __device__ __forceinline__ double cost_exp(double x)
 {
+#ifdef __HIP_DEVICE_COMPILE__
+#define BAGEL_ANEW(value, after) asm volatile("" : "+s"(value) : "v"(after))
+#else
+#define BAGEL_ANEW(value, after)
+#endif
     double c[14] = {0.0, 0.0, 1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880, 1.0 / 3628800, 1.0 / 39916800,
                     1.0 / 479001600, 1.0 / 6227020800.0};
     double log2e = 1.4426950408889634, hi = -0x1.62e42fefa0000p-1, lo = -0x1.cf79abc9e3b3ap-40;
-    asm volatile("" : "+s"(log2e), "+s"(hi), "+s"(lo));
-#pragma unroll
-    for (int k = 2; k < 14; ++k) asm volatile("" : "+s"(c[k]));
+    x = x < -746.0 ? -746.0 : x > 710.0 ? 710.0 : x;
+    BAGEL_ANEW(log2e, x);
+    BAGEL_ANEW(hi, x);
+    BAGEL_ANEW(lo, x);
     const double n = rint(x * log2e);
     const double r0 = fma(n, hi, x), r = fma(n, lo, r0), dr = fma(n, lo, r0 - r);
+    BAGEL_ANEW(c[13], r);
     double p = c[13];
 #pragma unroll
-    for (int k = 12; k >= 2; --k) p = fma(p, r, c[k]);
+    for (int k = 12; k >= 2; --k) {
+        BAGEL_ANEW(c[k], p);
+        p = fma(p, r, c[k]);
+    }
+#undef BAGEL_ANEW
     const double t = 1.0 + r;
     p = t + fma(r * r, p, ((1.0 - t) + r) + dr);
-    return x < -746.0 ? 0.0 : ldexp(p, (int)n);
+    return ldexp(p, (int)n);
 }
 
 }  // namespace

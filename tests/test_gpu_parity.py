@@ -561,6 +561,43 @@ def test_rollout_with_an_infinite_goal_gives_the_same_bits(hidden, monkeypatch):
             np.testing.assert_array_equal(b[k], a[k], err_msg=k)
 
 
+# every kernel that adds the cost: the rollout of one launch, ends of step of 16 trajectories (one instance per width of the layers) and of 32
+@pytest.mark.parametrize("rollout,tile,hidden", [("2", "", (8,)), ("2", "", (100, 37)), ("1", "16", (8,)), ("1", "16", (100, 37)), ("1", "16", (256, 130)),
+                                                 ("1", "32", (8,)), ("1", "32", (130, 64))])
+def test_saturating_cost_with_a_negative_weight(rollout, tile, hidden, monkeypatch):
+    """A negative weight makes the exponent of the saturating cost positive, up to infinity for a goal that is far away: the cost is minus
+    infinity then, zero where the other weight is the larger, and not a number only where the exponent is none."""
+    import torch
+    from paper_2202_13638_amd import binding
+    monkeypatch.setenv("BAGEL_ROLLOUT", rollout)
+    monkeypatch.setenv("BAGEL_POLICY_TILE", tile)
+    goals = [(0.3, 0.2), (3.0, 0.0), (0.0, 3.0), (9.0, 0.0), (20.0, 0.0), (40.0, 0.0), (0.0, 60.0), (1e5, 1.0), (1e8, 0.0), (3e8, 0.0), (1e9, 1e9), (1e13, 0.0),
+             (0.0, 1e13), (1e19, 0.0), (3e38, 0.0), (0.0, 3e38), (np.inf, 0.0), (0.0, np.inf), (np.inf, np.inf), (np.nan, 0.0)]
+    H, sigma_r, q = 3, 0.7, (-1.0, 0.5)
+    cfg = synth.Config("neg", 43, 2, 1, 2, 40, 30, len(goals), H, hidden, 0.8, "sinusoid", "steps", 0, 0.05, 1e-3)
+    inp = synth.make_inputs(cfg)
+    inp["goals"][:] = np.float32(0.1)
+    inp["goals"][H - 1] = np.asarray(goals, dtype=np.float32)              # (in the last step: the states before it stay ordinary ones)
+    inp["goals"][0, 13], inp["goals"][1, 8] = (1e19, 0.0), (0.0, 1e13)
+    dims = binding.make_dims(d_s=2, d_a=1, d_g=2, N=cfg.N, L=cfg.L, S=cfg.B, B=cfg.B, H=H, hidden=hidden, act_bound=0.8, q=q, cost_kind=1, sigma_r=sigma_r)
+    ctx = binding.Bagel(dims)
+    g = harness.to_gpu(inp)
+    v = torch.from_numpy((0.3 * np.random.default_rng(10).standard_normal((cfg.B, cfg.M, cfg.N))).astype(np.float32)).cuda()
+    ctx.bagel_set_samples(g["X"], g["lengthscale"], g["signal_var"], g["omega"], g["phase"], g["w"], v)
+    loss, lpt = torch.zeros(1, device="cuda"), torch.zeros(cfg.B, device="cuda")
+    states = torch.zeros((H + 1, cfg.B, 2), device="cuda")
+    ctx.bagel_rollout_loss(g["theta"], g["s0"], g["goals"], loss, lpt, states)
+    torch.cuda.synchronize()
+    ctx.close()
+    with np.errstate(all="ignore"):
+        e = (np.asarray(q) * (states.cpu().numpy()[1:].astype(np.float64) - inp["goals"].astype(np.float64)) ** 2).sum(-1)
+        want = -np.exp(-e / (2.0 * float(np.float32(sigma_r)) ** 2)).sum(0)
+        want32 = want.astype(np.float32)
+    assert np.isneginf(want).sum() >= 9 and np.isneginf(want32).sum() > np.isneginf(want).sum() and np.isnan(want).sum() >= 2
+    # a state of size 1 is rounded by 6e-8, which moves the exponent by up to 2 * 9 * 6e-8 / 0.98 = 1.1e-6 where the cost is finite in 32 bits
+    np.testing.assert_allclose(lpt.cpu().numpy(), want32, rtol=4e-6)
+
+
 @pytest.mark.parametrize("B,H,one_launch", [(256, 1, True), (257, 4, False), (257, 5, True), (768, 9, False), (768, 10, True), (769, 50, False)])
 def test_rollouts_of_several_rounds_and_few_steps_go_step_by_step(B, H, one_launch, monkeypatch):
     """One workgroup per trajectory, which reads the model first, takes five steps for every round of 256 workgroups after the first to
