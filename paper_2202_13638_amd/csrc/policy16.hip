@@ -35,6 +35,9 @@ struct policy16_args {
 // 16 trajectories, so neighbouring tiles are given to workgroups of one chiplet: its L2 then sees whole lines.  With this
 // and without activations that nobody reads (policy16_args::keep), forward passes at 256-256, B = 4096 took 57.7 instead of 68.4
 // us per step; gradient calls at 64-64, B = 2048, 53.3 instead of 54.2.
+// The number of tiles comes from B, which the end of a step has fetched for other reasons, not from the grid's size.  The sweep is compiled
+// differently with either (10 to 18 more scalar registers spilled in four instances) and takes the same time: 61 steps at B = 777, from B and from the grid,
+// <4, 1, 2, 2, false> 142.9 and 143.4 us, <4, 1, 6, 2, true> 145.5 and 146.5, <8, 1, 6, 2, true> 164.7 and 162.3, <8, 1, 8, 2, false> 169.3 and 170.9.
 __device__ __forceinline__ int first_trajectory(int B)
 {
     const int n = (B + PL - 1) / PL, x = blockIdx.x & 7, q = n >> 3, r = n & 7;
