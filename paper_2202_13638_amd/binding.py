@@ -138,7 +138,7 @@ def _ptr(t, shape, name, optional=False):
         if optional:
             return None
         raise ValueError(f"{name} is required")
-    if _Tensor is None:
+    if _float32 is None:         # (the one that is set last: another thread may come in between)
         from torch import Tensor as _Tensor, float32 as _float32
     if not isinstance(t, _Tensor) or not t.is_cuda or t.dtype is not _float32 or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous float32 tensor on the GPU")

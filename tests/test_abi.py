@@ -87,3 +87,40 @@ def test_binding_rejects_host_tensors():
     with pytest.raises(ValueError):
         binding._ptr(None, (3,), "x")
     assert binding._ptr(None, (3,), "x", optional=True) is None
+
+
+def test_a_second_thread_in_the_first_call_sees_a_good_tensor(monkeypatch):
+    """torch's names are looked up in the first check of a tensor.  A thread that comes between the two (here: when the second is
+    asked for) must not take a good tensor for a bad one."""
+    import sys
+    import threading
+    import torch
+
+    class OnTheGpu(torch.Tensor):
+        is_cuda = True
+
+    t, results = torch.zeros(3).as_subclass(OnTheGpu), []
+
+    def second():
+        try:
+            results.append(binding._ptr(t, (3,), "x"))
+        except ValueError as e:
+            results.append(e)
+
+    class Slow:
+        Tensor, asked = torch.Tensor, False
+
+        @property
+        def float32(self):
+            if not self.asked:
+                self.asked = True
+                thread = threading.Thread(target=second)
+                thread.start()
+                thread.join()
+            return torch.float32
+
+    monkeypatch.setattr(binding, "_Tensor", None)
+    monkeypatch.setattr(binding, "_float32", None)
+    monkeypatch.setitem(sys.modules, "torch", Slow())
+    results.append(binding._ptr(t, (3,), "x"))
+    assert results == [t.data_ptr()] * 2
