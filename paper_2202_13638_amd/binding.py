@@ -142,7 +142,7 @@ def _ptr(t, shape, name, optional=False):
         from torch import Tensor as _Tensor, float32 as _float32
     if not isinstance(t, _Tensor) or not t.is_cuda or t.dtype is not _float32 or not t.is_contiguous():
         raise ValueError(f"{name} must be a contiguous float32 tensor on the GPU")
-    if t.shape != shape:
+    if t.shape != shape and tuple(t.shape) != tuple(shape):      # (the tuples are made only for what is no tuple itself)
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     return t.data_ptr()
 

@@ -89,6 +89,19 @@ def test_binding_rejects_host_tensors():
     assert binding._ptr(None, (3,), "x", optional=True) is None
 
 
+def test_binding_takes_a_shape_as_any_sequence():
+    import torch
+
+    class OnTheGpu(torch.Tensor):
+        is_cuda = True
+
+    t = torch.zeros((2, 3)).as_subclass(OnTheGpu)
+    assert binding._ptr(t, [2, 3], "x") == binding._ptr(t, (2, 3), "x") == binding._ptr(t, t.shape, "x") == t.data_ptr()
+    for shape in ([3, 2], (2,), [2, 3, 1]):
+        with pytest.raises(ValueError, match="x has shape"):
+            binding._ptr(t, shape, "x")
+
+
 def test_a_second_thread_in_the_first_call_sees_a_good_tensor(monkeypatch):
     """torch's names are looked up in the first check of a tensor.  A thread that comes between the two (here: when the second is
     asked for) must not take a good tensor for a bad one."""
