@@ -128,11 +128,21 @@ __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_fence(__ATOMIC_AC
 
 // What a step leaves behind, as floats in one place: a lane that stores one of them to a tape knows its place
 struct step_values {
+    static constexpr int ACT = 144;          // floats of a layer
     double x[16];                            // inputs of the sample evaluation
-    float act[2][144];
+    float act[2][ACT];
     float hin[16];                           // policy input
     float a[8];                              // action tape
 };
+// places in it, in floats (those of x: two a value)
+constexpr int AT_ACT = offsetof(step_values, act) / sizeof(float), AT_HIN = offsetof(step_values, hin) / sizeof(float),
+              AT_A = offsetof(step_values, a) / sizeof(float);
+static_assert(offsetof(step_values, x) == 0 && AT_ACT == 2 * 16 && AT_HIN == AT_ACT + 2 * step_values::ACT && AT_A == AT_HIN + 16 &&
+                  sizeof(step_values) == (AT_A + 8) * sizeof(float),
+              "no gaps: a value is stored from its place counted in floats");
+// the second unit of a lane lies this far behind the first
+constexpr int ACT_MORE = act_place(64) - act_place(0);
+static_assert(act_place(127) < step_values::ACT && act_place(63 + 64) - act_place(63) == ACT_MORE, "units 64 apart lie equally far apart");
 
 template <int D, int CK, bool WIDE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void rollout_kernel(
@@ -226,7 +236,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const int n = l == 0 ? n1 : (l == 1 ? n2 : p.width[3]), off = l == 0 ? r.b_off[0] : (l == 1 ? r.b_off[1] : r.b_off[2]);
             biases[tid] = l < p.nl && u < n ? theta[off + u] : 0.0f;
         }
-        if (tid < 288) sv.act[tid / 144][tid % 144] = 0.0f;
+        if (tid < 2 * step_values::ACT) sv.act[tid / step_values::ACT][tid % step_values::ACT] = 0.0f;
         if (tid < MAX_SUMS) gsum[tid] = 0.0;                               // (group sums past an output's last are never written)
         if (tid < M * D) AS[tid / D][tid % D] = -0.5 * A[tid];
     }
@@ -258,7 +268,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     int keep_at = -1, keep_more = 0, keep_stride = 0;
     float *keep_to = nullptr;
     const float *const svf = reinterpret_cast<const float *>(&sv);
-    constexpr int AT_ACT = 32, AT_HIN = AT_ACT + 288, AT_A = AT_HIN + 16;
     {
         auto keep = [&](bool mine, float *base, size_t offset, int stride, int at) {
             if (mine && base) {
@@ -280,7 +289,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
             const int l = 6 - wave;          // wave 6: hidden layer 1
             if (l < p.nl - 1 && r.keep) {
                 const int n = l == 0 ? p.width[1] : p.width[2];
-                keep(lane < n, l == 0 ? r.h[1] : r.h[2], lane * Bz + b, n * B, AT_ACT + 144 * l + act_place(lane));
+                keep(lane < n, l == 0 ? r.h[1] : r.h[2], lane * Bz + b, n * B, AT_ACT + step_values::ACT * l + act_place(lane));
                 keep_more = n - 64;
             }
         }
@@ -560,7 +569,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 if (goal_lane && t + 2 < H) goal_ahead = load_pinned(keep_to);
             } else {
                 if (keep_at >= 0) *keep_to = svf[keep_at];
-                if (WIDE && lane < keep_more) keep_to[64 * (size_t)B] = svf[keep_at + 72];
+                if (WIDE && lane < keep_more) keep_to[64 * (size_t)B] = svf[keep_at + ACT_MORE];
             }
             keep_to += keep_stride;
         }
