@@ -265,13 +265,19 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     // ---- what is kept of a step: one value a lane (two of a layer of more than 64 units), by waves 5 to 7 --------------------
     // keep_at: place in sv (-1: none), keep_to: where it goes in this step, keep_stride: floats from step to step.  (Formed from the
     // arguments in every step instead, addresses and conditions took these waves 1400 cycles, and the others waited.)
+    // goal_from: of wave 4 instead, the goals to fetch next; it keeps nothing (keep_at, keep_more), so nothing is ever stored there.  The two
+    // share registers on purpose: with a pointer for each a launch took 792 instead of 775 us (B = 100, N = 2200, H = 300), 268 instead of 266 and,
+    // saturating, 290 instead of 278 (B = 256, N = 512, H = 100), with the goals' in scalar registers 806, 275 and 297.
     int keep_at = -1, keep_more = 0, keep_stride = 0;
-    float *keep_to = nullptr;
+    union {
+        float *keep_to = nullptr;
+        const float *goal_from;
+    } walk;
     const float *const svf = reinterpret_cast<const float *>(&sv);
     {
         auto keep = [&](bool mine, float *base, size_t offset, int stride, int at) {
             if (mine && base) {
-                keep_to = base + offset;
+                walk.keep_to = base + offset;
                 keep_stride = stride;
                 keep_at = at;
             }
@@ -301,10 +307,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const bool goal_lane = lane >= M && lane < r.d_in;
     float goal = goal_lane ? goals[(size_t)b * r.dg + lane - M] : 0.0f, goal_ahead = 0.0f;
     if (wave == 4) {
-        keep_to = const_cast<float *>(goals) + (size_t)b * r.dg + lane - M;    // (only read through)
+        walk.goal_from = goals + (size_t)b * r.dg + lane - M;
         keep_stride = B * r.dg;
-        if (goal_lane && r.H > 1) goal_ahead = keep_to[(size_t)keep_stride];
-        keep_to += 2 * (size_t)keep_stride;
+        if (goal_lane && r.H > 1) goal_ahead = walk.goal_from[(size_t)keep_stride];
+        walk.goal_from += 2 * (size_t)keep_stride;
     }
     if (tid < 16) {
         goalS[0][tid] = goal;
@@ -566,12 +572,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
         if (wave >= 4) {
             if (wave == 4) {
                 if (lane < 16) goalS[(t + 1) & 1][lane] = goal_lane ? goal_ahead : 0.0f;
-                if (goal_lane && t + 2 < H) goal_ahead = load_pinned(keep_to);
+                if (goal_lane && t + 2 < H) goal_ahead = load_pinned(walk.goal_from);
             } else {
-                if (keep_at >= 0) *keep_to = svf[keep_at];
-                if (WIDE && lane < keep_more) keep_to[64 * (size_t)B] = svf[keep_at + ACT_MORE];
+                if (keep_at >= 0) *walk.keep_to = svf[keep_at];
+                if (WIDE && lane < keep_more) walk.keep_to[64 * (size_t)B] = svf[keep_at + ACT_MORE];
             }
-            keep_to += keep_stride;
+            walk.goal_from += keep_stride;   // (either)
         }
         __syncthreads();
         // ---- state s_{t+1}: lanes 2 m add up the kernel rows of output m, lanes 2 m + 1 its features (8 sums, then the rest: see

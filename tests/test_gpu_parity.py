@@ -594,6 +594,7 @@ def test_saturating_cost_with_a_negative_weight(rollout, tile, hidden, monkeypat
         want = -np.exp(-e / (2.0 * float(np.float32(sigma_r)) ** 2)).sum(0)
         want32 = want.astype(np.float32)
     assert np.isneginf(want).sum() >= 9 and np.isneginf(want32).sum() > np.isneginf(want).sum() and np.isnan(want).sum() >= 2
+    np.testing.assert_array_equal(g["goals"].cpu().numpy(), inp["goals"])   # (read through a pointer that shares registers with the tapes')
     # a state of size 1 is rounded by 6e-8, which moves the exponent by up to 2 * 9 * 6e-8 / 0.98 = 1.1e-6 where the cost is finite in 32 bits
     np.testing.assert_allclose(lpt.cpu().numpy(), want32, rtol=4e-6)
 
