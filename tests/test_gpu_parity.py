@@ -1337,6 +1337,13 @@ def test_posterior_sampler_one_training_point():
     (7, 3, 1, 129, 33, 5, (8,), 0.0),         # D = 10
     (2, 1, 1, 700, 130, 4, (16,), 0.0),       # N over several tile rows, B over several tile columns
     (8, 8, 3, 64, 5, 3, (4,), 0.5),           # D = 16
+    # the end of a step of wider policies takes the posterior's values in instances of its own: 8 waves with one tile of a layer and with
+    # two, ragged tiles of 16 trajectories, more values (88 and 136) than thread rows, one hidden layer
+    (8, 2, 2, 70, 37, 3, (100, 37), 0.8),
+    (5, 1, 5, 65, 50, 3, (128, 128), 0.0),
+    (8, 8, 8, 64, 19, 3, (256, 256), 0.7),
+    (3, 2, 2, 129, 33, 4, (130,), 0.6),
+    (2, 1, 2, 40, 1, 1, (250, 20), 0.0),
 ])
 def test_posterior_sampler_shapes(d_s, d_a, d_g, N, B, H, hidden, bound):
     cfg = synth.Config("ps", 40 + d_s, d_s, d_a, d_g, N, 16, B, H, hidden, bound, "sinusoid", "steps", 0, 0.6, 1e-3)
