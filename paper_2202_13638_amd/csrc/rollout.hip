@@ -508,7 +508,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                     }
                 }
             };
-            features(features, std::integral_constant<int, 0>{});
+            // The order of points and features decides what the compiler keeps in registers.  100 steps, N = 300, L = 500, B = 128, one layer of 30, features
+            // first and last: D = 2 140.1 and 141.1 us, D = 3 149 and 154, D = 4 150.4 and 151.3, D = 5 182 and 171, D = 6 186 and 174, D = 7 224 and 216,
+            // D = 8 (N = 250, L = 300) 171 and 160.
+            if constexpr (D <= 4) features(features, std::integral_constant<int, 0>{});
             if (__builtin_expect(far == 0, 1)) {
                 points(points, std::integral_constant<int, 0>{});
             } else {
@@ -518,6 +521,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
                 for (int i = 0; i < E; ++i)
                     if (i < nk) point(i, far >> __builtin_amdgcn_readlane(m_of_chunk, i) & 1 ? outside + row[i][D] : exponent(i));
             }
+            if constexpr (D > 4) features(features, std::integral_constant<int, 0>{});
         }
         __syncthreads();
         // ---- sums of the work units, four of them to a group ---------------------------------------------------------
