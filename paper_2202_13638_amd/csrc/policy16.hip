@@ -177,14 +177,7 @@ struct tail16_args {
 
 constexpr int TAIL_GROUPS = 128;             // value sums of a trajectory that are staged in LDS
 
-// What a step waits for is trips to memory one after the other, so everything is requested before anything waits: the arguments
-// (they come from memory as well, and the compiler would fetch each where it is first used, a trip of 300 to 700 cycles a time), what is
-// summed, the weights of the narrow layers and half of a wide middle layer's.  The rest of that comes while the first layer is worked
-// on: all of it at once, 256 KB for a compute unit, held up the waves that were to write their sums to LDS.  No load stands
-// in a branch of its own: where paths join, the compiler waits for what one of them has requested.
-// What is kept of the state, and the cost, come last, beside the action.  (us a launch, before and now: 64-64, B = 1024 6.1 and 5.0, 100-37,
-// B = 777 7.0 and 6.0, 256-256, B = 4096 14.6 and 13.6, of which the matrix instructions take 3.4.)
-// the value of the lane 16 further on, in the even rows of 16 lanes
+// The value of the lane 16 further on, in the even rows of 16 lanes
 __device__ __forceinline__ double next_row(double v)
 {
     unsigned a = __double2loint(v), b = __double2hiint(v);
@@ -194,6 +187,13 @@ __device__ __forceinline__ double next_row(double v)
 
 enum tail_mode { TAIL_SUMS, TAIL_DIRECT, TAIL_START };                     // part: groups' sums, final values; s0 instead
 
+// What a step waits for is trips to memory one after the other, so everything is requested before anything waits: the arguments
+// (they come from memory as well, and the compiler would fetch each where it is first used, a trip of 300 to 700 cycles a time), what is
+// summed, the weights of the narrow layers and half of a wide middle layer's.  The rest of that comes while the first layer is worked
+// on: all of it at once, 256 KB for a compute unit, held up the waves that were to write their sums to LDS.  No load stands
+// in a branch of its own: where paths join, the compiler waits for what one of them has requested.
+// What is kept of the state, and the cost, come last, beside the action.  (us a launch, before and now: 64-64, B = 1024 6.1 and 5.0, 100-37,
+// B = 777 7.0 and 6.0, 256-256, B = 4096 14.6 and 13.6, of which the matrix instructions take 3.4.)
 template <int NW, int NT, int MODE>
 __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, policy16_args a, pack16 p)
 {
