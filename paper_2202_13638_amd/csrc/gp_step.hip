@@ -194,8 +194,10 @@ __global__ __launch_bounds__(BAGEL_BLOCK) void jac_reduce_kernel(jac_sums_arg<ST
 // What a wave then still waits for is the order of its loads.  Scalar loads return in any order, so a wait for one is a wait for
 // all: the rows of this pair are waited for (rows_arrived) before those of the next are requested, not after.  Vector loads
 // return in order, so the matrix-core operands, which hit in cache, come after the stream's float4 requested before them:
-// they are requested three float4 ahead, behind a request that has had as long.  Us a launch, before -> now: M = 4, N = L = 2048, B = 1024
-// 19.1 -> 18.1 (its 67 MB of streams alone take 11.5), M = 3, N = 1533, L = 901, B = 777 10.4 -> 9.8.
+// they are requested three float4 ahead, behind a request that has had as long.  Us a launch, before -> now, evaluations alone in a loop: M = 4,
+// D = 5, N = L = 2048, B = 1024 18.6 -> 17.6 (its 67 MB of streams alone take 11.5), M = 6, D = 8, N = 1533, L = 901, B = 777 21.6 -> 20.1; 56 shapes of
+// D = 2 .. 8, values alone and with the Jacobian, 1.06 on average, least at N = L = 2048, B = 1024 (values at D = 2 5.1 -> 5.3 and D = 4 8.4 -> 8.6,
+// D = 7 25.0 -> 25.6).  Between two ends of step of a rollout: the first of these 17.7 -> 17.3, M = 3, N = 1533, L = 901, B = 777 10.0 -> 9.3.
 __device__ __forceinline__ void rows_arrived()
 {
     __builtin_amdgcn_s_waitcnt(0xc07f);        // lgkmcnt(0) alone

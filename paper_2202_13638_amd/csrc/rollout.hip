@@ -5,11 +5,12 @@
 // there is to compute.  Here a trajectory never leaves its compute unit: 512 threads hold the rows of the model tables and the
 // trajectory's weights v and w in registers for the whole horizon (the policy's weights in LDS), and a step is three to five
 // barriers.  What bounds it is the float64 arithmetic of one compute unit and what lies between the barriers.  A forward step of a gradient
-// call takes 2.7 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 2.8 at M = 2, N = 2200, L = 1024, 8-8,
-// B = 100 (13.2) and 1.3 at M = 2, N = 64, L = 256, 16, B = 16 (8.6); the Jacobians afterwards take 1.5, 0.5 and 0.5 us a step.
-// Of a step of the first of them (6200 cycles) the policy and the state take 3000, one wave after the other with one contraction each,
+// call takes 2.4 us at M = 4, N = 512, L = 1024, 64-64, B = 256 (11.7 in two launches), 2.5 at M = 2, N = 2200, L = 1024, 8-8,
+// B = 100 (13.2) and 1.2 at M = 2, N = 64, L = 256, 16, B = 16 (8.6), reading the model and the weights 25, 14 and 7 us; the Jacobians afterwards
+// take 1.3, 0.4 and 0.3 us a step.
+// Of a step of the first of them (about 6000 cycles) the policy and the state take 3000, one wave after the other with one contraction each,
 // the terms 2300 (float64 instructions of two waves a SIMD, about 5 cycles each) and their sums 650 (a chain of dependent additions).
-// What is off that chain, the tapes, the goals ahead and the cost, belongs to waves that wait anyway.  (3.1, 3.0 and 1.5 us a step while
+// What is off that chain, the tapes, the goals ahead and the cost, belongs to waves that wait anyway.  (2.9, 2.8 and 1.4 us a step while
 // addresses were formed anew for every store, 1400 cycles of one wave, and the waits for the rows stood inside the loop.)
 //
 // Only values are computed here.  The Jacobians feed nothing but the backward pass, so they are computed afterwards for all
@@ -19,6 +20,7 @@
 // Every number is formed in the order of gp_step.hip and policy16.hip, so states and costs have the same bits as a rollout by
 // those kernels: terms are computed by whichever thread has the operands and left in LDS, and one thread per work unit adds
 // them up in order; four units make a group sum, group sums are added as step_tail16_kernel adds them.
+#include <cstddef>
 #include <type_traits>
 
 #include "policy16.h"
