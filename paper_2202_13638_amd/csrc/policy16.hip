@@ -56,7 +56,7 @@ struct forward_weights {
     f4v mid[NT][NW * NT], last[2], bias0[NT], bias1[NT];      // last: the two blocks of slice `wave`
 };
 
-// those of the narrow layers and the biases; blocks kb0 .. kb1 - 1 of the middle layer
+// those of the narrow layers and the biases, and the middle layer
 template <int NW, int NT>
 __device__ __forceinline__ void load_narrow(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane)
 {
@@ -75,7 +75,7 @@ __device__ __forceinline__ void load_narrow(forward_weights<NW, NT> &f, const fl
     for (int e = 0; e < 2; ++e) f.last[e] = reinterpret_cast<const f4v *>(pack + p.f_last() + min(2 * wave + e, TT - 1) * 256)[ul];
 }
 template <int NW, int NT>
-__device__ __forceinline__ void load_middle(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane, int kb0, int kb1)
+__device__ __forceinline__ void load_middle(forward_weights<NW, NT> &f, const float *pack, const pack16 &p, int wave, int lane)
 {
     constexpr int TT = NW * NT;
     const unsigned ul = lane;
@@ -83,8 +83,7 @@ __device__ __forceinline__ void load_middle(forward_weights<NW, NT> &f, const fl
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
-            for (int kb = 0; kb < TT; ++kb)
-                if (kb >= kb0 && kb < kb1) f.mid[t][kb] = reinterpret_cast<const f4v *>(pack + p.f_mid() + ((wave * NT + t) * TT + kb) * 256)[ul];
+            for (int kb = 0; kb < TT; ++kb) f.mid[t][kb] = reinterpret_cast<const f4v *>(pack + p.f_mid() + ((wave * NT + t) * TT + kb) * 256)[ul];
     }
 }
 
@@ -189,23 +188,22 @@ enum tail_mode { TAIL_SUMS, TAIL_DIRECT, TAIL_START };                     // pa
 
 // What a step waits for is trips to memory one after the other, so everything is requested before anything waits: the arguments
 // (they come from memory as well, and the compiler would fetch each where it is first used, a trip of 300 to 700 cycles a time), what is
-// summed, the weights of the narrow layers and half of a wide middle layer's.  The rest of that comes while the first layer is worked
-// on: all of it at once, 256 KB for a compute unit, held up the waves that were to write their sums to LDS.  No load stands
-// in a branch of its own: where paths join, the compiler waits for what one of them has requested.
-// What is kept of the state, and the cost, come last, beside the action.  (us a launch, before and now: 64-64, B = 1024 6.1 and 5.0, 100-37,
-// B = 777 7.0 and 6.0, 256-256, B = 4096 14.6 and 13.6, of which the matrix instructions take 3.4.)
+// summed, the weights, those of the narrow layers first.  No load stands in a branch of its own: where paths join, the compiler waits for what
+// one of them has requested.  What is kept of the state, and the cost, come last, beside the action.  (us a launch, before and now: 64-64,
+// B = 1024 6.0 and 4.9, 100-37, B = 777 6.9 and 6.1, 256-256, B = 4096 14.7 and 13.9, of which the matrix instructions take 3.4.  Of that: without the
+// arguments at once calls of 40 steps take 1.2 % longer, 1.7 with up to 64 units and 0.4 with 256, with the tapes before the policy 0.7 %.  Half of a
+// middle layer of 256 units requested only during the first layer gave nothing: 14.2 and 14.1 us at B = 4096, 13.7 and 13.0 at B = 1024.)
 template <int NW, int NT, int MODE>
 __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, policy16_args a, pack16 p)
 {
     using S = shape16<NW, NT>;
-    constexpr int TT = NW * NT, TT_AHEAD = NT == 2 ? TT / 2 : TT;          // blocks of the middle layer requested at the start
     __shared__ __align__(16) float act[2][PL * S::AS], h0[PL * HS], red[NW * 8 * PL];
     __shared__ double fS[TAIL_GROUPS][PL], sS[8][PL];
     asm volatile("" ::"s"(r.x_cur), "s"(r.part), "s"(r.amp), "s"(r.goals_t), "s"(r.goals_next), "s"(r.lpt), "s"(r.x_next), "s"(r.tape_s_next),
                  "s"(r.states_out_next), "s"(a.pack), "s"(a.h[0]), "s"(a.h[1]), "s"(a.h[2]), "s"(r.slot), "s"(r.D), "s"(r.M), "s"(r.dg), "s"(r.ngk),
                  "s"(r.ngl), "s"(r.do_policy), "s"(a.B), "s"(a.ds), "s"(a.width[0]), "s"(a.keep), "s"(p.nl), "s"(p.nsi), "s"(p.fs));
     asm volatile("" ::"s"(a.width[1]), "s"(a.width[2]), "s"(a.width[3]), "s"(a.da), "s"(a.act_bound), "s"(a.a_slot), "s"(r.cost_kind));
-    p.TT = TT;                               // (not an argument to wait for)
+    p.TT = NW * NT;                          // (not an argument to wait for)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bl = tid & (PL - 1), row = tid >> 4;
     const int b0 = first_trajectory(a.B);
@@ -249,7 +247,7 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
     if (r.do_policy) {
         load_narrow(f, a.pack, p, wave, lane);
         bias_in = a.pack[p.bias(2) + min(row, 7)];
-        load_middle(f, a.pack, p, wave, lane, 0, TT_AHEAD);
+        load_middle(f, a.pack, p, wave, lane);
     }
     if constexpr (MODE == TAIL_DIRECT) {
         for (int qi = row; qi < r.M * r.ncomp; qi += S::ROWS) {
@@ -285,7 +283,6 @@ __global__ __launch_bounds__(64 * NW) void step_tail16_kernel(tail16_args r, pol
     }
     if (MODE == TAIL_START && row == 0 && live) r.lpt[b] = 0.0;
     __syncthreads();
-    if (TT_AHEAD < TT && r.do_policy) load_middle(f, a.pack, p, wave, lane, TT_AHEAD, TT);
     if (r.do_policy) {
         policy16_layers<NW, NT>(a, p, f, r.slot, wave, lane, b, live, h0, act, red);
         __syncthreads();
@@ -337,7 +334,7 @@ __global__ __launch_bounds__(64 * NW) void policy_replay16_kernel(replay16_args 
     const int B = a.B, ds = a.ds, d_in = a.width[0];
     forward_weights<NW, NT> f;
     load_narrow(f, a.pack, p, wave, lane);
-    load_middle(f, a.pack, p, wave, lane, 0, NW * NT);
+    load_middle(f, a.pack, p, wave, lane);
     const float bias = a.pack[p.bias(2) + min(row, 7)];
     const int s_end = min(r.n_slots, (int)(blockIdx.y + 1) * r.per);
     auto input = [&](int sl) {

@@ -660,7 +660,7 @@ def test_measurement_hook_gives_the_same_bits():
 
 
 # all 16 thread rows with a state or a goal, in every instance of the layers; more groups of sums (144) than are staged; no policy to
-# follow; one hidden layer; a middle layer of more, as many and fewer blocks than are requested at the start
+# follow; one hidden layer; a middle layer of 16, 8 and fewer blocks
 @pytest.mark.parametrize("d_s,d_a,d_g,N,L,H,hidden,unit", [(8, 8, 8, 40, 30, 3, (8,), ""), (8, 1, 8, 600, 500, 3, (64, 64), "16"),
                                                            (8, 1, 8, 70, 50, 3, (100, 128), ""), (8, 2, 8, 70, 50, 3, (256, 256), ""),
                                                            (3, 1, 2, 40, 30, 3, (128, 250), ""), (1, 1, 1, 40, 30, 1, (130, 65), "")])
